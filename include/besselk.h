@@ -74,7 +74,8 @@ typedef enum { BK_RESULT_K = 0, BK_RESULT_SCALED = 1, BK_RESULT_LOG = 2 } bk_res
  * accumulated, never cleared by the library). bk_besselk_ex and bk_matern_tiles
  * fill them for every form (the paper form counts its integral branch only).
  * Counting costs time (the Matern kernels have counting variants), so time
- * calls without it. */
+ * calls without it. Where a Matern call takes tables (bk_matern_tiles), the counts
+ * are those of the per-entry form, which a call with statistics runs besides. */
 enum {
     BK_STAT_ENTRIES = 0,      /* entries evaluated by quadrature               */
     BK_STAT_NODES = 1,        /* sum over entries of (N + 1) trapezoid nodes    */
@@ -180,6 +181,13 @@ typedef struct {
  * bk_matern_tile_offset(I, J) + i + j * m_I. Diagonal tiles are written in full
  * (both triangles). With tile_size >= n and lower_only == 0 the output is the
  * whole n x n column-major matrix.
+ * Large calls with the default thresholds (0.01 <= nu <= 16, positive finite sigma2)
+ * in BK_PLAIN_F64, or in BK_MIXED_F32C or BK_LEARNED with BK_OUT_F32, evaluate the
+ * quadrature at the points of a table over r^2 and the entries by interpolation in it,
+ * at the form's accuracy or better (BK_PLAIN_F64: a few 1e-16 relative where z < 2); the
+ * table lies in the last bytes of out until those are written. Other calls, and
+ * distances outside the table (r / beta below 2^-14 (FP32: 2^-12) or above 128),
+ * evaluate each entry.
  * out : device buffer of bk_matern_out_elems(n, tile_size, lower_only) elements
  *       of params->out_dtype. params->mode selects the form; BK_LEARNED needs a
  *       model and a workspace of bk_matern_workspace_bytes(...) bytes, and only

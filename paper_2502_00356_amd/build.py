@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbesselk.so")
 RATES_LIB = os.path.join(HERE, "libvalurates.so")
-SOURCES = ["bk_kernels.hip", "bk_mlp.hip", "bk_mle.hip"]
+SOURCES = ["bk_kernels.hip", "bk_mlp.hip", "bk_mle.hip", "bk_table.hip"]
 # rocSOLVER (Cholesky, triangular solves, inverse) and the rocBLAS handle it runs on
 LIBS = ["-L/opt/rocm/lib", "-lrocsolver", "-lrocblas"]
 ARCH = os.environ.get("BK_OFFLOAD_ARCH", "gfx950")

@@ -57,6 +57,80 @@ inline int launch(void (*k)(P...), dim3 grid, dim3 block, hipStream_t stream, A&
     return launch_args(k, grid, block, stream, args, std::index_sequence_for<P...>{});
 }
 
+// Tiling of a Matern call: T x T tiles (or the lower ones) of ts rows and columns,
+// each cut into rb_per_tile row blocks of 64 and cb_per_tile column blocks.
+struct TileGeom {
+    int64_t n;
+    int32_t ts, T, lower;
+    int32_t rb_per_tile, cb_per_tile;
+};
+
+// Element offset of tile (I, J) in the packed output.
+__host__ __device__ inline int64_t tile_offset(int64_t n, int64_t ts, int64_t T, int lower, int64_t I, int64_t J)
+{
+    int64_t nJ = (J == T - 1) ? n - J * ts : ts;
+    if (lower) return ts * (J * n - ts * (J * (J - 1) / 2)) + nJ * (I - J) * ts;
+    return J * ts * n + nJ * I * ts;
+}
+
+// Tile (I, J) of packed tile p (tiles column by column). Lower: column J starts at
+// s(J) = J T - J (J - 1) / 2; the FP32 root of s(J) = p lands within a step or two of
+// J (values below 2^34 at ~6e-8 relative; the cancellation in b^2 - 8 p adds a few
+// steps only for T in the tens of thousands), and the loops settle it exactly. The
+// work is uniform across the wave: scalar integer loops after a handful of FP32
+// vector instructions.
+__device__ inline void tile_of(int64_t p, const TileGeom& g, int64_t& I, int64_t& J)
+{
+    int64_t T = g.T;
+    if (!g.lower) { J = p / T; I = p - J * T; return; }
+    const float b = 2.0f * (float)T + 1.0f;
+    int64_t j = (int64_t)((b - __builtin_amdgcn_sqrtf(fmaxf(fmaf(b, b, -8.0f * (float)p), 0.0f))) * 0.5f);
+    if (j < 0) j = 0;
+    if (j > T - 1) j = T - 1;
+    while (j > 0 && j * T - j * (j - 1) / 2 > p) --j;
+    while (j + 1 <= T - 1 && (j + 1) * T - (j + 1) * j / 2 <= p) ++j;
+    J = j;
+    I = J + (p - (J * T - J * (J - 1) / 2));
+}
+
+// One entry of the plain (MODE BK_PLAIN_F64) or mixed form at z = r / beta > 0:
+// sigma2 c z^nu K_nu(z), pref = ln c = ln(2^(1-nu) / Gamma(nu)). s: the entry's solve
+// (for the caller's counts and for dC/dnu). T: exp_tab's tables.
+template <int MODE>
+__device__ __forceinline__ double matern_entry(double nu, double z, double lz, double sigma2, double pref, double L,
+                                               double Lq, const double* T, Solved& s)
+{
+    s = plain_solve(nu, z, L, Lq, rule_tab(), T);
+    double hs;
+    if constexpr (MODE == BK_PLAIN_F64) {
+        hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, T);
+        hs = fma(hs, s.dlo, hs);
+    } else {
+        hs = s.p.h * sum_mixed(nu, z, s.p, s.A, T);
+    }
+    return sigma2 * exp(pref + nu * lz + (s.delta - z)) * hs;
+}
+
+// dC/dbeta = sigma2 c z^(nu+1) K_{nu-1}(z) / beta at z > 0 (lz = ln z).
+__device__ __forceinline__ double matern_dbeta(double nu, double z, double lz, double sigma2, double inv_beta,
+                                               double pref, double L, double Lq, const double* T)
+{
+    const double nu1 = fabs(nu - 1.0);
+    const Solved s1 = plain_solve(nu1, z, L, Lq, rule_tab(), T);
+    const double hs1 = s1.p.h * sum_f64(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    return sigma2 * inv_beta * exp(pref + (nu + 1.0) * lz + (s1.delta - z)) * fma(hs1, s1.dlo, hs1);
+}
+
+// dC/dnu = C (ln z - ln 2 - psi(nu)) + sigma2 c z^nu dK_nu/dnu(z) at z > 0, from C = vc
+// and the start t0 of its window.
+__device__ __forceinline__ double matern_dnu(double nu, double z, double lz, double sigma2, double pref, double psi,
+                                             double L, double Lq, const double* T, double vc, double t0)
+{
+    const Solved sd = dnu_solve(nu, z, t0, L, Lq, rule_tab(), T);
+    return vc * (lz - kLn2 - psi) +
+           sigma2 * exp(pref + nu * lz + (sd.delta - z)) * (sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T));
+}
+
 int bk_besselk_learned(const double* nu, const double* x, double* out, int64_t n, const bk_params* prm,
                        double L, double Lq, hipStream_t stream);
 // Workspace bytes of the learned Matern form for one call (window table, interval

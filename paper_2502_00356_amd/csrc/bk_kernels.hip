@@ -18,6 +18,7 @@
 #include "../../include/besselk.h"
 #include "bk_math.hpp"
 #include "bk_internal.hpp"
+#include "bk_table.hpp"
 
 namespace bk {
 
@@ -372,34 +373,6 @@ constexpr int kRowsPerWave = 64;
 constexpr int kColsPerWave = 8;
 constexpr int kColsPerGroup = 4 * kColsPerWave;
 
-struct TileGeom {
-    int64_t n;
-    int32_t ts, T, lower;
-    int32_t rb_per_tile, cb_per_tile;
-};
-
-__host__ __device__ inline int64_t tile_offset(int64_t n, int64_t ts, int64_t T, int lower, int64_t I, int64_t J)
-{
-    int64_t nJ = (J == T - 1) ? n - J * ts : ts;
-    if (lower) return ts * (J * n - ts * (J * (J - 1) / 2)) + nJ * (I - J) * ts;
-    return J * ts * n + nJ * I * ts;
-}
-
-__device__ inline void tile_of(int64_t p, const TileGeom& g, int64_t& I, int64_t& J)
-{
-    int64_t T = g.T;
-    if (!g.lower) { J = p / T; I = p - J * T; return; }
-    // largest J with off(J) = J T - J (J - 1) / 2 <= p
-    double b = 2.0 * (double)T + 1.0;
-    int64_t j = (int64_t)floor((b - sqrt(fmax(b * b - 8.0 * (double)p, 0.0))) * 0.5);
-    if (j < 0) j = 0;
-    if (j > T - 1) j = T - 1;
-    while (j > 0 && j * T - j * (j - 1) / 2 > p) --j;
-    while (j + 1 <= T - 1 && (j + 1) * T - (j + 1) * j / 2 <= p) ++j;
-    J = j;
-    I = J + (p - (J * T - J * (J - 1) / 2));
-}
-
 // kStats: the statistics variant, which also counts the entries evaluated by
 // quadrature and their nodes (lanes past a ragged tile's last row stay in the
 // wave, idle, so that the wave can sum its counts).
@@ -457,15 +430,8 @@ __global__ __launch_bounds__(256, 4) void k_matern(const double* __restrict__ lx
                     if (kStats) col_nodes[c] = (unsigned int)(bins + 1);
                 }
             } else {
-                Solved s = plain_solve(nu, z, L, Lq, rule_tab(), s_tab);
-                double hs;
-                if constexpr (MODE == BK_PLAIN_F64) {
-                    hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, s_tab);
-                    hs = fma(hs, s.dlo, hs);
-                } else {
-                    hs = s.p.h * sum_mixed(nu, z, s.p, s.A, s_tab);
-                }
-                val = sigma2 * exp(pref + nu * log(z) + (s.delta - z)) * hs;
+                Solved s;
+                val = matern_entry<MODE>(nu, z, log(z), sigma2, pref, L, Lq, s_tab, s);
                 c_nodes += (unsigned int)(s.p.N + 1);
                 c_ent += 1;
                 if (kStats) col_nodes[c] = (unsigned int)(s.p.N + 1);
@@ -517,7 +483,6 @@ __global__ __launch_bounds__(256) void k_matern_grad(const double* __restrict__ 
     const int64_t base = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
     const double xi = lx[I * g.ts + il], yi = ly[I * g.ts + il];
     const int cend = (int)min((int64_t)kColsPerWave, nJ - jl0);
-    const double nu1 = fabs(nu - 1.0);
     for (int c = 0; c < cend; ++c) {
         const int64_t jl = jl0 + c;
         const double xj = lx[J * g.ts + jl], yj = ly[J * g.ts + jl];
@@ -525,23 +490,12 @@ __global__ __launch_bounds__(256) void k_matern_grad(const double* __restrict__ 
         const double r = sqrt(dx * dx + dy * dy);
         double vc = sigma2, vb = 0.0, vn = 0.0;
         if (r != 0.0) {
-            const RuleTable& R = rule_tab();
             const double z = r * inv_beta, lz = log(z);
-            const Solved s0 = plain_solve(nu, z, L, Lq, R, s_tab);
-            // the same expression as k_matern, so that C is bit-identical with or without the derivatives
-            double hs0 = s0.p.h * sum_f64(nu, z, s0.p, s0.E, s0.Ei, s0.Sr, s_tab);
-            hs0 = fma(hs0, s0.dlo, hs0);
-            vc = sigma2 * exp(pref + nu * lz + (s0.delta - z)) * hs0;
-            if (ob) {
-                const Solved s1 = plain_solve(nu1, z, L, Lq, R, s_tab);
-                const double hs1 = s1.p.h * sum_f64(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, s_tab);
-                vb = sigma2 * inv_beta * exp(pref + (nu + 1.0) * lz + (s1.delta - z)) * fma(hs1, s1.dlo, hs1);
-            }
-            if (on) {
-                const Solved sd = dnu_solve(nu, z, s0.p.t0, L, Lq, R, s_tab);
-                vn = vc * (lz - kLn2 - psi) +
-                     sigma2 * exp(pref + nu * lz + (sd.delta - z)) * (sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, s_tab));
-            }
+            // the same function as k_matern, so that C is bit-identical with or without the derivatives
+            Solved s0;
+            vc = matern_entry<BK_PLAIN_F64>(nu, z, lz, sigma2, pref, L, Lq, s_tab, s0);
+            if (ob) vb = matern_dbeta(nu, z, lz, sigma2, inv_beta, pref, L, Lq, s_tab);
+            if (on) vn = matern_dnu(nu, z, lz, sigma2, pref, psi, L, Lq, s_tab, vc, s0.p.t0);
         }
         const int64_t o = base + il + jl * mI;
         if (oc) oc[o] = (OutT)vc;
@@ -707,6 +661,21 @@ int matern_tiles_dispatch(const bk_locs* locs, const bk_params* prm, int32_t til
     double L, Lq;
     resolve_thresholds(prm->mode, prm->L_window, prm->L_quad, &L, &Lq);
     const bool f32 = prm->out_dtype == BK_OUT_F32;
+    // Large builds by tables. A call with statistics first runs the per-entry form, which
+    // counts, and its output is then written as any other call of the size writes it.
+    if ((prm->mode == BK_PLAIN_F64 || (prm->mode == BK_MIXED_F32C && f32)) &&
+        table_route(locs, prm, tile_size, lower_only, kTabMinEntries)) {
+        if (prm->stats) {
+            bk_params count = *prm;
+            count.kernel_events[0] = count.kernel_events[1] = nullptr;
+            const int st = prm->mode == BK_MIXED_F32C
+                ? launch_matern<BK_MIXED_F32C, float>(locs, &count, g, ntiles, L, Lq, out, stream)
+                : (f32 ? launch_matern<BK_PLAIN_F64, float>(locs, &count, g, ntiles, L, Lq, out, stream)
+                       : launch_matern<BK_PLAIN_F64, double>(locs, &count, g, ntiles, L, Lq, out, stream));
+            if (st != BK_OK) return st;
+        }
+        return matern_table_tiles(locs, prm, tile_size, lower_only, out, stream);
+    }
     switch (prm->mode) {
     case BK_PLAIN_F64:
         return f32 ? launch_matern<BK_PLAIN_F64, float>(locs, prm, g, ntiles, L, Lq, out, stream)
@@ -808,6 +777,10 @@ extern "C" int bk_matern_grad_tiles(const bk_locs* locs, const bk_params* prm, i
     if (prm->L_window < 0.0 || prm->L_quad < 0.0) return BK_EINVAL;
     if (locs->n == 0) return BK_OK;
     if (!locs->x || !locs->y || (!c && !dc_dbeta && !dc_dnu)) return BK_EINVAL;
+    if (table_route(locs, prm, tile_size, lower_only, kTabMinEntries)) {
+        void* const outs[3] = {c, dc_dbeta, dc_dnu};
+        return matern_grad_table_tiles(locs, prm, digamma_host(prm->nu), tile_size, lower_only, outs, stream);
+    }
     TileGeom g;
     g.n = locs->n;
     g.ts = tile_size;

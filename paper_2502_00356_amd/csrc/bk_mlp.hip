@@ -1029,39 +1029,6 @@ __device__ __forceinline__ float log1p_small_f(float u)
     return p * u;
 }
 
-struct TileGeomL {
-    int64_t n;
-    int32_t ts, T, lower;
-    int32_t rb_per_tile, cb_per_tile;
-};
-
-__host__ __device__ inline int64_t tile_offset_l(int64_t n, int64_t ts, int64_t T, int lower, int64_t I, int64_t J)
-{
-    int64_t nJ = (J == T - 1) ? n - J * ts : ts;
-    if (lower) return ts * (J * n - ts * (J * (J - 1) / 2)) + nJ * (I - J) * ts;
-    return J * ts * n + nJ * I * ts;
-}
-
-// Tile (I, J) of packed tile p (tiles column by column). Lower: column J starts at
-// s(J) = J T - J (J - 1) / 2; the FP32 root of s(J) = p lands within a step or two of
-// J (values below 2^34 at ~6e-8 relative; the cancellation in b^2 - 8 p adds a few
-// steps only for T in the tens of thousands), and the loops settle it exactly. The
-// work is uniform across the wave: scalar integer loops after a handful of FP32
-// vector instructions.
-__device__ inline void tile_of_l(int64_t p, const TileGeomL& g, int64_t& I, int64_t& J)
-{
-    int64_t T = g.T;
-    if (!g.lower) { J = p / T; I = p - J * T; return; }
-    const float b = 2.0f * (float)T + 1.0f;
-    int64_t j = (int64_t)((b - __builtin_amdgcn_sqrtf(fmaxf(fmaf(b, b, -8.0f * (float)p), 0.0f))) * 0.5f);
-    if (j < 0) j = 0;
-    if (j > T - 1) j = T - 1;
-    while (j > 0 && j * T - j * (j - 1) / 2 > p) --j;
-    while (j + 1 <= T - 1 && (j + 1) * T - (j + 1) * j / 2 <= p) ++j;
-    J = j;
-    I = J + (p - (J * T - J * (J - 1) / 2));
-}
-
 // Sum of a per-lane count over a wave (every lane active), added once to a global
 // counter by lane 0.
 __device__ inline void wave_count_l(unsigned long long* dst, unsigned int v)
@@ -1138,7 +1105,7 @@ __device__ inline double matern_node_sum(double zl, double c, double cn, double 
 template <typename OutT, bool kStats>
 __global__ __launch_bounds__(256, 8) void k_matern_learned(const float4_t* __restrict__ rec,
                                                         const double* __restrict__ lx_, const double* __restrict__ ly_,
-                                                        TileGeomL g, int64_t tile_base, double sigma2, double kb,
+                                                        TileGeom g, int64_t tile_base, double sigma2, double kb,
                                                         float fa, float fb, int nu_ok, double nu, double sig_mul,
                                                         unsigned int* __restrict__ bitmap, OutT* __restrict__ out,
                                                         unsigned long long* __restrict__ stats)
@@ -1149,7 +1116,7 @@ __global__ __launch_bounds__(256, 8) void k_matern_learned(const float4_t* __res
     const int64_t p = tile_base + (int64_t)blockIdx.z;
     const int rb = (int)blockIdx.x, cb = (int)blockIdx.y;
     int64_t I, J;
-    tile_of_l(p, g, I, J);
+    tile_of(p, g, I, J);
     const int64_t mI = min((int64_t)g.ts, g.n - I * g.ts);
     const int64_t nJ = min((int64_t)g.ts, g.n - J * g.ts);
     const int lane = threadIdx.x & 63;
@@ -1159,7 +1126,7 @@ __global__ __launch_bounds__(256, 8) void k_matern_learned(const float4_t* __res
     const bool row_ok = il < mI;
     // the statistics variant keeps every wave to the end for its block-wide sums
     if (!kStats && (jl0 >= nJ || !row_ok)) return;
-    const int64_t base = tile_offset_l(g.n, g.ts, g.T, g.lower, I, J);
+    const int64_t base = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
     const int64_t ilr = row_ok ? il : 0;
     const double xi = lx_[I * g.ts + ilr], yi = ly_[I * g.ts + ilr];
     // the row point is waited for here, once: a wait for it inside the column loop
@@ -1299,7 +1266,7 @@ __global__ __launch_bounds__(256, 8) void k_matern_learned(const float4_t* __res
 // node terms). The marked waves are few, so the scan is the bulk of the work.
 template <typename OutT>
 __global__ __launch_bounds__(256) void k_matern_fallback(const double* __restrict__ lx_, const double* __restrict__ ly_,
-                                                         TileGeomL g, double sigma2, double inv_beta, double nu,
+                                                         TileGeom g, double sigma2, double inv_beta, double nu,
                                                          double pref, double L, double Lq,
                                                          const unsigned int* __restrict__ bitmap, int64_t nwords,
                                                          OutT* __restrict__ out, unsigned long long* __restrict__ stats)
@@ -1328,13 +1295,13 @@ __global__ __launch_bounds__(256) void k_matern_fallback(const double* __restric
                 const int64_t local = blk - p * wg_per_tile;
                 const int rb = (int)(local % g.rb_per_tile), cb = (int)(local / g.rb_per_tile);
                 int64_t I, J;
-                tile_of_l(p, g, I, J);
+                tile_of(p, g, I, J);
                 const int64_t mI = min((int64_t)g.ts, g.n - I * g.ts);
                 const int64_t nJ = min((int64_t)g.ts, g.n - J * g.ts);
                 const int64_t il = (int64_t)rb * 64 + lane;
                 const int64_t jl0 = (int64_t)cb * kColsPerGroup + (int64_t)wave * kColsPerWave;
                 if (il >= mI || jl0 >= nJ) continue;
-                const int64_t base = tile_offset_l(g.n, g.ts, g.T, g.lower, I, J);
+                const int64_t base = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
                 const double xi = lx_[I * g.ts + il], yi = ly_[I * g.ts + il];
                 const int cend = (int)min((int64_t)kColsPerWave, nJ - jl0);
                 for (int c = 0; c < cend; ++c) {
@@ -1793,7 +1760,7 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
     const MlpDev M = make_dev(m);
     const double nu = prm->nu;
     const double pref = (1.0 - nu) * kLn2 - lgamma(nu);
-    TileGeomL g;
+    TileGeom g;
     g.n = locs->n;
     g.ts = tile_size;
     g.T = (int32_t)((locs->n + tile_size - 1) / tile_size);

@@ -1,0 +1,206 @@
+// bk_table.hpp - Matern tiles by interpolation in r^2: table shapes, the interval
+// fit shared by the table builders (bk_table.hip, bk_mlp.hip), and the launches.
+//
+// At one (sigma^2, beta, nu) every entry of a Matern matrix is one function of the
+// squared distance q = r^2. A large build therefore evaluates the quadrature at the
+// Chebyshev points of a few hundred intervals of q, and every entry by its interval's
+// polynomial: no square root, no exponential and no window solve per entry.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "bk_internal.hpp"
+
+namespace bk {
+
+// Intervals: p(q) = fa bits(q) + fb sqrt(q) + fc advances by one per interval, q in
+// FP32, bits(q) its bit pattern (2^-23 of it is log2 q, linear within an octave): kA
+// intervals per octave of z^2 and kB per unit of z = r / beta, from z = kZMin. The
+// octaves keep an interval narrow against its distance from the branch point at z = 0,
+// the linear part against the e^-z decay; kN intervals (the first and last unused)
+// reach z = 128. FP64 table:
+// degree 8, truncation below 6e-16 relative for C and dC/dbeta over nu in [0.05, 15]
+// (largest near z = 64; below 2e-16 for z < 2). FP32 table: degree 4, below 2.3e-9.
+template <bool kF32>
+struct TabShape;
+template <>
+struct TabShape<false> {
+    static constexpr int kDeg = 8, kPlanes = 5, kN = 832;
+    static constexpr double kA = 10.0, kB = 3.2, kZMin = 0x1p-14;
+};
+template <>
+struct TabShape<true> {
+    static constexpr int kDeg = 4, kPlanes = 2, kN = 1075;
+    static constexpr double kA = 8.0, kB = 6.0, kZMin = 0x1p-12;
+};
+
+// The interval rule of a call and the scale of the FP32 table's argument (1 / beta^2).
+struct TabIndex {
+    float fa, fb, fc, vs;
+};
+
+__device__ __forceinline__ float tab_pos(const TabIndex& X, float q)
+{
+    return fmaf((float)__float_as_uint(q), X.fa, fmaf(__builtin_amdgcn_sqrtf(q), X.fb, X.fc));
+}
+
+typedef double tab2_t __attribute__((ext_vector_type(2)));
+typedef float tab4f_t __attribute__((ext_vector_type(4)));
+
+// A table is kPlanes planes of kN 16-byte slots, then the count of finished
+// workgroups. Slot i of the planes in turn: {centre, c0}, {c1, c2}, ... {c7, c8}, the
+// polynomial in q - centre (r^2 units); FP32 table: {centre, c0}, {c1 .. c4 in FP32,
+// relative to c0}, the polynomial's argument scaled by 1 / beta^2. Planes rather than records: the 16
+// slots of one LDS bank row are then 16 neighbouring intervals.
+template <bool kF32>
+constexpr size_t tab_bytes()
+{
+    return (size_t)TabShape<kF32>::kPlanes * TabShape<kF32>::kN * 16 + 16;
+}
+
+// Which function a table holds.
+enum TabFn { TAB_C = 0, TAB_DBETA = 1, TAB_DNU = 2 };
+
+// The function of a call: host values. pref = ln c, scale = sigma2 c, c = 2^(1-nu) /
+// Gamma(nu); psi = digamma(nu), for dC/dnu.
+struct TabParams {
+    double sigma2, beta, inv_beta, nu, pref, psi, scale;
+};
+TabParams tab_params(const bk_params* prm, double psi);
+
+// Least FP32 q with tab_pos(q) >= t (tab_pos increases with q): a search over the bit
+// patterns, with the evaluation's own arithmetic.
+__device__ __forceinline__ float tab_bound(const TabIndex& X, float t)
+{
+    unsigned lo = 0u;
+    for (int b = 30; b >= 0; --b) {
+        const unsigned m = lo | (1u << b);
+        if (m < 0x7f800000u && tab_pos(X, __uint_as_float(m)) < t) lo = m;
+    }
+    return __uint_as_float(lo + 1u);
+}
+
+// cos(n pi (j + 1/2) / M) and the monomial coefficients of T_n.
+template <int M>
+struct ChebTab {
+    double cosn[M][M], mono[M][M];
+};
+#include "bk_cheb.inc"      // kCheb5, kCheb9
+
+template <bool kF32>
+__device__ __forceinline__ const ChebTab<TabShape<kF32>::kDeg + 1>& cheb_tab()
+{
+    if constexpr (kF32) return kCheb5;
+    else return kCheb9;
+}
+
+// A builder's workgroup is one wave: kPer intervals, one lane per Chebyshev point.
+template <bool kF32>
+struct TabWave {
+    static constexpr int kM = TabShape<kF32>::kDeg + 1, kPer = 64 / kM;
+    static constexpr int kBlocks = (TabShape<kF32>::kN + kPer - 1) / kPer;
+    int g, j, i;          // interval within the wave, Chebyshev point, interval
+    double c, w, z;       // centre and half-width in r^2, the lane's point z = r / beta
+};
+
+// The lane's point. Idle lanes (past kPer intervals) repeat the last interval's first.
+template <bool kF32>
+__device__ __forceinline__ TabWave<kF32> tab_point(const TabIndex& X, double inv_beta, int block)
+{
+    TabWave<kF32> t;
+    const int lane = threadIdx.x & 63;
+    t.g = min(lane / TabWave<kF32>::kM, TabWave<kF32>::kPer - 1);
+    t.j = lane < TabWave<kF32>::kPer * TabWave<kF32>::kM ? lane - t.g * TabWave<kF32>::kM : 0;
+    const int i0 = block * TabWave<kF32>::kPer;
+    t.i = i0 + t.g;
+    const float qb = tab_bound(X, (float)(i0 + lane));      // lane's boundary
+    const double ql = (double)__shfl(qb, t.g, 64), qh = (double)__shfl(qb, t.g + 1, 64);
+    t.c = 0.5 * (ql + qh);
+    t.w = 0.5 * (qh - ql);
+    t.z = sqrt(fma(t.w, cheb_tab<kF32>().cosn[1][t.j], t.c)) * inv_beta;
+    return t;
+}
+
+// Fits the wave's intervals to the lanes' samples f and writes their slots. The
+// Chebyshev coefficients come from the differences to the middle sample and are then
+// expanded in powers, so that neither sum rounds at the size of f. sh: 64 doubles.
+template <bool kF32>
+__device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex& X, double* sh, char* table)
+{
+    constexpr int M = TabWave<kF32>::kM, kN = TabShape<kF32>::kN;
+    const ChebTab<M>& C = cheb_tab<kF32>();
+    const int lane = threadIdx.x & 63;
+    const bool live = lane < TabWave<kF32>::kPer * M && t.i < kN;
+    sh[lane] = f;
+    __syncthreads();
+    const double* s = sh + t.g * M;
+    const double mid = s[M / 2];
+    double cn = 0.0;
+    for (int j = 0; j < M; ++j) cn = fma(s[j] - mid, C.cosn[t.j][j], cn);
+    cn *= (t.j == 0 ? 1.0 : 2.0) / M;
+    __syncthreads();
+    sh[lane] = cn;
+    __syncthreads();
+    double a = 0.0;
+    for (int n = M - 1; n >= 0; --n) a = fma(C.mono[n][t.j], s[n], a);
+    if (t.j == 0) a += mid;
+    // powers of q - centre (FP32 table: of the scaled difference)
+    const double iw = 1.0 / (kF32 ? t.w * (double)X.vs : t.w);
+    for (int k = 0; k < t.j; ++k) a *= iw;
+    if (kF32) {
+        __syncthreads();
+        sh[lane] = a;
+        __syncthreads();
+        if (t.j > 0) a /= s[0];
+    }
+    if (!live) return;
+    double* slots = (double*)table;
+    if (t.j == 0) slots[2 * t.i] = t.c;
+    if (kF32 && t.j > 0) {
+        ((float*)table)[4 * (kN + t.i) + t.j - 1] = (float)a;
+    } else {
+        const int e = t.j + 1;
+        // the first and last slots stand for everything out of the table
+        slots[2 * ((e >> 1) * kN + t.i) + (e & 1)] = t.j == 0 && (t.i == 0 || t.i == kN - 1) ? __builtin_nan("") : a;
+    }
+}
+
+// scale z^e e^(delta - z) hs, the quadrature's assembly of a sample: the power taken as
+// such and the roundings of delta - z and of the products carried (the samples set the
+// error of every entry; the per-entry kernels add these factors' logarithms instead).
+__device__ __forceinline__ double tab_assemble(double scale, double z, double e, double delta, double hs)
+{
+    const double d = delta - z, lo = two_sum_err(delta, -z, d);
+    const double w = pow(z, e), x = exp(d);
+    const double p = scale * w, pe = fma(scale, w, -p), q = x * hs, qe = fma(x, hs, -q);
+    const double v = p * q, ve = fma(p, q, -v);
+    return v + fma(pe, q, fma(p, qe, fma(v, lo, ve)));
+}
+
+// The count of finished workgroups of the evaluation kernel, cleared by the builder.
+template <bool kF32>
+__device__ __forceinline__ unsigned int* tab_done(char* table)
+{
+    return (unsigned int*)(table + (size_t)TabShape<kF32>::kPlanes * TabShape<kF32>::kN * 16);
+}
+
+constexpr int64_t kTabMinEntries = 500000;
+
+// Whether a call takes the tables, and where in an output of elems elements of
+// elem_bytes its table is built: its last bytes, which the evaluation writes last.
+bool table_route(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, int64_t min_entries);
+char* table_in_output(void* out, int64_t elems, int elem_bytes, bool f32_table, int64_t* first);
+TabIndex tab_index(double beta, bool f32_table);
+
+// Evaluation over all tiles from the table in `out` (built on the same stream).
+// cold_mode: the per-entry form of the distances outside the table's range.
+// fn: a TabFn.
+int launch_table_eval(const bk_locs* locs, const TabParams& P, int32_t tile_size, int32_t lower_only, int fn,
+                      int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream);
+// Plain and mixed forms: builds the table and evaluates. bk_status.
+int matern_table_tiles(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, void* out,
+                       hipStream_t stream);
+int matern_grad_table_tiles(const bk_locs* locs, const bk_params* prm, double psi, int32_t tile_size,
+                            int32_t lower_only, void* const outs[3], hipStream_t stream);
+
+}  // namespace bk

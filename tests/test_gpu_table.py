@@ -1,0 +1,131 @@
+"""GPU test of the interpolated Matern builds: large calls take a table of the
+quadrature over intervals of r^2; the per-entry kernels still run for given window
+thresholds, so the same call with the defaults written out (L = 36, 35 plain; 15,
+14.5 mixed and learned) is the reference, entry by entry.
+
+Bars: each side is within 1e-13 (plain) or 2e-6 (mixed, learned) of the exact value,
+so they differ by at most twice that, plus one FP32 rounding a side for FP32 output.
+Tilings: every row-block width, one tile, a tile larger than n, 3 x 3 tiles, ragged
+edges. The points hold an exact duplicate, a pair closer than the table reaches
+(z < 2^-14) and one farther (z > 128). The output buffer starts one element past an
+aligned address and is guarded on both sides."""
+import math
+import os
+
+import numpy as np
+import pytest
+
+from gpu_util import TOL_MIXED, TOL_PLAIN, to_dev
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHAPES = [(720, 720, 0), (1031, 64, 1), (1031, 128, 1), (1100, 257, 0), (1300, 5000, 1), (760, 3, 0), (1490, 500, 1)]
+FORMS = [("plain", "f64"), ("plain", "f32"), ("mixed", "f32"), ("learned", "f32")]
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_00356_amd import api
+    return api
+
+
+@pytest.fixture(scope="module")
+def model(api):
+    return api.Model(os.path.join(ROOT, "paper_2502_00356_amd", "models", "window_mlp.bin"))
+
+
+def _points(n, beta):
+    from paper_2502_00356_amd import workloads as w
+    xy = w.uniform_locations(n, seed=900 + n)
+    xy[5] = xy[n // 2]                               # r == 0 off the diagonal
+    xy[n - 2] = xy[9] + [1e-6 * beta, 0.0]           # z = 1e-6
+    xy[n - 1] = [0.5 + 200.0 * beta, 0.5]            # z near 200
+    return xy, to_dev(xy[:, 0]), to_dev(xy[:, 1])
+
+
+def _close(got, ref, tol, f32, scale=None):
+    got, ref = got.double(), ref.double()
+    scale = ref.abs() if scale is None else scale
+    if f32:
+        tol, floor = tol + 2.0 ** -23, 2.0 ** -149 + 1e-36 * tol
+    else:
+        floor = 1e-300
+    return bool(((got - ref).abs() <= tol * scale + floor).all())
+
+
+def _guarded(elems, dt):
+    import torch
+    buf = torch.full((elems + 129,), -7.0, dtype=dt, device="cuda")
+    return buf, buf[65:65 + elems]
+
+
+def _untouched(buf, elems):
+    return bool((buf[:65] == -7.0).all()) and bool((buf[65 + elems:] == -7.0).all())
+
+
+@pytest.mark.parametrize("n,ts,lower", SHAPES)
+@pytest.mark.parametrize("mode,odt", FORMS)
+def test_table_matches_entries(api, model, mode, odt, n, ts, lower):
+    import torch
+    beta, nu, s2 = 0.07, 1.9, 1.3
+    _, lx, ly = _points(n, beta)
+    f32 = odt == "f32"
+    dt, od = (torch.float32, api.OUT_F32) if f32 else (torch.float64, api.OUT_F64)
+    L, Lq = (36.0, 35.0) if mode == "plain" else (15.0, 14.5)
+    elems = api.matern_out_elems(n, ts, lower)
+    kw = dict(mode=mode, out_dtype=od, model=model)
+    ref = api.matern_tiles(lx, ly, s2, beta, nu, ts, lower, L_window=L, L_quad=Lq, **kw)
+    buf, out = _guarded(elems, dt)
+    api.matern_tiles(lx, ly, s2, beta, nu, ts, lower, out=out, **kw)
+    torch.cuda.synchronize()
+    assert _untouched(buf, elems)
+    assert _close(out, ref, 2 * (TOL_PLAIN if mode == "plain" else TOL_MIXED), f32)
+    assert int((out == s2).sum()) >= n               # the diagonal
+    stats = torch.zeros(api.STATS_LEN, dtype=torch.int64, device="cuda")
+    counted = api.matern_tiles(lx, ly, s2, beta, nu, ts, lower, stats=stats, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(counted, out) and int(stats[api.STAT_ENTRIES]) > 0
+
+
+@pytest.mark.parametrize("nu,beta", [(0.02, 0.1), (0.5, 0.01), (3.0, 0.3), (9.5, 0.05), (15.5, 0.1)])
+@pytest.mark.parametrize("mode,odt", FORMS)
+def test_table_orders_and_ranges(api, model, mode, odt, nu, beta):
+    """Orders and ranges near the ends of what takes the tables."""
+    import torch
+    n, ts = 900, 256
+    _, lx, ly = _points(n, beta)
+    L, Lq = (36.0, 35.0) if mode == "plain" else (15.0, 14.5)
+    kw = dict(mode=mode, out_dtype=api.OUT_F32 if odt == "f32" else api.OUT_F64, model=model)
+    ref = api.matern_tiles(lx, ly, 0.8, beta, nu, ts, 0, L_window=L, L_quad=Lq, **kw)
+    out = api.matern_tiles(lx, ly, 0.8, beta, nu, ts, 0, **kw)
+    torch.cuda.synchronize()
+    assert _close(out, ref, 2 * (TOL_PLAIN if mode == "plain" else TOL_MIXED), odt == "f32")
+
+
+@pytest.mark.parametrize("odt", ["f64", "f32"])
+@pytest.mark.parametrize("n,ts,lower,nu", [(720, 720, 0, 0.8), (1031, 64, 1, 2.3), (1100, 257, 0, 1.0), (1490, 500, 1, 6.5)])
+def test_gradient_table_matches_entries(api, odt, n, ts, lower, nu):
+    """dC/dnu is a difference of two terms: its bar is relative to their sizes."""
+    import torch
+    beta, s2 = 0.07, 1.3
+    xy, lx, ly = _points(n, beta)
+    f32 = odt == "f32"
+    dt, od = (torch.float32, api.OUT_F32) if f32 else (torch.float64, api.OUT_F64)
+    elems = api.matern_out_elems(n, ts, lower)
+    ref = api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, lower, L_window=36.0, L_quad=35.0)
+    bufs = {k: _guarded(elems, dt) for k in ("c", "dbeta", "dnu")}
+    out = api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, lower, out_dtype=od, out={k: v[1] for k, v in bufs.items()})
+    only = api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, lower, out_dtype=od, want=("dnu",))
+    torch.cuda.synchronize()
+    assert torch.equal(only["dnu"], out["dnu"])
+    for k in bufs:
+        assert _untouched(bufs[k][0], elems), k
+    assert _close(out["c"], ref["c"], 2 * TOL_PLAIN, f32)
+    assert _close(out["dbeta"], ref["dbeta"], 2 * TOL_PLAIN, f32)
+    # |C (ln z - ln 2 - psi)| + |the other term|, with |ln z| <= 14 over these points
+    scale = ref["c"].abs() * (14.0 + math.log(2.0) + 3.0) * 2 + ref["dnu"].abs()
+    assert _close(out["dnu"], ref["dnu"], 2 * TOL_PLAIN, f32, scale)

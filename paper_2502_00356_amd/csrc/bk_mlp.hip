@@ -35,6 +35,7 @@
 
 #include "../../include/besselk.h"
 #include "bk_internal.hpp"
+#include "bk_table.hpp"
 
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -58,6 +59,8 @@ static_assert(kNParam == BK_MLP_NPARAM, "parameter count");
 // node, relative to the whole. With the L = 15 window (quadrature error <= ~2.5e-7)
 // and FP32 node rounding (~2e-7) this keeps the total well inside 2e-6.
 constexpr float kTailTol = 3e-7f;
+// FP32 output from this many entries on takes the interpolation table.
+constexpr int64_t kTabMinLearned = 65536;
 constexpr int kTableSize = 1024;       // Matern: MLP tabulated over log10 x at fixed nu
 // Standalone K_nu: prediction cells over the training box, log10 x by nu.
 constexpr int kCellsLx = 512, kCellsNu = 64, kCells = kCellsLx * kCellsNu;
@@ -896,7 +899,8 @@ __global__ __launch_bounds__(256) void k_besselk_fallback(const double* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Matern, learned form: the MLP is tabulated once per launch over log10 x on
+// Matern, learned form, per entry (FP64 output, small calls, given thresholds, and the
+// counts of calls with statistics): the MLP is tabulated once per launch over log10 x on
 // kTableSize points of the training box at the launch's nu, and each interval
 // between two points gets the quadrature plan of the union of their predictions
 // (k_matern_plans). An entry takes its interval's plan; entries that fail the
@@ -1015,6 +1019,88 @@ __global__ __launch_bounds__(256) void k_matern_plans(MlpDev M, double nu, doubl
     q5f[2] = (float)h;
     q5f[3] = __int_as_float(raised ? 1 : 0);
     r[5] = q5f;
+}
+
+// Interpolation table of the learned form (bk_table.hpp): one lane per Chebyshev point.
+// The points of an interval share the union of the network's windows at them, with the
+// model's margins and the step floor at the largest z, so that the samples are those of
+// one smooth quadrature; node terms in FP64 relative to the largest. An interval with a
+// point outside the training box, or whose window fails the acceptance tests at a point,
+// takes the plain form instead. kSolver: windows from the plain solver (L, Lqs).
+// 316 x 316 sites, FP32: 17.5 ms per entry (121 VALU instructions each), 5.0 ms by the
+// table, bound by the 20 GB written; 517 sites: five launches and 56 us, two and 36.
+template <bool kSolver>
+__global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P, TabIndex X, double Lq, double L,
+                                                          double Lqs, char* table)
+{
+    __shared__ double s_tab[kTabLen], sh[64];
+    __shared__ float sy[4][64];
+    __shared__ int s_bad[64];
+    stage_tab(s_tab);
+    const TabWave<true> t = tab_point<true>(X, P.inv_beta, blockIdx.x);
+    const int lane = threadIdx.x & 63;
+    const float lx = log10f((float)t.z), nuf = (float)P.nu;
+    float y0, y1, y2;
+    if constexpr (kSolver) solver_prediction(M, lx, nuf, L, Lqs, y0, y1, y2);
+    else mlp_wave(M, (lx - M.cx) * M.isx, (nuf - M.cnu) * M.isnu, y0, y1, y2);
+    sy[0][lane] = y0;
+    sy[1][lane] = y1;
+    sy[2][lane] = y2;
+    sy[3][lane] = (float)t.z;
+    s_bad[t.g] = 0;
+    __syncthreads();
+    float zmax = 0.0f;
+    for (int k = t.g * TabWave<true>::kM; k < (t.g + 1) * TabWave<true>::kM; ++k) {
+        y0 = fminf(y0, sy[0][k]);
+        y1 = fmaxf(y1, sy[1][k]);
+        y2 = fmaxf(y2, sy[2][k]);
+        zmax = fmaxf(zmax, sy[3][k]);
+    }
+    double tlo, thi;
+    int N;
+    bool raised;
+    decode_window(M, y0, y1, y2, P.nu, (double)zmax, Lq, tlo, thi, N, raised);
+    bool ok = in_box(M, lx, nuf) && thi > tlo && isfinite(thi) && N >= 0;
+    double f = 0.0;
+    if (ok) {
+        const double h = (thi - tlo) / (double)N;
+        const double c0 = cosh(tlo), c1 = cosh(tlo + h), kappa = 2.0 * cosh(h), nh = P.nu * h;
+        auto exponent = [&](int m, double c) { return fma((double)m, nh, -t.z * (c - c0)); };
+        double c = c0, cn = c1, big = 0.0;
+        for (int m = 0; m <= N; ++m) {
+            big = fmax(big, exponent(m, c));
+            const double c2 = fma(kappa, cn, -c);
+            c = cn;
+            cn = c2;
+        }
+        const double rho = exp_tab(-2.0 * nh, s_tab), omr = 1.0 - rho;
+        double Q = 1.0 + exp_tab(-2.0 * P.nu * tlo, s_tab), S = 0.0, e0 = 0.0, e1 = 0.0, eprev = 0.0, elast = 0.0;
+        c = c0;
+        cn = c1;
+        for (int m = 0; m <= N; ++m) {
+            eprev = elast;
+            elast = exp_tab(exponent(m, c) - big, s_tab) * Q;
+            if (m == 0) e0 = elast;
+            if (m == 1) e1 = elast;
+            S = fma(m == 0 || m == N ? 0.5 : 1.0, elast, S);
+            Q = fma(Q, rho, omr);
+            const double c2 = fma(kappa, cn, -c);
+            c = cn;
+            cn = c2;
+        }
+        const double D = P.nu * tlo - kLn2 - t.z * (c0 - 1.0);
+        ok = S > 0.0 && isfinite(S) && right_tail_ok((float)eprev, (float)elast, (float)S) &&
+             (!(tlo > 0.0) || left_tail_ok(t.z, P.nu, (float)tlo, (float)h, (float)e0, (float)e1, (float)D, (float)S));
+        f = tab_assemble(P.scale, t.z, P.nu, D + big, h * S);
+    }
+    if (!ok) s_bad[t.g] = 1;
+    __syncthreads();
+    if (s_bad[t.g]) {
+        const Solved s = plain_solve(P.nu, t.z, kDefaultLPlain, kDefaultLqPlain, rule_tab(), s_tab);
+        f = tab_assemble(P.scale, t.z, P.nu, s.delta, s.p.h * sum_f64(P.nu, t.z, s.p, s.E, s.Ei, s.Sr, s_tab));
+    }
+    tab_fit<true>(t, f, X, sh, table);
+    if (blockIdx.x == 0 && lane == 0) *tab_done<true>(table) = 0u;
 }
 
 // log(1 + u) for |u| <= 0.02 in FP32, by its Taylor series through u^4: the
@@ -1745,13 +1831,11 @@ size_t matern_learned_workspace_bytes(int64_t n, int32_t tile_size, int32_t lowe
     return kMaternTabBytes + (((size_t)words * 4 + 255) & ~(size_t)255);
 }
 
-int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, void* out,
-                      double L, double Lq, void* workspace, size_t workspace_bytes, hipStream_t stream)
+// The per-entry learned form (arguments checked; need: its workspace bytes).
+static int matern_learned_entries(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only,
+                                  void* out, double L, double Lq, void* workspace, size_t need, hipStream_t stream)
 {
     const bk_model* m = prm->model;
-    if (!m || !m->params || !m->trained) return BK_ENOMODEL;
-    const size_t need = matern_learned_workspace_bytes(locs->n, tile_size, lower_only);
-    if (!workspace || workspace_bytes < need) return BK_ENOMEM;
     char* ws = (char*)workspace;
     float* table = (float*)(ws + kMaternTableOff);
     float4_t* rec = (float4_t*)(ws + kMaternRecOff);
@@ -1821,6 +1905,40 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
                         pref, L, Lq, (const unsigned int*)bitmap, nwords, (float*)out, prm->stats)
                : launch(k_matern_fallback<double>, fgrid, dim3(256), stream, locs->x, locs->y, g, prm->sigma2, ib,
                         nu, pref, L, Lq, (const unsigned int*)bitmap, nwords, (double*)out, prm->stats);
+}
+
+
+int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, void* out,
+                      double L, double Lq, void* workspace, size_t workspace_bytes, hipStream_t stream)
+{
+    const bk_model* m = prm->model;
+    if (!m || !m->params || !m->trained) return BK_ENOMODEL;
+    const size_t need = matern_learned_workspace_bytes(locs->n, tile_size, lower_only);
+    if (!workspace || workspace_bytes < need) return BK_ENOMEM;
+    // FP32 output by interpolation (bk_table.hpp). A call with statistics first runs the
+    // per-entry form, which counts, and is then written like any other.
+    if (prm->out_dtype == BK_OUT_F32 && table_route(locs, prm, tile_size, lower_only, kTabMinLearned)) {
+        if (prm->stats) {
+            const int st = matern_learned_entries(locs, prm, tile_size, lower_only, out, L, Lq, workspace, need, stream);
+            if (st != BK_OK) return st;
+        }
+        const TabParams P = tab_params(prm, 0.0);
+        const TabIndex X = tab_index(prm->beta, true);
+        int64_t first;
+        char* tab = table_in_output(out, bk_matern_out_elems(locs->n, tile_size, lower_only), 4, true, &first);
+        const MlpDev M = make_dev(m);
+        int st = m->table_source == BK_TABLE_SOLVER
+                     ? launch(k_tab_build_learned<true>, dim3(TabWave<true>::kBlocks), dim3(64), stream, M, P, X, Lq,
+                              m->train_L[0], m->train_L[1], tab)
+                     : launch(k_tab_build_learned<false>, dim3(TabWave<true>::kBlocks), dim3(64), stream, M, P, X, Lq,
+                              0.0, 0.0, tab);
+        if (st != BK_OK) return st;
+        if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
+        st = launch_table_eval(locs, P, tile_size, lower_only, TAB_C, BK_MIXED_F32C, true, BK_OUT_F32, out, stream);
+        if (st != BK_OK) return st;
+        return mark_kernel_event(prm, 1, stream) == hipSuccess ? BK_OK : BK_EHIP;
+    }
+    return matern_learned_entries(locs, prm, tile_size, lower_only, out, L, Lq, workspace, need, stream);
 }
 
 }  // namespace bk

@@ -100,12 +100,13 @@ template <int MODE>
 __device__ __forceinline__ double matern_entry(double nu, double z, double lz, double sigma2, double pref, double L,
                                                double Lq, const double* T, Solved& s)
 {
-    s = plain_solve(nu, z, L, Lq, rule_tab(), T);
     double hs;
     if constexpr (MODE == BK_PLAIN_F64) {
+        s = plain_plan(nu, z, L, Lq, rule_tab(), T);
         hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, T);
         hs = fma(hs, s.dlo, hs);
     } else {
+        s = plain_solve(nu, z, L, Lq, rule_tab(), T);
         hs = s.p.h * sum_mixed(nu, z, s.p, s.A, T);
     }
     return sigma2 * exp(pref + nu * lz + (s.delta - z)) * hs;
@@ -116,7 +117,7 @@ __device__ __forceinline__ double matern_dbeta(double nu, double z, double lz, d
                                                double pref, double L, double Lq, const double* T)
 {
     const double nu1 = fabs(nu - 1.0);
-    const Solved s1 = plain_solve(nu1, z, L, Lq, rule_tab(), T);
+    const Solved s1 = plain_plan(nu1, z, L, Lq, rule_tab(), T);
     const double hs1 = s1.p.h * sum_f64(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
     return sigma2 * inv_beta * exp(pref + (nu + 1.0) * lz + (s1.delta - z)) * fma(hs1, s1.dlo, hs1);
 }

@@ -76,7 +76,12 @@ __device__ __forceinline__ double assemble(double z, double delta, double hs, in
 {
     if (result == BK_RESULT_SCALED) return exp(delta) * hs;
     if (result == BK_RESULT_LOG) return (delta - z) + log(hs);
-    if (z < 708.0) return exp(-z) * exp(delta) * hs;   // exp(-z) still a normal number
+    const double d = delta - z;
+    if (d > -700.0 && z < 708.0) {                     // e^d a normal number; its argument's rounding carried
+        const double v = exp(d) * hs;
+        return fma(v, two_sum_err(delta, -z, d), v);
+    }
+    if (z < 708.0) return exp(-z) * exp(delta) * hs;
     // subnormal range: e^(-z) formed 2^64 larger, product scaled back (one rounding)
     return ldexp(exp(64.0 * kLn2 - z) * exp(delta) * hs, -64);
 }
@@ -187,7 +192,8 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
         out[(int64_t)blockIdx.x * kSolveBlock + li] = temme_result(v2, z2, result);
         li = -1;
     } else if (li >= 0) {
-        sv = plain_solve(v2, z2, L, Lq, rule_tab(), s_tab);
+        if constexpr (MODE == BK_PLAIN_F64) sv = plain_plan(v2, z2, L, Lq, rule_tab(), s_tab);
+        else sv = plain_solve(v2, z2, L, Lq, rule_tab(), s_tab);
     }
     // phase 2 -> 3: sort by node count
     const int nkey = li < 0 ? 0 : (sv.p.N < 63 ? sv.p.N : 63);
@@ -331,7 +337,7 @@ __global__ __launch_bounds__(256, 3) void k_besselk_deriv(const double* __restri
             rn = copysign(0.0, nr);
         } else {
             const RuleTable& R = rule_tab();
-            const Solved s0 = plain_solve(v, z, L, Lq, R, s_tab);
+            const Solved s0 = plain_plan(v, z, L, Lq, R, s_tab);
             double hs0 = s0.p.h * sum_f64(v, z, s0.p, s0.E, s0.Ei, s0.Sr, s_tab);
             hs0 = fma(hs0, s0.dlo, hs0);
             rk = assemble(z, s0.delta, hs0, result);
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(256, 3) void k_besselk_deriv(const double* __restri
             rx = 0.0;
             if (dkdx) {
                 const double v1 = fabs(v - 1.0);
-                const Solved s1 = plain_solve(v1, z, L, Lq, R, s_tab);
+                const Solved s1 = plain_plan(v1, z, L, Lq, R, s_tab);
                 double hs1 = s1.p.h * sum_f64(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, s_tab);
                 hs1 = fma(hs1, s1.dlo, hs1);
                 nodes += (unsigned long long)(s1.p.N + 1);

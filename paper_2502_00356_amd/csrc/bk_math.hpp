@@ -141,6 +141,24 @@ __device__ __forceinline__ double exp_tab(double x, const double* T)
     return ldexp(T[ki & 63] * p, ki >> 6);
 }
 
+// e^x as exp_tab for a finite x, as the node walks of the plain form call it: the
+// integer is rounded to nearest by adding 1.5 2^52 (its low word is the integer), which
+// halves the remainder (|f| <= ln2/128: degree 5, truncation below 4e-17) and leaves 13
+// instructions of 18.
+__device__ __forceinline__ double exp_node(double x, const double* T)
+{
+    const double m = fma(x, 92.332482616893656, 6755399441055744.0);
+    const int ki = __double2loint(m);
+    const double f = fma(-(m - 6755399441055744.0), 0.010830424696249145, x);
+    double p = 1.0 / 120.0;
+    p = fma(p, f, 1.0 / 24.0);
+    p = fma(p, f, 1.0 / 6.0);
+    p = fma(p, f, 0.5);
+    p = fma(p, f, 1.0);
+    const double t = T[ki & 63];
+    return ldexp(fma(t * f, p, t), ki >> 6);
+}
+
 // log(1 + p) for 0 <= p <= 1 from the same tables: with j = floor(64 p) and
 // c = 1 + j/64, log(1 + p) = log c + log(1 + r), r = (p - j/64) / c in [0, 1/64)
 // (p - j/64 is exact), the second by its Taylor series through r^9 (truncation
@@ -434,6 +452,128 @@ __device__ inline Solved plain_solve(double nu, double x, double L, double Lq, c
     return s;
 }
 
+// Step floor for the learned forms and the plain form: the strip bound of node_step at a single
+// half-width, a = min(sqrt(2 (Lq + ln 2) / (x + nu + 1)), 1.3) (the maximiser of
+// the bound's small-a expansion, capped), in FP32 with 1 - cos a = 2 sin^2(a/2),
+// shrunk by 0.1% so that rounding can only add nodes. Any a in (0, pi/2) gives an
+// admissible step; over the grid law this one is within 6% of the best of the 15
+// candidates the plain solver tries (median 0.5%), for a fraction of the work.
+__device__ __forceinline__ float node_step_learned(float nu, float x, float Lq)
+{
+    const float c = Lq + 0.693147181f, nu1 = nu + 1.0f;
+    const float a = fminf(__builtin_amdgcn_sqrtf(2.0f * c * __builtin_amdgcn_rcpf(x + nu1)), 1.3f);
+    const float s = __sinf(0.5f * a);
+    // cos a >= cos 1.3 > 0.26: the hardware logarithm needs no range handling
+    const float den = c + 2.0f * x * s * s - nu1 * 0.69314718f * __builtin_amdgcn_logf(__cosf(a));
+    return 6.28318531f * 0.999f * a * __builtin_amdgcn_rcpf(den);
+}
+
+// The plain form's plan without the exact solve: a window that contains {t : g(t) >=
+// g(t*) - L}, and a reference near t*, in FP32. A wider window costs nodes, not accuracy:
+// here at most ln 2 in L on a side and what two Newton steps leave (about 1% more nodes),
+// for 150 instructions in place of the roots' 1,500.
+//  - The reference tp = asinh(nu / x) >= t* (0 where nu^2 <= x, as t*); g(tp) <= g(t*), so
+//    a threshold below g(tp) lies below g(t*).
+//  - Right end: log cosh(nu t) grows by at most nu (t - tp), so G(tp + d) <= -F(d),
+//    F(d) = x (cosh(tp + d) - cosh tp) - nu d - L, convex: a Newton step from either side
+//    lands at or right of the root. cosh differences as 2 sinh sinh (no cancellation).
+//  - Left end: log cosh(nu t) <= nu t and g(tp) >= nu tp - ln 2 - x cosh tp, so G(tp - e)
+//    <= F(e) = L + ln 2 - nu e + x (cosh tp - cosh(tp - e)), concave and decreasing: a Newton
+//    step lands at or past the root; F(tp) >= 0 leaves the window starting at 0.
+// FP32 rounding moves an end by 1e-5 of its distance; L carries 0.01 for it. For 1e-12 <=
+// x <= 1e5, nu <= 1e4, L <= 500 (plan_fast_ok); plain_solve covers the rest.
+__device__ __forceinline__ bool plan_fast_ok(double nu, double x, double L)
+{
+    return x >= 1e-12 && x <= 1e5 && nu <= 1e4 && L <= 500.0;
+}
+
+__device__ __forceinline__ void window_fast(float nu, float x, float L, float& t0, float& t1, float& tp)
+{
+    auto ex = [](float y) { return __builtin_amdgcn_exp2f(y * 1.44269504f); };
+    L += 0.01f;
+    const float ix = __builtin_amdgcn_rcpf(x);
+    tp = 0.0f;
+    if (nu * nu > x) {
+        const float y = nu * ix;
+        tp = 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
+    }
+    const float E = ex(tp), Ei = __builtin_amdgcn_rcpf(E);
+    // start: the x term alone drops by L
+    const float ec = 0.5f * (E + Ei) - 1.0f + L * ix;
+    float d = fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + ec + __builtin_amdgcn_sqrtf(ec * (ec + 2.0f))) - tp, 1e-3f);
+    const float hx = 0.5f * x;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const float a = ex(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
+        const float b = E * a, bi = Ei * ai;                       // e^(tp + d/2)
+        const float F = hx * (a - ai) * (b - bi) - nu * d - L;     // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
+        const float D = hx * (b * a - bi * ai) - nu;
+        d -= F * __builtin_amdgcn_rcpf(D);
+    }
+    t1 = tp + d * 1.0001f;
+    t0 = 0.0f;
+    const float L2 = L + 0.69314718f;
+    const float e0 = L2 + x * (0.5f * (E + Ei) - 1.0f);
+    if (e0 < nu * tp) {
+        float e = e0 * __builtin_amdgcn_rcpf(nu);
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const float a = ex(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
+            const float b = E * ai, bi = Ei * a;                   // e^(tp - e/2)
+            const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
+            const float D = hx * (b * ai - bi * a) - nu;
+            e -= F * __builtin_amdgcn_rcpf(D);
+        }
+        t0 = fmaxf(tp - e * 1.0001f, 0.0f);
+    }
+}
+
+// expm1(y) for 0 <= y <= 1/8 (Taylor through y^10, truncation below 1e-18 relative).
+__device__ __forceinline__ double expm1_small(double y)
+{
+    double p = 1.0 / 3628800.0;
+    p = fma(p, y, 1.0 / 362880.0);
+    p = fma(p, y, 1.0 / 40320.0);
+    p = fma(p, y, 1.0 / 5040.0);
+    p = fma(p, y, 1.0 / 720.0);
+    p = fma(p, y, 1.0 / 120.0);
+    p = fma(p, y, 1.0 / 24.0);
+    p = fma(p, y, 1.0 / 6.0);
+    p = fma(p, y, 0.5);
+    return fma(p * y, y, y);
+}
+
+// Plan of the plain sum: the fast window where it applies, else the exact solve.
+__device__ inline Solved plain_plan(double nu, double x, double L, double Lq, const RuleTable& R, const double* T)
+{
+    if (!plan_fast_ok(nu, x, L)) return plain_solve(nu, x, L, Lq, R, T);
+    float t0f, t1f, tpf;
+    window_fast((float)nu, (float)x, (float)L, t0f, t1f, tpf);
+    const double t0 = (double)t0f;
+    Solved s;
+    const float wf = t1f - t0f;
+    float nf = ceilf(wf * __builtin_amdgcn_rcpf(node_step_learned((float)nu, (float)x, (float)Lq)));
+    nf = fminf(fmaxf(nf, (float)kNodeMin), (float)kNodeMax);
+    const float mf = fminf(rintf((tpf - t0f) * nf * __builtin_amdgcn_rcpf(wf)), nf);
+    const double h = ((double)t1f - t0) * recip((double)nf);
+    const double tref = fma((double)mf, h, t0);
+    const double em = expm1(0.5 * tref);
+    s.Sr = em * (em + 2.0);                            // expm1(t_ref), no cancellation
+    s.E = s.Sr + 1.0;
+    s.Ei = recip(s.E);
+    const double sh2 = 0.5 * fma(em, recip(em + 1.0), em);   // sinh(t/2) = (em + em / (em + 1)) / 2
+    s.p.tref = tref;
+    s.p.t0 = t0;
+    s.p.N = (int)nf;
+    s.p.mc = (int)mf;
+    s.p.h = h;
+    delta_dd(nu, tref, 2.0 * x * sh2 * sh2, s.delta, s.dlo);
+    s.A = s.B = 0.0;                                   // not used by the paired walk
+    s.gstar = 0.0;
+    s.t1 = (double)t1f;
+    return s;
+}
+
 // Geometric-progression state of one entry's node walk.
 struct Walk {
     double k, V, Bw, Bb, P;        // at the current node; k = m - mc (exact), u = k h
@@ -498,35 +638,39 @@ __device__ __forceinline__ void walk_step(Walk& w, int m)
 __device__ inline double sum_f64(double nu, double x, const Plan& p, double E, double Ei, double Sr, const double* T)
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
-    const double h = p.h, xh = 0.5 * x;
-    const double qm1 = expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
-    const double rho = exp_tab(-2.0 * nu * h, T), rhoi = recip(rho);
+    const double h = p.h, xh = 0.5 * x, nh = nu * h;
+    const double qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
+    const double rho = exp_tab(-2.0 * nh, T), rhoi = recip(rho);
     double V = 0.0, Bq = 1.0;                 // expm1(|w|), e^-|w|
     double SR = Sr, ER = Ei;                  // expm1(t_ref + |w|), e^-(t_ref + |w|)
     double PR = exp_tab(-2.0 * nu * p.tref, T), PL = PR;   // e^(-2 nu t) at nodes mc + j, mc - j
-    double S = 0.0, jd = 0.0;
-    for (int j = 0; j <= jmax; ++j) {
-        const double nuu = nu * (jd * h);     // j h formed per node: no drift
-        const double xs = xh * fma(V, Bq, V);
-        if (j <= nr) {
-            const double ss = fma(SR, ER, SR);
-            const double t = exp_tab(fma(-xs, ss, nuu), T) * (1.0 + PR);
-            S = fma((j == nr || (j == 0 && nl == 0)) ? 0.5 : 1.0, t, S);   // ends: node N; node 0 if mc = 0
-        }
-        if (j >= 1 && j <= nl) {
-            const double ss = fma(E, Bq, -Ei * (V + 1.0));
-            const double t = exp_tab(fma(xs, ss, -nuu), T) * (1.0 + PL);
-            S = fma(j == nl ? 0.5 : 1.0, t, S);                          // node 0
-        }
+    double jd = 0.0, S = 0.0, tr = 0.0, tl = 0.0;
+    // node mc: the exponent is 0; it is node 0 if mc = 0 and node N if mc = N
+    const double t0 = 1.0 + PR;
+    for (int j = 1; j <= jmax; ++j) {
+        jd += 1.0;
         V = fma(V, q, qm1);
         Bq *= qi;
+        const double nuu = jd * nh;           // nu j h formed per node: no drift
+        const double xs = xh * fma(V, Bq, V);
         SR = fma(SR, q, qm1);
         ER *= qi;
         PR *= rho;
         PL *= rhoi;
-        jd += 1.0;
+        if (j <= nr) {
+            const double e = exp_node(fma(-xs, fma(SR, ER, SR), nuu), T);
+            tr = fma(e, PR, e);
+            S += tr;
+        }
+        if (j <= nl) {
+            const double e = exp_node(fma(xs, fma(E, Bq, -Ei * (V + 1.0)), -nuu), T);
+            tl = fma(e, PL, e);
+            S += tl;
+        }
     }
-    return S;
+    // trapezoid ends: half of node N and of node 0
+    S = fma(-0.5, tr + tl, S);
+    return fma(nl == 0 || nr == 0 ? 0.5 : 1.0, t0, S);
 }
 
 // Node walk of the FP32-term forms (mixed and learned). Their terms need the
@@ -837,48 +981,55 @@ __device__ __forceinline__ double cheb_eval(const double* c, double u)
 }
 
 // K_nu(x) for 0 < x (intended for x < 0.1, where the series converges in a few
-// terms); returns K (not scaled).
+// terms); returns K (not scaled). One reciprocal a term: p and q take their divisors
+// k -+ mu from that of k^2 - mu^2, 1/Gamma(1 + mu) and 1/Gamma(1 - mu) give pi mu /
+// sin(pi mu) = Gamma(1 + mu) Gamma(1 - mu), and 2/x serves the logarithm, the series and
+// the recurrence, whose M factors of its rounding are taken out at the end.
 __device__ inline double temme_k(double nu, double x, const TemmeCoef& C)
 {
     const double M = floor(nu + 0.5);
-    const double mu = nu - M;
-    const double u = 8.0 * mu * mu - 1.0;
+    const double mu = nu - M, mu2 = mu * mu;
+    const double u = 8.0 * mu2 - 1.0;
     const double G1 = cheb_eval(C.g1, u), G2 = cheb_eval(C.g2, u);
     const double rgp = G2 - mu * G1;                   // 1 / Gamma(1 + mu)
     const double rgm = G2 + mu * G1;                   // 1 / Gamma(1 - mu)
-    const double lx = log(2.0 / x);
-    const double sg = mu * lx;
-    const double pimu = 3.14159265358979323846 * mu;
-    const double fact = fabs(pimu) < 1e-8 ? 1.0 + pimu * pimu / 6.0 : pimu / sin(pimu);
-    const double esg = exp(sg);
-    const double chs = 0.5 * (esg + 1.0 / esg);
-    const double shs_s = fabs(sg) < 1e-4 ? 1.0 + sg * sg / 6.0 : 0.5 * (esg - 1.0 / esg) / sg;
+    const double ix = 2.0 / x;
+    const double lx = log(ix);
+    const double sg = mu * lx, s2 = sg * sg;
+    const double fact = recip(rgp * rgm);              // pi mu / sin(pi mu)
+    const double esg = exp(sg), esi = recip(esg);
+    const double chs = 0.5 * (esg + esi);
+    // sinh(s) / s: the series below 0.3 (truncation 1e-17)
+    const double ser = fma(fma(fma(fma(fma(s2, 1.0 / 39916800.0, 1.0 / 362880.0), s2, 1.0 / 5040.0), s2, 1.0 / 120.0),
+                               s2, 1.0 / 6.0), s2, 1.0);
+    const double shs_s = fabs(sg) < 0.3 ? ser : 0.5 * (esg - esi) * recip(sg);
     double f = fact * (G1 * chs + G2 * shs_s * lx);
-    double p = 0.5 * esg / rgp;                        // (x/2)^-mu Gamma(1+mu) / 2
-    double q = 0.5 / (esg * rgm);                      // (x/2)^mu Gamma(1-mu) / 2
+    double p = 0.5 * esg * (rgm * fact);               // (x/2)^-mu Gamma(1+mu) / 2
+    double q = 0.5 * esi * (rgp * fact);               // (x/2)^mu Gamma(1-mu) / 2
     const double d = 0.25 * x * x;
     double c = 1.0, sum = f, sum1 = p;
     for (int k = 1; k < 200; ++k) {
         const double kk = (double)k;
-        f = (kk * f + p + q) / (kk * kk - mu * mu);
-        c *= d / kk;
-        p /= (kk - mu);
-        q /= (kk + mu);
+        const double r = recip(fma(kk, kk, -mu2));
+        f = (kk * f + p + q) * r;
+        c *= d * recip(kk);
+        p *= (kk + mu) * r;
+        q *= (kk - mu) * r;
         const double del = c * f;
         sum += del;
         sum1 += c * (p - kk * f);
         if (fabs(del) < 1.1102230246251565e-16 * fabs(sum)) break;
     }
     double km = sum;                                   // K_mu
-    double kp = sum1 * 2.0 / x;                        // K_{mu+1}
+    double kp = sum1 * ix;                             // K_{mu+1}
     // forward recurrence K_{eta+1} = (2 eta / x) K_eta + K_{eta-1}, eta = mu + 1, ..., nu - 1
     for (int j = 1; j < (int)M; ++j) {
-        const double eta = mu + (double)j;
-        const double kn = fma(2.0 * eta / x, kp, km);
+        const double kn = fma((mu + (double)j) * ix, kp, km);
         km = kp;
         kp = kn;
     }
-    return M >= 1.0 ? kp : km;
+    // kp grows as ix^M (its other term is below x^2 / 4 of it): ix = (2/x)(1 - e)
+    return M >= 1.0 ? fma(kp * M, 0.5 * fma(-x, ix, 2.0), kp) : km;
 }
 
 }  // namespace bk

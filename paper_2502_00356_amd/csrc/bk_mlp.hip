@@ -549,22 +549,6 @@ __device__ inline LearnedOut learned_walk(double x, double nu, const LearnedPlan
     return o;
 }
 
-// Step floor for the learned forms: the strip bound of node_step at a single
-// half-width, a = min(sqrt(2 (Lq + ln 2) / (x + nu + 1)), 1.3) (the maximiser of
-// the bound's small-a expansion, capped), in FP32 with 1 - cos a = 2 sin^2(a/2),
-// shrunk by 0.1% so that rounding can only add nodes. Any a in (0, pi/2) gives an
-// admissible step; over the grid law this one is within 6% of the best of the 15
-// candidates the plain solver tries (median 0.5%), for a fraction of the work.
-__device__ __forceinline__ float node_step_learned(float nu, float x, float Lq)
-{
-    const float c = Lq + 0.693147181f, nu1 = nu + 1.0f;
-    const float a = fminf(__builtin_amdgcn_sqrtf(2.0f * c * __builtin_amdgcn_rcpf(x + nu1)), 1.3f);
-    const float s = __sinf(0.5f * a);
-    // cos a >= cos 1.3 > 0.26: the hardware logarithm needs no range handling
-    const float den = c + 2.0f * x * s * s - nu1 * 0.69314718f * __builtin_amdgcn_logf(__cosf(a));
-    return 6.28318531f * 0.999f * a * __builtin_amdgcn_rcpf(den);
-}
-
 // Window from a prediction (normalised outputs y), with the model's margins; the
 // node count is the prediction or the step floor's count for this window,
 // whichever is larger (raised says which). N = -1 if the floor asks for more than
@@ -1096,7 +1080,7 @@ __global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P,
     if (!ok) s_bad[t.g] = 1;
     __syncthreads();
     if (s_bad[t.g]) {
-        const Solved s = plain_solve(P.nu, t.z, kDefaultLPlain, kDefaultLqPlain, rule_tab(), s_tab);
+        const Solved s = plain_plan(P.nu, t.z, kDefaultLPlain, kDefaultLqPlain, rule_tab(), s_tab);
         f = tab_assemble(P.scale, t.z, P.nu, s.delta, s.p.h * sum_f64(P.nu, t.z, s.p, s.E, s.Ei, s.Sr, s_tab));
     }
     tab_fit<true>(t, f, X, sh, table);

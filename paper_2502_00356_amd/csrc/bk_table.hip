@@ -17,7 +17,7 @@ __device__ inline double tab_sample(const TabParams& P, double z, int fn, const 
 {
     const double L = kDefaultLPlain, Lq = kDefaultLqPlain;
     const double nu = kGrad && fn == TAB_DBETA ? fabs(P.nu - 1.0) : P.nu;
-    const Solved s = plain_solve(nu, z, L, Lq, rule_tab(), T);
+    const Solved s = plain_plan(nu, z, L, Lq, rule_tab(), T);
     double hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, T);
     hs = fma(hs, s.dlo, hs);
     if (kGrad && fn == TAB_DBETA) return tab_assemble(P.scale * P.inv_beta, z, P.nu + 1.0, s.delta, hs);

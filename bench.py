@@ -476,7 +476,7 @@ def grid_bench(a, torch, api, workloads):
         "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "TOP/s (full-rate VALU lane-op slots)",
                      "frac": achieved / VALU_PEAK_TOPS,
                      "traffic": (tr["bytes"] if tr else None),
-                     "kernel": "k_besselk_learned" if form == "learned" else "k_besselk<%s>" % form,
+                     "kernel": "k_besselk_learned" if form == "learned" else "k_besselk_%s" % form,
                      "kernel_ms": head["kernel_ms"],
                      "work": "%.2f VALU issue clocks (full-rate lane-op slots) per trapezoid node x %d nodes per step"
                              % (NODE_SLOTS[form], head["node_total"]),

@@ -72,13 +72,14 @@ __device__ __forceinline__ bool special_value(double v, double z, int result, do
 }
 
 // Final assembly from exp(-x) exp(Delta) h S (see bk_math.hpp).
-__device__ __forceinline__ double assemble(double z, double delta, double hs, int result)
+__device__ __forceinline__ double assemble(double z, double delta, double hs, int result, const double* T)
 {
+    if (result == BK_RESULT_SCALED && fabs(delta) < 700.0) return exp_wide(delta, T) * hs;
     if (result == BK_RESULT_SCALED) return exp(delta) * hs;
     if (result == BK_RESULT_LOG) return (delta - z) + log(hs);
     const double d = delta - z;
-    if (d > -700.0 && z < 708.0) {                     // e^d a normal number; its argument's rounding carried
-        const double v = exp(d) * hs;
+    if (fabs(d) < 700.0 && z < 708.0) {                     // e^d a normal number; its argument's rounding carried
+        const double v = exp_wide(d, T) * hs;
         return fma(v, two_sum_err(delta, -z, d), v);
     }
     if (z < 708.0) return exp(-z) * exp(delta) * hs;
@@ -102,9 +103,9 @@ __device__ __forceinline__ bool temme_applies(double v, double z)
 }
 
 // K_nu(z) by Temme's series, as the requested result (K, e^z K or log K).
-__device__ __forceinline__ double temme_result(double v, double z, int result)
+__device__ __forceinline__ double temme_result(double v, double z, int result, const double* T)
 {
-    const double k = temme_k(v, z, temme_tab());
+    const double k = temme_k(v, z, temme_tab(), T);
     if (result == BK_RESULT_SCALED) return k * exp(z);
     if (result == BK_RESULT_LOG) return log(k);
     return k;
@@ -131,7 +132,7 @@ __device__ unsigned int block_sort_slot(int key, unsigned int* hist)
     return slot;
 }
 
-// Plain and mixed K_nu. A block of kSolveBlock entries is processed in three
+// Mixed K_nu. A block of kSolveBlock entries is processed in three
 // phases, with the lanes re-sorted between them through LDS so that each wave
 // holds entries that take the same branches and loop counts:
 //  1. entry order: special values; key = peak regime (0: nu^2 <= x, t* = 0;
@@ -143,10 +144,7 @@ __device__ unsigned int block_sort_slot(int key, unsigned int* hist)
 //     entry's own index.
 constexpr int kSolveBlock = 512;
 
-// Six waves per SIMD is what the block's LDS allows (three 512-lane blocks per CU);
-// without the hint the plain form takes 81 VGPRs and gets five (7% slower).
-template <int MODE>
-__global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_besselk(const double* __restrict__ nu,
+__global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_besselk_mixed(const double* __restrict__ nu,
                                                          const double* __restrict__ x,
                                                          double* __restrict__ out, int64_t n, int result,
                                                          double L, double Lq, 
@@ -154,11 +152,8 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
 {
     __shared__ unsigned int hist[64];
     __shared__ double s_tab[kTabLen];
-    // staged per entry between phases: v, z, t_ref, h, Delta, then for the plain
-    // form dlo, e^t_ref, e^-t_ref, expm1(t_ref) (paired walk), for the mixed form
-    // t0 and x cosh(t_ref) / 2
-    constexpr int kRows = MODE == BK_PLAIN_F64 ? 9 : 7;
-    __shared__ double s_d[kRows][kSolveBlock];
+    // staged per entry between phases: v, z, t_ref, h, Delta, t0, x cosh(t_ref) / 2
+    __shared__ double s_d[7][kSolveBlock];
     __shared__ int s_i[3][kSolveBlock];
     const int tid = threadIdx.x;
     if (tid < kTabLen) s_tab[tid] = rule_tab().tab[tid];   // read after the sorts' barriers
@@ -189,11 +184,10 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
     Solved sv;
     sv.p.N = -1;
     if (temme) {
-        out[(int64_t)blockIdx.x * kSolveBlock + li] = temme_result(v2, z2, result);
+        out[(int64_t)blockIdx.x * kSolveBlock + li] = temme_result(v2, z2, result, s_tab);
         li = -1;
     } else if (li >= 0) {
-        if constexpr (MODE == BK_PLAIN_F64) sv = plain_plan(v2, z2, L, Lq, rule_tab(), s_tab);
-        else sv = plain_solve(v2, z2, L, Lq, rule_tab(), s_tab);
+        sv = plain_solve(v2, z2, L, Lq, rule_tab(), s_tab);
     }
     // phase 2 -> 3: sort by node count
     const int nkey = li < 0 ? 0 : (sv.p.N < 63 ? sv.p.N : 63);
@@ -203,15 +197,8 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
     s_d[2][slot] = sv.p.tref;
     s_d[3][slot] = sv.p.h;
     s_d[4][slot] = sv.delta;
-    if constexpr (MODE == BK_PLAIN_F64) {
-        s_d[5][slot] = sv.dlo;
-        s_d[6][slot] = sv.E;
-        s_d[7][slot] = sv.Ei;
-        s_d[8][slot] = sv.Sr;
-    } else {
-        s_d[5][slot] = sv.p.t0;
-        s_d[6][slot] = sv.A;
-    }
+    s_d[5][slot] = sv.p.t0;
+    s_d[6][slot] = sv.A;
     s_i[0][slot] = li;
     s_i[1][slot] = sv.p.N;
     s_i[2][slot] = sv.p.mc;
@@ -225,16 +212,9 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
         p.h = s_d[3][tid];
         p.N = s_i[1][tid];
         p.mc = s_i[2][tid];
-        double hs;
-        if constexpr (MODE == BK_PLAIN_F64) {
-            p.t0 = 0.0;                       // not used by the paired walk
-            hs = p.h * sum_f64(v3, z3, p, s_d[6][tid], s_d[7][tid], s_d[8][tid], s_tab);
-            hs = fma(hs, s_d[5][tid], hs);    // the low part of Delta
-        } else {
-            p.t0 = s_d[5][tid];
-            hs = p.h * sum_mixed(v3, z3, p, s_d[6][tid], s_tab);
-        }
-        out[(int64_t)blockIdx.x * kSolveBlock + l3] = assemble(z3, s_d[4][tid], hs, result);
+        p.t0 = s_d[5][tid];
+        const double hs = p.h * sum_mixed(v3, z3, p, s_d[6][tid], s_tab);
+        out[(int64_t)blockIdx.x * kSolveBlock + l3] = assemble(z3, s_d[4][tid], hs, result, s_tab);
         nodes = (unsigned long long)(p.N + 1);
         ents = 1;
     }
@@ -243,6 +223,117 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
         block_count_w(stats + BK_STAT_ENTRIES, ents, kSolveBlock / 64);
         const unsigned int wmax = wave_max_u32((unsigned int)nodes);
         block_count_w(stats + BK_STAT_LANE_SLOTS, (threadIdx.x & 63) == 0 ? 64ull * wmax : 0ull, kSolveBlock / 64);
+    }
+}
+
+// Plain K_nu. A workgroup takes kThreads x kPer entries in two phases:
+//  1. entry order: special values; the FP32 window and node count (cheap enough to run
+//     before any sort), or Temme's series (x < 0.1), or the exact solve (plan_fast_ok
+//     false) as keys of their own; counting sort into LDS, largest node counts first;
+//  2. its waves draw the sorted entries 64 at a time: set-up at the reference node, the
+//     paired walk, the prefactor and the store to the entry's own index; or the whole of
+//     the other two.
+// VALU-bound. 2^24 pairs of the (nu, x) grid: 1,264 us with the exact solve between two
+// sorts (2,266 VALU instructions a wave of 64), 755 with the FP32 window there, 640 with
+// one sort of 512 entries, one a lane (1,207 instructions), 463 with 1,024 drawn by four
+// waves: fewer waves hold both branches, and none waits for a block's slowest. (512
+// entries in 128 lanes 528, in 256 489; constants hoisted out of the draw loop spill: 548.)
+template <int kThreads, int kPer>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_besselk_plain(
+    const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ out, int64_t n, int result,
+    double L, double Lq, unsigned long long* __restrict__ stats)
+{
+    constexpr int kEntries = kThreads * kPer;
+    static_assert(kEntries <= 1024, "entry index bits");
+    __shared__ unsigned int hist[64], s_next;
+    __shared__ double s_tab[kTabLen];
+    __shared__ double s_v[kEntries], s_z[kEntries];
+    __shared__ float s_t0[kEntries], s_t1[kEntries];
+    __shared__ unsigned int s_e[kEntries];       // entry | mc << 10 | N << 20 (N <= 512; 0: none)
+    constexpr unsigned kTemme = 1023u, kExact = 1022u;
+    const int tid = threadIdx.x;
+    for (int j = tid; j < kTabLen; j += kThreads) s_tab[j] = rule_tab().tab[j];   // read after the barriers
+    if (tid < 64) hist[tid] = 0u;
+    if (tid == 0) s_next = 0u;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kEntries;
+    double v[kPer], z[kPer];
+    float t0[kPer], t1[kPer];
+    unsigned int e[kPer], rank[kPer];
+    int key[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t i = i0 + k * kThreads + tid;
+        unsigned int N = 0u, mc = 0u;
+        v[k] = 0.0;
+        z[k] = 1.0;
+        t0[k] = t1[k] = 0.0f;
+        if (i < n) {
+            v[k] = fabs(nu[i]);
+            z[k] = x[i];
+            double r;
+            if (special_value(v[k], z[k], result, r)) out[i] = r;
+            else if (temme_applies(v[k], z[k])) N = kTemme;
+            else if (!plan_fast_ok(v[k], z[k], L)) N = kExact;
+            else window_count(v[k], z[k], L, Lq, t0[k], t1[k], N, mc);
+        }
+        e[k] = (unsigned int)(k * kThreads + tid) | (mc << 10) | (N << 20);
+        key[k] = N == kTemme ? (v[k] < 4.5 ? 62 : 61) : (N == 0u ? 63 : 60 - (int)min(N, 60u));
+        rank[k] = atomicAdd(&hist[key[k]], 1u);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        const unsigned int h = hist[tid];
+        hist[tid] = wave_incl_scan(h) - h;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const unsigned int slot = hist[key[k]] + rank[k];
+        s_v[slot] = v[k];
+        s_z[slot] = z[k];
+        s_t0[slot] = t0[k];
+        s_t1[slot] = t1[k];
+        s_e[slot] = e[k];
+    }
+    __syncthreads();
+    const int lane = tid & 63;
+    unsigned int nodes = 0u, ents = 0u, slots = 0u;
+    for (;;) {
+        unsigned int chunk = 0u;
+        if (lane == 0) chunk = atomicAdd(&s_next, 1u);
+        chunk = __builtin_amdgcn_readfirstlane(chunk);
+        if (chunk >= (unsigned)(kEntries / 64)) break;
+        const int j = (int)chunk * 64 + lane;
+        const unsigned int ej = s_e[j], N = ej >> 20;
+        unsigned int walked = 0u;
+        if (N != 0u) {
+            const double vj = s_v[j], zj = s_z[j];
+            double r;
+            if (N == kTemme) {
+                r = temme_result(vj, zj, result, s_tab);
+            } else {
+                Solved s;
+                if (N == kExact) s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
+                else s = plan_setup(vj, zj, s_t0[j], s_t1[j], N, (ej >> 10) & 1023u);
+                double hs = s.p.h * sum_f64(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                hs = fma(hs, s.dlo, hs);          // the low part of Delta
+                r = assemble(zj, s.delta, hs, result, s_tab);
+                walked = (unsigned int)(s.p.N + 1);
+            }
+            out[i0 + (ej & 1023u)] = r;
+        }
+        if (stats) {
+            nodes += walked;
+            ents += walked ? 1u : 0u;
+            const unsigned int w = wave_max_u32(walked);
+            slots += lane == 0 ? 64u * w : 0u;
+        }
+    }
+    if (stats) {
+        block_count_w(stats + BK_STAT_NODES, nodes, kThreads / 64);
+        block_count_w(stats + BK_STAT_ENTRIES, ents, kThreads / 64);
+        block_count_w(stats + BK_STAT_LANE_SLOTS, slots, kThreads / 64);
     }
 }
 
@@ -264,12 +355,12 @@ __global__ __launch_bounds__(256) void k_besselk_paper(const double* __restrict_
         if (!special_value(v, z, result, r)) {
             if (z < kPaperTemmeX) {
                 // K directly; written as exp(-z) exp(0) (e^z K) for the shared assembly
-                r = assemble(z, 0.0, temme_k(v, z, temme_tab()) * exp(z), result);
+                r = assemble(z, 0.0, temme_k(v, z, temme_tab(), s_tab) * exp(z), result, s_tab);
             } else {
                 const FixedOut f = paper_fixed(v, z, bins, T, s_tab);
                 // K = exp(lscale) h S, written through Delta = lscale + z so that the
                 // shared assembly (exp(-z) exp(Delta) h S) applies
-                r = assemble(z, f.lscale + z, f.hs, result);
+                r = assemble(z, f.lscale + z, f.hs, result, s_tab);
                 nodes = (unsigned long long)(bins + 1);
                 ents = 1;
             }
@@ -340,7 +431,7 @@ __global__ __launch_bounds__(256, 3) void k_besselk_deriv(const double* __restri
             const Solved s0 = plain_plan(v, z, L, Lq, R, s_tab);
             double hs0 = s0.p.h * sum_f64(v, z, s0.p, s0.E, s0.Ei, s0.Sr, s_tab);
             hs0 = fma(hs0, s0.dlo, hs0);
-            rk = assemble(z, s0.delta, hs0, result);
+            rk = assemble(z, s0.delta, hs0, result, s_tab);
             nodes += (unsigned long long)(s0.p.N + 1);
             rx = 0.0;
             if (dkdx) {
@@ -356,7 +447,7 @@ __global__ __launch_bounds__(256, 3) void k_besselk_deriv(const double* __restri
                 const Solved sd = dnu_solve(v, z, s0.p.t0, L, Lq, R, s_tab);
                 const double hsd = sd.p.h * sum_dnu_f64(v, sd.p, sd.A, sd.B, s_tab);
                 nodes += (unsigned long long)(sd.p.N + 1);
-                rn = copysign(assemble(z, sd.delta, hsd, result), nr);
+                rn = copysign(assemble(z, sd.delta, hsd, result, s_tab), nr);
             } else if (dkdnu) {
                 rn = copysign(0.0, nr);
             }
@@ -427,7 +518,7 @@ __global__ __launch_bounds__(256, 4) void k_matern(const double* __restrict__ lx
             const double z = r * inv_beta;
             if (MODE == BK_PAPER_REFINED) {
                 if (z < kPaperTemmeX) {
-                    val = sigma2 * exp(pref + nu * log(z)) * temme_k(nu, z, temme_tab());
+                    val = sigma2 * exp(pref + nu * log(z)) * temme_k(nu, z, temme_tab(), s_tab);
                 } else {
                     const FixedOut f = paper_fixed(nu, z, bins, T, s_tab);
                     val = sigma2 * exp(pref + nu * log(z) + f.lscale) * f.hs;
@@ -541,6 +632,8 @@ extern "C" int bk_besselk(const double* nu, const double* x, double* out, int64_
     return bk_besselk_ex(nu, x, out, n, &p, stream);
 }
 
+constexpr int64_t kPlainSmall = 1 << 17;
+
 // One kernel between the caller's optional event pair.
 template <typename K, typename... A>
 static int launch_timed(const bk_params* prm, K k, dim3 grid, dim3 block, hipStream_t stream, A&&... a)
@@ -565,10 +658,15 @@ extern "C" int bk_besselk_ex(const double* nu, const double* x, double* out, int
     if (blocks > 0x7fffffffLL) return BK_EINVAL;
     switch (prm->mode) {
     case BK_PLAIN_F64:
-        return launch_timed(prm, k_besselk<BK_PLAIN_F64>, dim3((unsigned)blocks), dim3(kSolveBlock), stream, nu, x,
-                            out, n, prm->result, L, Lq, prm->stats);
+        // Small calls take one wave a workgroup: no CU waits for another's sort (4,096 pairs
+        // 11.4 us against 21.5; 65,536 15 against 22; 200,000 28 against 19 to 23).
+        if (n < kPlainSmall)
+            return launch_timed(prm, k_besselk_plain<64, 1>, dim3((unsigned)((n + 63) / 64)), dim3(64), stream, nu, x,
+                                out, n, prm->result, L, Lq, prm->stats);
+        return launch_timed(prm, k_besselk_plain<256, 4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), stream, nu,
+                            x, out, n, prm->result, L, Lq, prm->stats);
     case BK_MIXED_F32C:
-        return launch_timed(prm, k_besselk<BK_MIXED_F32C>, dim3((unsigned)blocks), dim3(kSolveBlock), stream, nu, x,
+        return launch_timed(prm, k_besselk_mixed, dim3((unsigned)blocks), dim3(kSolveBlock), stream, nu, x,
                             out, n, prm->result, L, Lq, prm->stats);
     case BK_LEARNED:
         return bk_besselk_learned(nu, x, out, n, prm, L, Lq, stream);

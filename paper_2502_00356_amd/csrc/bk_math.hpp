@@ -47,16 +47,16 @@ struct RuleTable {
     double tab[kTabLen];
 };
 
-// Chebyshev coefficients of Temme's Gamma1 and Gamma2 (see temme_k below).
-constexpr int kTemmeCheb = 14;
+// Taylor coefficients in mu^2 of Temme's Gamma1 and Gamma2 (see temme_k below).
+constexpr int kTemmeTerms = 10;
 
 struct TemmeCoef {
-    double g1[kTemmeCheb];
-    double g2[kTemmeCheb];
+    double g1[kTemmeTerms];
+    double g2[kTemmeTerms];
 };
 
 // kRuleTab and kTemmeTab: the two tables above as device constants (values made
-// by gen_tables.py at 40 digits and rounded to double), so no call sets anything
+// by gen_tables.py at 60 digits and rounded to double), so no call sets anything
 // up on the GPU.
 #include "bk_tables.inc"
 
@@ -151,6 +151,23 @@ __device__ __forceinline__ double exp_node(double x, const double* T)
     const int ki = __double2loint(m);
     const double f = fma(-(m - 6755399441055744.0), 0.010830424696249145, x);
     double p = 1.0 / 120.0;
+    p = fma(p, f, 1.0 / 24.0);
+    p = fma(p, f, 1.0 / 6.0);
+    p = fma(p, f, 0.5);
+    p = fma(p, f, 1.0);
+    const double t = T[ki & 63];
+    return ldexp(fma(t * f, p, t), ki >> 6);
+}
+
+// e^x for |x| <= 708 from the same table, with ln2/64 in two parts (about an ulp).
+__device__ __forceinline__ double exp_wide(double x, const double* T)
+{
+    const double m = fma(x, 92.332482616893656, 6755399441055744.0);
+    const int ki = __double2loint(m);
+    const double k = m - 6755399441055744.0;
+    const double f = fma(-k, 3.623510646634843e-19, fma(-k, 0.010830424696249145, x));
+    double p = 1.0 / 720.0;
+    p = fma(p, f, 1.0 / 120.0);
     p = fma(p, f, 1.0 / 24.0);
     p = fma(p, f, 1.0 / 6.0);
     p = fma(p, f, 0.5);
@@ -543,35 +560,50 @@ __device__ __forceinline__ double expm1_small(double y)
     return fma(p * y, y, y);
 }
 
-// Plan of the plain sum: the fast window where it applies, else the exact solve.
-__device__ inline Solved plain_plan(double nu, double x, double L, double Lq, const RuleTable& R, const double* T)
+// The fast window with its node count N and the index mc of the reference node.
+__device__ __forceinline__ void window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
+                                             unsigned int& N, unsigned int& mc)
 {
-    if (!plan_fast_ok(nu, x, L)) return plain_solve(nu, x, L, Lq, R, T);
-    float t0f, t1f, tpf;
-    window_fast((float)nu, (float)x, (float)L, t0f, t1f, tpf);
-    const double t0 = (double)t0f;
-    Solved s;
-    const float wf = t1f - t0f;
-    float nf = ceilf(wf * __builtin_amdgcn_rcpf(node_step_learned((float)nu, (float)x, (float)Lq)));
+    float tp;
+    window_fast((float)nu, (float)x, (float)L, t0, t1, tp);
+    const float w = t1 - t0;
+    float nf = ceilf(w * __builtin_amdgcn_rcpf(node_step_learned((float)nu, (float)x, (float)Lq)));
     nf = fminf(fmaxf(nf, (float)kNodeMin), (float)kNodeMax);
-    const float mf = fminf(rintf((tpf - t0f) * nf * __builtin_amdgcn_rcpf(wf)), nf);
-    const double h = ((double)t1f - t0) * recip((double)nf);
-    const double tref = fma((double)mf, h, t0);
+    N = (unsigned int)nf;
+    mc = (unsigned int)fminf(rintf((tp - t0) * nf * __builtin_amdgcn_rcpf(w)), nf);
+}
+
+// Set-up of the paired walk on the nodes t0 + m (t1 - t0) / N.
+__device__ __forceinline__ Solved plan_setup(double nu, double x, float t0, float t1, unsigned int N, unsigned int mc)
+{
+    Solved s;
+    const double h = ((double)t1 - (double)t0) * recip((double)N);
+    const double tref = fma((double)mc, h, (double)t0);
     const double em = expm1(0.5 * tref);
     s.Sr = em * (em + 2.0);                            // expm1(t_ref), no cancellation
     s.E = s.Sr + 1.0;
     s.Ei = recip(s.E);
     const double sh2 = 0.5 * fma(em, recip(em + 1.0), em);   // sinh(t/2) = (em + em / (em + 1)) / 2
     s.p.tref = tref;
-    s.p.t0 = t0;
-    s.p.N = (int)nf;
-    s.p.mc = (int)mf;
+    s.p.t0 = (double)t0;
+    s.p.N = (int)N;
+    s.p.mc = (int)mc;
     s.p.h = h;
     delta_dd(nu, tref, 2.0 * x * sh2 * sh2, s.delta, s.dlo);
     s.A = s.B = 0.0;                                   // not used by the paired walk
     s.gstar = 0.0;
-    s.t1 = (double)t1f;
+    s.t1 = (double)t1;
     return s;
+}
+
+// Plan of the plain sum: the fast window where it applies, else the exact solve.
+__device__ inline Solved plain_plan(double nu, double x, double L, double Lq, const RuleTable& R, const double* T)
+{
+    if (!plan_fast_ok(nu, x, L)) return plain_solve(nu, x, L, Lq, R, T);
+    float t0, t1;
+    unsigned int N, mc;
+    window_count(nu, x, L, Lq, t0, t1, N, mc);
+    return plan_setup(nu, x, t0, t1, N, mc);
 }
 
 // Geometric-progression state of one entry's node walk.
@@ -964,40 +996,32 @@ __device__ inline FixedOut paper_fixed(double nu, double x, int bins, double T, 
 //   s = mu ln(2/x), Gamma1 = (1/Gamma(1-mu) - 1/Gamma(1+mu)) / (2 mu),
 //   Gamma2 = (1/Gamma(1-mu) + 1/Gamma(1+mu)) / 2,
 // then K_{eta+1} = (2 eta / x) K_eta + K_{eta-1} up to nu. Gamma1 and Gamma2 are
-// even entire functions of mu; they are evaluated from Chebyshev coefficients in
-// 8 mu^2 - 1 (kTemmeTab). The series stops when a
-// term falls below 2^-53 of the sum (the paper caps it at 15000 terms).
+// even entire functions of mu, evaluated by their Taylor series in mu^2 (kTemmeTab).
+// c_k f_k falls faster than (x^2/4)^k / k!^2: five terms leave below 1e-19 of the sum at
+// x = 0.1 (the paper caps the series at 15000 terms).
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ double cheb_eval(const double* c, double u)
-{
-    double b1 = 0.0, b2 = 0.0;
-    for (int j = kTemmeCheb - 1; j >= 1; --j) {
-        const double t = fma(2.0 * u, b1, c[j] - b2);
-        b2 = b1;
-        b1 = t;
-    }
-    return fma(u, b1, c[0] - b2);
-}
-
-// K_nu(x) for 0 < x (intended for x < 0.1, where the series converges in a few
-// terms); returns K (not scaled). One reciprocal a term: p and q take their divisors
+// K_nu(x) for 0 < x < 0.1; returns K (not scaled). One reciprocal a term: p and q take their divisors
 // k -+ mu from that of k^2 - mu^2, 1/Gamma(1 + mu) and 1/Gamma(1 - mu) give pi mu /
 // sin(pi mu) = Gamma(1 + mu) Gamma(1 - mu), and 2/x serves the logarithm, the series and
 // the recurrence, whose M factors of its rounding are taken out at the end.
-__device__ inline double temme_k(double nu, double x, const TemmeCoef& C)
+__device__ inline double temme_k(double nu, double x, const TemmeCoef& C, const double* T)
 {
     const double M = floor(nu + 0.5);
     const double mu = nu - M, mu2 = mu * mu;
-    const double u = 8.0 * mu2 - 1.0;
-    const double G1 = cheb_eval(C.g1, u), G2 = cheb_eval(C.g2, u);
+    double G1 = C.g1[kTemmeTerms - 1], G2 = C.g2[kTemmeTerms - 1];
+#pragma unroll
+    for (int j = kTemmeTerms - 2; j >= 0; --j) {
+        G1 = fma(G1, mu2, C.g1[j]);
+        G2 = fma(G2, mu2, C.g2[j]);
+    }
     const double rgp = G2 - mu * G1;                   // 1 / Gamma(1 + mu)
     const double rgm = G2 + mu * G1;                   // 1 / Gamma(1 - mu)
     const double ix = 2.0 / x;
     const double lx = log(ix);
     const double sg = mu * lx, s2 = sg * sg;
     const double fact = recip(rgp * rgm);              // pi mu / sin(pi mu)
-    const double esg = exp(sg), esi = recip(esg);
+    const double esg = exp_wide(sg, T), esi = recip(esg);
     const double chs = 0.5 * (esg + esi);
     // sinh(s) / s: the series below 0.3 (truncation 1e-17)
     const double ser = fma(fma(fma(fma(fma(s2, 1.0 / 39916800.0, 1.0 / 362880.0), s2, 1.0 / 5040.0), s2, 1.0 / 120.0),
@@ -1008,17 +1032,16 @@ __device__ inline double temme_k(double nu, double x, const TemmeCoef& C)
     double q = 0.5 * esi * (rgp * fact);               // (x/2)^mu Gamma(1-mu) / 2
     const double d = 0.25 * x * x;
     double c = 1.0, sum = f, sum1 = p;
-    for (int k = 1; k < 200; ++k) {
+#pragma unroll
+    for (int k = 1; k <= 5; ++k) {
         const double kk = (double)k;
         const double r = recip(fma(kk, kk, -mu2));
         f = (kk * f + p + q) * r;
-        c *= d * recip(kk);
+        c *= d * (1.0 / kk);
         p *= (kk + mu) * r;
         q *= (kk - mu) * r;
-        const double del = c * f;
-        sum += del;
-        sum1 += c * (p - kk * f);
-        if (fabs(del) < 1.1102230246251565e-16 * fabs(sum)) break;
+        sum = fma(c, f, sum);
+        sum1 = fma(c, p - kk * f, sum1);
     }
     double km = sum;                                   // K_mu
     double kp = sum1 * ix;                             // K_{mu+1}

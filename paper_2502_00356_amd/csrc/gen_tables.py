@@ -5,22 +5,22 @@ so that no call has to set anything up on the GPU.
              k = 1..8 (15 distinct values), with 1 - cos a_k and log sec a_k
              (node-count rule); 2^(j/64), j = 0..63 (table-driven exponential);
              log(1 + j/64) and 1 / (1 + j/64), j = 0..64 (table-driven log1p).
-  kTemmeTab  Chebyshev coefficients, in u = 8 mu^2 - 1, of Temme's
+  kTemmeTab  Taylor coefficients, in mu^2, of Temme's
              Gamma1(mu) = (1/Gamma(1 - mu) - 1/Gamma(1 + mu)) / (2 mu) and
-             Gamma2(mu) = (1/Gamma(1 - mu) + 1/Gamma(1 + mu)) / 2 on |mu| <= 1/2
-             (both even in mu), by interpolation at the Chebyshev points.
+             Gamma2(mu) = (1/Gamma(1 - mu) + 1/Gamma(1 + mu)) / 2 (both even in mu);
+             ten terms leave below 4e-18 at |mu| = 1/2.
 
-Every value is computed in mpmath at 40 digits and rounded to the nearest double.
+Every value is computed in mpmath at 60 digits and rounded to the nearest double.
 Run: python gen_tables.py (rewrites bk_tables.inc beside this file).
 """
 import os
 
 import mpmath as mp
 
-mp.mp.dps = 40
+mp.mp.dps = 60
 HERE = os.path.dirname(os.path.abspath(__file__))
 RULE_CAND = 15
-TEMME_CHEB = 14
+TEMME_TERMS = 10
 
 
 def dbl(v):
@@ -38,22 +38,11 @@ def half_widths():
     return vals
 
 
-def temme_cheb():
-    n = TEMME_CHEB
-    f1, f2 = [], []
-    for k in range(n):
-        u = mp.cos(mp.pi * (k + mp.mpf("0.5")) / n)
-        mu = mp.sqrt((u + 1) / 8)
-        gm, gp = 1 / mp.gamma(1 - mu), 1 / mp.gamma(1 + mu)
-        f1.append((gm - gp) / (2 * mu))
-        f2.append((gm + gp) / 2)
-    c1, c2 = [], []
-    for j in range(n):
-        w = [mp.cos(mp.pi * j * (k + mp.mpf("0.5")) / n) for k in range(n)]
-        sc = (1 if j == 0 else 2) / mp.mpf(n)
-        c1.append(sc * mp.fsum(a * b for a, b in zip(f1, w)))
-        c2.append(sc * mp.fsum(a * b for a, b in zip(f2, w)))
-    return c1, c2
+def temme_taylor():
+    """Coefficients of mu^(2k), k < TEMME_TERMS: 1/Gamma(1 + mu) = sum_n c_n mu^n gives
+    Gamma1 = -sum c_(2k+1) mu^(2k) and Gamma2 = sum c_(2k) mu^(2k)."""
+    c = mp.taylor(lambda z: mp.rgamma(1 + z), 0, 2 * TEMME_TERMS)
+    return [-c[2 * k + 1] for k in range(TEMME_TERMS)], [c[2 * k] for k in range(TEMME_TERMS)]
 
 
 def fmt(vals, per_line=4):
@@ -69,8 +58,8 @@ def main():
     tab = [mp.power(2, mp.mpf(j) / 64) for j in range(64)]
     tab += [mp.log1p(mp.mpf(j) / 64) for j in range(65)]
     tab += [1 / (1 + mp.mpf(j) / 64) for j in range(65)]
-    g1, g2 = temme_cheb()
-    text = ("// Generated by gen_tables.py (mpmath, 40 digits, rounded to double); do not edit.\n"
+    g1, g2 = temme_taylor()
+    text = ("// Generated by gen_tables.py (mpmath, 60 digits, rounded to double); do not edit.\n"
             "// Constant tables of the device code; see gen_tables.py for their definitions.\n"
             "static __constant__ RuleTable kRuleTab = {\n"
             "    " + fmt(a) + ",\n    " + fmt(omc) + ",\n    " + fmt(lsec) + ",\n    " + fmt(tab) + "};\n\n"

@@ -267,8 +267,8 @@ int bk_matern_grad_tiles(const bk_locs* locs, const bk_params* params, int32_t t
  * under the Matern covariance Sigma of bk_matern_tiles (Sec. III-A; the matrix the
  * paper generates is the covariance of this likelihood):
  *   l = -1/2 z^T Sigma^-1 z - 1/2 log det Sigma - n/2 log(2 pi),
- * by Sigma = L L^T (rocSOLVER potrf) and a = Sigma^-1 z (potrs). With with_grad != 0
- * also the gradient, from bk_matern_grad_tiles and Sigma^-1 (potri):
+ * by a blocked Cholesky factorisation Sigma = L L^T. With with_grad != 0 also the
+ * gradient, from bk_matern_grad_tiles, L^-T and Sigma^-1:
  *   dl/dtheta = 1/2 a^T (dSigma/dtheta) a - 1/2 tr(Sigma^-1 dSigma/dtheta),
  * theta = (sigma2, beta, nu); dSigma/dsigma2 = Sigma / sigma2.
  * result : HOST array, result[0] = l and, with the gradient, result[1..3] =
@@ -278,8 +278,8 @@ int bk_matern_grad_tiles(const bk_locs* locs, const bk_params* params, int32_t t
  * workspace : device scratch of bk_matern_loglik_workspace_bytes(n, with_grad)
  *          bytes (the n x n matrices: 8 n^2 bytes each, three with the gradient).
  * 1 <= n <= 46340. Synchronises the stream (the results are host values).
- * Returns BK_ENOTPD if the Cholesky factorisation fails. Calls on one device are
- * serialised (one rocBLAS handle per device, kept for the life of the process). */
+ * Returns BK_ENOTPD if the Cholesky factorisation fails. Calls with workspaces of
+ * their own may overlap. */
 int bk_matern_loglik(const bk_locs* locs, const double* z, const bk_params* params, int32_t with_grad,
                      double* result, void* workspace, size_t workspace_bytes, hipStream_t stream);
 

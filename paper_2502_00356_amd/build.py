@@ -12,12 +12,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbesselk.so")
 RATES_LIB = os.path.join(HERE, "libvalurates.so")
-SOURCES = ["bk_kernels.hip", "bk_mlp.hip", "bk_mle.hip", "bk_table.hip"]
+SOURCES = ["bk_kernels.hip", "bk_mlp.hip", "bk_mle.hip", "bk_chol.hip", "bk_table.hip"]
 # bk_kernels.hip: constants stay where they are used. Hoisted out of the FP64 loops they
 # take more registers than there are (spills; the 2^24-pair plain grid 548 us against 463).
 FILE_FLAGS = {"bk_kernels.hip": ["-mllvm", "-disable-machine-licm"]}
-# rocSOLVER (Cholesky, triangular solves, inverse) and the rocBLAS handle it runs on
-LIBS = ["-L/opt/rocm/lib", "-lrocsolver", "-lrocblas"]
 ARCH = os.environ.get("BK_OFFLOAD_ARCH", "gfx950")
 
 
@@ -70,9 +68,9 @@ def _loops(lines):
 def node_slots(asm_path):
     """VALU issue cost of one trapezoid node per K_nu kernel, in CU clocks per wave
     (issue_cost above), read from the gfx950 assembly of this build: the node loop
-    is the loop that evaluates the most node exponentials a trip, without divisions or logarithms (v_exp_f32 for the
-    FP32-term forms; the inlined FP64 exp, one v_ldexp_f64 without divisions or
-    logarithms, for the plain form), and its cost is divided by the exponentials
+    is the innermost loop (plain form: the one with the most exponentials a trip) that
+    evaluates the node exponential (v_exp_f32 for the FP32-term forms; the inlined FP64
+    exp, one v_ldexp_f64 without divisions or logarithms, for the plain form), and its cost is divided by the exponentials
     one trip evaluates (the plain form's paired walk evaluates two nodes a trip
     when both sides of the reference node are live)."""
     text = open(asm_path).read().split("\n")
@@ -108,9 +106,10 @@ def node_slots(asm_path):
                 per_trip = (ops.count("v_ldexp_f64") if form in ("plain", "matern_plain")
                             else sum(o.startswith("v_exp_f32") for o in ops))
                 slots = slots / max(1, per_trip)
-                # the node walk evaluates the most exponentials a trip; among equals, the innermost
-                if best is None or (-per_trip, b - a) < best[0]:
-                    best = ((-per_trip, b - a), slots)
+                # the plain walk evaluates the most exponentials a trip; else the innermost loop
+                rank = (-per_trip if form in ("plain", "matern_plain") else 0, b - a)
+                if best is None or rank < best[0]:
+                    best = (rank, slots)
         if best is not None:
             out[form] = best[1]
     return out
@@ -143,7 +142,7 @@ def build(verbose=False, jobs=None):
             sys.stderr.write(msg + "\n")
     if failed:
         raise RuntimeError("HIP build failed")
-    cmd = [hipcc, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs + LIBS
+    cmd = [hipcc, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -1,0 +1,67 @@
+"""GPU test of the blocked factorisation behind the likelihood, at the edges of its
+128-blocks and of the four-block steps of its trailing update, against numpy's
+Cholesky of the same covariance (built by the library's own Matern tiles).
+
+Bars: the value within 1e-9 of |z^T Sigma^-1 z| + n and every gradient component
+within 1e-9 of the sum of the magnitudes of its two terms, as in the likelihood's
+tests (cond(Sigma) <= 1e4 here, so both factorisations are good to ~1e-12)."""
+import math
+
+import numpy as np
+import pytest
+
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_00356_amd import api
+    return api
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 17, 127, 128, 129, 255, 257, 384, 511, 512, 513, 641, 1027])
+def test_loglik_block_edges(api, n):
+    from paper_2502_00356_amd import workloads as w
+    s2, nu = 1.2, 0.8
+    beta = 0.3 / math.sqrt(n)
+    side = math.isqrt(n - 1) + 1
+    xy = w.jittered_grid_locations(side, seed=n)[:n]
+    z = np.random.default_rng(n).standard_normal(n)
+    lx, ly = to_dev(xy[:, 0]), to_dev(xy[:, 1])
+    ts = max(n, 2)
+    g = {k: api.unpack_tiles(v, n, ts, 0).numpy() for k, v in
+         api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, 0).items()}
+    assert np.linalg.cond(g["c"]) <= 1e4
+    L = np.linalg.cholesky(g["c"])
+    a = np.linalg.solve(L.T, np.linalg.solve(L, z))
+    inv = np.linalg.inv(g["c"])
+    quad = z @ a
+    ll = -0.5 * quad - np.log(np.diag(L)).sum() - 0.5 * n * math.log(2 * math.pi)
+    terms = [(0.5 * quad / s2, 0.5 * n / s2)] + [(0.5 * a @ g[k] @ a, 0.5 * (inv * g[k]).sum()) for k in ("dbeta", "dnu")]
+    got = api.matern_loglik(lx, ly, to_dev(z), s2, beta, nu)
+    got_g, grad = api.matern_loglik(lx, ly, to_dev(z), s2, beta, nu, grad=True)
+    assert got_g == got
+    assert abs(got - ll) <= 1e-9 * (abs(quad) + n)
+    for (q, t), d in zip(terms, grad):
+        assert abs((q - t) - d) <= 1e-9 * (abs(q) + abs(t)) + 1e-300
+
+
+@pytest.mark.parametrize("n,k", [(5, 2), (200, 150), (700, 699)])
+def test_loglik_singular(api, n, k):
+    """A repeated point makes two equal rows: the pivot is zero up to rounding, and where
+    it is not positive the call says so instead of returning a number."""
+    from paper_2502_00356_amd import workloads as w
+    xy = w.jittered_grid_locations(math.isqrt(n - 1) + 1, seed=n)[:n]
+    xy[k] = xy[0]
+    z = np.ones(n)
+    try:
+        l = api.matern_loglik(to_dev(xy[:, 0]), to_dev(xy[:, 1]), to_dev(z), 1.0, 0.01, 0.5)
+    except api.BkError as e:
+        assert e.status == 6        # BK_ENOTPD
+    else:
+        assert np.isfinite(l)

@@ -236,7 +236,8 @@ int64_t bk_matern_tile_offset(int64_t n, int32_t tile_size, int32_t lower_only, 
 int bk_window(const double* nu, const double* x, double* t_lo, double* t_hi, int32_t* nodes,
               int64_t n, double L_window, double L_quad, hipStream_t stream);
 
-/* K_nu(x) and its partial derivatives in x and nu, FP64 (plain solve), for n pairs.
+/* K_nu(x) and its partial derivatives in x and nu, FP64, for n pairs, by one window and
+ * one set of nodes for the three integrals.
  * Defines (derivatives are the paper's future work, Sec. VI; both come from
  * differentiating the integral of Sec. IV-B under the integral sign):
  *   dK/dx  = -int_0^inf cosh t cosh(nu t) exp(-x cosh t) dt = -(K_{nu-1} + (nu/x) K_nu)

@@ -127,9 +127,9 @@ __device__ __forceinline__ double matern_dbeta(double nu, double z, double lz, d
 __device__ __forceinline__ double matern_dnu(double nu, double z, double lz, double sigma2, double pref, double psi,
                                              double L, double Lq, const double* T, double vc, double t0)
 {
-    const Solved sd = dnu_solve(nu, z, t0, L, Lq, rule_tab(), T);
-    return vc * (lz - kLn2 - psi) +
-           sigma2 * exp(pref + nu * lz + (sd.delta - z)) * (sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T));
+    double delta, hs;
+    dnu_integral(nu, z, t0, L, Lq, rule_tab(), T, delta, hs);
+    return vc * (lz - kLn2 - psi) + sigma2 * exp(pref + nu * lz + (delta - z)) * hs;
 }
 
 int bk_besselk_learned(const double* nu, const double* x, double* out, int64_t n, const bk_params* prm,

@@ -226,6 +226,87 @@ __global__ __launch_bounds__(kSolveBlock) __attribute__((amdgpu_waves_per_eu(6, 
     }
 }
 
+// The entries of a workgroup, sorted by key in LDS: kThreads lanes place kPer each, and the
+// workgroup's waves then draw them 64 at a time. Equal keys keep no particular order;
+// results do not depend on it, since every entry is computed by one lane from its own inputs.
+constexpr unsigned kEntryTemme = 1023u, kEntryExact = 1022u;      // in place of a node count
+
+template <int kThreads, int kPer>
+struct DrawBlock {
+    static constexpr int kEntries = kThreads * kPer;
+    static_assert(kEntries <= 1024, "entry index bits");
+    unsigned int hist[64], next;
+    double v[kEntries], z[kEntries];
+    float t0[kEntries], t1[kEntries];
+    unsigned int e[kEntries];        // entry | mc << 10 | N << 20 (N <= 512; 0: none)
+
+    __device__ __forceinline__ void begin()
+    {
+        if (threadIdx.x < 64) hist[threadIdx.x] = 0u;
+        if (threadIdx.x == 0) next = 0u;
+        __syncthreads();
+    }
+
+    // Largest node counts first, then the series; entries with nothing to do last.
+    static __device__ __forceinline__ int key_of(unsigned int N, double nu)
+    {
+        return N == kEntryTemme ? (nu < 4.5 ? 62 : 61) : (N == 0u ? 63 : 60 - (int)min(N, 60u));
+    }
+
+    __device__ __forceinline__ void place(const double (&pv)[kPer], const double (&pz)[kPer], const float (&p0)[kPer],
+                                          const float (&p1)[kPer], const unsigned int (&pe)[kPer],
+                                          const int (&key)[kPer], const unsigned int (&rank)[kPer])
+    {
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            const unsigned int h = hist[threadIdx.x];
+            hist[threadIdx.x] = wave_incl_scan(h) - h;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const unsigned int slot = hist[key[k]] + rank[k];
+            v[slot] = pv[k];
+            z[slot] = pz[k];
+            t0[slot] = p0[k];
+            t1[slot] = p1[k];
+            e[slot] = pe[k];
+        }
+        __syncthreads();
+    }
+
+    // An entry's rank among those of its key (taken as soon as its key is known).
+    __device__ __forceinline__ unsigned int rank(int key) { return atomicAdd(&hist[key], 1u); }
+
+    // The wave's next 64 entries: their first slot, or -1.
+    __device__ __forceinline__ int draw()
+    {
+        unsigned int c = 0u;
+        if ((threadIdx.x & 63) == 0) c = atomicAdd(&next, 1u);
+        c = __builtin_amdgcn_readfirstlane(c);
+        return c < (unsigned)(kEntries / 64) ? (int)(c * 64u) : -1;
+    }
+};
+
+// Per-lane sums of a kernel that draws entries, for the statistics.
+struct DrawCounts {
+    unsigned int nodes = 0u, ents = 0u, slots = 0u;
+
+    __device__ __forceinline__ void add(unsigned int walked)      // every lane of the wave
+    {
+        nodes += walked;
+        ents += walked ? 1u : 0u;
+        const unsigned int w = wave_max_u32(walked);
+        slots += (threadIdx.x & 63) == 0 ? 64u * w : 0u;
+    }
+    __device__ __forceinline__ void store(unsigned long long* stats, int waves) const
+    {
+        block_count_w(stats + BK_STAT_NODES, nodes, waves);
+        block_count_w(stats + BK_STAT_ENTRIES, ents, waves);
+        block_count_w(stats + BK_STAT_LANE_SLOTS, slots, waves);
+    }
+};
+
 // Plain K_nu. A workgroup takes kThreads x kPer entries in two phases:
 //  1. entry order: special values; the FP32 window and node count (cheap enough to run
 //     before any sort), or Temme's series (x < 0.1), or the exact solve (plan_fast_ok
@@ -243,20 +324,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
     const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ out, int64_t n, int result,
     double L, double Lq, unsigned long long* __restrict__ stats)
 {
-    constexpr int kEntries = kThreads * kPer;
-    static_assert(kEntries <= 1024, "entry index bits");
-    __shared__ unsigned int hist[64], s_next;
     __shared__ double s_tab[kTabLen];
-    __shared__ double s_v[kEntries], s_z[kEntries];
-    __shared__ float s_t0[kEntries], s_t1[kEntries];
-    __shared__ unsigned int s_e[kEntries];       // entry | mc << 10 | N << 20 (N <= 512; 0: none)
-    constexpr unsigned kTemme = 1023u, kExact = 1022u;
+    __shared__ DrawBlock<kThreads, kPer> B;
     const int tid = threadIdx.x;
     for (int j = tid; j < kTabLen; j += kThreads) s_tab[j] = rule_tab().tab[j];   // read after the barriers
-    if (tid < 64) hist[tid] = 0u;
-    if (tid == 0) s_next = 0u;
-    __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kEntries;
+    B.begin();
+    const int64_t i0 = (int64_t)blockIdx.x * B.kEntries;
     double v[kPer], z[kPer];
     float t0[kPer], t1[kPer];
     unsigned int e[kPer], rank[kPer];
@@ -273,49 +346,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
             z[k] = x[i];
             double r;
             if (special_value(v[k], z[k], result, r)) out[i] = r;
-            else if (temme_applies(v[k], z[k])) N = kTemme;
-            else if (!plan_fast_ok(v[k], z[k], L)) N = kExact;
+            else if (temme_applies(v[k], z[k])) N = kEntryTemme;
+            else if (!plan_fast_ok(v[k], z[k], L)) N = kEntryExact;
             else window_count(v[k], z[k], L, Lq, t0[k], t1[k], N, mc);
         }
         e[k] = (unsigned int)(k * kThreads + tid) | (mc << 10) | (N << 20);
-        key[k] = N == kTemme ? (v[k] < 4.5 ? 62 : 61) : (N == 0u ? 63 : 60 - (int)min(N, 60u));
-        rank[k] = atomicAdd(&hist[key[k]], 1u);
+        key[k] = B.key_of(N, v[k]);
+        rank[k] = B.rank(key[k]);
     }
-    __syncthreads();
-    if (tid < 64) {
-        const unsigned int h = hist[tid];
-        hist[tid] = wave_incl_scan(h) - h;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const unsigned int slot = hist[key[k]] + rank[k];
-        s_v[slot] = v[k];
-        s_z[slot] = z[k];
-        s_t0[slot] = t0[k];
-        s_t1[slot] = t1[k];
-        s_e[slot] = e[k];
-    }
-    __syncthreads();
-    const int lane = tid & 63;
-    unsigned int nodes = 0u, ents = 0u, slots = 0u;
-    for (;;) {
-        unsigned int chunk = 0u;
-        if (lane == 0) chunk = atomicAdd(&s_next, 1u);
-        chunk = __builtin_amdgcn_readfirstlane(chunk);
-        if (chunk >= (unsigned)(kEntries / 64)) break;
-        const int j = (int)chunk * 64 + lane;
-        const unsigned int ej = s_e[j], N = ej >> 20;
+    B.place(v, z, t0, t1, e, key, rank);
+    DrawCounts cnt;
+    for (int c = B.draw(); c >= 0; c = B.draw()) {
+        const int j = c + (tid & 63);
+        const unsigned int ej = B.e[j], N = ej >> 20;
         unsigned int walked = 0u;
         if (N != 0u) {
-            const double vj = s_v[j], zj = s_z[j];
+            const double vj = B.v[j], zj = B.z[j];
             double r;
-            if (N == kTemme) {
+            if (N == kEntryTemme) {
                 r = temme_result(vj, zj, result, s_tab);
             } else {
                 Solved s;
-                if (N == kExact) s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
-                else s = plan_setup(vj, zj, s_t0[j], s_t1[j], N, (ej >> 10) & 1023u);
+                if (N == kEntryExact) s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
+                else s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
                 double hs = s.p.h * sum_f64(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
                 hs = fma(hs, s.dlo, hs);          // the low part of Delta
                 r = assemble(zj, s.delta, hs, result, s_tab);
@@ -323,18 +376,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
             }
             out[i0 + (ej & 1023u)] = r;
         }
-        if (stats) {
-            nodes += walked;
-            ents += walked ? 1u : 0u;
-            const unsigned int w = wave_max_u32(walked);
-            slots += lane == 0 ? 64u * w : 0u;
-        }
+        if (stats) cnt.add(walked);
     }
-    if (stats) {
-        block_count_w(stats + BK_STAT_NODES, nodes, kThreads / 64);
-        block_count_w(stats + BK_STAT_ENTRIES, ents, kThreads / 64);
-        block_count_w(stats + BK_STAT_LANE_SLOTS, slots, kThreads / 64);
-    }
+    if (stats) cnt.store(stats, kThreads / 64);
 }
 
 // The paper's refined algorithm (Alg. 2), one lane per entry, FP64: Temme's
@@ -400,67 +444,117 @@ __device__ __forceinline__ double unscale(double z, double s, int result)
     return ldexp(exp(64.0 * kLn2 - z) * s, -64);
 }
 
-// K_nu(x), dK/dx and dK/dnu, one lane per entry, FP64: the K integral at orders
-// nu and |nu - 1| and the dK/dnu integral, each with its own plain solve. NULL
-// outputs are skipped (dK/dx still evaluates K_nu). dK/dnu carries the sign of nu.
-__global__ __launch_bounds__(256, 3) void k_besselk_deriv(const double* __restrict__ nu, const double* __restrict__ x,
-                                                       double* __restrict__ k, double* __restrict__ dkdx,
-                                                       double* __restrict__ dkdnu, int64_t n, int result, double L,
-                                                       double Lq, 
-                                                       unsigned long long* __restrict__ stats)
+// K, dK/dx and dK/dnu where the fast window does not apply: the K integral at orders nu and
+// |nu - 1| and the dK/dnu integral, each with its own exact solve. Out of line and rare.
+struct DerivOut {
+    double k, dx, dn;
+    unsigned int nodes;
+};
+
+__device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, double Lq, int result)
+{
+    const RuleTable& R = rule_tab();
+    const double* T = R.tab;
+    DerivOut o;
+    const Solved s0 = plain_plan(v, z, L, Lq, R, T);
+    double hs0 = s0.p.h * sum_f64(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
+    hs0 = fma(hs0, s0.dlo, hs0);
+    o.k = assemble(z, s0.delta, hs0, result, T);
+    const double v1 = fabs(v - 1.0);
+    const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
+    double hs1 = s1.p.h * sum_f64(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    hs1 = fma(hs1, s1.dlo, hs1);
+    o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
+    o.nodes = (unsigned int)(s0.p.N + s1.p.N + 2);
+    o.dn = 0.0;
+    if (v > 0.0) {
+        const Solved sd = dnu_solve(v, z, s0.p.t0, L, Lq, R, T);
+        o.dn = assemble(z, sd.delta, sd.p.h * sum_dnu_f64(v, sd.p, sd.A, sd.B, T), result, T);
+        o.nodes += (unsigned int)(sd.p.N + 1);
+    }
+    return o;
+}
+
+// K_nu(x), dK/dx and dK/dnu, FP64, by one window and one walk for the three integrals
+// (sum_deriv), the entries sorted and drawn as in k_besselk_plain. NULL outputs are not
+// stored. dK/dnu carries the sign of nu. 2^22 pairs of the (nu, x) grid: 1,729 us with a
+// solve and a walk for each integral, unsorted (1,205 with the FP32 windows there); 301 now.
+template <int kThreads, int kPer>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_besselk_deriv(
+    const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ k, double* __restrict__ dkdx,
+    double* __restrict__ dkdnu, int64_t n, int result, double L, double Lq, unsigned long long* __restrict__ stats)
 {
     __shared__ double s_tab[kTabLen];
-    stage_tab(s_tab);
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    unsigned long long nodes = 0, ents = 0;
-    if (i < n) {
-        const double nr = nu[i], z = x[i], v = fabs(nr);
-        double rk, rx, rn;
-        if (isnan(nr) || isnan(z) || z < 0.0) {
-            rk = rx = rn = __builtin_nan("");
-        } else if (z == 0.0 || isinf(v)) {
-            rk = __builtin_inf();
-            rx = -__builtin_inf();
-            rn = v == 0.0 ? 0.0 : copysign(__builtin_inf(), nr);
-        } else if (isinf(z)) {
-            rk = 0.0;
-            rx = -0.0;
-            rn = copysign(0.0, nr);
-        } else {
-            const RuleTable& R = rule_tab();
-            const Solved s0 = plain_plan(v, z, L, Lq, R, s_tab);
-            double hs0 = s0.p.h * sum_f64(v, z, s0.p, s0.E, s0.Ei, s0.Sr, s_tab);
-            hs0 = fma(hs0, s0.dlo, hs0);
-            rk = assemble(z, s0.delta, hs0, result, s_tab);
-            nodes += (unsigned long long)(s0.p.N + 1);
-            rx = 0.0;
-            if (dkdx) {
-                const double v1 = fabs(v - 1.0);
-                const Solved s1 = plain_plan(v1, z, L, Lq, R, s_tab);
-                double hs1 = s1.p.h * sum_f64(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, s_tab);
-                hs1 = fma(hs1, s1.dlo, hs1);
-                nodes += (unsigned long long)(s1.p.N + 1);
-                rx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
-            }
-            rn = 0.0;
-            if (dkdnu && v > 0.0) {
-                const Solved sd = dnu_solve(v, z, s0.p.t0, L, Lq, R, s_tab);
-                const double hsd = sd.p.h * sum_dnu_f64(v, sd.p, sd.A, sd.B, s_tab);
-                nodes += (unsigned long long)(sd.p.N + 1);
-                rn = copysign(assemble(z, sd.delta, hsd, result, s_tab), nr);
-            } else if (dkdnu) {
-                rn = copysign(0.0, nr);
-            }
-            ents = 1;
-        }
+    __shared__ DrawBlock<kThreads, kPer> B;
+    const int tid = threadIdx.x;
+    for (int j = tid; j < kTabLen; j += kThreads) s_tab[j] = rule_tab().tab[j];   // read after the barriers
+    B.begin();
+    const int64_t i0 = (int64_t)blockIdx.x * B.kEntries;
+    auto store = [&](int64_t i, double rk, double rx, double rn) {
         if (k) k[i] = rk;
         if (dkdx) dkdx[i] = rx;
         if (dkdnu) dkdnu[i] = rn;
+    };
+    double v[kPer], z[kPer];
+    float t0[kPer], t1[kPer];
+    unsigned int e[kPer], rank[kPer];
+    int key[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int64_t i = i0 + q * kThreads + tid;
+        unsigned int N = 0u, mc = 0u;
+        v[q] = 0.0;
+        z[q] = 1.0;
+        t0[q] = t1[q] = 0.0f;
+        if (i < n) {
+            const double nr = nu[i], av = fabs(nr);
+            v[q] = nr;
+            z[q] = x[i];
+            if (isnan(nr) || isnan(z[q]) || z[q] < 0.0)
+                store(i, __builtin_nan(""), __builtin_nan(""), __builtin_nan(""));
+            else if (z[q] == 0.0 || isinf(av))
+                store(i, __builtin_inf(), -__builtin_inf(), av == 0.0 ? 0.0 : copysign(__builtin_inf(), nr));
+            else if (isinf(z[q]))
+                store(i, 0.0, -0.0, copysign(0.0, nr));
+            else if (!deriv_fast_ok(av, z[q], L))
+                N = kEntryExact;
+            else
+                deriv_window_count(av, z[q], L, Lq, t0[q], t1[q], N, mc);
+        }
+        e[q] = (unsigned int)(q * kThreads + tid) | (mc << 10) | (N << 20);
+        key[q] = B.key_of(N, v[q]);
+        rank[q] = B.rank(key[q]);
     }
-    if (stats) {
-        block_count_w(stats + BK_STAT_NODES, nodes, 4);
-        block_count_w(stats + BK_STAT_ENTRIES, ents, 4);
+    B.place(v, z, t0, t1, e, key, rank);
+    DrawCounts cnt;
+    for (int c = B.draw(); c >= 0; c = B.draw()) {
+        const int j = c + (tid & 63);
+        const unsigned int ej = B.e[j], N = ej >> 20;
+        unsigned int walked = 0u;
+        if (N != 0u) {
+            const double nr = B.v[j], vj = fabs(nr), zj = B.z[j];
+            double rk, rx, rn;
+            if (N == kEntryExact) {
+                const DerivOut o = deriv_exact(vj, zj, L, Lq, result);
+                rk = o.k;
+                rx = o.dx;
+                rn = o.dn;
+                walked = o.nodes;
+            } else {
+                const Solved s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
+                const DerivSums S = sum_deriv(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                const double h = fma(s.p.h, s.dlo, s.p.h);      // with the low part of Delta
+                rk = assemble(zj, s.delta, h * S.k, result, s_tab);
+                // cosh t = cosh t_ref + (x (cosh t - cosh t_ref)) / x
+                rx = -assemble(zj, s.delta, h * fma(0.5 * (s.E + s.Ei), S.k, S.x * recip(zj)), result, s_tab);
+                rn = assemble(zj, s.delta, h * S.d, result, s_tab);
+                walked = (unsigned int)(s.p.N + 1);
+            }
+            store(i0 + (ej & 1023u), rk, rx, copysign(vj > 0.0 ? rn : 0.0, nr));
+        }
+        if (stats) cnt.add(walked);
     }
+    if (stats) cnt.store(stats, kThreads / 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -632,7 +726,7 @@ extern "C" int bk_besselk(const double* nu, const double* x, double* out, int64_
     return bk_besselk_ex(nu, x, out, n, &p, stream);
 }
 
-constexpr int64_t kPlainSmall = 1 << 17;
+constexpr int64_t kPlainSmall = 1 << 17, kDerivSmall = 300000;
 
 // One kernel between the caller's optional event pair.
 template <typename K, typename... A>
@@ -844,10 +938,14 @@ extern "C" int bk_besselk_deriv(const double* nu, const double* x, double* k, do
     if (!nu || !x || (!k && !dk_dx && !dk_dnu)) return BK_EINVAL;
     double L, Lq;
     resolve_thresholds(BK_PLAIN_F64, p.L_window, p.L_quad, &L, &Lq);
-    const int64_t blocks = (n + 255) / 256;
-    if (blocks > 0x7fffffffLL) return BK_EINVAL;
-    return launch(k_besselk_deriv, dim3((unsigned)blocks), dim3(256), stream, nu, x, k, dk_dx, dk_dnu, n, p.result,
-                  L, Lq, p.stats);
+    if ((n + 255) / 256 > 0x7fffffffLL) return BK_EINVAL;
+    // as bk_besselk_ex's plain form: 16,384 pairs 19 us against 42; 262,144 39 against 44;
+    // 1,048,576 122 against 90
+    if (n < kDerivSmall)
+        return launch(k_besselk_deriv<64, 1>, dim3((unsigned)((n + 63) / 64)), dim3(64), stream, nu, x, k, dk_dx, dk_dnu,
+                      n, p.result, L, Lq, p.stats);
+    return launch(k_besselk_deriv<256, 4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), stream, nu, x, k, dk_dx,
+                  dk_dnu, n, p.result, L, Lq, p.stats);
 }
 
 template <typename OutT>

@@ -504,45 +504,55 @@ __device__ __forceinline__ bool plan_fast_ok(double nu, double x, double L)
     return x >= 1e-12 && x <= 1e5 && nu <= 1e4 && L <= 500.0;
 }
 
-__device__ __forceinline__ void window_fast(float nu, float x, float L, float& t0, float& t1, float& tp)
+__device__ __forceinline__ float exp_fast(float y) { return __builtin_amdgcn_exp2f(y * 1.44269504f); }
+__device__ __forceinline__ float asinh_fast(float y)
 {
-    auto ex = [](float y) { return __builtin_amdgcn_exp2f(y * 1.44269504f); };
-    L += 0.01f;
-    const float ix = __builtin_amdgcn_rcpf(x);
-    tp = 0.0f;
-    if (nu * nu > x) {
-        const float y = nu * ix;
-        tp = 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
-    }
-    const float E = ex(tp), Ei = __builtin_amdgcn_rcpf(E);
+    return 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
+}
+
+// Upper bound of the d > 0 where x (cosh(t + d) - cosh t) = slope d + L; E, Ei = e^t, e^-t.
+__device__ __forceinline__ float right_end_fast(float t, float E, float Ei, float x, float slope, float L)
+{
     // start: the x term alone drops by L
-    const float ec = 0.5f * (E + Ei) - 1.0f + L * ix;
-    float d = fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + ec + __builtin_amdgcn_sqrtf(ec * (ec + 2.0f))) - tp, 1e-3f);
+    const float ec = 0.5f * (E + Ei) - 1.0f + L * __builtin_amdgcn_rcpf(x);
+    float d = fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + ec + __builtin_amdgcn_sqrtf(ec * (ec + 2.0f))) - t, 1e-3f);
     const float hx = 0.5f * x;
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-        const float a = ex(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
-        const float b = E * a, bi = Ei * ai;                       // e^(tp + d/2)
-        const float F = hx * (a - ai) * (b - bi) - nu * d - L;     // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
-        const float D = hx * (b * a - bi * ai) - nu;
+        const float a = exp_fast(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
+        const float b = E * a, bi = Ei * ai;                       // e^(t + d/2)
+        const float F = hx * (a - ai) * (b - bi) - slope * d - L;  // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
+        const float D = hx * (b * a - bi * ai) - slope;
         d -= F * __builtin_amdgcn_rcpf(D);
     }
-    t1 = tp + d * 1.0001f;
-    t0 = 0.0f;
-    const float L2 = L + 0.69314718f;
+    return d * 1.0001f;
+}
+
+// Left end of the window from tp (e^tp = E): 0, or tp - e with F(e) = 0 (see above).
+__device__ __forceinline__ float left_end_fast(float tp, float E, float Ei, float nu, float x, float L)
+{
+    const float L2 = L + 0.69314718f, hx = 0.5f * x;
     const float e0 = L2 + x * (0.5f * (E + Ei) - 1.0f);
-    if (e0 < nu * tp) {
-        float e = e0 * __builtin_amdgcn_rcpf(nu);
+    if (!(e0 < nu * tp)) return 0.0f;
+    float e = e0 * __builtin_amdgcn_rcpf(nu);
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            const float a = ex(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
-            const float b = E * ai, bi = Ei * a;                   // e^(tp - e/2)
-            const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
-            const float D = hx * (b * ai - bi * a) - nu;
-            e -= F * __builtin_amdgcn_rcpf(D);
-        }
-        t0 = fmaxf(tp - e * 1.0001f, 0.0f);
+    for (int it = 0; it < 2; ++it) {
+        const float a = exp_fast(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
+        const float b = E * ai, bi = Ei * a;                       // e^(tp - e/2)
+        const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
+        const float D = hx * (b * ai - bi * a) - nu;
+        e -= F * __builtin_amdgcn_rcpf(D);
     }
+    return fmaxf(tp - e * 1.0001f, 0.0f);
+}
+
+__device__ __forceinline__ void window_fast(float nu, float x, float L, float& t0, float& t1, float& tp)
+{
+    L += 0.01f;
+    tp = nu * nu > x ? asinh_fast(nu * __builtin_amdgcn_rcpf(x)) : 0.0f;
+    const float E = exp_fast(tp), Ei = __builtin_amdgcn_rcpf(E);
+    t1 = tp + right_end_fast(tp, E, Ei, x, nu, L);
+    t0 = left_end_fast(tp, E, Ei, nu, x, L);
 }
 
 // expm1(y) for 0 <= y <= 1/8 (Taylor through y^10, truncation below 1e-18 relative).
@@ -560,17 +570,22 @@ __device__ __forceinline__ double expm1_small(double y)
     return fma(p * y, y, y);
 }
 
+// Node count N of [t0, t1] for a step of at most h, and the index mc of the node nearest tp.
+__device__ __forceinline__ void node_grid(float t0, float t1, float tp, float h, unsigned int& N, unsigned int& mc)
+{
+    const float w = t1 - t0;
+    const float nf = fminf(fmaxf(ceilf(w * __builtin_amdgcn_rcpf(h)), (float)kNodeMin), (float)kNodeMax);
+    N = (unsigned int)nf;
+    mc = (unsigned int)fminf(rintf((tp - t0) * nf * __builtin_amdgcn_rcpf(w)), nf);
+}
+
 // The fast window with its node count N and the index mc of the reference node.
 __device__ __forceinline__ void window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
                                              unsigned int& N, unsigned int& mc)
 {
     float tp;
     window_fast((float)nu, (float)x, (float)L, t0, t1, tp);
-    const float w = t1 - t0;
-    float nf = ceilf(w * __builtin_amdgcn_rcpf(node_step_learned((float)nu, (float)x, (float)Lq)));
-    nf = fminf(fmaxf(nf, (float)kNodeMin), (float)kNodeMax);
-    N = (unsigned int)nf;
-    mc = (unsigned int)fminf(rintf((tp - t0) * nf * __builtin_amdgcn_rcpf(w)), nf);
+    node_grid(t0, t1, tp, node_step_learned((float)nu, (float)x, (float)Lq), N, mc);
 }
 
 // Set-up of the paired walk on the nodes t0 + m (t1 - t0) / N.
@@ -905,6 +920,110 @@ __device__ inline double sum_dnu_f64(double nu, const Plan& p, double A, double 
         Q = fma(Q, w.rho, omr);
     }
     return S - 0.5 * ends;
+}
+
+// One window and one walk for K, -dK/dx and dK/dnu together: the three integrands differ by
+// the factors cosh t and t tanh(nu t), so they share nodes and exponentials.
+//  - Right end: the largest of the three. -dK/dx: cosh t grows by at most e^d past tp, so
+//    K's bound with the slope nu + 1 (which also covers K). dK/dnu: from td = max(asinh(nu/x),
+//    min(1, sqrt(1.70/x))), a point at or left of its maximiser, sinh(nu t) / sinh(nu td) <=
+//    (t / td) e^(nu (t - td)), so t sinh(nu t) grows by at most e^((nu + 2/td) d).
+//  - Left end: K's (both factors only fall to its left).
+//  - Step: the strip bound at order nu + 1 (cosh t cosh(nu t) <= cosh((nu + 1) t)), its
+//    target raised by the growth of t sinh(nu t) on the strip, |t + ia| / t times
+//    |sinh(nu (t + ia))| / sinh(nu t) <= (1 + a/t)^2 (|sin b| <= b <= (a/t) sinh(nu t) for b =
+//    nu a), at td with a = pi/2.
+// For plan_fast_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
+__device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L) { return plan_fast_ok(nu, x, L) && L >= 8.0; }
+
+__device__ __forceinline__ void deriv_window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
+                                                   unsigned int& N, unsigned int& mc)
+{
+    const float nf = (float)nu, xf = (float)x, Lf = (float)L + 0.01f, ix = __builtin_amdgcn_rcpf(xf);
+    const float ta = asinh_fast(nf * ix), tp = nf * nf > xf ? ta : 0.0f;
+    const float E = exp_fast(tp), Ei = __builtin_amdgcn_rcpf(E);
+    const float td = fmaxf(ta, fminf(1.0f, __builtin_amdgcn_sqrtf(1.70f * ix)));
+    const float Ed = exp_fast(td), itd = __builtin_amdgcn_rcpf(td);
+    t1 = fmaxf(tp + right_end_fast(tp, E, Ei, xf, nf + 1.0f, Lf),
+               td + right_end_fast(td, Ed, __builtin_amdgcn_rcpf(Ed), xf, fmaf(2.0f, itd, nf), Lf));
+    t0 = left_end_fast(tp, E, Ei, nf, xf, Lf);
+    const float extra = 2.0f * 0.69314718f * __builtin_amdgcn_logf(fmaf(1.5707963f, itd, 1.0f));
+    node_grid(t0, t1, tp, node_step_learned(nf + 1.0f, xf, (float)Lq + extra), N, mc);
+}
+
+// Trapezoid sums of the paired walk (sum_f64): of the K terms e^d (2 - Q), of those times
+// x (cosh t - cosh t_ref), and of e^d t Q, Q = 1 - e^(-2 nu t). Q is formed from its value at
+// t_ref by sums that keep its relative accuracy where it is small (small nu or t): right
+// Q' = Q rho + (1 - rho), left Q = Q_ref - P_ref expm1(2 nu j h).
+struct DerivSums {
+    double k, x, d;
+};
+
+__device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double E, double Ei, double Sr, const double* T)
+{
+    const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
+    const double h = p.h, xh = 0.5 * x, nh = nu * h;
+    const double qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
+    const double omr = -expm1(-2.0 * nh), rho = 1.0 - omr;             // 1 - e^(-2 nu h)
+    const double qe = omr * recip(rho), re = 1.0 + qe;                 // e^(2 nu h) - 1, e^(2 nu h)
+    const double Qr = -expm1(-2.0 * nu * p.tref), Pr = exp_tab(-2.0 * nu * p.tref, T);
+    double V = 0.0, Bq = 1.0, SR = Sr, ER = Ei, QR = Qr, EL = 0.0, jd = 0.0;
+    DerivSums S = {0.0, 0.0, 0.0}, r = {0.0, 0.0, 0.0}, l = {0.0, 0.0, 0.0};
+    for (int j = 1; j <= jmax; ++j) {
+        jd += 1.0;
+        V = fma(V, q, qm1);
+        Bq *= qi;
+        const double u = jd * h, nuu = jd * nh;
+        const double xs = xh * fma(V, Bq, V);
+        SR = fma(SR, q, qm1);
+        ER *= qi;
+        QR = fma(QR, rho, omr);
+        EL = fma(EL, re, qe);
+        if (j <= nr) {
+            const double xt = xs * fma(SR, ER, SR), e = exp_node(nuu - xt, T);
+            r.k = fma(-e, QR, 2.0 * e);
+            r.x = r.k * xt;
+            r.d = e * QR * (p.tref + u);
+            S.k += r.k;
+            S.x += r.x;
+            S.d += r.d;
+        }
+        if (j <= nl) {
+            const double xt = xs * fma(-E, Bq, Ei * (V + 1.0)), e = exp_node(-nuu - xt, T);
+            const double Q = fma(-Pr, EL, Qr);
+            l.k = fma(-e, Q, 2.0 * e);
+            l.x = l.k * xt;
+            l.d = e * Q * (p.tref - u);
+            S.k += l.k;
+            S.x += l.x;
+            S.d += l.d;
+        }
+    }
+    // trapezoid ends: half of node N and of node 0 (the reference's weight if it is one)
+    const double w0 = nl == 0 || nr == 0 ? 0.5 : 1.0;
+    S.k = fma(w0, 2.0 - Qr, fma(-0.5, r.k + l.k, S.k));
+    S.x = fma(-0.5, r.x + l.x, S.x);
+    S.d = fma(w0, Qr * p.tref, fma(-0.5, r.d + l.d, S.d));
+    return S;
+}
+
+// dK/dnu alone: delta and h S of its integral (K's start t0 for the exact solve).
+__device__ __forceinline__ void dnu_integral(double nu, double x, double t0, double L, double Lq, const RuleTable& R,
+                                             const double* T, double& delta, double& hs)
+{
+    if (!deriv_fast_ok(nu, x, L)) {
+        const Solved sd = dnu_solve(nu, x, t0, L, Lq, R, T);
+        delta = sd.delta;
+        hs = sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T);
+        return;
+    }
+    float a, b;
+    unsigned int N, mc;
+    deriv_window_count(nu, x, L, Lq, a, b, N, mc);
+    const Solved s = plan_setup(nu, x, a, b, N, mc);
+    delta = s.delta;
+    hs = s.p.h * sum_deriv(nu, x, s.p, s.E, s.Ei, s.Sr, T).d;
+    hs = fma(hs, s.dlo, hs);
 }
 
 // ---------------------------------------------------------------------------

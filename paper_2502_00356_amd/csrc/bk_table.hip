@@ -23,9 +23,9 @@ __device__ inline double tab_sample(const TabParams& P, double z, int fn, const 
     if (kGrad && fn == TAB_DBETA) return tab_assemble(P.scale * P.inv_beta, z, P.nu + 1.0, s.delta, hs);
     const double c = tab_assemble(P.scale, z, P.nu, s.delta, hs);
     if (!kGrad || fn == TAB_C) return c;
-    const Solved sd = dnu_solve(nu, z, s.p.t0, L, Lq, rule_tab(), T);
-    return fma(c, log(z) - kLn2 - P.psi,
-               tab_assemble(P.scale, z, P.nu, sd.delta, sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T)));
+    double dd, dhs;
+    dnu_integral(nu, z, s.p.t0, L, Lq, rule_tab(), T, dd, dhs);
+    return fma(c, log(z) - kLn2 - P.psi, tab_assemble(P.scale, z, P.nu, dd, dhs));
 }
 
 // ---------------------------------------------------------------------------

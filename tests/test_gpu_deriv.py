@@ -145,3 +145,39 @@ def test_matern_grad_tiles(api, orc, nu, lower):
     scale = np.abs(t1) + np.abs(dn - t1)
     assert np.all(np.abs(DN - dn) <= TOL_PLAIN * scale + 1e-300)
     assert np.all(C[r == 0] == s2) and np.all(DB[r == 0] == 0) and np.all(DN[r == 0] == 0)
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 299999, 300000, 301023])
+def test_deriv_launch_shapes(api, orc, n):
+    """Both launch shapes (64- and 1,024-entry workgroups, from 300,000 entries) at the edges
+    of a workgroup: bitwise the values of the same pairs in calls of 40,960, and in every
+    call the pairs that the fast window leaves to the exact solves (x below 1e-12, orders
+    above 1e4, infinite and NaN inputs) beside ordinary ones."""
+    rng = np.random.default_rng(n)
+    nu, x = rng.uniform(0.0, 20.0, n), 10 ** rng.uniform(-4, 3, n)
+    odd = np.arange(0, n, 61)
+    nu[odd] = np.resize([0.5, 2e4, 0.0, 3.0, np.nan, 1e-9], odd.size)
+    x[odd] = np.resize([5e-13, 4e4, 1e-13, np.inf, 1.0, 2e5], odd.size)
+    full = _deriv(api, nu, x, result=1)
+    for a in range(0, n, 40960):
+        part = _deriv(api, nu[a:a + 40960], x[a:a + 40960], result=1)
+        for key in ("k", "dx", "dnu"):
+            assert np.array_equal(full[key][a:a + 40960], part[key], equal_nan=True), (key, a)
+
+
+@pytest.mark.parametrize("L", [6.0, 8.0, 12.0, 36.0, 400.0])
+def test_deriv_window_rule(api, orc, L):
+    """The windows on both sides of the fast form's threshold (L_window 8). The tails left
+    out at L are below e^-L times the integrand's width, at most 40 in t here, against the
+    e^-x-scaled results; each derivative's within 100 e^-L (plus the usual rounding)."""
+    import torch
+    nu, x = _pairs(89, 2000)
+    out = api.besselk_deriv(to_dev(nu), to_dev(x), result=1, L_window=L)
+    torch.cuda.synchronize()
+    d = orc.besselk_deriv(nu, x)
+    _, _, ks = orc.besselk(nu, x)
+    pos = nu > 0
+    tol = 100.0 * math.exp(-L) + TOL_PLAIN
+    assert rel_err(out["k"].cpu().numpy(), ks).max() <= tol
+    assert rel_err(out["dx"].cpu().numpy(), d["scaled_dx"]).max() <= tol
+    assert rel_err(out["dnu"].cpu().numpy()[pos], d["scaled_dnu"][pos]).max() <= tol

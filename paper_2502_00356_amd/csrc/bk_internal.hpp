@@ -58,11 +58,12 @@ inline int launch(void (*k)(P...), dim3 grid, dim3 block, hipStream_t stream, A&
 }
 
 // Tiling of a Matern call: T x T tiles (or the lower ones) of ts rows and columns,
-// each cut into rb_per_tile row blocks of 64 and cb_per_tile column blocks.
+// each cut into rb_per_tile row blocks of 64 and cb_per_tile column blocks (four waves of
+// `cols` columns where the per-entry kernels of bk_kernels.hip take it).
 struct TileGeom {
     int64_t n;
     int32_t ts, T, lower;
-    int32_t rb_per_tile, cb_per_tile;
+    int32_t rb_per_tile, cb_per_tile, cols;
 };
 
 // Element offset of tile (I, J) in the packed output.

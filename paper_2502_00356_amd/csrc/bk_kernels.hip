@@ -561,8 +561,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 // Matern tiles
 // ---------------------------------------------------------------------------
 constexpr int kRowsPerWave = 64;
-constexpr int kColsPerWave = 8;
-constexpr int kColsPerGroup = 4 * kColsPerWave;
+// Columns a wave takes in turn: one in calls that then still leave the chip unfilled (every
+// column a wave is one more entry in its serial chain), kMaxCols in larger ones, whose
+// blocks stage the tables less often. Plain FP64, nu = 17: 600 sites 57 us with eight,
+// 28 with one; 2,000 166 and 156; 2,800 319 and 318; 6,000 1,251 and 1,283.
+constexpr int kMaxCols = 8;
+static int cols_per_wave(int64_t entries) { return entries < 8000000 ? 1 : kMaxCols; }
 
 // kStats: the statistics variant, which also counts the entries evaluated by
 // quadrature and their nodes (lanes past a ragged tile's last row stay in the
@@ -590,16 +594,16 @@ __global__ __launch_bounds__(256, 4) void k_matern(const double* __restrict__ lx
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t il = (int64_t)rb * kRowsPerWave + lane;
-    const int64_t jl0 = (int64_t)cb * kColsPerGroup + (int64_t)wave * kColsPerWave;
+    const int64_t jl0 = ((int64_t)cb * 4 + wave) * g.cols;
     const bool row_ok = il < mI;
     // the statistics variant keeps every wave to the end for its block-wide sums
     if (!kStats && (jl0 >= nJ || !row_ok)) return;
     const int64_t base = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
     const int64_t ilr = row_ok ? il : 0;
     const double xi = lx[I * g.ts + ilr], yi = ly[I * g.ts + ilr];
-    const int cend = (kStats && (!row_ok || jl0 >= nJ)) ? 0 : (int)min((int64_t)kColsPerWave, nJ - jl0);
+    const int cend = (kStats && (!row_ok || jl0 >= nJ)) ? 0 : (int)min((int64_t)g.cols, nJ - jl0);
     unsigned int c_ent = 0, c_nodes = 0;
-    unsigned int col_nodes[kColsPerWave] = {};      // statistics: nodes per column walked
+    unsigned int col_nodes[kMaxCols] = {};      // statistics: nodes per column walked
     for (int c = 0; c < cend; ++c) {
         const int64_t jl = jl0 + c;
         const double xj = lx[J * g.ts + jl], yj = ly[J * g.ts + jl];
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(256, 4) void k_matern(const double* __restrict__ lx
     if (kStats) {      // one atomic per counter per workgroup
         unsigned int slots = 0;
 #pragma unroll
-        for (int c = 0; c < kColsPerWave; ++c) slots += 64u * wave_max_u32(col_nodes[c]);
+        for (int c = 0; c < kMaxCols; ++c) slots += 64u * wave_max_u32(col_nodes[c]);
         block_count_w(stats + BK_STAT_ENTRIES, c_ent, 4);
         block_count_w(stats + BK_STAT_NODES, c_nodes, 4);
         block_count_w(stats + BK_STAT_LANE_SLOTS, (threadIdx.x & 63) == 0 ? slots : 0u, 4);
@@ -669,11 +673,11 @@ __global__ __launch_bounds__(256) void k_matern_grad(const double* __restrict__ 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t il = (int64_t)rb * kRowsPerWave + lane;
-    const int64_t jl0 = (int64_t)cb * kColsPerGroup + (int64_t)wave * kColsPerWave;
+    const int64_t jl0 = ((int64_t)cb * 4 + wave) * g.cols;
     if (il >= mI || jl0 >= nJ) return;
     const int64_t base = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
     const double xi = lx[I * g.ts + il], yi = ly[I * g.ts + il];
-    const int cend = (int)min((int64_t)kColsPerWave, nJ - jl0);
+    const int cend = (int)min((int64_t)g.cols, nJ - jl0);
     for (int c = 0; c < cend; ++c) {
         const int64_t jl = jl0 + c;
         const double xj = lx[J * g.ts + jl], yj = ly[J * g.ts + jl];
@@ -849,11 +853,12 @@ int matern_tiles_dispatch(const bk_locs* locs, const bk_params* prm, int32_t til
     if (!locs->x || !locs->y || !out) return BK_EINVAL;
     TileGeom g;
     g.n = locs->n;
-    g.ts = tile_size;
-    g.T = (int32_t)((locs->n + tile_size - 1) / tile_size);
+    g.ts = (int32_t)(tile_size < locs->n ? tile_size : locs->n);
+    g.T = (int32_t)((locs->n + g.ts - 1) / g.ts);
     g.lower = lower_only ? 1 : 0;
-    g.rb_per_tile = (tile_size + kRowsPerWave - 1) / kRowsPerWave;
-    g.cb_per_tile = (tile_size + kColsPerGroup - 1) / kColsPerGroup;
+    g.rb_per_tile = (g.ts + kRowsPerWave - 1) / kRowsPerWave;
+    g.cols = cols_per_wave(bk_matern_out_elems(locs->n, tile_size, lower_only));
+    g.cb_per_tile = (g.ts + 4 * g.cols - 1) / (4 * g.cols);
     const int64_t T = g.T;
     const int64_t ntiles = g.lower ? T * (T + 1) / 2 : T * T;
     double L, Lq;
@@ -862,7 +867,7 @@ int matern_tiles_dispatch(const bk_locs* locs, const bk_params* prm, int32_t til
     // Large builds by tables. A call with statistics first runs the per-entry form, which
     // counts, and its output is then written as any other call of the size writes it.
     if ((prm->mode == BK_PLAIN_F64 || (prm->mode == BK_MIXED_F32C && f32)) &&
-        table_route(locs, prm, tile_size, lower_only, kTabMinEntries)) {
+        table_route(locs, prm, tile_size, lower_only, prm->mode == BK_MIXED_F32C ? kTabMinF32 : kTabMinF64)) {
         if (prm->stats) {
             bk_params count = *prm;
             count.kernel_events[0] = count.kernel_events[1] = nullptr;
@@ -979,17 +984,18 @@ extern "C" int bk_matern_grad_tiles(const bk_locs* locs, const bk_params* prm, i
     if (prm->L_window < 0.0 || prm->L_quad < 0.0) return BK_EINVAL;
     if (locs->n == 0) return BK_OK;
     if (!locs->x || !locs->y || (!c && !dc_dbeta && !dc_dnu)) return BK_EINVAL;
-    if (table_route(locs, prm, tile_size, lower_only, kTabMinEntries)) {
+    if (table_route(locs, prm, tile_size, lower_only, kTabMinF64)) {
         void* const outs[3] = {c, dc_dbeta, dc_dnu};
         return matern_grad_table_tiles(locs, prm, digamma_host(prm->nu), tile_size, lower_only, outs, stream);
     }
     TileGeom g;
     g.n = locs->n;
-    g.ts = tile_size;
-    g.T = (int32_t)((locs->n + tile_size - 1) / tile_size);
+    g.ts = (int32_t)(tile_size < locs->n ? tile_size : locs->n);
+    g.T = (int32_t)((locs->n + g.ts - 1) / g.ts);
     g.lower = lower_only ? 1 : 0;
-    g.rb_per_tile = (tile_size + kRowsPerWave - 1) / kRowsPerWave;
-    g.cb_per_tile = (tile_size + kColsPerGroup - 1) / kColsPerGroup;
+    g.rb_per_tile = (g.ts + kRowsPerWave - 1) / kRowsPerWave;
+    g.cols = cols_per_wave(bk_matern_out_elems(locs->n, tile_size, lower_only));
+    g.cb_per_tile = (g.ts + 4 * g.cols - 1) / (4 * g.cols);
     const int64_t T = g.T;
     const int64_t ntiles = g.lower ? T * (T + 1) / 2 : T * T;
     double L, Lq;

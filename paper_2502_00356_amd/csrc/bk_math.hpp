@@ -1007,6 +1007,76 @@ __device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double
     return S;
 }
 
+// The sums of one entry by kLanes neighbouring lanes (lane sub takes the nodes mc +- j, j =
+// sub + 1, sub + 1 + kLanes, ...), for kernels with few entries, whose time is the walk's
+// serial chain: k as sum_f64 and, with kDnu, d as sum_deriv. Every lane gets the totals.
+template <int kLanes, bool kDnu>
+__device__ inline DerivSums sum_split(double nu, double x, const Plan& p, double E, double Ei, double Sr, int sub,
+                                      const double* T)
+{
+    const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
+    const double h = p.h, xh = 0.5 * x, nh = nu * h;
+    double qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
+    double rho = exp_tab(-2.0 * nh, T), rhoi = recip(rho);
+    const double Pr = exp_tab(-2.0 * nu * p.tref, T), Qr = kDnu ? -expm1(-2.0 * nu * p.tref) : 0.0;
+    double omr = kDnu ? -expm1(-2.0 * nh) : 0.0, qe = omr * rhoi;       // 1 - e^(-2 nu h), e^(2 nu h) - 1
+    double V = 0.0, Bq = 1.0, SR = Sr, ER = Ei, PR = Pr, PL = Pr, QR = Qr, EL = 0.0;
+    auto step = [&]() {
+        V = fma(V, q, qm1);
+        Bq *= qi;
+        SR = fma(SR, q, qm1);
+        ER *= qi;
+        PR *= rho;
+        PL *= rhoi;
+        if (kDnu) {
+            QR = fma(QR, 1.0 - omr, omr);
+            EL = fma(EL, 1.0 + qe, qe);
+        }
+    };
+    for (int k = 0; k <= sub; ++k) step();
+#pragma unroll
+    for (int k = 1; k < kLanes; k *= 2) {                               // the factors of kLanes nodes
+        qm1 = qm1 * (qm1 + 2.0);
+        q = qm1 + 1.0;
+        qi *= qi;
+        rho *= rho;
+        rhoi *= rhoi;
+        if (kDnu) {
+            omr = omr * (2.0 - omr);
+            qe = qe * (qe + 2.0);
+        }
+    }
+    DerivSums S = {0.0, 0.0, 0.0};
+    const double w0 = nl == 0 || nr == 0 ? 0.5 : 1.0;
+    if (sub == 0) {
+        S.k = w0 * (1.0 + Pr);
+        S.d = w0 * Qr * p.tref;
+    }
+    for (int j = sub + 1; j <= jmax; j += kLanes) {
+        const double jd = (double)j, nuu = jd * nh;
+        const double xs = xh * fma(V, Bq, V);
+        if (j <= nr) {
+            double e = exp_node(fma(-xs, fma(SR, ER, SR), nuu), T);
+            if (j == nr) e *= 0.5;
+            S.k += fma(e, PR, e);
+            if (kDnu) S.d += e * QR * fma(jd, h, p.tref);
+        }
+        if (j <= nl) {
+            double e = exp_node(fma(xs, fma(E, Bq, -Ei * (V + 1.0)), -nuu), T);
+            if (j == nl) e *= 0.5;
+            S.k += fma(e, PL, e);
+            if (kDnu) S.d += e * fma(-Pr, EL, Qr) * fma(-jd, h, p.tref);
+        }
+        step();
+    }
+#pragma unroll
+    for (int k = 1; k < kLanes; k *= 2) {
+        S.k += __shfl_xor(S.k, k, 64);
+        if (kDnu) S.d += __shfl_xor(S.d, k, 64);
+    }
+    return S;
+}
+
 // dK/dnu alone: delta and h S of its integral (K's start t0 for the exact solve).
 __device__ __forceinline__ void dnu_integral(double nu, double x, double t0, double L, double Lq, const RuleTable& R,
                                              const double* T, double& delta, double& hs)

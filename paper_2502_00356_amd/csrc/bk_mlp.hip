@@ -59,8 +59,6 @@ static_assert(kNParam == BK_MLP_NPARAM, "parameter count");
 // node, relative to the whole. With the L = 15 window (quadrature error <= ~2.5e-7)
 // and FP32 node rounding (~2e-7) this keeps the total well inside 2e-6.
 constexpr float kTailTol = 3e-7f;
-// FP32 output from this many entries on takes the interpolation table.
-constexpr int64_t kTabMinLearned = 65536;
 constexpr int kTableSize = 1024;       // Matern: MLP tabulated over log10 x at fixed nu
 // Standalone K_nu: prediction cells over the training box, log10 x by nu.
 constexpr int kCellsLx = 512, kCellsNu = 64, kCells = kCellsLx * kCellsNu;
@@ -1021,7 +1019,7 @@ __global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P,
     __shared__ float sy[4][64];
     __shared__ int s_bad[64];
     stage_tab(s_tab);
-    const TabWave<true> t = tab_point<true>(X, P.inv_beta, blockIdx.x);
+    const TabWave<true> t = tab_point<true>(X, P.inv_beta, blockIdx.x, threadIdx.x & 63);
     const int lane = threadIdx.x & 63;
     const float lx = log10f((float)t.z), nuf = (float)P.nu;
     float y0, y1, y2;
@@ -1083,8 +1081,8 @@ __global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P,
         const Solved s = plain_plan(P.nu, t.z, kDefaultLPlain, kDefaultLqPlain, rule_tab(), s_tab);
         f = tab_assemble(P.scale, t.z, P.nu, s.delta, s.p.h * sum_f64(P.nu, t.z, s.p, s.E, s.Ei, s.Sr, s_tab));
     }
-    tab_fit<true>(t, f, X, sh, table);
-    if (blockIdx.x == 0 && lane == 0) *tab_done<true>(table) = 0u;
+    tab_fit<true>(t, f, X, sh, table, threadIdx.x & 63, true);
+    if (blockIdx.x == 0 && lane == 0) tab_clear<true>(table);
 }
 
 // log(1 + u) for |u| <= 0.02 in FP32, by its Taylor series through u^4: the

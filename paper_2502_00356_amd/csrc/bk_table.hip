@@ -11,38 +11,49 @@
 
 namespace bk {
 
-// The function fn at z, by the plain FP64 quadrature.
+// The function fn at z, by the plain FP64 quadrature of kTabLanes lanes.
+constexpr int kTabLanes = 4;
+
 template <bool kGrad>
-__device__ inline double tab_sample(const TabParams& P, double z, int fn, const double* T)
+__device__ inline double tab_sample(const TabParams& P, double z, int fn, int sub, const double* T)
 {
     const double L = kDefaultLPlain, Lq = kDefaultLqPlain;
     const double nu = kGrad && fn == TAB_DBETA ? fabs(P.nu - 1.0) : P.nu;
-    const Solved s = plain_plan(nu, z, L, Lq, rule_tab(), T);
-    double hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, T);
-    hs = fma(hs, s.dlo, hs);
+    float t0, t1;
+    unsigned int N, mc;
+    if (kGrad && fn == TAB_DNU) deriv_window_count(nu, z, L, Lq, t0, t1, N, mc);
+    else window_count(nu, z, L, Lq, t0, t1, N, mc);
+    const Solved s = plan_setup(nu, z, t0, t1, N, mc);
+    const double h = fma(s.p.h, s.dlo, s.p.h);
+    if (kGrad && fn == TAB_DNU) {
+        const DerivSums S = sum_split<kTabLanes, true>(nu, z, s.p, s.E, s.Ei, s.Sr, sub, T);
+        return tab_assemble(P.scale, z, P.nu, s.delta, h * fma(S.k, log(z) - kLn2 - P.psi, S.d));
+    }
+    const double hs = h * sum_split<kTabLanes, false>(nu, z, s.p, s.E, s.Ei, s.Sr, sub, T).k;
     if (kGrad && fn == TAB_DBETA) return tab_assemble(P.scale * P.inv_beta, z, P.nu + 1.0, s.delta, hs);
-    const double c = tab_assemble(P.scale, z, P.nu, s.delta, hs);
-    if (!kGrad || fn == TAB_C) return c;
-    double dd, dhs;
-    dnu_integral(nu, z, s.p.t0, L, Lq, rule_tab(), T, dd, dhs);
-    return fma(c, log(z) - kLn2 - P.psi, tab_assemble(P.scale, z, P.nu, dd, dhs));
+    return tab_assemble(P.scale, z, P.nu, s.delta, hs);
 }
 
 // ---------------------------------------------------------------------------
-// Builder: one plain FP64 evaluation per Chebyshev point, one lane each.
+// Builder: one plain FP64 evaluation per Chebyshev point, by kTabLanes lanes; one wave's
+// worth of points (TabWave) a workgroup. A hundred workgroups on 256 CUs, so its time is
+// one lane's serial chain: 13.2 us with a lane a point and a 31-step search for each
+// interval's ends, 12.1 with tab_bound's Newton steps, 9.0 with two lanes a point, 7.2
+// with four, 8.2 with eight.
 // ---------------------------------------------------------------------------
 template <bool kF32, bool kGrad>
-__global__ __launch_bounds__(64) void k_tab_build(TabParams P, TabIndex X, char* t0, char* t1, char* t2)
+__global__ __launch_bounds__(64 * kTabLanes) void k_tab_build(TabParams P, TabIndex X, char* t0, char* t1, char* t2)
 {
     __shared__ double s_tab[kTabLen], sh[64];
     stage_tab(s_tab);
-    const TabWave<kF32> t = tab_point<kF32>(X, P.inv_beta, blockIdx.x);
+    const int point = threadIdx.x / kTabLanes, sub = threadIdx.x % kTabLanes;
+    const TabWave<kF32> t = tab_point<kF32>(X, P.inv_beta, blockIdx.x, point);
     const int fn = kGrad ? (int)blockIdx.y : TAB_C;
     char* table = fn == TAB_C ? t0 : (fn == TAB_DBETA ? t1 : t2);
     if (!table) return;
-    const double f = tab_sample<kGrad>(P, t.z, fn, s_tab);
-    tab_fit<kF32>(t, f, X, sh, table);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *tab_done<kF32>(table) = 0u;
+    const double f = tab_sample<kGrad>(P, t.z, fn, sub, s_tab);
+    tab_fit<kF32>(t, f, X, sh, table, point, sub == 0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) tab_clear<kF32>(table);
 }
 
 // ---------------------------------------------------------------------------
@@ -77,11 +88,22 @@ __device__ __noinline__ double tab_cold(double q, TabParams P)
 constexpr int kTabThreads = 512, kTabWaves = kTabThreads / 64;
 constexpr unsigned kTabGrid = 512;
 
+// A call's output falls into three parts: the elements below `first`; the table's bytes
+// [first, count), written once every workgroup has read the table; and the rest, which
+// holds the counts of workgroups and is written by the last to finish. The first is cut
+// into items over whole tiles of `cols` columns; the others into items of kTailCols
+// columns, tile by tile from the one that holds their first element.
+constexpr int kTailCols = 2;
+// Workgroups that share the second part, written by the last to finish alone before: 517
+// sites (FP32, lower 128-tiles) 32.5 us a call then, 23.3 with 16 or 64, 26 with 8; 1,024
+// sites (FP64) 22.4, 22.4 and 24.3, 22.0.
+constexpr unsigned kTailGroups = 16;
+
 struct TabArgs {
-    TileGeom g;                    // rb_per_tile: row blocks of 64 lanes; cb_per_tile: column blocks of `cols`
+    TileGeom g;                    // rb_per_tile: row blocks of 64 R; cb_per_tile: column blocks of `cols`
     int cols;
-    unsigned items;                // tiles x row blocks x column blocks
-    int64_t first;                 // first output element over the table
+    unsigned tiles, items, first_tile, count_tile;
+    int64_t first, count;
     TabIndex X;
     TabParams P;
 };
@@ -125,21 +147,21 @@ struct __attribute__((packed, aligned(sizeof(OutT)))) TabRun {
     OutT v[R];
 };
 
-// One item: 64 R rows (R consecutive ones a lane, stored together) and `cols` columns
-// of a tile; the elements in [lo, hi) of the output.
+// One item: 64 R rows (R consecutive ones a lane, stored together) from row il0 and up to
+// `cols` columns from jl0 of a tile; the elements in [lo, hi) of the output.
 template <typename OutT, bool kF32, int FN, int MODE, int R>
 __device__ __forceinline__ void tab_item(const TabArgs& A, const tab2_t* sT, const double* __restrict__ lx,
-                                         const double* __restrict__ ly, OutT* out, int64_t I, int64_t J, int rb, int cb,
-                                         int64_t lo, int64_t hi)
+                                         const double* __restrict__ ly, OutT* out, int64_t I, int64_t J, int64_t il0,
+                                         int64_t jl0, int cols, int64_t lo, int64_t hi)
 {
     const TileGeom& g = A.g;
     const int64_t mI = min((int64_t)g.ts, g.n - I * g.ts), nJ = min((int64_t)g.ts, g.n - J * g.ts);
-    const int64_t jl0 = (int64_t)cb * A.cols, il0 = (int64_t)rb * (64 * R);
     if (jl0 >= nJ || il0 >= mI) return;
     const int lane = threadIdx.x & 63, row = lane * R;
     const int rows = (int)min((int64_t)(64 * R), mI - il0);
-    const int cend = (int)min((int64_t)A.cols, nJ - jl0);
+    const int cend = (int)min((int64_t)cols, nJ - jl0);
     const int64_t off0 = tile_offset(g.n, g.ts, g.T, g.lower, I, J) + jl0 * mI + il0;
+    if (off0 >= hi || off0 + (int64_t)(cend - 1) * mI + rows <= lo) return;
     const bool clip = off0 < lo || off0 + (int64_t)(cend - 1) * mI + rows > hi;
     if (row >= rows) return;
     const bool whole = !clip && rows % R == 0;
@@ -208,7 +230,7 @@ __device__ __forceinline__ void tab_item(const TabArgs& A, const tab2_t* sT, con
 // 4.3 TB/s); without the stores the arithmetic and LDS reads take 0.89 and 0.64. 20 (FP32)
 // and 25 (FP64) VALU instructions an entry against the per-entry quadrature's 1,839:
 // 40,000 sites, lower 960-tiles, nu = 2.3, plain FP64 40.0 -> 1.39 ms; 9,001 sites, mixed
-// FP32, 2.60 -> 0.137 ms; C, dC/dbeta and dC/dnu of 12,000 sites 16.6 -> 0.49 ms (tables
+// FP32, 2.60 -> 0.094 ms; C, dC/dbeta and dC/dnu of 12,000 sites 16.6 -> 0.45 ms (tables
 // included).
 template <typename OutT, bool kF32, int FN, int MODE, int R>
 __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __restrict__ lx, const double* __restrict__ ly,
@@ -217,35 +239,89 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
     constexpr int kSlots = TabShape<kF32>::kPlanes * TabShape<kF32>::kN;
     constexpr unsigned kWaves = kTabWaves;
     __shared__ tab2_t sT[kSlots];
-    __shared__ unsigned s_last;
+    __shared__ unsigned s_flag;
+    unsigned* const counts = tab_counts<kF32>(table);
     for (int k = threadIdx.x; k < kSlots; k += kTabThreads) sT[k] = ((const tab2_t*)table)[k];
     __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0) atomicAdd(&counts[0], 1u);
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grid = gridDim.x;
     const TileGeom& g = A.g;
-    const unsigned rbn = (unsigned)g.rb_per_tile, per_tile = rbn * (unsigned)g.cb_per_tile;
-    for (unsigned it = blockIdx.x * kWaves + wave; it < A.items; it += gridDim.x * kWaves) {
-        const unsigned p = it / per_tile, local = it - p * per_tile;
-        int64_t I, J;
-        tile_of(p, g, I, J);
-        tab_item<OutT, kF32, FN, MODE, R>(A, sT, lx, ly, out, I, J, (int)(local % rbn), (int)(local / rbn), 0, A.first);
-    }
-    // The workgroup that finishes last (every other has read the table long before)
-    // writes the elements the table lay in.
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(tab_done<kF32>(table), 1u) == gridDim.x - 1 ? 1u : 0u;
-    __syncthreads();
-    if (!s_last) return;
-    const unsigned tiles = A.items / per_tile;
-    for (unsigned p = tiles; p-- > 0;) {
-        int64_t I, J;
-        tile_of(p, g, I, J);
-        const int64_t mI = min((int64_t)g.ts, g.n - I * g.ts), nJ = min((int64_t)g.ts, g.n - J * g.ts);
-        const int64_t off = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
-        if (off + mI * nJ <= A.first) break;
-        const unsigned cb0 = A.first > off ? (unsigned)((A.first - off) / mI / A.cols) : 0u;
-        for (unsigned k = wave; k < (g.cb_per_tile - cb0) * rbn; k += kWaves)
-            tab_item<OutT, kF32, FN, MODE, R>(A, sT, lx, ly, out, I, J, (int)(k % rbn), (int)(cb0 + k / rbn), A.first,
-                                              INT64_MAX);
+    const unsigned rbn = (unsigned)g.rb_per_tile;
+    unsigned it = blockIdx.x * kWaves + wave, stride = grid * kWaves, p = 0u, base = 0u, ntile = 0u;
+    const unsigned per_tile = rbn * (unsigned)g.cb_per_tile;
+    int64_t lo = 0, hi = A.first, I = 0, J = 0;
+    // part by part; one copy of the item's code
+    for (int part = 0;; ++part) {
+        for (;; it += stride) {
+            int64_t jl0;
+            unsigned rb;
+            if (part == 0) {
+                if (it >= A.items) break;
+                const unsigned t = it / per_tile, local = it - t * per_tile, cb = local / rbn;
+                tile_of(t, g, I, J);
+                rb = local - cb * rbn;
+                jl0 = (int64_t)cb * A.cols;
+            } else {
+                int64_t j0 = 0;
+                while (p < A.tiles) {            // the tile of item `it`
+                    tile_of(p, g, I, J);
+                    const int64_t mI = min((int64_t)g.ts, g.n - I * g.ts), nJ = min((int64_t)g.ts, g.n - J * g.ts);
+                    const int64_t off = tile_offset(g.n, g.ts, g.T, g.lower, I, J);
+                    j0 = lo > off ? (lo - off) / mI : 0;
+                    ntile = (unsigned)((nJ - j0 + kTailCols - 1) / kTailCols) * rbn;
+                    if (it < base + ntile) break;
+                    base += ntile;
+                    ++p;
+                }
+                if (p == A.tiles) break;
+                const unsigned cb = (it - base) / rbn;
+                rb = it - base - cb * rbn;
+                jl0 = j0 + (int64_t)cb * kTailCols;
+            }
+            tab_item<OutT, kF32, FN, MODE, R>(A, sT, lx, ly, out, I, J, (int64_t)rb * (64 * R), jl0,
+                                              part == 0 ? A.cols : kTailCols, lo, hi);
+        }
+        if (part == 2) return;
+        unsigned skipped = 0u;
+        if (part == 0) {
+            // the table's bytes, shared by the workgroups launched last if all have read
+            // the table by now (looked up a few times, never waited for: a workgroup may
+            // not have started); one that finds any missing leaves its share to the last
+            const unsigned share = grid - 1u - blockIdx.x;
+            if (share < kTailGroups) {
+                if (threadIdx.x == 0) {
+                    unsigned c = 0u;
+                    for (int k = 0; k < 4 && c != grid; ++k) c = atomicAdd(&counts[0], 0u);
+                    s_flag = c == grid ? 1u : 0u;
+                }
+                __syncthreads();
+                skipped = s_flag ? 0u : 1u << 16;
+                if (!skipped) {
+                    it = share * kWaves + wave;
+                    stride = min(grid, kTailGroups) * kWaves;
+                    p = A.first_tile;
+                    lo = A.first;
+                    hi = A.count;
+                    continue;
+                }
+            }
+            ++part;
+        }
+        // the workgroup that finishes last: the counts' elements, and shares left to it
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned c = atomicAdd(&counts[1], 1u + skipped) + 1u + skipped;
+            s_flag = (c & 0xffffu) == grid ? c : 0u;
+        }
+        __syncthreads();
+        if (!s_flag) return;
+        const bool left = (s_flag >> 16) != 0u;
+        it = wave;
+        stride = kWaves;
+        base = 0u;
+        p = left ? A.first_tile : A.count_tile;
+        lo = left ? A.first : A.count;
+        hi = INT64_MAX;
     }
 }
 
@@ -269,9 +345,24 @@ bool table_route(const bk_locs* locs, const bk_params* prm, int32_t tile_size, i
     if (!(prm->sigma2 >= 1e-100 && prm->sigma2 <= 1e100)) return false;
     const int64_t n = locs->n, ts = tile_size < n ? tile_size : n, T = (n + ts - 1) / ts;
     if (n >= (1LL << 31)) return false;
-    const int64_t items = (lower_only ? T * (T + 1) / 2 : T * T) * ((ts + 63) / 64) * ((ts + 7) / 8);
+    const int64_t items = (lower_only ? T * (T + 1) / 2 : T * T) * ((ts + 63) / 64) * ((ts + 1) / 2);
     if (T >= 60000 || items >= (1LL << 31)) return false;
     return bk_matern_out_elems(n, tile_size, lower_only) >= min_entries;
+}
+
+// The packed tile that holds element e.
+static unsigned tile_at(const TileGeom& g, int64_t e)
+{
+    const int64_t T = g.T, ts = g.ts;
+    int64_t lo = 0, hi = T - 1;                       // last column of tiles that starts at or before e
+    while (lo < hi) {
+        const int64_t m = (lo + hi + 1) / 2;
+        if (tile_offset(g.n, ts, T, g.lower, g.lower ? m : 0, m) <= e) lo = m;
+        else hi = m - 1;
+    }
+    const int64_t J = lo, I0 = g.lower ? J : 0, nJ = J == T - 1 ? g.n - J * ts : ts;
+    const int64_t k = (e - tile_offset(g.n, ts, T, g.lower, I0, J)) / (nJ * ts), I = I0 + k < T ? I0 + k : T - 1;
+    return (unsigned)(g.lower ? J * T - J * (J - 1) / 2 + (I - J) : J * T + I);
 }
 
 template <typename OutT, bool kF32, int FN, int MODE, int R>
@@ -285,6 +376,10 @@ static int eval_rows(const bk_locs* locs, TabArgs& A, char* table, OutT* out, hi
         A.items = (unsigned)(tiles * A.g.rb_per_tile * A.g.cb_per_tile);
         if (A.cols == 2 || A.items >= kTabWaves * kTabGrid) break;
     }
+    A.tiles = (unsigned)tiles;
+    A.count = ((char*)tab_counts<kF32>(table) - (char*)out) / (int64_t)sizeof(OutT);
+    A.first_tile = tile_at(A.g, A.first);
+    A.count_tile = tile_at(A.g, A.count);
     const unsigned need = (A.items + kTabWaves - 1) / kTabWaves;
     return launch(k_matern_tab<OutT, kF32, FN, MODE, R>, dim3(need < kTabGrid ? need : kTabGrid), dim3(kTabThreads),
                   stream, locs->x, locs->y, A, table, out);
@@ -325,7 +420,7 @@ TabIndex tab_index(double beta, bool f32_table)
 int launch_table_eval(const bk_locs* locs, const TabParams& P, int32_t tile_size, int32_t lower_only, int fn,
                       int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream)
 {
-    TabArgs A;
+    TabArgs A = {};
     A.P = P;
     const int64_t n = locs->n;
     const int elem = out_dtype == BK_OUT_F32 ? 4 : 8;
@@ -365,9 +460,9 @@ int matern_table_tiles(const bk_locs* locs, const bk_params* prm, int32_t tile_s
     int64_t first;
     char* table = table_in_output(out, bk_matern_out_elems(locs->n, tile_size, lower_only),
                                   prm->out_dtype == BK_OUT_F32 ? 4 : 8, f32_table, &first);
-    int st = f32_table ? launch(k_tab_build<true, false>, dim3(TabWave<true>::kBlocks), dim3(64), stream, P, X, table,
+    int st = f32_table ? launch(k_tab_build<true, false>, dim3(TabWave<true>::kBlocks), dim3(64 * kTabLanes), stream, P, X, table,
                                 nullptr, nullptr)
-                       : launch(k_tab_build<false, false>, dim3(TabWave<false>::kBlocks), dim3(64), stream, P, X, table,
+                       : launch(k_tab_build<false, false>, dim3(TabWave<false>::kBlocks), dim3(64 * kTabLanes), stream, P, X, table,
                                 nullptr, nullptr);
     if (st != BK_OK) return st;
     if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
@@ -385,8 +480,8 @@ int matern_grad_table_tiles(const bk_locs* locs, const bk_params* prm, double ps
     char* tab[3];
     int64_t first;
     for (int k = 0; k < 3; ++k) tab[k] = outs[k] ? table_in_output(outs[k], elems, elem, false, &first) : nullptr;
-    int st = launch(k_tab_build<false, true>, dim3(TabWave<false>::kBlocks, 3), dim3(64), stream, P, tab_index(prm->beta, false), tab[0], tab[1],
-                    tab[2]);
+    int st = launch(k_tab_build<false, true>, dim3(TabWave<false>::kBlocks, 3), dim3(64 * kTabLanes), stream, P,
+                    tab_index(prm->beta, false), tab[0], tab[1], tab[2]);
     for (int k = 0; k < 3 && st == BK_OK; ++k)
         if (outs[k])
             st = launch_table_eval(locs, P, tile_size, lower_only, k, BK_PLAIN_F64, false, prm->out_dtype, outs[k],

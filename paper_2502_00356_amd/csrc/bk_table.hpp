@@ -47,8 +47,7 @@ __device__ __forceinline__ float tab_pos(const TabIndex& X, float q)
 typedef double tab2_t __attribute__((ext_vector_type(2)));
 typedef float tab4f_t __attribute__((ext_vector_type(4)));
 
-// A table is kPlanes planes of kN 16-byte slots, then the count of finished
-// workgroups. Slot i of the planes in turn: {centre, c0}, {c1, c2}, ... {c7, c8}, the
+// A table is kPlanes planes of kN 16-byte slots, then 16 bytes of counts. Slot i of the planes in turn: {centre, c0}, {c1, c2}, ... {c7, c8}, the
 // polynomial in q - centre (r^2 units); FP32 table: {centre, c0}, {c1 .. c4 in FP32,
 // relative to c0}, the polynomial's argument scaled by 1 / beta^2. Planes rather than records: the 16
 // slots of one LDS bank row are then 16 neighbouring intervals.
@@ -68,16 +67,25 @@ struct TabParams {
 };
 TabParams tab_params(const bk_params* prm, double psi);
 
-// Least FP32 q with tab_pos(q) >= t (tab_pos increases with q): a search over the bit
-// patterns, with the evaluation's own arithmetic.
+// The q where tab_pos(q) = t, to a few of tab_pos's own roundings (1e-4 of an interval:
+// an entry that the rule puts on the other side of a boundary reads its neighbour's
+// polynomial that far past the end). Newton on the bit pattern b, in which tab_pos is
+// convex up to the steps of log2's linear pieces, from the smaller of the two terms' own
+// solutions (the other at most doubles the value there); five steps leave up to 0.25 of an
+// interval, six and seven 2.4e-4.
 __device__ __forceinline__ float tab_bound(const TabIndex& X, float t)
 {
-    unsigned lo = 0u;
-    for (int b = 30; b >= 0; --b) {
-        const unsigned m = lo | (1u << b);
-        if (m < 0x7f800000u && tab_pos(X, __uint_as_float(m)) < t) lo = m;
+    // the log term alone, and the linear one over the first boundary's log term
+    const float rfa = __builtin_amdgcn_rcpf(X.fa), b1 = (t - X.fc) * rfa;
+    const float r = fmaxf(t, 0.0f) * __builtin_amdgcn_rcpf(X.fb), b2 = (float)__float_as_uint(fmaxf(r * r, 0x1p-120f));
+    unsigned b = (unsigned)fminf(fmaxf(fminf(b1, b2), 0x1p24f), 0x7f0p20f);
+    for (int k = 0; k < 7; ++k) {
+        const float q = __uint_as_float(b);
+        const float e = __uint_as_float(b & 0x7f800000u) * 0x1p-23f;                // dq/db
+        const float d = fmaf(0.5f * X.fb * e, __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(q)), X.fa);
+        b = (unsigned)min(max((int)b + (int)((t - tab_pos(X, q)) * __builtin_amdgcn_rcpf(d)), 1 << 24), 0x7f000000);
     }
-    return __uint_as_float(lo + 1u);
+    return __uint_as_float(b);
 }
 
 // cos(n pi (j + 1/2) / M) and the monomial coefficients of T_n.
@@ -103,17 +111,16 @@ struct TabWave {
     double c, w, z;       // centre and half-width in r^2, the lane's point z = r / beta
 };
 
-// The lane's point. Idle lanes (past kPer intervals) repeat the last interval's first.
+// Point `lane` of a workgroup. Idle ones (past kPer intervals) repeat the last interval's first.
 template <bool kF32>
-__device__ __forceinline__ TabWave<kF32> tab_point(const TabIndex& X, double inv_beta, int block)
+__device__ __forceinline__ TabWave<kF32> tab_point(const TabIndex& X, double inv_beta, int block, int lane)
 {
     TabWave<kF32> t;
-    const int lane = threadIdx.x & 63;
     t.g = min(lane / TabWave<kF32>::kM, TabWave<kF32>::kPer - 1);
     t.j = lane < TabWave<kF32>::kPer * TabWave<kF32>::kM ? lane - t.g * TabWave<kF32>::kM : 0;
     const int i0 = block * TabWave<kF32>::kPer;
     t.i = i0 + t.g;
-    const float qb = tab_bound(X, (float)(i0 + lane));      // lane's boundary
+    const float qb = tab_bound(X, (float)(i0 + (threadIdx.x & 63)));      // the wave's lane's boundary
     const double ql = (double)__shfl(qb, t.g, 64), qh = (double)__shfl(qb, t.g + 1, 64);
     t.c = 0.5 * (ql + qh);
     t.w = 0.5 * (qh - ql);
@@ -125,13 +132,13 @@ __device__ __forceinline__ TabWave<kF32> tab_point(const TabIndex& X, double inv
 // Chebyshev coefficients come from the differences to the middle sample and are then
 // expanded in powers, so that neither sum rounds at the size of f. sh: 64 doubles.
 template <bool kF32>
-__device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex& X, double* sh, char* table)
+__device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex& X, double* sh, char* table, int lane,
+                               bool first)
 {
     constexpr int M = TabWave<kF32>::kM, kN = TabShape<kF32>::kN;
     const ChebTab<M>& C = cheb_tab<kF32>();
-    const int lane = threadIdx.x & 63;
-    const bool live = lane < TabWave<kF32>::kPer * M && t.i < kN;
-    sh[lane] = f;
+    const bool live = first && lane < TabWave<kF32>::kPer * M && t.i < kN;
+    if (first) sh[lane] = f;
     __syncthreads();
     const double* s = sh + t.g * M;
     const double mid = s[M / 2];
@@ -139,7 +146,7 @@ __device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex&
     for (int j = 0; j < M; ++j) cn = fma(s[j] - mid, C.cosn[t.j][j], cn);
     cn *= (t.j == 0 ? 1.0 : 2.0) / M;
     __syncthreads();
-    sh[lane] = cn;
+    if (first) sh[lane] = cn;
     __syncthreads();
     double a = 0.0;
     for (int n = M - 1; n >= 0; --n) a = fma(C.mono[n][t.j], s[n], a);
@@ -149,7 +156,7 @@ __device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex&
     for (int k = 0; k < t.j; ++k) a *= iw;
     if (kF32) {
         __syncthreads();
-        sh[lane] = a;
+        if (first) sh[lane] = a;
         __syncthreads();
         if (t.j > 0) a /= s[0];
     }
@@ -177,14 +184,28 @@ __device__ __forceinline__ double tab_assemble(double scale, double z, double e,
     return v + fma(pe, q, fma(p, qe, fma(v, lo, ve)));
 }
 
-// The count of finished workgroups of the evaluation kernel, cleared by the builder.
+// The evaluation kernel's counts, cleared by the builder: workgroups that have read the
+// table, and that have finished (in the high half: those that left their share of the
+// table's bytes to the last).
 template <bool kF32>
-__device__ __forceinline__ unsigned int* tab_done(char* table)
+__host__ __device__ __forceinline__ unsigned int* tab_counts(char* table)
 {
     return (unsigned int*)(table + (size_t)TabShape<kF32>::kPlanes * TabShape<kF32>::kN * 16);
 }
 
-constexpr int64_t kTabMinEntries = 500000;
+template <bool kF32>
+__device__ __forceinline__ void tab_clear(char* table)
+{
+    tab_counts<kF32>(table)[0] = 0u;
+    tab_counts<kF32>(table)[1] = 0u;
+}
+
+// Entries from which a call takes a table (FP64: plain form and gradient; FP32: mixed).
+// Per-entry form against table, us: plain 130,000 entries 16.9 / 20.2, 262,000 21.3 / 19.8;
+// gradient 44 / 48 and 57 / 48; mixed 65,500 16.4 / 16.9, 130,000 20.8 / 17.6. The learned
+// form's own launches take longer at any size (10,000 entries 47 / 22): from the least
+// output that holds its table on.
+constexpr int64_t kTabMinF64 = 200000, kTabMinF32 = 70000, kTabMinLearned = 10000;
 
 // Whether a call takes the tables, and where in an output of elems elements of
 // elem_bytes its table is built: its last bytes, which the evaluation writes last.

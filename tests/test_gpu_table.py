@@ -129,3 +129,42 @@ def test_gradient_table_matches_entries(api, odt, n, ts, lower, nu):
     # |C (ln z - ln 2 - psi)| + |the other term|, with |ln z| <= 14 over these points
     scale = ref["c"].abs() * (14.0 + math.log(2.0) + 3.0) * 2 + ref["dnu"].abs()
     assert _close(out["dnu"], ref["dnu"], 2 * TOL_PLAIN, f32, scale)
+
+
+@pytest.mark.parametrize("mode,odt,n,ts,lower", [
+    ("plain", "f64", 447, 5000, 0), ("plain", "f64", 448, 5000, 0), ("plain", "f32", 460, 23, 0),
+    ("plain", "f64", 620, 100, 1), ("mixed", "f32", 264, 264, 0), ("mixed", "f32", 265, 264, 0),
+    ("mixed", "f32", 371, 1, 1), ("learned", "f32", 99, 128, 1), ("learned", "f32", 100, 128, 1),
+    ("learned", "f32", 101, 100, 0), ("learned", "f32", 150, 1, 1), ("learned", "f32", 143, 11, 1),
+    ("learned", "f32", 517, 128, 1), ("mixed", "f64", 300, 97, 0), ("plain", "f64", 2001, 2001, 0),
+    ("plain", "f64", 30, 2147483647, 0)])
+def test_smallest_tables(api, model, mode, odt, n, ts, lower):
+    """Calls on both sides of the size from which a form takes the tables: almost the whole
+    output lies in the table's own bytes there, over one tile or thousands."""
+    import torch
+    _, lx, ly = _points(n, 0.07)
+    f32 = odt == "f32"
+    dt, od = (torch.float32, api.OUT_F32) if f32 else (torch.float64, api.OUT_F64)
+    L, Lq = (36.0, 35.0) if mode == "plain" else (15.0, 14.5)
+    elems = api.matern_out_elems(n, ts, lower)
+    kw = dict(mode=mode, out_dtype=od, model=model)
+    ref = api.matern_tiles(lx, ly, 1.3, 0.07, 1.9, ts, lower, L_window=L, L_quad=Lq, **kw)
+    for _ in range(3):
+        buf, out = _guarded(elems, dt)
+        api.matern_tiles(lx, ly, 1.3, 0.07, 1.9, ts, lower, out=out, **kw)
+        torch.cuda.synchronize()
+        assert _untouched(buf, elems)
+        assert _close(out, ref, 2 * (TOL_PLAIN if mode == "plain" else TOL_MIXED), f32)
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed", "paper"])
+def test_columns_a_wave(api, mode):
+    """Per-entry calls on both sides of 8,000,000 entries (one and eight columns a wave):
+    the same sites give the same bits."""
+    import torch
+    _, lx, ly = _points(2901, 0.07)
+    kw = dict(mode=mode) if mode == "paper" else dict(mode=mode, L_window=20.0, L_quad=19.0)
+    a = api.unpack_tiles(api.matern_tiles(lx, ly, 1.3, 0.07, 1.9, 300, 0, **kw), 2901, 300, 0)
+    b = api.unpack_tiles(api.matern_tiles(lx[:1001], ly[:1001], 1.3, 0.07, 1.9, 300, 0, **kw), 1001, 300, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(a[:1001, :1001], b)

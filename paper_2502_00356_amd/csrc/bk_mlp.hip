@@ -1421,23 +1421,27 @@ __global__ __launch_bounds__(256) void k_make_targets(const double* __restrict__
     tgt[3 * i + 2] = (float)nodes[i] / sn;
 }
 
-// Training gradient of one tile of kTrainTile = 64 samples per 256-lane workgroup
-// (FP32 on the vector ALU: on gfx950 the FP32 matrix cores have the vector units'
-// peak, and these 64 x 64 x 64 products are too small to gain from them). The
-// tile's activations and back-propagated gradients live in LDS, one row per
-// sample; every 64 x 64 product is split over the 256 lanes, 16 outputs each
-// (lane t: sample or unit t / 4, units or columns 16 (t % 4) ... + 15), so each
-// lane runs a quarter of one sample's work instead of a whole sample:
+// Training gradient of one tile of kTrainTile = 64 samples per workgroup, 16 samples a
+// wave, every product on the FP32 matrix cores (16x16x4; a wave has the chip's SIMD to
+// itself, and operands in registers take the place of an LDS read per multiply-add):
 //   h1 = relu(W1 u + b1), z2 = W2 h1 + b2, h2 = relu(z2), y = W3 h2 + b3,
 //   gy = dL/dy, g2 = [z2 > 0] W3^T gy, g1 = [h1 > 0] W2^T g2,
 //   dW2 = sum_s g2 h1^T, dW1 = sum_s g1 u^T, dW3 = sum_s gy h2^T, biases likewise.
-// The tile's gradient (kNParam floats) goes to its row of `partial`; k_grad_reduce
-// sums the rows in a fixed order. Sample b of the batch is row perm(b) =
-// (pa * (start + b) + pb) mod n of the data (n = 0: row b); samples past B add
-// nothing (their gy is zero).
+// Lane (s = lane % 16, q = lane / 16) holds sample s. The order of a product's sum over
+// units is free, so that of z2 = W2 h1 runs as unit 16 q + c (W2's rows then load as runs of
+// 16) and those over z2's units as 16 m + 4 q + i, which is how the product left them:
+// forward and backward pass need no exchange between lanes. The sums over samples take g2,
+// g1 and h2 transposed through LDS. The waves' sums are added in LDS and go to the
+// workgroup's row of `partial` (kNParam floats); k_grad_reduce sums the rows in a fixed
+// order. Sample b of the batch is row perm(b) = (pa * (start + b) + pb) mod n of the data (n
+// = 0: row b); samples past B add nothing (their gy is zero). loss_rows: the tile's share of
+// the loss is stored there, else added to *loss.
+// 4,096 samples: 64 workgroups, so a wave's own chain of loads and 260 products (3.5 us)
+// bounds it: 11 us, and 3 for the row sum, against 32 and 16 with four lanes a sample on
+// the vector ALU, an LDS read a multiply-add, and one lane adding a column of rows.
 constexpr int kTrainTile = 64;
 constexpr int kTrainThreads = 256;
-constexpr int kTrainLd = kH + 1;          // padded LDS rows
+constexpr int kTrainLd = kH + 4;          // padded LDS rows, 16-byte aligned
 
 __device__ __forceinline__ uint64_t train_row(int64_t start, int64_t b, int64_t n, uint64_t pa, uint64_t pb)
 {
@@ -1446,140 +1450,231 @@ __device__ __forceinline__ uint64_t train_row(int64_t start, int64_t b, int64_t 
     return row;
 }
 
+typedef float f4_t __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(4))) F4Run {      // four floats at any float's address
+    f4_t v;
+};
+__device__ __forceinline__ f4_t load4(const float* p) { return ((const F4Run*)p)->v; }
+
 __global__ __launch_bounds__(kTrainThreads) void k_train_tile(const float* __restrict__ P, const float* __restrict__ U,
                                                               const float* __restrict__ T, const float* __restrict__ tau,
                                                               int64_t B, int64_t n, uint64_t pa, uint64_t pb,
                                                               int64_t start, float* __restrict__ partial,
-                                                              float* __restrict__ loss)
+                                                              float* __restrict__ loss, float* __restrict__ loss_rows)
 {
-    __shared__ float sP[kNParam];
-    __shared__ float sW2T[kH * kH];           // W2 transposed (rows of W2^T for g1)
-    __shared__ float sH1[kTrainTile * kTrainLd], sH2[kTrainTile * kTrainLd];
-    __shared__ float sG1[kTrainTile * kTrainLd], sG2[kTrainTile * kTrainLd];
-    __shared__ float sU[kTrainTile * 2], sGy[kTrainTile * 4];
-    const int t = threadIdx.x;
-    for (int k = t; k < kNParam; k += kTrainThreads) sP[k] = P[k];
-    for (int k = t; k < kH * kH; k += kTrainThreads) sW2T[(k % kH) * kH + k / kH] = P[kOffW2 + k];
-    const int64_t tile0 = (int64_t)blockIdx.x * kTrainTile;
-    const int r = t >> 2, q0 = 16 * (t & 3);  // lane's sample (or unit) r and its 16 columns
-    const bool live_r = tile0 + r < B;
-    float u0 = 0.0f, u1 = 0.0f;
-    if (live_r) {
-        const uint64_t row = train_row(start, tile0 + r, n, pa, pb);
-        u0 = U[2 * row];
-        u1 = U[2 * row + 1];
-    }
-    if ((t & 3) == 0) {
-        sU[2 * r] = u0;
-        sU[2 * r + 1] = u1;
-    }
-    __syncthreads();
-    // h1 (sample r, units q0..q0+15)
+    constexpr int kWaves = kTrainThreads / 64;
+    __shared__ float sRow[kWaves][kNParam];
+    __shared__ __attribute__((aligned(16))) float sX[kWaves][16 * kTrainLd];
+    __shared__ float sLoss[kWaves];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    auto mfma = [](float a, float b, f4_t acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); };
+    const f4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    // this lane's sample (lanes of all four q)
+    const int64_t b = (int64_t)blockIdx.x * kTrainTile + 16 * wave + r;
+    const bool live = b < B;
+    const uint64_t row = train_row(start, live ? b : 0, n, pa, pb);
+    const float u0 = live ? U[2 * row] : 0.0f, u1 = live ? U[2 * row + 1] : 0.0f;
+    float tgt[3];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int j = q0 + k;
-        sH1[r * kTrainLd + j] = fmaxf(fmaf(sP[kOffW1 + 2 * j], u0, fmaf(sP[kOffW1 + 2 * j + 1], u1, sP[kOffB1 + j])), 0.0f);
+    for (int o = 0; o < 3; ++o) tgt[o] = T[3 * row + o];
+    // operands of the forward and backward products
+    f4_t w2[4][4];                                       // W2[16 m + r][16 q + 4 c ..]
+    float w2t[4][4][4];                                  // W2[16 m + 4 q + i][16 j + r]
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w2[m][c] = load4(P + kOffW2 + (16 * m + r) * kH + 16 * q + 4 * c);
+    float h1[16];                                        // units 16 q + c
+#pragma unroll
+    for (int c = 0; c < 16; c += 4) {
+        const f4_t wa = load4(P + kOffW1 + 2 * (16 * q + c)), wb = load4(P + kOffW1 + 2 * (16 * q + c) + 4),
+                   bb = load4(P + kOffB1 + 16 * q + c);
+        h1[c] = fmaxf(fmaf(wa[0], u0, fmaf(wa[1], u1, bb[0])), 0.0f);
+        h1[c + 1] = fmaxf(fmaf(wa[2], u0, fmaf(wa[3], u1, bb[1])), 0.0f);
+        h1[c + 2] = fmaxf(fmaf(wb[0], u0, fmaf(wb[1], u1, bb[2])), 0.0f);
+        h1[c + 3] = fmaxf(fmaf(wb[2], u0, fmaf(wb[3], u1, bb[3])), 0.0f);
     }
-    __syncthreads();
-    {   // h2 = relu(W2 h1 + b2)
-        float h[kH];
 #pragma unroll
-        for (int j = 0; j < kH; ++j) h[j] = sH1[r * kTrainLd + j];
-        for (int k = 0; k < 16; ++k) {
-            const int i = q0 + k;
-            float z = sP[kOffB2 + i];
+    for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int j = 0; j < kH; ++j) z = fmaf(sP[kOffW2 + i * kH + j], h[j], z);
-            sH2[r * kTrainLd + i] = fmaxf(z, 0.0f);   // h2 > 0 iff z2 > 0
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w2t[m][i][j] = P[kOffW2 + (16 * m + 4 * q + i) * kH + 16 * j + r];
+    f4_t h2[4];                                          // units 16 m + 4 q + i, i the component
+#pragma unroll
+    for (int m = 0; m < 4; ++m) h2[m] = load4(P + kOffB2 + 16 * m + 4 * q);
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) h2[m] = mfma(w2[m][c >> 2][c & 3], h1[c], h2[m]);
+    f4_t y0 = zero, y1 = zero;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        f4_t w3 = load4(P + kOffW3 + min(r, 2) * kH + 16 * m + 4 * q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h2[m][i] = fmaxf(h2[m][i], 0.0f);           // h2 > 0 iff z2 > 0
+            const float a = r < 3 ? w3[i] : 0.0f;
+            if (i & 1) y1 = mfma(a, h2[m][i], y1);
+            else y0 = mfma(a, h2[m][i], y0);
         }
     }
-    __syncthreads();
-    // output, loss and gy: lanes 0..191, sample t / 3, output t % 3
-    float l = 0.0f;
-    if (t < 3 * kTrainTile) {
-        const int s = t / 3, o = t - 3 * (t / 3);
-        float gy = 0.0f;
-        if (tile0 + s < B) {
-            float y = sP[kOffB3 + o];
-#pragma unroll 16
-            for (int i = 0; i < kH; ++i) y = fmaf(sP[kOffW3 + o * kH + i], sH2[s * kTrainLd + i], y);
-            const uint64_t row = train_row(start, tile0 + s, n, pa, pb);
-            const float e = T[3 * row + o] - y;
-            const float w = e < 0.0f ? 1.0f - tau[o] : tau[o];
-            l = w * e * e;
-            gy = -2.0f * w * e / (float)B;
-        }
-        sGy[4 * s + o] = gy;
+    // outputs, loss and gy: rows 0 .. 2 of the product, lanes q = 0
+    float gy[3], l = 0.0f;
+#pragma unroll
+    for (int o = 0; o < 3; ++o) {
+        const float e = tgt[o] - ((y0[o] + y1[o]) + P[kOffB3 + o]), ta = tau[o];
+        const float w = e < 0.0f ? 1.0f - ta : ta;
+        const bool on = live && q == 0;
+        l += on ? w * e * e : 0.0f;
+        gy[o] = on ? -2.0f * w * e / (float)B : 0.0f;
     }
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
-    if ((t & 63) == 0 && t < 3 * kTrainTile) atomicAdd(loss, l / (float)B);
-    __syncthreads();
-    // g2 = [h2 > 0] W3^T gy (sample r, units q0..q0+15)
-    {
-        const float gy0 = sGy[4 * r], gy1 = sGy[4 * r + 1], gy2 = sGy[4 * r + 2];
+    float db3[3] = {gy[0], gy[1], gy[2]};
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int i = q0 + k;
-            const float g = sP[kOffW3 + i] * gy0 + sP[kOffW3 + kH + i] * gy1 + sP[kOffW3 + 2 * kH + i] * gy2;
-            sG2[r * kTrainLd + i] = sH2[r * kTrainLd + i] > 0.0f ? g : 0.0f;
+    for (int d = 8; d > 0; d >>= 1) {
+        l += __shfl_xor(l, d, 64);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) db3[o] += __shfl_xor(db3[o], d, 64);
+    }
+    float* const sw = sRow[wave];
+    if (lane == 0) {
+        sLoss[wave] = l;
+#pragma unroll
+        for (int o = 0; o < 3; ++o) sw[kOffB3 + o] = db3[o];
+    }
+    // gy of sample r at output q, and of samples 4 c + q at output r; likewise u and 1
+    const float ga = __shfl(gy[0], r, 64), gb = __shfl(gy[1], r, 64), gc = __shfl(gy[2], r, 64);
+    const float gq = q == 0 ? ga : (q == 1 ? gb : (q == 2 ? gc : 0.0f));
+    float gt[4], ut[4], us0[4], us1[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float a0 = __shfl(gy[0], 4 * c + q, 64), a1 = __shfl(gy[1], 4 * c + q, 64),
+                    a2 = __shfl(gy[2], 4 * c + q, 64);
+        us0[c] = __shfl(u0, 4 * c + q, 64);
+        us1[c] = __shfl(u1, 4 * c + q, 64);
+        gt[c] = r == 0 ? a0 : (r == 1 ? a1 : (r == 2 ? a2 : 0.0f));
+        ut[c] = r == 0 ? us0[c] : (r == 1 ? us1[c] : (r == 2 ? 1.0f : 0.0f));
+    }
+    f4_t g2[4], g1[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        g2[m] = mfma(q < 3 ? P[kOffW3 + min(q, 2) * kH + 16 * m + r] : 0.0f, gq, zero);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g2[m][i] = h2[m][i] > 0.0f ? g2[m][i] : 0.0f;
+        g1[m] = zero;
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) g1[j] = mfma(w2t[m][i][j], g2[m][i], g1[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {                        // [h1 > 0] at units 16 j + 4 q + i
+        const int k = 16 * j + 4 * q;
+        const f4_t wa = load4(P + kOffW1 + 2 * k), wb = load4(P + kOffW1 + 2 * k + 4), bb = load4(P + kOffB1 + k);
+        if (!(fmaf(wa[0], u0, fmaf(wa[1], u1, bb[0])) > 0.0f)) g1[j][0] = 0.0f;
+        if (!(fmaf(wa[2], u0, fmaf(wa[3], u1, bb[1])) > 0.0f)) g1[j][1] = 0.0f;
+        if (!(fmaf(wb[0], u0, fmaf(wb[1], u1, bb[2])) > 0.0f)) g1[j][2] = 0.0f;
+        if (!(fmaf(wb[2], u0, fmaf(wb[3], u1, bb[3])) > 0.0f)) g1[j][3] = 0.0f;
+    }
+    // a wave's 16 x 64 values to LDS by samples, and back as [m][c] = value of unit 16 m + r
+    // at sample 4 c + q
+    float xt[4][4];
+    auto transpose = [&](const f4_t (&x)[4]) {
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) *(f4_t*)&sX[wave][r * kTrainLd + 16 * m + 4 * q] = x[m];
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) xt[m][c] = sX[wave][(4 * c + q) * kTrainLd + 16 * m + r];
+    };
+    // products over the samples with gy's, or u's and 1's, columns: component i is unit 16 m +
+    // 4 q + i, column r
+    auto columns = [&](int m, const float (&col)[4]) {
+        f4_t acc = zero;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc = mfma(xt[m][c], col[c], acc);
+        return acc;
+    };
+    transpose(h2);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const f4_t d = columns(m, gt);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (r < 3) sw[kOffW3 + r * kH + 16 * m + 4 * q + i] = d[i];
+    }
+    transpose(g1);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const f4_t d = columns(m, ut);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = 16 * m + 4 * q + i;
+            if (r < 2) sw[kOffW1 + 2 * k + r] = d[i];
+            else if (r == 2) sw[kOffB1 + k] = d[i];
         }
     }
-    __syncthreads();
-    {   // g1 = [h1 > 0] W2^T g2 (sample r, units q0..q0+15)
-        float g2[kH];
+    transpose(g2);
+    float ht[4][4];                                      // h1 of unit 16 j + r at sample 4 c + q
 #pragma unroll
-        for (int i = 0; i < kH; ++i) g2[i] = sG2[r * kTrainLd + i];
-        for (int k = 0; k < 16; ++k) {
-            const int j = q0 + k;
-            float g = 0.0f;
+    for (int j = 0; j < 4; ++j) {
+        const int k = 16 * j + r;
+        const float wa = P[kOffW1 + 2 * k], wb = P[kOffW1 + 2 * k + 1], bb = P[kOffB1 + k];
 #pragma unroll
-            for (int i = 0; i < kH; ++i) g = fmaf(sW2T[j * kH + i], g2[i], g);
-            sG1[r * kTrainLd + j] = sH1[r * kTrainLd + j] > 0.0f ? g : 0.0f;
+        for (int c = 0; c < 4; ++c) ht[j][c] = fmaxf(fmaf(wa, us0[c], fmaf(wb, us1[c], bb)), 0.0f);
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const f4_t d = columns(m, ut);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (r == 2) sw[kOffB2 + 16 * m + 4 * q + i] = d[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f4_t acc = zero;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc = mfma(xt[m][c], ht[j][c], acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sw[kOffW2 + (16 * m + 4 * q + i) * kH + 16 * j + r] = acc[i];
         }
     }
     __syncthreads();
     float* out = partial + (int64_t)blockIdx.x * kNParam;
-    {   // dW2 row r, columns q0..q0+15, and db2[r]
-        float acc[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] = 0.0f;
-        float db = 0.0f;
-        for (int s = 0; s < kTrainTile; ++s) {
-            const float g = sG2[s * kTrainLd + r];
-            db += g;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) acc[k] = fmaf(g, sH1[s * kTrainLd + q0 + k], acc[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) out[kOffW2 + r * kH + q0 + k] = acc[k];
-        if ((t & 3) == 0) out[kOffB2 + r] = db;
+    for (int k = threadIdx.x; k < kNParam; k += kTrainThreads)
+        out[k] = (sRow[0][k] + sRow[1][k]) + (sRow[2][k] + sRow[3][k]);
+    if (threadIdx.x == 0) {
+        const float lt = ((sLoss[0] + sLoss[1]) + (sLoss[2] + sLoss[3])) / (float)B;
+        if (loss_rows) loss_rows[blockIdx.x] = lt;
+        else atomicAdd(loss, lt);
     }
-    // dW1 and db1: lanes 0..191 (unit t / 3; column 0, 1 or the bias)
-    if (t < 3 * kH) {
-        const int j = t / 3, c = t - 3 * (t / 3);
-        float acc = 0.0f;
-        for (int s = 0; s < kTrainTile; ++s) acc = fmaf(sG1[s * kTrainLd + j], c < 2 ? sU[2 * s + (c & 1)] : 1.0f, acc);
-        if (c < 2) out[kOffW1 + 2 * j + c] = acc;
-        else out[kOffB1 + j] = acc;
-    } else {
-        // dW3 and db3: lanes 192..255 (unit t - 192, all three outputs)
-        const int i = t - 3 * kH;
-        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
-        for (int s = 0; s < kTrainTile; ++s) {
-            const float h = sH2[s * kTrainLd + i];
-            a0 = fmaf(sGy[4 * s], h, a0);
-            a1 = fmaf(sGy[4 * s + 1], h, a1);
-            a2 = fmaf(sGy[4 * s + 2], h, a2);
-        }
-        out[kOffW3 + i] = a0;
-        out[kOffW3 + kH + i] = a1;
-        out[kOffW3 + 2 * kH + i] = a2;
-        if (i < 3) {
-            float d = 0.0f;
-            for (int s = 0; s < kTrainTile; ++s) d += sGy[4 * s + i];
-            out[kOffB3 + i] = d;
-        }
+}
+
+// The sum of the tiles' rows of `partial` at 64 parameters a workgroup of 256: wave w takes
+// rows w, w + 4, ..., several loads in flight, and the four sums are added in order. Valid
+// in the first wave.
+constexpr int kReduceBlocks = (kNParam + 63) / 64;
+
+__device__ __forceinline__ float row_sum(const float* __restrict__ partial, int tiles, int k)
+{
+    __shared__ float red[3][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const float* p = partial + min(k, kNParam - 1);
+    float s = 0.0f;
+    int t = wave;
+    for (; t + 28 < tiles; t += 32) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = p[(int64_t)(t + 4 * e) * kNParam];
+        s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     }
+    for (; t < tiles; t += 4) s += p[(int64_t)t * kNParam];
+    if (wave > 0) red[wave - 1][lane] = s;
+    __syncthreads();
+    return wave == 0 ? (s + red[0][lane]) + (red[1][lane] + red[2][lane]) : 0.0f;
 }
 
 // Training step after k_train_tile: the batch gradient (the tiles' rows summed in
@@ -1588,10 +1683,9 @@ __global__ __launch_bounds__(256) void k_grad_adam(const float* __restrict__ par
                                                    float* __restrict__ m, float* __restrict__ v, float lr, float b1,
                                                    float b2, float eps, float c1, float c2)
 {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= kNParam) return;
-    float gi = 0.0f;
-    for (int t = 0; t < tiles; ++t) gi += partial[(int64_t)t * kNParam + k];
+    const int k = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float gi = row_sum(partial, tiles, k);
+    if (threadIdx.x >= 64 || k >= kNParam) return;
     const float mi = b1 * m[k] + (1.0f - b1) * gi;
     const float vi = b2 * v[k] + (1.0f - b2) * gi * gi;
     m[k] = mi;
@@ -1599,15 +1693,23 @@ __global__ __launch_bounds__(256) void k_grad_adam(const float* __restrict__ par
     p[k] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// Batch gradient: the sum of the tiles' rows of `partial`, in tile order.
+// Batch gradient: the sum of the tiles' rows of `partial`; with loss_rows also the loss, in
+// a workgroup of its own.
 __global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ partial, int tiles,
-                                                     float* __restrict__ grad)
+                                                     float* __restrict__ grad, const float* __restrict__ loss_rows,
+                                                     float* __restrict__ loss)
 {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= kNParam) return;
-    float s = 0.0f;
-    for (int t = 0; t < tiles; ++t) s += partial[(int64_t)t * kNParam + k];
-    grad[k] = s;
+    if (blockIdx.x == kReduceBlocks) {
+        if (threadIdx.x >= 64) return;
+        float l = 0.0f;
+        for (int t = threadIdx.x; t < tiles; t += 64) l += loss_rows[t];
+        for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+        if (threadIdx.x == 0) *loss = l;
+        return;
+    }
+    const int k = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float s = row_sum(partial, tiles, k);
+    if (threadIdx.x < 64 && k < kNParam) grad[k] = s;
 }
 
 __global__ void k_zero_f32(float* p, int64_t n)
@@ -1755,19 +1857,10 @@ static int model_upload(bk_model* m, const float* hostP)
     return model_cells(m);
 }
 
-// Per-tile gradient rows of one batch.
-static size_t grad_scratch_floats(int64_t B) { return (size_t)((B + kTrainTile - 1) / kTrainTile) * kNParam; }
-
-static int launch_grad(const float* params, const float* u, const float* tgt, const float* tau, int64_t B,
-                       int64_t n, uint64_t pa, uint64_t pb, int64_t start, float* grad, float* loss, float* scr,
-                       hipStream_t s)
-{
-    const unsigned tiles = (unsigned)((B + kTrainTile - 1) / kTrainTile);
-    const int st = launch(k_train_tile, dim3(tiles), dim3(kTrainThreads), s, params, u, tgt, tau, B, n, pa, pb, start,
-                          scr, loss);
-    if (st != BK_OK) return st;
-    return launch(k_grad_reduce, dim3((kNParam + 255) / 256), dim3(256), s, (const float*)scr, (int)tiles, grad);
-}
+// Per-tile gradient rows of one batch, and the tiles' shares of the loss.
+static unsigned train_tiles(int64_t B) { return (unsigned)((B + kTrainTile - 1) / kTrainTile); }
+static size_t grad_row_floats(int64_t B) { return (size_t)train_tiles(B) * kNParam; }
+static size_t grad_scratch_floats(int64_t B) { return grad_row_floats(B) + train_tiles(B); }
 
 }  // namespace bk
 
@@ -2148,10 +2241,19 @@ extern "C" int bk_mlp_grad(const float* params, const float* u, const float* tgt
                            float* grad, float* loss, void* scratch, size_t scratch_bytes, hipStream_t s)
 {
     if (!params || !u || !tgt || !tau || !grad || !loss || !scratch || B <= 0 || B > (1 << 20)) return BK_EINVAL;
-    if (scratch_bytes < bk_mlp_grad_scratch_bytes(B)) return BK_ENOMEM;
-    const int st = launch(k_zero_f32, dim3(1), dim3(256), s, loss, (int64_t)1);
+    if (scratch_bytes < sizeof(float) * grad_row_floats(B)) return BK_ENOMEM;
+    // scratch of the rows alone: the loss by atomics
+    float *rows = (float*)scratch, *loss_rows = nullptr;
+    int st = BK_OK;
+    if (scratch_bytes >= bk_mlp_grad_scratch_bytes(B)) loss_rows = rows + grad_row_floats(B);
+    else st = launch(k_zero_f32, dim3(1), dim3(256), s, loss, (int64_t)1);
     if (st != BK_OK) return st;
-    return launch_grad(params, u, tgt, tau, B, 0, 1, 0, 0, grad, loss, (float*)scratch, s);
+    const unsigned tiles = train_tiles(B);
+    st = launch(k_train_tile, dim3(tiles), dim3(kTrainThreads), s, params, u, tgt, tau, B, (int64_t)0, (uint64_t)1,
+                (uint64_t)0, (int64_t)0, rows, loss, loss_rows);
+    if (st != BK_OK) return st;
+    return launch(k_grad_reduce, dim3(kReduceBlocks + (loss_rows ? 1 : 0)), dim3(256), s, (const float*)rows, (int)tiles,
+                  grad, (const float*)loss_rows, loss);
 }
 
 extern "C" int bk_adam_step(float* p, const float* g, float* m, float* v, int64_t n, int32_t step, float lr,
@@ -2270,13 +2372,13 @@ extern "C" int bk_model_train(bk_model* m, const double* nu, const double* x, in
             const float lr = (float)(cfg->lr * (0.05 + 0.95 * 0.5 * (1.0 + cos(M_PI * frac))));
             // tile gradients, then their sum and the Adam update in one launch (the same
             // arithmetic as bk_mlp_grad followed by bk_adam_step)
-            const unsigned tiles = (unsigned)((bs + kTrainTile - 1) / kTrainTile);
+            const unsigned tiles = train_tiles(bs);
             st = launch(k_train_tile, dim3(tiles), dim3(kTrainThreads), s, (const float*)m->params, (const float*)U,
-                        (const float*)T, (const float*)tau, bs, n, pa, pb, b0, scr, loss);
+                        (const float*)T, (const float*)tau, bs, n, pa, pb, b0, scr, loss, (float*)nullptr);
             if (st == BK_OK) {
                 const int32_t t = (int32_t)std::min<int64_t>(step, 1 << 30);
                 const float c1 = 1.0f - powf(cfg->beta1, (float)t), c2 = 1.0f - powf(cfg->beta2, (float)t);
-                st = launch(k_grad_adam, dim3((kNParam + 255) / 256), dim3(256), s, (const float*)scr, (int)tiles,
+                st = launch(k_grad_adam, dim3(kReduceBlocks), dim3(256), s, (const float*)scr, (int)tiles,
                             m->params, mom, vel, lr, cfg->beta1, cfg->beta2, cfg->eps, c1, c2);
             }
         }

@@ -66,6 +66,44 @@ def test_gradient_kernels_match_oracle(api, orc):
     assert np.all(np.abs(g - gref) <= 1e-5 * np.abs(gref) + 1e-6 * np.abs(gref).max())
 
 
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 63, 64, 65, 129, 2047, 8192 + 33])
+def test_gradient_tile_edges(api, orc, B):
+    """Batches at the edges of a wave's 16 and a workgroup's 64 samples, and of the row
+    sum's groups of 32 tiles: every gradient entry and the loss within 64 FP32 roundings
+    (2^-24 each) of the largest term's size, for which the largest gradient of its layer
+    and the loss stand; and with scratch for the tiles' rows alone, where the loss is
+    summed by atomics, the same gradient bits and that loss."""
+    import torch
+    p = _rand_params(8)
+    rng = np.random.default_rng(B)
+    u = rng.uniform(-1, 1, (B, 2)).astype(np.float32)
+    tgt = rng.normal(0.5, 0.5, (B, 3)).astype(np.float32)
+    tau = np.array([0.1, 0.9, 0.9], np.float32)
+    pf = _flat(p).astype(np.float32)
+    args = [to_dev(a) for a in (pf, u, tgt, tau)]
+    loss, grad = api.mlp_grad(*args)
+    tiles = (B + 63) // 64
+    rows = torch.empty(4 * tiles * api.MLP_NPARAM, dtype=torch.uint8, device="cuda")
+    loss2, grad2 = torch.full_like(loss, 7.0), torch.empty_like(grad)
+    st = api._mlp_grad(*[a.data_ptr() for a in args], B, grad2.data_ptr(), loss2.data_ptr(), rows.data_ptr(),
+                       rows.numel(), 0)
+    short = api._mlp_grad(*[a.data_ptr() for a in args], B, grad2.data_ptr(), loss2.data_ptr(), rows.data_ptr(),
+                          rows.numel() - 1, 0)
+    torch.cuda.synchronize()
+    assert st == 0 and short != 0
+    p64 = _unflat(pf.astype(np.float64))
+    y, cache = orc.mlp_forward(p64, u.astype(np.float64))
+    lref = orc.mlp_loss(y, tgt.astype(np.float64), tau.astype(np.float64))
+    gref = orc.mlp_backward(p64, cache, y, tgt.astype(np.float64), tau.astype(np.float64))
+    tol = 64 * 2.0 ** -24
+    g = _unflat(grad.cpu().numpy().astype(np.float64))
+    for k in gref:
+        assert np.abs(g[k] - gref[k]).max() <= tol * np.abs(gref[k]).max(), k
+    assert torch.equal(grad, grad2)
+    for l in (loss, loss2):
+        assert abs(float(l.cpu()[0]) - lref) <= tol * lref
+
+
 def test_adam_kernel_matches_oracle(api, orc):
     import torch
     rng = np.random.default_rng(5)

@@ -57,6 +57,13 @@ inline int launch(void (*k)(P...), dim3 grid, dim3 block, hipStream_t stream, A&
     return launch_args(k, grid, block, stream, args, std::index_sequence_for<P...>{});
 }
 
+// Largest per-lane value over a wave (every lane active).
+__device__ inline unsigned int wave_max_u32(unsigned int v)
+{
+    for (int o = 32; o > 0; o >>= 1) v = max(v, (unsigned int)__shfl_xor((int)v, o, 64));
+    return v;
+}
+
 // Tiling of a Matern call: T x T tiles (or the lower ones) of ts rows and columns,
 // each cut into rb_per_tile row blocks of 64 and cb_per_tile column blocks (four waves of
 // `cols` columns where the per-entry kernels of bk_kernels.hip take it).

@@ -55,13 +55,6 @@ __device__ inline void wave_count(unsigned long long* dst, unsigned int v)
     if ((threadIdx.x & 63) == 0 && a) atomicAdd(dst, a);
 }
 
-// Largest per-lane value over a wave (every lane active).
-__device__ inline unsigned int wave_max_u32(unsigned int v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (unsigned int)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
 // Special values shared by every form; returns true if handled.
 __device__ __forceinline__ bool special_value(double v, double z, int result, double& r)
 {

@@ -709,8 +709,12 @@ __device__ void block_stats_w(unsigned long long* stats, const unsigned long lon
 // for), the cell's quadrature plan, else the window decoded for this entry.
 // Phase 2: the block's entries are counting-sorted by node count
 // through LDS, so each wave walks entries of similar N (the wave runs as many
-// node steps as its largest N). Phase 3 (sorted order): node sums, tail checks,
-// stores to the entry's own index or the fallback queue.
+// node steps as its largest N). Phase 3 (sorted order): node sums, tail checks; results
+// go back to entry order through LDS (each wave's stores whole lines: 243 -> 238 us for
+// 2^24 pairs), entries without a window to the fallback queue. VALU-bound at 450
+// instructions a wave of 64 (86% of the time; the left tail's test is 18 us of it);
+// sorting 512 or 1,024 entries at a time, or by whether that test is needed too, took
+// 249 to 279: the gathered plans then come later and fewer waves are in flight.
 constexpr int kLearnedBlock = 256;
 constexpr int kSortBins = 64;
 
@@ -726,6 +730,7 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
     __shared__ unsigned int hist[kSortBins];
     __shared__ double s_exp2[64];
     __shared__ double s_v[kLearnedBlock], s_z[kLearnedBlock], s_tlo[kLearnedBlock], s_thi[kLearnedBlock];
+    __shared__ double s_out[kLearnedBlock];      // in entry order
     __shared__ int s_N[kLearnedBlock];
     __shared__ unsigned int s_idx[kLearnedBlock];
     __shared__ int s_cell[kLearnedBlock];        // plan path only
@@ -829,13 +834,15 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
         c_nodes = (unsigned int)(Ns + 1);
         c_ent = 1;
         if (lo.reason == 0) {
-            out[idx] = assemble_k(zs, lo.delta, lo.hs, result);
+            s_out[idx & (kLearnedBlock - 1)] = assemble_k(zs, lo.delta, lo.hs, result);
         } else {
             if (lo.reason == BK_STAT_FB_TAIL) c_tail += 1; else c_nonfin += 1;
             const unsigned int slot = atomicAdd(qcount, 1u);
             queue[slot] = idx;
         }
     }
+    __syncthreads();
+    if (N >= 0) out[i] = s_out[tid];         // queued entries are written again by the fallback
     if (stats) {
         unsigned long long cnt[8];
         cnt[BK_STAT_ENTRIES] = c_ent;
@@ -849,6 +856,102 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
         for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, (unsigned int)__shfl_xor((int)wmax, o, 64));
         cnt[BK_STAT_LANE_SLOTS] = (threadIdx.x & 63) == 0 ? 64ull * wmax : 0ull;
         block_stats_w(stats, cnt, 8, kLearnedBlock / 64);
+    }
+}
+
+// One entry by the plain solve with FP32 terms: what the learned form does where it has
+// no window. nodes: those walked.
+__device__ __forceinline__ double learned_fallback(double v, double z, double L, double Lq, int result, const double* T,
+                                                   int& nodes)
+{
+    const Solved s = plain_solve(v, z, L, Lq, rule_tab(), T);
+    nodes = s.p.N + 1;
+    return assemble_k(z, s.delta, s.p.h * sum_mixed(v, z, s.p, s.A, T), result);
+}
+
+// The learned form of small calls, whose time is latency: one launch in place of three
+// (clear, walk, queue), an entry a lane in one-wave workgroups, no sort, the fallback in
+// place. By the three launches and by this, us: 4,096 pairs 14.7 / 10.2, 131,072 16 / 12,
+// 1,048,576 28 / 25, 2,097,152 41 / 40, 4,194,304 65 / 70.
+constexpr int64_t kLearnedSmall = 2000000;
+
+template <bool kPlan>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_besselk_learned_small(MlpDev M, const double* __restrict__ nu,
+                                                              const double* __restrict__ x, double* __restrict__ out,
+                                                              int64_t n, int result, double L, double Lq,
+                                                              unsigned long long* __restrict__ stats)
+{
+    __shared__ double s_tab[kTabLen];
+    stage_tab(s_tab);
+    const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    unsigned int c_range = 0, c_tail = 0, c_raised = 0, c_nonfin = 0, c_ent = 0;
+    int walked = 0, fb_nodes = 0;
+    if (i < n) {
+        const double v = fabs(nu[i]), z = x[i];
+        double r;
+        if (!special_k(v, z, result, r)) {
+            const float lx = __log2f((float)z) * 0.30102999566f;
+            bool ok = in_box(M, lx, (float)v);
+            c_range = ok ? 0 : 1;
+            if (ok) {
+                const int cell = cell_index(M, lx, (float)v);
+                LearnedPlan P;
+                double eb = 0.0;
+                if constexpr (kPlan) {
+                    const float4_t a = M.plan_a[cell];
+                    const double4_t b = M.plan_b[cell];
+                    const int fl = __float_as_int(a[3]);
+                    P.tlo = (double)a[0];
+                    P.N = __float_as_int(a[2]);
+                    P.h = b[0];
+                    P.c0 = b[1];
+                    P.c1 = b[2];
+                    P.kappa = b[3];
+                    c_raised = (unsigned int)(fl & 1);
+                    ok = P.N >= 0;
+                    eb = (v * ((double)(fl >> 1) * P.h) - z * (double)a[1]) * kLog2e;
+                } else {
+                    bool raised;
+                    int N;
+                    double tlo, thi;
+                    const float4_t y = M.cells[cell];
+                    decode_window(M, y[0], y[1], y[2], v, z, Lq, tlo, thi, N, raised);
+                    c_raised = raised ? 1u : 0u;
+                    ok = thi > tlo && isfinite(thi) && N >= 0;
+                    if (ok) P = learned_plan(tlo, thi, N, s_tab);
+                }
+                c_nonfin = ok ? 0 : 1;
+                if (ok) {
+                    plan_for_nu(P, v, s_tab);
+                    const LearnedOut lo = learned_walk<kPlan>(z, v, P, eb);
+                    walked = P.N + 1;
+                    c_ent = 1;
+                    ok = lo.reason == 0;
+                    if (ok) r = assemble_k(z, lo.delta, lo.hs, result);
+                    else if (lo.reason == BK_STAT_FB_TAIL) c_tail = 1;
+                    else c_nonfin = 1;
+                }
+            }
+            if (!ok) {
+                r = learned_fallback(v, z, L, Lq, result, s_tab, fb_nodes);
+                c_ent += 1;
+            }
+        }
+        out[i] = r;
+    }
+    if (stats) {
+        unsigned long long cnt[8];
+        cnt[BK_STAT_ENTRIES] = c_ent;
+        cnt[BK_STAT_NODES] = (unsigned int)(walked + fb_nodes);
+        cnt[BK_STAT_FB_RANGE] = c_range;
+        cnt[BK_STAT_FB_TAIL] = c_tail;
+        cnt[BK_STAT_NODE_RAISED] = c_raised;
+        cnt[BK_STAT_FB_NONFINITE] = c_nonfin;
+        cnt[BK_STAT_FB_NODES] = 0;
+        int wmax = walked;
+        for (int o = 32; o > 0; o >>= 1) wmax = max(wmax, __shfl_xor(wmax, o, 64));
+        cnt[BK_STAT_LANE_SLOTS] = threadIdx.x == 0 ? 64ull * wmax : 0ull;
+        block_stats_w(stats, cnt, 8, 1);
     }
 }
 
@@ -868,10 +971,9 @@ __global__ __launch_bounds__(256) void k_besselk_fallback(const double* __restri
     for (unsigned int j = blockIdx.x * 256 + threadIdx.x; j < cnt; j += gridDim.x * 256) {
         const unsigned int i = queue[j];
         const double v = fabs(nu[i]), z = x[i];
-        Solved s = plain_solve(v, z, L, Lq, rule_tab(), s_tab);
-        const double S = sum_mixed(v, z, s.p, s.A, s_tab);
-        out[i] = assemble_k(z, s.delta, s.p.h * S, result);
-        nodes += (unsigned long long)(s.p.N + 1);
+        int walked;
+        out[i] = learned_fallback(v, z, L, Lq, result, s_tab, walked);
+        nodes += (unsigned long long)walked;
         ents += 1;
     }
     if (stats) {
@@ -1881,6 +1983,16 @@ int bk_besselk_learned(const double* nu, const double* x, double* out, int64_t n
     unsigned int* qcount = (unsigned int*)prm->workspace;
     unsigned int* queue = (unsigned int*)((char*)prm->workspace + 256);
     const MlpDev M = make_dev(m);
+    if (n < kLearnedSmall) {
+        if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
+        const dim3 grid((unsigned)((n + 63) / 64));
+        const int st = m->plan_Lq == Lq ? launch(k_besselk_learned_small<true>, grid, dim3(64), stream, M, nu, x, out, n,
+                                                 prm->result, L, Lq, prm->stats)
+                                        : launch(k_besselk_learned_small<false>, grid, dim3(64), stream, M, nu, x, out,
+                                                 n, prm->result, L, Lq, prm->stats);
+        if (st != BK_OK) return st;
+        return mark_kernel_event(prm, 1, stream) == hipSuccess ? BK_OK : BK_EHIP;
+    }
     int st = launch(k_zero_u32, dim3(1), dim3(64), stream, qcount);
     if (st != BK_OK) return st;
     const unsigned blocks = (unsigned)((n + kLearnedBlock - 1) / kLearnedBlock);

@@ -273,6 +273,40 @@ def test_learned_ragged_sizes(api, orc, trained, n):
         assert rel_err(out.cpu().numpy(), ks).max() <= TOL_MIXED, (n, lq)
 
 
+@pytest.mark.parametrize("lq", [0.0, 14.5000001])
+def test_learned_launch_shapes(api, trained, lq):
+    """Calls on both sides of 2,000,000 pairs (one launch with the fallback in place; sorted
+    blocks and a fallback queue): the same values, up to FP64 roundings of the prefactor
+    (|delta| below 1e3 here: 2^10 2^-52 and a few more), and the same statistics, with
+    inputs outside the box, special values and ordinary ones mixed."""
+    import torch
+    from paper_2502_00356_amd import workloads
+    n = 2000077
+    nu, x, _ = workloads.grid_pairs(1 << 21, seed=15)
+    nu, x = nu[:n].copy(), x[:n].copy()
+    nu[::1009] = np.resize([25.0, np.nan, 0.0, -3.0, np.inf], nu[::1009].size)
+    x[::1511] = np.resize([0.0, 2e3, 1e-7, np.inf, -1.0], x[::1511].size)
+    dn, dx = to_dev(nu), to_dev(x)
+
+    def run(a, b):
+        st = torch.zeros(api.STATS_LEN, dtype=torch.int64, device="cuda")
+        o = api.besselk(dn[a:b], dx[a:b], mode="learned", model=trained, result=api.RESULT_SCALED, L_quad=lq, stats=st)
+        torch.cuda.synchronize()
+        return o, st
+
+    full, st = run(0, n)
+    parts = [run(a, min(n, a + 400000)) for a in range(0, n, 400000)]
+    small = torch.cat([p[0] for p in parts])
+    assert bool((torch.isnan(full) == torch.isnan(small)).all())
+    assert bool((torch.isinf(full) == torch.isinf(small)).all())
+    ok = torch.isfinite(full)
+    assert bool(((full - small).abs()[ok] <= 4e-13 * small.abs()[ok]).all())
+    tot = sum(p[1] for p in parts)
+    for k in (api.STAT_ENTRIES, api.STAT_NODES, api.STAT_FB_RANGE, api.STAT_FB_TAIL, api.STAT_FB_NONFINITE,
+              api.STAT_NODE_RAISED):
+        assert int(st[k]) == int(tot[k]), k
+
+
 def test_learned_out_of_range_falls_back(api, orc, trained):
     """Pairs outside the training box all take the plain-solver path and stay exact."""
     import torch

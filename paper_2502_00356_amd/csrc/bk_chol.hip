@@ -11,7 +11,7 @@
 //  - Sigma^-1 = Y Y^T, tile by tile, only to be multiplied into dSigma and summed.
 // n^3 operations in all with the gradient (7.4 ms at the library product's rate for 8,100
 // sites), n^3 / 3 for the value. rocSOLVER's potrf, potrs and potri took 76 ms and 41 (its
-// 128-column unblocked kernel alone 64 x 171 us); this 18.0 and 9.9.
+// 128-column unblocked kernel alone 64 x 171 us); this 16.4 and 8.4.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -212,180 +212,198 @@ __device__ __forceinline__ double lane_value(double v, int l)
                             __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-// 1 / sqrt(d) from the hardware's estimate and two Newton steps.
-__device__ __forceinline__ double rsqrt_newton(double d)
+// 1 / sqrt(d) from the hardware's estimate y (about 2^-22) and one third-order step, y (1 +
+// e / 2 + 3 e^2 / 8), e = 1 - d y^2.
+__device__ __forceinline__ double rsqrt_step(double d)
 {
-    double y = __builtin_amdgcn_rsq(d);
-    y = fma(y * 0.5, fma(-d * y, y, 1.0), y);
-    return fma(y * 0.5, fma(-d * y, y, 1.0), y);
+    const double y = __builtin_amdgcn_rsq(d), e = fma(-d * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// Diagonal block k: its factor, the factor's inverse W_k (and transpose), u_k = W_k zrow_k,
-// and the block's share of log det L and |u|^2. One workgroup, the block in LDS, by
-// 16 x 16 sub-blocks: one wave factors the sub-block in registers, a lane a row solves for
-// the rows below, the matrix cores update the rest; then the sub-blocks' inverses, a lane a
-// column, and the whole inverse, a block column a wave. Rows past n are the identity's. A
-// serial chain, bound by latency: 136 us with each sub-block inverted before its panel, the
-// logarithms and divisions on the chain and the block loaded a value at a time; 53 now.
-__global__ __launch_bounds__(256) void k_chol_diag(const double* __restrict__ S, int64_t n, int nb, int k,
+// Orders the LDS accesses of a wave whose lanes exchange data (the hardware runs them in
+// program order; the compiler must not reorder them).
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
+
+// The sum of a lane's value over the four lanes of its lane % 16 (swaps of half waves and of
+// rows of 16: vector instructions, where a shuffle goes through LDS).
+__device__ __forceinline__ double sum_rows(double v)
+{
+    {
+        const unsigned lo = __double2loint(v), hi = __double2hiint(v);
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        v = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    }
+    const unsigned lo = __double2loint(v), hi = __double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+
+// A barrier that orders LDS alone: __syncthreads also waits for the wave's global stores.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Diagonal block k: the inverse W_k of its factor (and its transpose), u_k = W_k zrow_k, and
+// the block's share of log det L and |u|^2. One workgroup; by 16 x 16 sub-blocks, wave I
+// holds block row I in the matrix cores' accumulators, every tile transposed: the lower
+// tiles of A, then, in their place from the diagonal on, those of Y = L^-T, which is what
+// the same operations make of an identity below A (see the head of this file). Column s:
+//  1. wave s factors its diagonal tile as L D L^T, a lane a row, then scales by D^-1/2. The
+//     chain from pivot to pivot is d' = a' - a^2 / d in every lane (a, a' read from their
+//     lanes beforehand): a reciprocal and four operations. Lanes 16 - 31 carry identity rows,
+//     which the same instructions turn into rows of G^T = L_ss^-T, and lane 32 the
+//     right-hand side's segment, which becomes u_s.
+//  2. the other waves multiply by G (X^T = G A^T: a product's registers are the next one's
+//     right operand); rows above s have their final tile of Y, which goes to memory;
+//  3. every wave updates its tiles right of s from its own X and the others', in LDS in
+//     operand order. Wave s + 1 has one such product, and then factors while others update.
+// Rows past n are the identity's. A serial chain, bound by latency: 136 us in the first
+// version, 53 with the block in LDS and its inverse built after its factor, 29 now: 128
+// pivots of 0.1 us, 8 exchanges of 1.4 us, and 5 us before and after.
+__global__ __launch_bounds__(512) void k_chol_diag(const double* __restrict__ S, int64_t n, int nb, int k,
                                                    double* __restrict__ w, double* __restrict__ wt,
                                                    const double* __restrict__ zrow, double* __restrict__ u,
                                                    double* __restrict__ part, int* __restrict__ info)
 {
-    constexpr int LD = kB + 1, NS = kB / 16;
-    __shared__ double A[kB * LD];
-    __shared__ double G[NS][16 * 17];              // inverses of the diagonal sub-blocks
-    __shared__ double zs[kB], ip[kB], red[2][4];   // ip: 1 / L_ii
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, q = lane >> 4;
+    constexpr int NS = kB / 16;
+    static_assert(NS == 8, "a wave a block row");
+    __shared__ double sT[16 * 17], sG[16 * 17], su[16], sX[NS][4][64], red[2][NS];
+    const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    const int I = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t g0 = (int64_t)k * kB;
     const int live = (int)min((int64_t)kB, n - g0);
-    {
-        const int r = t & (kB - 1), h = t >> 7, rr = min(r, live - 1);
-        const double* src = S + g0 + rr + g0 * n;
-        for (int c0 = h; c0 < kB; c0 += 32) {      // 16 loads in flight; columns past the row's own stay in the block
+    const int row = 16 * I + r16;
+    chol4_t acc[NS];                     // [j]: tile (I, s + j), rows of it in lanes r16
+#pragma unroll
+    for (int J = 0; J < NS; ++J)         // every load in flight; tiles right of the diagonal repeat its columns
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            acc[J][c] = S[g0 + min(row, live - 1) + (g0 + min(16 * min(J, I) + q + 4 * c, live - 1)) * n];
+#pragma unroll
+    for (int J = 0; J < NS; ++J)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int col = 16 * J + q + 4 * c;
+            if (J > I) acc[J][c] = 0.0;
+            else if (row >= live || col >= live) acc[J][c] = row == col ? 1.0 : 0.0;
+        }
+    double z = row < live ? zrow[g0 + row] : 0.0, us = 0.0, logs = 0.0;
+    double* const wk = w + (int64_t)k * kB * kB;
+    double* const wtk = wt + (int64_t)k * kB * kB;
+    auto store = [&](int J, const chol4_t& y) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int col = 16 * J + q + 4 * c;
+            wtk[row + col * kB] = y[c];
+            wk[col + row * kB] = y[c];
+        }
+    };
+    for (int s = 0; s < NS; ++s) {
+        if (I == s) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sT[(q + 4 * c) * 17 + r16] = acc[0][c];
+            if (q == 0) su[r16] = z;
+            wave_lds_order();
             double v[16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = src[(int64_t)min(c0 + 2 * e, rr) * n];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int c = c0 + 2 * e;
-                A[r * LD + c] = r < live && c <= r ? v[e] : (r == c ? 1.0 : 0.0);
+            for (int c = 0; c < 16; ++c) {
+                const double a = q == 0 ? sT[c * 17 + r16] : su[c];      // A's row r16, or z
+                v[c] = q == 1 ? (r16 == c ? 1.0 : 0.0) : a;
             }
-        }
-    }
-    if (t < kB) zs[t] = t < live ? zrow[g0 + t] : 0.0;
-    __syncthreads();
-    for (int s = 0; s < NS; ++s) {
-        const int o = 16 * s;
-        if (wave == 0) {
-            double v[16], own = 0.0;
-            bool bad = false;
-#pragma unroll
-            for (int c = 0; c < 16; ++c) v[c] = A[(o + r16) * LD + o + c];
+            double d = lane_value(v[0], 0), pivot = d;
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                const double d = lane_value(v[c], c);
-                bad |= !(d > 0.0);
-                const double y = rsqrt_newton(d);
-                own = r16 == c ? y : own;
-                v[c] *= y;                          // row c: d / sqrt(d)
+                double r = __builtin_amdgcn_rcp(d);              // about 2^-22, and one third-order step
+                // the column's values in the rows below, and the next pivot before it: read
+                // together (a lane read just before its use costs wait states)
+                double b[16], a = 0.0;
+                if (c < 15) a = lane_value(v[c + 1], c + 1);
 #pragma unroll
-                for (int c2 = c + 1; c2 < 16; ++c2) v[c2] = fma(-v[c], lane_value(v[c], c2), v[c2]);
-            }
-            if (lane < 16) {
-                ip[o + r16] = own;
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    if (c <= r16) A[(o + r16) * LD + o + c] = v[c];
-            }
-            if (bad && lane == 0) *info = 1;
-        }
-        __syncthreads();
-        // rows below: x L_ss^T = a by columns, a lane a row
-        const int row = o + 16 + t;
-        if (row < kB) {
-            double x[16];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) x[c] = A[row * LD + o + c];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                x[c] *= ip[o + c];
-#pragma unroll
-                for (int c2 = c + 1; c2 < 16; ++c2) x[c2] = fma(-x[c], A[(o + c2) * LD + o + c], x[c2]);
-            }
-#pragma unroll
-            for (int c = 0; c < 16; ++c) A[row * LD + o + c] = x[c];
-        }
-        __syncthreads();
-        // the rest: A_IJ -= A_Is A_Js^T
-        const int rem = NS - 1 - s, tiles = rem * (rem + 1) / 2;
-        for (int f = wave; f < tiles; f += 4) {
-            int I = 0, f0 = f;
-            while (f0 > I) f0 -= ++I;
-            const int ri = 16 * (s + 1 + I), rj = 16 * (s + 1 + f0);
-            chol4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[(ri + r16) * LD + o + 4 * c + q],
-                                                           A[(rj + r16) * LD + o + 4 * c + q], acc, 0, 0, 0);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) A[(ri + q + 4 * c) * LD + rj + r16] -= acc[c];
-        }
-        __syncthreads();
-    }
-    if (t < kB) {                                   // column r16 of sub-block t / 16's inverse
-        const int s = t >> 4, o = 16 * s;
-        double x[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = r16 == i ? 1.0 : 0.0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            x[i] *= ip[o + i];
-#pragma unroll
-            for (int m = i + 1; m < 16; ++m) x[m] = fma(-A[(o + m) * LD + o + i], x[i], x[m]);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) G[s][i * 17 + r16] = x[i];
-    }
-    __syncthreads();
-    // W_IJ = -G_I sum_{J <= K < I} L_IK W_KJ, kept transposed in the upper blocks (J, I)
-    for (int pass = 0; pass < 2; ++pass) {
-        const int J = pass == 0 ? wave : NS - 1 - wave;
-        for (int I = J + 1; I < NS; ++I) {
-            chol4_t acc = {0.0, 0.0, 0.0, 0.0};
-            for (int K = J; K < I; ++K) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int m = 4 * c + q;
-                    const double b = K == J ? G[J][m * 17 + r16] : A[(16 * J + r16) * LD + 16 * K + m];
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[(16 * I + r16) * LD + 16 * K + m], b, acc, 0, 0, 0);
+                for (int c2 = c + 1; c2 < 16; ++c2) b[c2] = lane_value(v[c], c2);
+                __builtin_amdgcn_sched_barrier(0);
+                const double e = fma(-d, r, 1.0);
+                r = fma(r, fma(e, e, e), r);
+                const double wc = v[c] * r;
+                if (c < 15) {
+                    d = fma(-b[c + 1] * b[c + 1], r, a);
+                    pivot = r16 == c + 1 ? d : pivot;
                 }
+#pragma unroll
+                for (int c2 = c + 1; c2 < 16; ++c2) v[c2] = fma(-wc, b[c2], v[c2]);
             }
-            chol4_t wij = {0.0, 0.0, 0.0, 0.0};
-            // a product's registers hold rows lane / 16 + 4 c: the next product's operand
+            const double y = rsqrt_step(pivot);
+            us = y;                                              // 1 / L_rr until the barrier
+#pragma unroll
+            for (int c = 0; c < 16; ++c) v[c] *= lane_value(y, c);
+            if (q == 1)
+#pragma unroll
+                for (int c = 0; c < 16; ++c) sG[c * 17 + r16] = v[c];
+            if (lane == 32)
+#pragma unroll
+                for (int c = 0; c < 16; ++c) su[c] = v[c];
+            if (!(pivot > 0.0)) *info = 1;
+        }
+        lds_barrier();
+        chol4_t x = {0.0, 0.0, 0.0, 0.0};
+        const double un = su[r16];
+        if (I == s) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = sG[(q + 4 * c) * 17 + r16];
+        } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                wij = __builtin_amdgcn_mfma_f64_16x16x4f64(G[I][r16 * 17 + 4 * c + q], acc[c], wij, 0, 0, 0);
+                x = __builtin_amdgcn_mfma_f64_16x16x4f64(sG[r16 * 17 + q + 4 * c], acc[0][c], x, 0, 0, 0);
+        }
+        if (I > s) {
+            double t = 0.0;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) A[(16 * J + r16) * LD + 16 * I + q + 4 * c] = -wij[c];
+            for (int c = 0; c < 4; ++c) {
+                sX[I][c][lane] = x[c];
+                t = fma(su[q + 4 * c], x[c], t);
+            }
+            z -= sum_rows(t);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int j = 1; j < NS; ++j) {
+            const int m = s + j;
+            chol4_t t = acc[j];
+            if (m < NS && (I <= s || m <= I)) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) t = __builtin_amdgcn_mfma_f64_16x16x4f64(sX[m][c][lane], -x[c], t, 0, 0, 0);
+            }
+            acc[j - 1] = t;
+        }
+        // Y's tile (I, s), zero below the diagonal; the next wave to factor leaves its zeros
+        // for the end
+        if (I != s + 1) store(s, I <= s ? x : chol4_t{0.0, 0.0, 0.0, 0.0});
+        if (I == s) {
+            logs = -log(us);
+            us = un;
         }
     }
-    __syncthreads();
-    // the diagonal blocks' lower parts, transposed into the upper half with the rest
-    for (int e = t; e < NS * 256; e += 256) {
-        const int s = e >> 8, i = (e >> 4) & 15, j = e & 15;
-        if (i >= j) A[(16 * s + j) * LD + 16 * s + i] = G[s][i * 17 + j];
-    }
-    __syncthreads();
-    double* wk = w + (int64_t)k * kB * kB;
-    double* wtk = wt + (int64_t)k * kB * kB;
-    {
-        const int r = t & (kB - 1), h = t >> 7;
-#pragma unroll 8
-        for (int c = h; c < kB; c += 2) {
-            wk[r + c * kB] = r >= c ? A[c * LD + r] : 0.0;
-            wtk[r + c * kB] = c >= r ? A[r * LD + c] : 0.0;
-        }
-    }
-    double sum = 0.0;
-    const int ru = t >> 1, h = t & 1;
-#pragma unroll 8
-    for (int c = h; c <= ru; c += 2) sum = fma(A[c * LD + ru], zs[c], sum);
-    sum += __shfl_xor(sum, 1, 64);
-    if (h == 0) u[g0 + ru] = sum;
-    double sq = h == 0 ? sum * sum : 0.0, logs = h == 0 ? -log(ip[ru]) : 0.0;
-    for (int d = 32; d > 0; d >>= 1) {
+    if (I > 0) store(I - 1, chol4_t{0.0, 0.0, 0.0, 0.0});
+    if (q == 0) u[g0 + row] = us;
+    double sq = us * us;
+    for (int d = 8; d > 0; d >>= 1) {
         sq += __shfl_xor(sq, d, 64);
         logs += __shfl_xor(logs, d, 64);
     }
     if (lane == 0) {
-        red[0][wave] = logs;
-        red[1][wave] = sq;
+        red[0][I] = logs;
+        red[1][I] = sq;
     }
     __syncthreads();
-    if (t == 0) {
-        part[k] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-        part[nb + k] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) t += red[threadIdx.x][i];
+        part[(int64_t)threadIdx.x * nb + k] = t;
     }
 }
 
@@ -510,7 +528,7 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
     int st = launch(k_chol_begin, dim3((unsigned)((n + 255) / 256)), wg, stream, z, wk.zrow, n, wk.info);
     auto diag = [&](int k) {
         if (st == BK_OK)
-            st = launch(k_chol_diag, dim3(1), wg, stream, Sc, n, nb, k, wk.w, wk.wt, zrow, wk.u, wk.part, wk.info);
+            st = launch(k_chol_diag, dim3(1), dim3(512), stream, Sc, n, nb, k, wk.w, wk.wt, zrow, wk.u, wk.part, wk.info);
     };
     auto panel = [&](int k) {
         const int blocks = nb - 1 - k + (inverse ? k : 0);

@@ -11,7 +11,7 @@
 //  - Sigma^-1 = Y Y^T, tile by tile, only to be multiplied into dSigma and summed.
 // n^3 operations in all with the gradient (7.4 ms at the library product's rate for 8,100
 // sites), n^3 / 3 for the value. rocSOLVER's potrf, potrs and potri took 76 ms and 41 (its
-// 128-column unblocked kernel alone 64 x 171 us); this 16.4 and 8.4.
+// 128-column unblocked kernel alone 64 x 171 us); this 14.5 and 7.3.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -23,9 +23,19 @@ namespace bk {
 
 typedef double chol4_t __attribute__((ext_vector_type(4)));
 constexpr int kB = kCholB;
-// Block columns a trailing update: 8,100 sites with gradient 19.3 ms with two, 18.0 with
-// four, 17.5 with eight; value alone 10.3, 9.9, 10.4.
+// Block columns a trailing update: 8,100 sites with gradient 15.25 ms with four, 15.2 with
+// six and with eight; value alone 7.7, 7.7, 8.2; 1,024 sites 0.79, 0.85, 0.79.
 constexpr int kStep = 4;
+// Where a launch has few blocks its tiles are cut finer, so that a wave's chain of products
+// is shorter and more SIMDs have one (likelihood with gradient / value, ms):
+//  - panels and columns by 16 rows in place of 32 up to this many blocks: 1,024 sites (8
+//    blocks) 0.61 / 0.48 -> 0.57 / 0.45, 4,096 (32) 3.15 / 2.16 -> 2.96 / 1.99, 5,625 (44)
+//    5.93 -> 6.04 with gradient;
+constexpr int kFewBlocks = 40;
+//  - the update by quarters of a block below this many: 1,024 sites 0.54 -> 0.49 (value),
+//    4,096 sites 2.39 -> 2.17 against 2.25 with 256 and 2.19 with 512;
+constexpr int kFewTiles = 1024;
+//  - the traces by quarters (chol_trace_tiles): 1,024 sites 158 us -> 60.
 
 // One operand block: rows contiguous, columns (k) ld apart; rows past lim repeat row lim.
 struct Operand {
@@ -50,7 +60,8 @@ struct Acc {
 // 16 NA x 16 NB part: lane holds X row 16 a + lane % 16 and Y rows 16 b + lane / 16 + 4 r of
 // the product. The loads of D - 1 k steps (4 columns each) are in flight under the products.
 // cols: a multiple of 4 D, or with kTail any number up to kB (columns past it count as 0).
-template <int D, bool kTail, int NA, int NB>
+// kNeg: 1 negates Y.
+template <int D, bool kTail, int NA, int NB, int kNeg = 0>
 __device__ __forceinline__ void nt_run(Acc<NA, NB>& acc, const Operand& X, const Operand& Y, int x0, int y0, int cols)
 {
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
@@ -80,7 +91,7 @@ __device__ __forceinline__ void nt_run(Acc<NA, NB>& acc, const Operand& X, const
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int a = 0; a < NA; ++a)
-                    acc.v[b][a] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[d][b], x[d][a], acc.v[b][a], 0, 0, 0);
+                    acc.v[b][a] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[d][b], x[d][a], acc.v[b][a], 0, 0, kNeg);
         }
     }
 }
@@ -91,9 +102,27 @@ __device__ __forceinline__ Operand s_block(const double* S, int64_t n, int i, in
     return {S + (int64_t)i * kB + (int64_t)k * kB * n, n, (int)min((int64_t)(kB - 1), n - 1 - (int64_t)i * kB)};
 }
 
-// S's (or, for an upper block's first update, the identity's zero) minus the product.
+// The accumulators' elements of S, from row row0 and column col0: read before the products
+// (zero for an upper block's first update, whose identity S does not hold) ...
 template <int NA, int NB>
-__device__ __forceinline__ void subtract(double* S, int64_t n, int64_t row0, int64_t col0, bool over, const Acc<NA, NB>& acc)
+__device__ __forceinline__ void read_part(Acc<NA, NB>& acc, const double* S, int64_t n, int64_t row0, int64_t col0, bool over)
+{
+    if (over) return;
+    const int lane = threadIdx.x & 63;
+    row0 += lane & 15;
+    col0 += lane >> 4;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+                acc.v[b][a][r] = S[min(row0 + 16 * a, n - 1) + min(col0 + 16 * b + 4 * r, n - 1) * n];
+}
+
+// ... and written after them.
+template <int NA, int NB>
+__device__ __forceinline__ void write_part(double* S, int64_t n, int64_t row0, int64_t col0, const Acc<NA, NB>& acc)
 {
     const int lane = threadIdx.x & 63;
     row0 += lane & 15;
@@ -104,83 +133,88 @@ __device__ __forceinline__ void subtract(double* S, int64_t n, int64_t row0, int
         for (int r = 0; r < 4; ++r) {
             const int64_t col = col0 + 16 * b + 4 * r;
 #pragma unroll
-            for (int a = 0; a < NA; ++a) {
-                const int64_t row = row0 + 16 * a;
-                if (row < n && col < n) {
-                    double* c = S + row + col * n;
-                    *c = (over ? 0.0 : *c) - acc.v[b][a][r];
-                }
-            }
+            for (int a = 0; a < NA; ++a)
+                if (row0 + 16 * a < n && col < n) S[row0 + 16 * a + col * n] = acc.v[b][a][r];
         }
 }
 
-// Rows of block row i against block row m, block columns k0 .. k1 - 1 of L (lower i) or Y
+// Minus rows of block row i times block row m's, block columns k0 .. k1 - 1 of L (lower i) or Y
 // (upper i < k1, whose diagonal block is W^T).
 template <int D, int NA, int NB>
 __device__ __forceinline__ void panel_products(Acc<NA, NB>& acc, const double* S, int64_t n, const double* wt, int i, int m,
                                                int k0, int k1, int x0, int y0)
 {
     if (i < m && i >= k0) {
-        nt_run<D, false>(acc, Operand{wt + (int64_t)i * kB * kB, kB, kB - 1}, s_block(S, n, m, i), x0, y0, kB);
+        nt_run<D, false, NA, NB, 1>(acc, Operand{wt + (int64_t)i * kB * kB, kB, kB - 1}, s_block(S, n, m, i), x0, y0, kB);
         k0 = i + 1;
     }
-    if (k0 < k1) nt_run<D, false>(acc, s_block(S, n, i, k0), s_block(S, n, m, k0), x0, y0, kB * (k1 - k0));
+    if (k0 < k1) nt_run<D, false, NA, NB, 1>(acc, s_block(S, n, i, k0), s_block(S, n, m, k0), x0, y0, kB * (k1 - k0));
 }
 
 // Trailing update of the block columns m >= m0 by the block columns k0 .. k1 - 1 (blockIdx.y:
 // m - m0; blockIdx.x: lower blocks i = m ..., then with the inverse the upper ones i < k1).
-// A tile is 128 x 128, a wave a quarter of it: 16 products of 2,048 operations a k step
+// A tile is 128 x 128 (NA = 4; with NA = 2 a quarter of it, four workgroups a block, where
+// there are few), a wave a quarter of that: NA = 4: 16 products of 2,048 operations a k step
 // against 8 loads, so the matrix cores bound it (FP64: 78.6 TFLOP/s nominal, the library's
-// product 71): 38 TFLOP/s over all steps of 8,100 sites, 8.6 ms of the 18.0; one block
-// column a step reached 31.
+// product 71): 8.6 ms over all steps of 8,100 sites (38 TFLOP/s) with S's part read after the
+// products and one k step of operands in flight; read before them 7.4, three steps in
+// flight (64 more registers) 6.9 (48 TFLOP/s); seven spill.
+template <int NA>
 __global__ __launch_bounds__(256, 2) void k_chol_update(double* S, int64_t n, int nb, const double* __restrict__ wt,
                                                         int k0, int k1, int m0, int inverse)
 {
     const int m = m0 + (int)blockIdx.y, lower = nb - m;
-    const int x = (int)blockIdx.x;
+    const int x = NA == 4 ? (int)blockIdx.x : (int)blockIdx.x >> 2, quarter = NA == 4 ? 0 : (int)blockIdx.x & 3;
     const int i = x < lower ? m + x : x - lower;
     if (x >= lower && (!inverse || i >= k1)) return;
-    const int wave = threadIdx.x >> 6, x0 = 64 * (wave & 1), y0 = 64 * (wave >> 1);
-    Acc<4, 4> acc;
-    panel_products<2>(acc, S, n, wt, i, m, k0, k1, x0, y0);
-    subtract(S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, i < m && i >= k0, acc);
+    const int wave = threadIdx.x >> 6;
+    const int x0 = 64 * (quarter & 1) + 16 * NA * (wave & 1), y0 = 64 * (quarter >> 1) + 16 * NA * (wave >> 1);
+    Acc<NA, NA> acc;
+    read_part(acc, S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, i < m && i >= k0);
+    panel_products<4>(acc, S, n, wt, i, m, k0, k1, x0, y0);
+    write_part(S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, acc);
 }
 
-// The same for one block column m, 32 rows a workgroup (a wave 32 x 32): four times the
-// workgroups, for a column's few tiles (24 us a launch at 8,100 sites; 128-row tiles took
-// 29 for the panels, 13 now).
+// The same for one block column m, 16 NA rows a workgroup (a wave 16 NA x 32), for a column's
+// few tiles (8,100 sites: 24 us a launch as the update was, 17 with S's part read first and
+// seven k steps in flight).
+template <int NA>
 __global__ __launch_bounds__(256) void k_chol_column(double* S, int64_t n, int nb, const double* __restrict__ wt, int k0,
                                                      int k1, int m)
 {
-    const int lower = nb - m, x = (int)blockIdx.x >> 2;
+    constexpr int kPer = 8 / NA;
+    const int lower = nb - m, x = (int)blockIdx.x / kPer;
     const int i = x < lower ? m + x : x - lower;
-    const int x0 = 32 * ((int)blockIdx.x & 3), y0 = 32 * (int)(threadIdx.x >> 6);
-    Acc<2, 2> acc;
-    panel_products<4>(acc, S, n, wt, i, m, k0, k1, x0, y0);
-    subtract(S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, i < m && i >= k0, acc);
+    const int x0 = 16 * NA * ((int)blockIdx.x % kPer), y0 = 32 * (int)(threadIdx.x >> 6);
+    Acc<NA, 2> acc;
+    read_part(acc, S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, i < m && i >= k0);
+    panel_products<8>(acc, S, n, wt, i, m, k0, k1, x0, y0);
+    write_part(S, n, (int64_t)i * kB + x0, (int64_t)m * kB + y0, acc);
 }
 
-// Panel k: S_ik <- S_ik W_k^T for every block i > k (and i < k with the inverse), 32 rows a
+// Panel k: S_ik <- S_ik W_k^T for every block i > k (and i < k with the inverse), 16 NA rows a
 // workgroup (which alone reads and writes them), and for i > k the right-hand side's rows:
 // zrow_i -= L_ik u_k.
+template <int NA>
 __global__ __launch_bounds__(256) void k_chol_panel(double* S, int64_t n, int nb, const double* __restrict__ w,
                                                     const double* __restrict__ u, double* __restrict__ zrow, int k)
 {
-    __shared__ double red[4][32];
-    const int below = nb - 1 - k, x = (int)blockIdx.x >> 2;
+    constexpr int kPer = 8 / NA;
+    __shared__ double red[4][16 * NA];
+    const int below = nb - 1 - k, x = (int)blockIdx.x / kPer;
     const int i = x < below ? k + 1 + x : x - below;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
-    const int x0 = 32 * ((int)blockIdx.x & 3), y0 = 32 * wave;
+    const int x0 = 16 * NA * ((int)blockIdx.x % kPer), y0 = 32 * wave;
     const Operand X = s_block(S, n, i, k), W = {w + (int64_t)k * kB * kB, kB, kB - 1};
     const int kw = (int)min((int64_t)kB, n - (int64_t)k * kB);     // the last block column may be narrow
-    Acc<2, 2> acc;
+    Acc<NA, 2> acc;
     if (kw == kB) nt_run<4, false>(acc, X, W, x0, y0, kB);
     else nt_run<4, true>(acc, X, W, x0, y0, kw);
     __syncthreads();                 // the other waves have read these rows
     double* C = S + (int64_t)i * kB + (int64_t)k * kB * n;
     const int rows = (int)min((int64_t)kB, n - (int64_t)i * kB);
     const double* uk = u + (int64_t)k * kB;
-    double dot[2] = {0.0, 0.0};
+    double dot[NA] = {};
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -188,7 +222,7 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* S, int64_t n, int nb
             const int col = y0 + 16 * b + 4 * r + q;
             const double uc = uk[col];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
+            for (int a = 0; a < NA; ++a) {
                 const int row = x0 + 16 * a + r16;
                 if (row < rows && col < kw) C[row + (int64_t)col * n] = acc.v[b][a][r];
                 dot[a] = fma(acc.v[b][a][r], uc, dot[a]);
@@ -196,14 +230,14 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* S, int64_t n, int nb
         }
     if (i < k) return;               // uniform over the workgroup
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < NA; ++a) {
         dot[a] += __shfl_xor(dot[a], 16, 64);
         dot[a] += __shfl_xor(dot[a], 32, 64);
         if (q == 0) red[wave][16 * a + r16] = dot[a];
     }
     __syncthreads();
     const int t = (int)threadIdx.x;
-    if (t < 32 && x0 + t < rows) zrow[(int64_t)i * kB + x0 + t] -= (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+    if (t < 16 * NA && x0 + t < rows) zrow[(int64_t)i * kB + x0 + t] -= (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
 __device__ __forceinline__ double lane_value(double v, int l)
@@ -439,7 +473,8 @@ __global__ __launch_bounds__(256) void k_chol_ysum(const double* __restrict__ yp
 // Tile (c, d), c >= d, of Sigma^-1 = Y Y^T, multiplied into dB and dN at once:
 //   part[4 x ..] = sum w a_i a_j dB_ij, sum w Sinv_ij dB_ij, and the same of dN,
 // over the tile's part of the lower triangle (w = 2 off the diagonal). Tiles with the
-// longest sums (small c) come first. 177 GFLOP in 3.3 ms at 8,100 sites (54 TFLOP/s).
+// longest sums (small c) come first. 177 GFLOP in 3.1 ms at 8,100 sites (57 TFLOP/s).
+template <int NA>
 __global__ __launch_bounds__(256, 2) void k_chol_traces(const double* __restrict__ S, int64_t n, int nb,
                                                         const double* __restrict__ wt, const double* __restrict__ av,
                                                         const double* __restrict__ dB, const double* __restrict__ dN,
@@ -450,28 +485,34 @@ __global__ __launch_bounds__(256, 2) void k_chol_traces(const double* __restrict
     int c = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)f + 1.0f) - 1.0f) * 0.5f);
     while (c * (c + 1) / 2 > f) --c;
     while ((c + 1) * (c + 2) / 2 <= f) ++c;
-    const int d = f - c * (c + 1) / 2;
+    int d = f - c * (c + 1) / 2;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int x0 = 64 * (wave & 1), y0 = 64 * (wave >> 1);
-    Acc<4, 4> acc;
+    int x0 = 16 * NA * (wave & 1), y0 = 16 * NA * (wave >> 1);
+    if (NA == 2) {                                    // tiles of 64 rows: their blocks and halves
+        x0 += 64 * (c & 1);
+        y0 += 64 * (d & 1);
+        c >>= 1;
+        d >>= 1;
+    }
+    Acc<NA, NA> acc;
     const Operand Wc = {wt + (int64_t)c * kB * kB, kB, kB - 1};
     const int full = (int)(n / kB);                   // block columns of full width
     if (c < full) {
-        nt_run<2, false>(acc, Wc, c == d ? Wc : s_block(S, n, d, c), x0, y0, kB);
-        if (c + 1 < full) nt_run<2, false>(acc, s_block(S, n, c, c + 1), s_block(S, n, d, c + 1), x0, y0, kB * (full - c - 1));
+        nt_run<4, false>(acc, Wc, c == d ? Wc : s_block(S, n, d, c), x0, y0, kB);
+        if (c + 1 < full) nt_run<4, false>(acc, s_block(S, n, c, c + 1), s_block(S, n, d, c + 1), x0, y0, kB * (full - c - 1));
     }
     if (full < nb)
-        nt_run<2, true>(acc, c == full ? Wc : s_block(S, n, c, full), d == full ? Wc : s_block(S, n, d, full), x0, y0,
+        nt_run<4, true>(acc, c == full ? Wc : s_block(S, n, c, full), d == full ? Wc : s_block(S, n, d, full), x0, y0,
                         (int)(n - (int64_t)full * kB));
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     const int64_t row0 = (int64_t)c * kB + x0 + (lane & 15), col0 = (int64_t)d * kB + y0 + (lane >> 4);
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NA; ++b)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int64_t j = col0 + 16 * b + 4 * r;
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
+            for (int a = 0; a < NA; ++a) {
                 const int64_t i = row0 + 16 * a;
                 if (i < n && j <= i) {
                     const double wgt = i == j ? 1.0 : 2.0;
@@ -532,11 +573,15 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
     };
     auto panel = [&](int k) {
         const int blocks = nb - 1 - k + (inverse ? k : 0);
-        if (st == BK_OK && blocks > 0) st = launch(k_chol_panel, dim3(4 * blocks), wg, stream, S, n, nb, w, u, wk.zrow, k);
+        if (st != BK_OK || blocks <= 0) return;
+        st = blocks <= kFewBlocks ? launch(k_chol_panel<1>, dim3(8 * blocks), wg, stream, S, n, nb, w, u, wk.zrow, k)
+                                  : launch(k_chol_panel<2>, dim3(4 * blocks), wg, stream, S, n, nb, w, u, wk.zrow, k);
     };
     auto column = [&](int k0, int m) {
-        if (st == BK_OK && k0 < m)
-            st = launch(k_chol_column, dim3(4 * (nb - m + (inverse ? m : 0))), wg, stream, S, n, nb, wt, k0, m, m);
+        if (st != BK_OK || k0 >= m) return;
+        const int blocks = nb - m + (inverse ? m : 0);
+        st = blocks <= kFewBlocks ? launch(k_chol_column<1>, dim3(8 * blocks), wg, stream, S, n, nb, wt, k0, m, m)
+                                  : launch(k_chol_column<2>, dim3(4 * blocks), wg, stream, S, n, nb, wt, k0, m, m);
     };
     // kStep panels a trailing update (its blocks of S are read and written that much less
     // often), each block column of the step brought up to date just before its turn
@@ -547,9 +592,12 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
             diag(j);
             panel(j);
         }
-        if (st == BK_OK && ke < nb)
-            st = launch(k_chol_update, dim3(nb - ke + (inverse ? ke : 0), nb - ke), wg, stream, S, n, nb, wt, k, ke, ke,
-                        inverse);
+        if (st == BK_OK && ke < nb) {
+            const int rows = nb - ke + (inverse ? ke : 0), cols = nb - ke;
+            st = rows * cols >= kFewTiles ? launch(k_chol_update<4>, dim3(rows, cols), wg, stream, S, n, nb, wt, k, ke, ke, inverse)
+                                         : launch(k_chol_update<2>, dim3(4 * rows, cols), wg, stream, S, n, nb, wt, k, ke, ke,
+                                                  inverse);
+        }
     }
     const double* part = wk.part;
     if (st == BK_OK) st = launch(k_chol_sum, dim3(1), wg, stream, part, (int64_t)nb, 1, wk.res + 0);
@@ -558,9 +606,12 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
     st = launch(k_chol_yu, dim3(nb, nb), wg, stream, Sc, n, wt, u, wk.ypart);
     if (st == BK_OK)
         st = launch(k_chol_ysum, dim3((unsigned)((n + 255) / 256)), wg, stream, (const double*)wk.ypart, n, nb, wk.a);
-    const int64_t tiles = (int64_t)nb * (nb + 1) / 2;
+    const int64_t tiles = chol_trace_tiles(n);
+    const dim3 grid((unsigned)tiles);
     if (st == BK_OK)
-        st = launch(k_chol_traces, dim3((unsigned)tiles), wg, stream, Sc, n, nb, wt, (const double*)wk.a, dB, dN, wk.part);
+        st = nb >= kTraceBlocks
+            ? launch(k_chol_traces<4>, grid, wg, stream, Sc, n, nb, wt, (const double*)wk.a, dB, dN, wk.part)
+            : launch(k_chol_traces<2>, grid, wg, stream, Sc, n, nb, wt, (const double*)wk.a, dB, dN, wk.part);
     if (st == BK_OK) st = launch(k_chol_sum, dim3(1), wg, stream, part, tiles, 4, wk.res + 2);
     return st;
 }

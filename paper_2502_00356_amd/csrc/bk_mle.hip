@@ -33,7 +33,7 @@ static MleLayout mle_layout(int64_t n, int with_grad)
     MleLayout L;
     const size_t mat = align256(sizeof(double) * (size_t)n * (size_t)n);
     const size_t nb = (size_t)chol_blocks(n), blocks = align256(sizeof(double) * nb * kCholB * kCholB);
-    const size_t tiles = nb * (nb + 1) / 2;
+    const size_t tiles = (size_t)chol_trace_tiles(n);
     size_t o = 0;
     L.S = o; o += mat;
     L.dB = o; o += with_grad ? mat : 0;

@@ -65,3 +65,32 @@ def test_loglik_singular(api, n, k):
         assert e.status == 6        # BK_ENOTPD
     else:
         assert np.isfinite(l)
+
+
+@pytest.mark.parametrize("n", [4747, 4993, 5377])
+def test_loglik_tile_rules(api, n):
+    """Sizes around which the launches change their tiles (38 block rows for the traces, 40
+    blocks for panels and columns, 1,024 tiles for the update), against torch's own
+    factorisation of the same matrix on the GPU; the bars as above."""
+    import torch
+    from paper_2502_00356_amd import workloads as w
+    s2, nu = 1.2, 0.8
+    beta = 0.3 / math.sqrt(n)
+    side = math.isqrt(n - 1) + 1
+    xy = w.jittered_grid_locations(side, seed=n)[:n]
+    z = to_dev(np.random.default_rng(n).standard_normal(n))
+    lx, ly = to_dev(xy[:, 0]), to_dev(xy[:, 1])
+    got = api.matern_loglik(lx, ly, z, s2, beta, nu)
+    got_g, grad = api.matern_loglik(lx, ly, z, s2, beta, nu, grad=True)
+    g = {k: v.view(n, n) for k, v in api.matern_grad_tiles(lx, ly, s2, beta, nu, n, 0).items()}
+    L = torch.linalg.cholesky(g["c"])
+    a = torch.cholesky_solve(z[:, None], L)[:, 0]
+    inv = torch.cholesky_inverse(L)
+    quad = float(z @ a)
+    ll = -0.5 * quad - float(torch.log(torch.diagonal(L)).sum()) - 0.5 * n * math.log(2 * math.pi)
+    terms = [(0.5 * quad / s2, 0.5 * n / s2)]
+    terms += [(0.5 * float(a @ (g[k] @ a)), 0.5 * float((inv * g[k]).sum())) for k in ("dbeta", "dnu")]
+    assert got_g == got
+    assert abs(got - ll) <= 1e-9 * (abs(quad) + n)
+    for (q, t), d in zip(terms, grad):
+        assert abs((q - t) - d) <= 1e-9 * (abs(q) + abs(t)) + 1e-300

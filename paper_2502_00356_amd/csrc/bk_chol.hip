@@ -536,20 +536,18 @@ __global__ __launch_bounds__(256, 2) void k_chol_traces(const double* __restrict
             red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
 }
 
-// res[k] = sum_p part[p * stride + k] for k < stride, one workgroup, fixed order.
-__global__ __launch_bounds__(256) void k_chol_sum(const double* __restrict__ part, int64_t np, int stride,
+// res[k] = sum_p part[p * ps + k * ks], a workgroup each k, fixed order.
+__global__ __launch_bounds__(256) void k_chol_sum(const double* __restrict__ part, int64_t np, int64_t ps, int64_t ks,
                                                   double* __restrict__ res)
 {
     __shared__ double red[4];
-    for (int k = 0; k < stride; ++k) {
-        double s = 0.0;
-        for (int64_t p = threadIdx.x; p < np; p += 256) s += part[p * stride + k];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) res[k] = red[0] + red[1] + red[2] + red[3];
-        __syncthreads();
-    }
+    const int k = (int)blockIdx.x;
+    double s = 0.0;
+    for (int64_t p = threadIdx.x; p < np; p += 256) s += part[p * ps + k * ks];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) res[k] = red[0] + red[1] + red[2] + red[3];
 }
 
 __global__ __launch_bounds__(256) void k_chol_begin(const double* __restrict__ z, double* __restrict__ zrow, int64_t n,
@@ -600,8 +598,7 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
         }
     }
     const double* part = wk.part;
-    if (st == BK_OK) st = launch(k_chol_sum, dim3(1), wg, stream, part, (int64_t)nb, 1, wk.res + 0);
-    if (st == BK_OK) st = launch(k_chol_sum, dim3(1), wg, stream, part + nb, (int64_t)nb, 1, wk.res + 1);
+    if (st == BK_OK) st = launch(k_chol_sum, dim3(2), wg, stream, part, (int64_t)nb, (int64_t)1, (int64_t)nb, wk.res);
     if (!inverse || st != BK_OK) return st;
     st = launch(k_chol_yu, dim3(nb, nb), wg, stream, Sc, n, wt, u, wk.ypart);
     if (st == BK_OK)
@@ -612,7 +609,7 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
         st = nb >= kTraceBlocks
             ? launch(k_chol_traces<4>, grid, wg, stream, Sc, n, nb, wt, (const double*)wk.a, dB, dN, wk.part)
             : launch(k_chol_traces<2>, grid, wg, stream, Sc, n, nb, wt, (const double*)wk.a, dB, dN, wk.part);
-    if (st == BK_OK) st = launch(k_chol_sum, dim3(1), wg, stream, part, tiles, 4, wk.res + 2);
+    if (st == BK_OK) st = launch(k_chol_sum, dim3(4), wg, stream, part, tiles, (int64_t)4, (int64_t)1, wk.res + 2);
     return st;
 }
 

@@ -11,6 +11,7 @@
 // the traces are bk_chol.hip's (sums in a fixed order).
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <string.h>
 
@@ -26,6 +27,11 @@ static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct MleLayout {
     size_t S, dB, dN, w, wt, zrow, u, a, ypart, part, res, info, mws, total;
+};
+
+struct MleResult {
+    double sums[6];
+    int info;
 };
 
 static MleLayout mle_layout(int64_t n, int with_grad)
@@ -45,8 +51,8 @@ static MleLayout mle_layout(int64_t n, int with_grad)
     L.a = o; o += with_grad ? align256(sizeof(double) * (size_t)n) : 0;
     L.ypart = o; o += with_grad ? align256(sizeof(double) * nb * (size_t)n) : 0;
     L.part = o; o += align256(sizeof(double) * (with_grad ? 4 * tiles + 2 * nb : 2 * nb));
-    L.res = o; o += 256;
-    L.info = o; o += 256;
+    L.res = o;                                       // six sums and the info word, read back together
+    L.info = L.res + offsetof(MleResult, info); o += 256;
     L.mws = o; o += matern_learned_workspace_bytes(n, (int32_t)n, 0);   // for a learned-form Sigma
     L.total = o;
     return L;
@@ -89,13 +95,11 @@ extern "C" int bk_matern_loglik(const bk_locs* locs, const double* z, const bk_p
 
     st = chol_solve(S, dB, dN, z, n, wk, stream);
     if (st != BK_OK) return st;
-    double hres[6] = {0, 0, 0, 0, 0, 0};
-    int hinfo = 0;
-    if (hipMemcpyAsync(hres, wk.res, sizeof(hres), hipMemcpyDeviceToHost, stream) != hipSuccess) return BK_EHIP;
-    if (hipMemcpyAsync(&hinfo, wk.info, sizeof(hinfo), hipMemcpyDeviceToHost, stream) != hipSuccess) return BK_EHIP;
+    MleResult h = {};
+    if (hipMemcpyAsync(&h, wk.res, sizeof(h), hipMemcpyDeviceToHost, stream) != hipSuccess) return BK_EHIP;
     if (hipStreamSynchronize(stream) != hipSuccess) return BK_EHIP;
-    if (hinfo != 0) return BK_ENOTPD;
-    const double logdet = 2.0 * hres[0], quad = hres[1];
+    if (h.info != 0) return BK_ENOTPD;
+    const double *hres = h.sums, logdet = 2.0 * hres[0], quad = hres[1];
     result[0] = -0.5 * quad - 0.5 * logdet - 0.5 * (double)n * 1.8378770664093454836;   // log(2 pi)
     if (with_grad) {
         result[1] = 0.5 * (quad - (double)n) / prm->sigma2;

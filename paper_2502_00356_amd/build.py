@@ -68,7 +68,8 @@ def _loops(lines):
 def node_slots(asm_path):
     """VALU issue cost of one trapezoid node per K_nu kernel, in CU clocks per wave
     (issue_cost above), read from the gfx950 assembly of this build: the node loop
-    is the innermost loop (plain form: the one with the most exponentials a trip) that
+    is the innermost loop (plain form: the cheapest a node of those with several
+    exponentials a trip) that
     evaluates the node exponential (v_exp_f32 for the FP32-term forms; the inlined FP64
     exp, one v_ldexp_f64 without divisions or logarithms, for the plain form), and its cost is divided by the exponentials
     one trip evaluates (the plain form's paired walk evaluates two nodes a trip
@@ -106,8 +107,11 @@ def node_slots(asm_path):
                 per_trip = (ops.count("v_ldexp_f64") if form in ("plain", "matern_plain")
                             else sum(o.startswith("v_exp_f32") for o in ops))
                 slots = slots / max(1, per_trip)
-                # the plain walk evaluates the most exponentials a trip; else the innermost loop
-                rank = (-per_trip if form in ("plain", "matern_plain") else 0, b - a)
+                # the plain walk is the cheapest loop a node of those with both sides (the loops
+                # around it hold other work too); else the innermost loop
+                if form in ("plain", "matern_plain") and per_trip < 2:
+                    continue
+                rank = (slots if form in ("plain", "matern_plain") else 0, b - a)
                 if best is None or rank < best[0]:
                     best = (rank, slots)
         if best is not None:

@@ -111,7 +111,7 @@ __device__ __forceinline__ double matern_entry(double nu, double z, double lz, d
     double hs;
     if constexpr (MODE == BK_PLAIN_F64) {
         s = plain_plan(nu, z, L, Lq, rule_tab(), T);
-        hs = s.p.h * sum_f64(nu, z, s.p, s.E, s.Ei, s.Sr, T);
+        hs = s.p.h * sum_f64<true>(nu, z, s.p, s.E, s.Ei, s.Sr, T);
         hs = fma(hs, s.dlo, hs);
     } else {
         s = plain_solve(nu, z, L, Lq, rule_tab(), T);
@@ -126,7 +126,7 @@ __device__ __forceinline__ double matern_dbeta(double nu, double z, double lz, d
 {
     const double nu1 = fabs(nu - 1.0);
     const Solved s1 = plain_plan(nu1, z, L, Lq, rule_tab(), T);
-    const double hs1 = s1.p.h * sum_f64(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    const double hs1 = s1.p.h * sum_f64<true>(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
     return sigma2 * inv_beta * exp(pref + (nu + 1.0) * lz + (s1.delta - z)) * fma(hs1, s1.dlo, hs1);
 }
 

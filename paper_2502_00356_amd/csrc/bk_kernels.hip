@@ -310,7 +310,8 @@ struct DrawCounts {
 // VALU-bound. 2^24 pairs of the (nu, x) grid: 1,264 us with the exact solve between two
 // sorts (2,266 VALU instructions a wave of 64), 755 with the FP32 window there, 640 with
 // one sort of 512 entries, one a lane (1,207 instructions), 463 with 1,024 drawn by four
-// waves: fewer waves hold both branches, and none waits for a block's slowest. (512
+// waves: fewer waves hold both branches, and none waits for a block's slowest; 450 with the
+// nodes' exponents by second differences (CoshPair). (512
 // entries in 128 lanes 528, in 256 489; constants hoisted out of the draw loop spill: 548.)
 template <int kThreads, int kPer>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_besselk_plain(
@@ -360,9 +361,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
                 r = temme_result(vj, zj, result, s_tab);
             } else {
                 Solved s;
-                if (N == kEntryExact) s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
-                else s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
-                double hs = s.p.h * sum_f64(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                double hs;
+                if (N == kEntryExact) {           // any x: the left side by products
+                    s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
+                    hs = s.p.h * sum_f64<true>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                } else {                          // x >= 0.1, or nu far above 1 (temme_applies)
+                    s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
+                    hs = s.p.h * sum_f64<false>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                }
                 hs = fma(hs, s.dlo, hs);          // the low part of Delta
                 r = assemble(zj, s.delta, hs, result, s_tab);
                 walked = (unsigned int)(s.p.N + 1);
@@ -450,12 +456,12 @@ __device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, doubl
     const double* T = R.tab;
     DerivOut o;
     const Solved s0 = plain_plan(v, z, L, Lq, R, T);
-    double hs0 = s0.p.h * sum_f64(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
+    double hs0 = s0.p.h * sum_f64<true>(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
     hs0 = fma(hs0, s0.dlo, hs0);
     o.k = assemble(z, s0.delta, hs0, result, T);
     const double v1 = fabs(v - 1.0);
     const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
-    double hs1 = s1.p.h * sum_f64(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    double hs1 = s1.p.h * sum_f64<true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
     hs1 = fma(hs1, s1.dlo, hs1);
     o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
     o.nodes = (unsigned int)(s0.p.N + s1.p.N + 2);
@@ -471,7 +477,8 @@ __device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, doubl
 // K_nu(x), dK/dx and dK/dnu, FP64, by one window and one walk for the three integrals
 // (sum_deriv), the entries sorted and drawn as in k_besselk_plain. NULL outputs are not
 // stored. dK/dnu carries the sign of nu. 2^22 pairs of the (nu, x) grid: 1,729 us with a
-// solve and a walk for each integral, unsorted (1,205 with the FP32 windows there); 301 now.
+// solve and a walk for each integral, unsorted (1,205 with the FP32 windows
+// there), 300 with one walk, 292 with its right side by second differences.
 template <int kThreads, int kPer>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_besselk_deriv(
     const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ k, double* __restrict__ dkdx,

@@ -669,51 +669,91 @@ __device__ __forceinline__ void walk_step(Walk& w, int m)
 
 // FP64 trapezoid sum of the plain form, S = sum_m c_m exp(d_m) (1 + P_m),
 // c_0 = c_N = 1/2, as a paired walk outward from the reference node: iteration j
-// takes node mc + j (right, j <= N - mc) and node mc - j (left, 1 <= j <= mc),
-// both at |w| = j h / 2. With x (cosh t - cosh t_ref) = 2 x sinh(w) sinh(s),
-// s = (t + t_ref) / 2 >= |w| (product-to-sum, no cancellation):
-//   right: d = nu j h - (x/2) 2 sinh|w| 2 sinh(t_ref + |w|),
-//   left:  d = -nu j h + (x/2) 2 sinh|w| 2 sinh(t_ref - |w|).
-// 2 sinh|w| = V (1 + e^-|w|) with V = expm1(|w|) from V' = V q + expm1(h/2),
-// which only ever runs outward from V = 0 (its relative error grows by about an
-// ulp per step; an inward run loses relative accuracy as V shrinks, and that loss
-// reached ~5e-14 of K left of interior peaks); 2 sinh(t_ref + |w|) the same way
-// from expm1(t_ref); 2 sinh(t_ref - |w|) = e^t_ref e^-|w| - e^-t_ref e^|w|, whose
-// terms differ by a factor e^(2 (t_ref - |w|)) >= e^t_ref. The two sides share V,
-// e^-|w| and nu j h; a side no lane of the wave needs is skipped. T is exp_tab's
-// table; E, Ei, Sr = e^t_ref, e^-t_ref, expm1(t_ref) from the solve.
+// takes node mc + j (right, j <= N - mc) and node mc - j (left, 1 <= j <= mc), with
+// d = +- nu j h - X, X = x (cosh t - cosh t_ref), P = e^(-2 nu t). X follows its second
+// difference,
+//   X_(j+1) = X_j + S_(j+1),  S_(j+1) = S_j + (2 cosh h - 2) (X_j + x cosh t_ref),
+// from the exact first step on either side (X_1 = S_1 = +-2 x sinh(h/2) sinh(t_ref +- h/2)):
+// it never holds the size of x cosh t itself. On the right all terms are positive and X
+// keeps its relative accuracy (about an ulp a step). On the left the recurrence's growing
+// solution e^(j h) is not the sum's: a rounding of X (<= nu) there has grown by e^s at a
+// distance s, where the term has fallen to about e^(-nu (s - 1)), and s <= ln(2 nu / x). So
+// it costs no more than a few ulps of max(nu, 1) where nu >= 1 or x >= 0.1, as in the
+// standalone form (Temme's series below); elsewhere (x = 1e-4, nu = 0.3: 1e-14) the left
+// side takes the product 2 sinh(j h / 2) 2 sinh(t_ref - j h / 2) from running exponentials,
+// kProduct. Three operations a node against seven: 2^24 pairs of the (nu, x) grid 466 ->
+// 450 us. T is exp_tab's table; E, Ei, Sr = e^t_ref, e^-t_ref, expm1(t_ref) from the solve.
+
+struct CoshWalk {
+    double X, S;
+    __device__ __forceinline__ void step(double k2, double c)
+    {
+        S = fma(k2, X, S + c);
+        X += S;
+    }
+};
+
+template <bool kProduct>
+struct CoshPair {
+    CoshWalk R, L;
+    double k2, c;                        // 2 cosh h - 2, and its product with x cosh t_ref
+    double V, Bq, q, qm1, qi, E, Ei, xh; // product form: expm1(w), e^-w, w = j h / 2
+
+    __device__ __forceinline__ CoshPair(double x, double h, double E_, double Ei_, double Sr)
+    {
+        E = E_;
+        Ei = Ei_;
+        xh = 0.5 * x;
+        qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h);
+        q = qm1 + 1.0;
+        qi = recip(q);
+        V = qm1;
+        Bq = qi;
+        const double s1 = fma(V, Bq, V), SR = fma(Sr, q, V);         // 2 sinh(h/2), expm1(t_ref + h/2)
+        R.X = R.S = xh * s1 * fma(SR, Ei * qi, SR);
+        L.X = L.S = -xh * s1 * fma(E, qi, -Ei * q);
+        k2 = s1 * s1;
+        c = k2 * (xh * (E + Ei));
+    }
+    __device__ __forceinline__ void step()
+    {
+        R.step(k2, c);
+        if (kProduct) {
+            V = fma(V, q, qm1);
+            Bq *= qi;
+            L.X = -xh * fma(V, Bq, V) * fma(E, Bq, -Ei * (V + 1.0));
+        } else {
+            L.step(k2, c);
+        }
+    }
+};
+
+template <bool kProduct>
 __device__ inline double sum_f64(double nu, double x, const Plan& p, double E, double Ei, double Sr, const double* T)
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
-    const double h = p.h, xh = 0.5 * x, nh = nu * h;
-    const double qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
+    const double nh = nu * p.h;
     const double rho = exp_tab(-2.0 * nh, T), rhoi = recip(rho);
-    double V = 0.0, Bq = 1.0;                 // expm1(|w|), e^-|w|
-    double SR = Sr, ER = Ei;                  // expm1(t_ref + |w|), e^-(t_ref + |w|)
     double PR = exp_tab(-2.0 * nu * p.tref, T), PL = PR;   // e^(-2 nu t) at nodes mc + j, mc - j
-    double jd = 0.0, S = 0.0, tr = 0.0, tl = 0.0;
+    double jd = 1.0, S = 0.0, tr = 0.0, tl = 0.0;
+    CoshPair<kProduct> W(x, p.h, E, Ei, Sr);
     // node mc: the exponent is 0; it is node 0 if mc = 0 and node N if mc = N
     const double t0 = 1.0 + PR;
     for (int j = 1; j <= jmax; ++j) {
-        jd += 1.0;
-        V = fma(V, q, qm1);
-        Bq *= qi;
-        const double nuu = jd * nh;           // nu j h formed per node: no drift
-        const double xs = xh * fma(V, Bq, V);
-        SR = fma(SR, q, qm1);
-        ER *= qi;
         PR *= rho;
         PL *= rhoi;
         if (j <= nr) {
-            const double e = exp_node(fma(-xs, fma(SR, ER, SR), nuu), T);
+            const double e = exp_node(fma(jd, nh, -W.R.X), T);
             tr = fma(e, PR, e);
             S += tr;
         }
         if (j <= nl) {
-            const double e = exp_node(fma(xs, fma(E, Bq, -Ei * (V + 1.0)), -nuu), T);
+            const double e = exp_node(fma(-jd, nh, -W.L.X), T);
             tl = fma(e, PL, e);
             S += tl;
         }
+        W.step();
+        jd += 1.0;
     }
     // trapezoid ends: half of node N and of node 0
     S = fma(-0.5, tr + tl, S);
@@ -962,42 +1002,36 @@ struct DerivSums {
 __device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double E, double Ei, double Sr, const double* T)
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
-    const double h = p.h, xh = 0.5 * x, nh = nu * h;
-    const double qm1 = h <= 0.25 ? expm1_small(0.5 * h) : expm1(0.5 * h), q = qm1 + 1.0, qi = recip(q);
+    const double h = p.h, nh = nu * h;
     const double omr = -expm1(-2.0 * nh), rho = 1.0 - omr;             // 1 - e^(-2 nu h)
     const double qe = omr * recip(rho), re = 1.0 + qe;                 // e^(2 nu h) - 1, e^(2 nu h)
     const double Qr = -expm1(-2.0 * nu * p.tref), Pr = exp_tab(-2.0 * nu * p.tref, T);
-    double V = 0.0, Bq = 1.0, SR = Sr, ER = Ei, QR = Qr, EL = 0.0, jd = 0.0;
+    double QR = Qr, EL = 0.0, jd = 1.0;
+    CoshPair<true> W(x, h, E, Ei, Sr);
     DerivSums S = {0.0, 0.0, 0.0}, r = {0.0, 0.0, 0.0}, l = {0.0, 0.0, 0.0};
     for (int j = 1; j <= jmax; ++j) {
-        jd += 1.0;
-        V = fma(V, q, qm1);
-        Bq *= qi;
-        const double u = jd * h, nuu = jd * nh;
-        const double xs = xh * fma(V, Bq, V);
-        SR = fma(SR, q, qm1);
-        ER *= qi;
         QR = fma(QR, rho, omr);
         EL = fma(EL, re, qe);
         if (j <= nr) {
-            const double xt = xs * fma(SR, ER, SR), e = exp_node(nuu - xt, T);
+            const double e = exp_node(fma(jd, nh, -W.R.X), T);
             r.k = fma(-e, QR, 2.0 * e);
-            r.x = r.k * xt;
-            r.d = e * QR * (p.tref + u);
+            r.x = r.k * W.R.X;
+            r.d = e * QR * fma(jd, h, p.tref);
             S.k += r.k;
             S.x += r.x;
             S.d += r.d;
         }
         if (j <= nl) {
-            const double xt = xs * fma(-E, Bq, Ei * (V + 1.0)), e = exp_node(-nuu - xt, T);
-            const double Q = fma(-Pr, EL, Qr);
+            const double e = exp_node(fma(-jd, nh, -W.L.X), T), Q = fma(-Pr, EL, Qr);
             l.k = fma(-e, Q, 2.0 * e);
-            l.x = l.k * xt;
-            l.d = e * Q * (p.tref - u);
+            l.x = l.k * W.L.X;
+            l.d = e * Q * fma(-jd, h, p.tref);
             S.k += l.k;
             S.x += l.x;
             S.d += l.d;
         }
+        W.step();
+        jd += 1.0;
     }
     // trapezoid ends: half of node N and of node 0 (the reference's weight if it is one)
     const double w0 = nl == 0 || nr == 0 ? 0.5 : 1.0;

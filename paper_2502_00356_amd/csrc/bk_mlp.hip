@@ -1181,7 +1181,7 @@ __global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P,
     __syncthreads();
     if (s_bad[t.g]) {
         const Solved s = plain_plan(P.nu, t.z, kDefaultLPlain, kDefaultLqPlain, rule_tab(), s_tab);
-        f = tab_assemble(P.scale, t.z, P.nu, s.delta, s.p.h * sum_f64(P.nu, t.z, s.p, s.E, s.Ei, s.Sr, s_tab));
+        f = tab_assemble(P.scale, t.z, P.nu, s.delta, s.p.h * sum_f64<true>(P.nu, t.z, s.p, s.E, s.Ei, s.Sr, s_tab));
     }
     tab_fit<true>(t, f, X, sh, table, threadIdx.x & 63, true);
     if (blockIdx.x == 0 && lane == 0) tab_clear<true>(table);

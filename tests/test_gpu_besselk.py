@@ -226,3 +226,25 @@ def test_kernel_events_bracket_the_kernel(api, mode):
     np.testing.assert_array_equal(got.cpu().numpy(), ref)
     t_k, t_all = ev[0].elapsed_time(ev[1]), outer[0].elapsed_time(outer[1])
     assert 0.0 < t_k <= t_all, (t_k, t_all)
+
+
+@pytest.mark.parametrize("x", [1e-300, 1e-250, 1e-100, 1e-20, 9e-13])
+def test_plain_tiny_arguments(api, x):
+    """Orders just below 1 at arguments below the FP32 windows' range, where the walk left of
+    the peak is hundreds of units of t long: log K against its leading terms
+    log(Gamma(nu) / 2) + nu log(2 / x) + log(1 + Gamma(-nu) / Gamma(nu) (x / 2)^(2 nu)) (the
+    next is x^2 / (4 (1 - nu))), to 1e-13 and four roundings of log K."""
+    from math import gamma, lgamma, log, log1p
+    nu = np.array([0.5, 0.86, 0.9, 0.95, 0.99, 0.999])
+    got = _gpu(api, nu, np.full(nu.size, x), "plain", 2)
+    ref = np.array([lgamma(v) - log(2.0) + v * (log(2.0) - log(x)) +
+                    log1p(gamma(-v) / gamma(v) * (x / 2) ** (2 * v)) for v in nu])
+    assert np.all(np.abs(got - ref) <= TOL_PLAIN + 4 * np.finfo(float).eps * np.abs(ref))
+
+
+def test_plain_left_of_the_peak(api, orc):
+    """The lower end of the windowed form (x just above 0.1), where small orders walk
+    furthest to the left of the reference."""
+    rng = np.random.default_rng(41)
+    nu = np.concatenate([10 ** rng.uniform(-4, 0.3, 4000), rng.uniform(0.3, 1.1, 4000)])
+    _check_form(api, orc, nu, rng.uniform(0.1, 0.2, nu.size), "plain", TOL_PLAIN)

@@ -5,9 +5,9 @@ Default workload (one step): the 316 x 316 jittered grid in [0, 1]^2 (jitter
 U[-0.4, 0.4] cell, seed 7, Morton order; n = 99,856), sigma^2 = 1, beta = 0.02,
 nu = 3.7, lower-triangle 1,024-tiles, 5,036,605,696 entries, locations resident
 in HBM. A step is one bk_matern_tiles call in the learned form with FP32 output
-(window table, interval plans, main kernel, fallback). The mixed form (FP32
-output) and the plain FP64 form (FP64 output) are timed on the same inputs and
-reported beside it.
+(the quadrature, with learned windows, at the points of a table over r^2, then every
+entry by its interval's polynomial). The mixed form (FP32 output) and the plain FP64
+form (FP64 output) are timed on the same inputs and reported beside it.
 
 Other workloads (--workload): grid (2^24 standalone (nu, x) pairs), matern-medium,
 deriv-grid, matern-grad-medium, loglik, paper-grid.
@@ -52,19 +52,23 @@ NODE_SLOTS = load_node_slots()
 # null: HBM bytes from the FETCH_SIZE and WRITE_SIZE runs scaled by a plain 1 GiB
 # copy, and SQ_INSTS_VALU of one launch without statistics.
 TRAFFIC = {
-    "grid": {"src_sha": "53987bbd1f5b7a90", "n": 1 << 24, "bytes": 4.22539e8, "valu_insts": 1.17947e8},
-    "matern_large": {"src_sha": "53987bbd1f5b7a90", "bytes": 2.02873e10, "valu_insts": 9.58373e9},
+    "grid": {"src_sha": "8e6a1b892644c30e", "n": 1 << 24, "bytes": 4.1546e8, "valu_insts": 1.18467e8},
+    "matern_large": {"src_sha": "4ed0583a0a88a4bf", "bytes": 2.13061e10, "valu_insts": 1.98362e9},
 }
-KERNEL_SOURCES = ("bk_mlp.hip", "bk_math.hpp", "bk_internal.hpp")
+KERNEL_SOURCES = {
+    "grid": ("bk_mlp.hip", "bk_math.hpp", "bk_internal.hpp"),
+    "matern_large": ("bk_table.hip", "bk_table.hpp", "bk_internal.hpp"),
+}
+HBM_PEAK_GBPS = 8000.0
 
 
-def kernel_src_sha():
-    """Hash of the learned kernel's sources with comments and blank space removed,
-    so that edits to comments alone do not invalidate the traffic figure."""
+def kernel_src_sha(key):
+    """Hash of a kernel's sources with comments and blank space removed, so that edits
+    to comments alone do not invalidate its counter figures."""
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES:
+    for f in KERNEL_SOURCES[key]:
         with open(os.path.join(ROOT, "paper_2502_00356_amd", "csrc", f)) as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -218,7 +222,7 @@ def traffic_entry(key, n=None):
     """The counter figures of TRAFFIC[key] if they were taken on the current kernel
     sources (and size), else None."""
     t = TRAFFIC.get(key)
-    if t is None or kernel_src_sha() != t["src_sha"] or (n is not None and t.get("n") != n):
+    if t is None or kernel_src_sha(key) != t["src_sha"] or (n is not None and t.get("n") != n):
         return None
     return t
 
@@ -277,11 +281,11 @@ def matern_headline(a, torch, api, workloads):
     outs = {torch.float32: torch.empty(elems, dtype=torch.float32, device=dev)}
     if "plain" in want:
         outs[torch.float64] = torch.empty(elems, dtype=torch.float64, device=dev)
-    forms = tuple(f for f in (("learned", api.OUT_F32, "matern_learned"), ("mixed", api.OUT_F32, "matern_mixed"),
-                              ("plain", api.OUT_F64, "matern_plain")) if f[0] in want or f[0] == "learned")
+    forms = tuple(f for f in (("learned", api.OUT_F32), ("mixed", api.OUT_F32), ("plain", api.OUT_F64))
+                  if f[0] in want or f[0] == "learned")
     stream = torch.cuda.current_stream()
     res = {}
-    for f, odt, slot_key in forms:
+    for f, odt in forms:
         out = outs[torch.float32 if odt == api.OUT_F32 else torch.float64]
         kw = dict(mode=f, out_dtype=odt, out=out, model=model, workspace=ws)
         steps = a.steps if f == "learned" else max(1, min(a.steps, 5))
@@ -302,7 +306,8 @@ def matern_headline(a, torch, api, workloads):
         wall = (time.perf_counter() - t0) / steps * 1e3
         ms = ev0.elapsed_time(ev1) / steps
         kms = sum(e0.elapsed_time(e1) for e0, e1 in kev) / steps
-        # the counting variant, once, outside the timed region
+        # nodes and lane efficiency are the per-entry kernels', which a call with statistics
+        # runs to count; the timed calls evaluate the quadrature at the table's points only
         st = torch.zeros(api.STATS_LEN, dtype=torch.int64, device=dev)
         api.matern_tiles(lx, ly, s2, beta, nu, ts, 1, stats=st, **kw)
         torch.cuda.synchronize()
@@ -319,9 +324,7 @@ def matern_headline(a, torch, api, workloads):
                       mean_nodes=nodes_main / max(1, quad_main), node_total_main=nodes_main,
                       lane_efficiency=nodes_main / max(1, int(st[api.STAT_LANE_SLOTS])),
                       fallbacks=fb, fallback_nodes=int(st[api.STAT_FB_NODES]),
-                      node_slots=NODE_SLOTS.get(slot_key),
-                      node_work_frac=(NODE_SLOTS[slot_key] * nodes_main / (kms * 1e-3) / 1e12 / VALU_PEAK_TOPS
-                                      if slot_key in NODE_SLOTS else None))
+                      hbm_frac=elems * out.element_size() / (kms * 1e-3) / 1e9 / HBM_PEAK_GBPS)
     head = res["learned"]
 
     # accuracy of each form's timed output on the CPU sample, and the oracle's own
@@ -340,13 +343,13 @@ def matern_headline(a, torch, api, workloads):
                           "OpenMP over entries, %.1f s" % (a.cpu_sample, max(0, min(4, a.cpu_tiles)), i.size, dt))
         pidx = torch.from_numpy(packed_index(api, n, ts, i, j)).to(dev)
         m = ref > 1e-30
-        for f, odt, _ in forms:
+        for f, odt in forms:
             out = outs[torch.float32 if odt == api.OUT_F32 else torch.float64]
             api.matern_tiles(lx, ly, s2, beta, nu, ts, 1, mode=f, out_dtype=odt, out=out, model=model, workspace=ws)
             got = out[pidx].double().cpu().numpy()
             acc[f] = float((np.abs(got[m] - ref[m]) / ref[m]).max())
     kms = head["kernel_ms"]
-    achieved = NODE_SLOTS["matern_learned"] * head["node_total_main"] / (kms * 1e-3) / 1e12
+    achieved = 4.0 * elems / (kms * 1e-3) / 1e9
     tr = traffic_entry("matern_large")
     line = {
         "metric": "K_nu evals/s (Matern entries/s) mixed+learned vs FP64 at <=2e-6 rel err",
@@ -359,7 +362,7 @@ def matern_headline(a, torch, api, workloads):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f64 solve and distance + f32 node terms, f32 out",
+        "dtype": "f64 samples and distance + f32 interpolation, f32 out",
         "data": "synthetic",
         "config": {"workload": "Matern build on a 316x316 jittered grid in [0,1]^2 (jitter U[-0.4,0.4] cell, seed 7, "
                                "Morton order), n=99856, sigma2=1, beta=0.02, nu=3.7, lower-triangle 1024-tiles, "
@@ -370,14 +373,10 @@ def matern_headline(a, torch, api, workloads):
         "speedup_vs_plain_f64": res["plain"]["ms_per_step"] / head["ms_per_step"] if "plain" in res else None,
         "speedup_vs_mixed": res["mixed"]["ms_per_step"] / head["ms_per_step"] if "mixed" in res else None,
         "max_rel_err_sample": acc,
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS,
-                     "unit": "TOP/s (full-rate VALU lane-op slots)", "frac": achieved / VALU_PEAK_TOPS,
-                     "traffic": tr["bytes"] if tr else None,
-                     "kernel": "k_matern_learned<float>", "kernel_ms": kms,
-                     "work": "%.2f VALU issue clocks (full-rate lane-op slots) per trapezoid node x %d nodes per step"
-                             % (NODE_SLOTS["matern_learned"], head["node_total_main"]),
-                     "hbm_gbps": 4.0 * elems / (kms * 1e-3) / 1e9,
-                     "hbm_frac": 4.0 * elems / (kms * 1e-3) / 8e12,
+        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+                     "frac": achieved / HBM_PEAK_GBPS, "traffic": tr["bytes"] if tr else None,
+                     "kernel": "k_matern_tab<float>", "kernel_ms": kms,
+                     "work": "%d entries x 4 bytes written per step" % elems,
                      "valu_issue_per_cu_clock": (tr["valu_insts"] / (kms * 1e-3 * 256 * 2.4e9) if tr else None)},
         "cpu_baseline": cpu,
     }

@@ -83,7 +83,7 @@ def node_slots(asm_path):
             funcs[cur] = []
         elif cur is not None:
             funcs[cur].append(l)
-    want = {"plain": "k_besselk_plain", "mixed": "k_besselk_mixed", "learned": "k_besselk_learnedILb1",
+    want = {"plain": "k_besselk_plain", "mixed": "k_besselk_mixed", "learned": "k_besselk_learnedILb1ELb0",
             # Matern kernels without statistics: FP64 output for plain, FP32 for the others
             "matern_plain": "k_maternILi0EdLb0", "matern_mixed": "k_maternILi1EfLb0",
             "matern_learned": "k_matern_learnedIfLb0"}

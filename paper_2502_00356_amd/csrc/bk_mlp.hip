@@ -31,6 +31,7 @@
 #include <cmath>
 #include <mutex>
 #include <random>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/besselk.h"
@@ -484,9 +485,11 @@ __device__ inline bool left_tail_ok(double x, double nu, float tlof, float hf, f
     float up = F(1.0f) * 1.0009765625f, lo = 0.0f;
     if (!(tlof >= up)) {                        // t_lo near t_c: narrow the bounds
         lo = F(coshf_(up)) * 0.9990234375f;
-        up = fminf(up, F(coshf_(lo)) * 1.0009765625f);
-        lo = fmaxf(lo, F(coshf_(up)) * 0.9990234375f);
-        up = fminf(up, F(coshf_(lo)) * 1.0009765625f);
+        if (!(tlof <= lo)) {                    // else settled: lo only grows (236 -> 231 us, 2^24 pairs)
+            up = fminf(up, F(coshf_(lo)) * 1.0009765625f);
+            lo = fmaxf(lo, F(coshf_(up)) * 0.9990234375f);
+            up = fminf(up, F(coshf_(lo)) * 1.0009765625f);
+        }
     }
     const float D = fmaxf(delta, 0.0f);
     float bound;
@@ -710,15 +713,18 @@ __device__ void block_stats_w(unsigned long long* stats, const unsigned long lon
 // Phase 2: the block's entries are counting-sorted by node count
 // through LDS, so each wave walks entries of similar N (the wave runs as many
 // node steps as its largest N). Phase 3 (sorted order): node sums, tail checks; results
-// go back to entry order through LDS (each wave's stores whole lines: 243 -> 238 us for
-// 2^24 pairs), entries without a window to the fallback queue. VALU-bound at 450
-// instructions a wave of 64 (86% of the time; the left tail's test is 18 us of it);
+// go back to entry order through LDS (each wave's stores whole lines: 243 -> 236 us for
+// 2^24 pairs), entries without a window to the fallback queue. VALU-bound: 450
+// instructions a wave of 64 took 86% of the time at 242 us; the left tail's second pair of
+// iterates where a lane needs it (231) and no counters without statistics (225) since.
+// The left tail's test is 15 us of what is left;
 // sorting 512 or 1,024 entries at a time, or by whether that test is needed too, took
 // 249 to 279: the gathered plans then come later and fewer waves are in flight.
 constexpr int kLearnedBlock = 256;
 constexpr int kSortBins = 64;
 
-template <bool kPlan>
+// kStats: the statistics variant (its counters cost registers and moves in every entry).
+template <bool kPlan, bool kStats>
 __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, const double* __restrict__ nu,
                                                                    const double* __restrict__ x,
                                                                    double* __restrict__ out, int64_t n, int result,
@@ -729,11 +735,13 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
 {
     __shared__ unsigned int hist[kSortBins];
     __shared__ double s_exp2[64];
-    __shared__ double s_v[kLearnedBlock], s_z[kLearnedBlock], s_tlo[kLearnedBlock], s_thi[kLearnedBlock];
+    using win_t = typename std::conditional<kPlan, float, double>::type;     // plans hold FP32 windows
+    __shared__ double s_v[kLearnedBlock], s_z[kLearnedBlock];
+    __shared__ win_t s_tlo[kLearnedBlock], s_thi[kLearnedBlock];
     __shared__ double s_out[kLearnedBlock];      // in entry order
     __shared__ int s_N[kLearnedBlock];
-    __shared__ unsigned int s_idx[kLearnedBlock];
-    __shared__ int s_cell[kLearnedBlock];        // plan path only
+    static_assert(kLearnedBlock <= 256 && kCells <= 1 << 24, "entry word");
+    __shared__ unsigned int s_e[kLearnedBlock];  // entry | cell << 8
     const int tid = threadIdx.x;
     const int64_t i = (int64_t)blockIdx.x * kLearnedBlock + tid;
     int cell = 0;
@@ -745,7 +753,7 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
     const float lx = __log2f((float)(z > 0.0 ? z : 1.0)) * 0.30102999566f;   // log10 x in FP32
     // per-lane statistics as scalars (a dynamically indexed array would live in scratch)
     unsigned int c_range = 0, c_tail = 0, c_raised = 0, c_nonfin = 0, c_nodes = 0, c_ent = 0;
-    double tlo = 0.0, thi = 0.0;             // plan path: thi holds the cell's dc
+    win_t tlo = 0, thi = 0;                  // plan path: thi holds the cell's dc
     int N = -1, mpk = 0;
     // the ordinary case (finite nu, 0 < x < inf) in three compares; special_k covers
     // every other input
@@ -764,8 +772,8 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
                 if constexpr (kPlan) {
                     cell = cell_index(M, lx, (float)v);
                     const float4_t a = M.plan_a[cell];
-                    tlo = (double)a[0];
-                    thi = (double)a[1];
+                    tlo = a[0];
+                    thi = a[1];
                     const int Nd = __float_as_int(a[2]), fl = __float_as_int(a[3]);
                     c_raised = (unsigned int)(fl & 1);
                     if (Nd < 0) { reject = true; c_nonfin = 1; }
@@ -801,19 +809,18 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
     s_z[dst] = z;
     s_tlo[dst] = tlo;
     s_thi[dst] = thi;
-    if constexpr (kPlan) s_cell[dst] = cell;
     s_N[dst] = N < 0 ? -1 : (N | (mpk << 16));   // N <= kNodeMax < 2^16
-    s_idx[dst] = (unsigned int)i;
+    s_e[dst] = (unsigned int)tid | ((unsigned int)cell << 8);
     __syncthreads();
     const int Np = s_N[tid];
     if (Np >= 0) {
         const int Ns = Np & 0xffff;
         const double vs = s_v[tid], zs = s_z[tid];
-        const unsigned int idx = s_idx[tid];
+        const unsigned int e = s_e[tid], own = e & 255u;
         LearnedPlan P;
         if constexpr (kPlan) {
-            const double4_t b = M.plan_b[s_cell[tid]];
-            P.tlo = s_tlo[tid];
+            const double4_t b = M.plan_b[e >> 8];
+            P.tlo = (double)s_tlo[tid];
             P.h = b[0];
             P.c0 = b[1];
             P.c1 = b[2];
@@ -826,7 +833,7 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
         LearnedOut lo;
         if constexpr (kPlan) {
             // log2 of the term at the cell's peak node t_pk relative to node 0, at this entry
-            const double eb = (vs * ((double)(Np >> 16) * P.h) - zs * s_thi[tid]) * kLog2e;
+            const double eb = (vs * ((double)(Np >> 16) * P.h) - zs * (double)s_thi[tid]) * kLog2e;
             lo = learned_walk<true>(zs, vs, P, eb);
         } else {
             lo = learned_walk<false>(zs, vs, P);
@@ -834,16 +841,16 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
         c_nodes = (unsigned int)(Ns + 1);
         c_ent = 1;
         if (lo.reason == 0) {
-            s_out[idx & (kLearnedBlock - 1)] = assemble_k(zs, lo.delta, lo.hs, result);
+            s_out[own] = assemble_k(zs, lo.delta, lo.hs, result);
         } else {
             if (lo.reason == BK_STAT_FB_TAIL) c_tail += 1; else c_nonfin += 1;
             const unsigned int slot = atomicAdd(qcount, 1u);
-            queue[slot] = idx;
+            queue[slot] = (unsigned int)blockIdx.x * kLearnedBlock + own;
         }
     }
     __syncthreads();
     if (N >= 0) out[i] = s_out[tid];         // queued entries are written again by the fallback
-    if (stats) {
+    if constexpr (kStats) {
         unsigned long long cnt[8];
         cnt[BK_STAT_ENTRIES] = c_ent;
         cnt[BK_STAT_NODES] = c_nodes;
@@ -1997,11 +2004,12 @@ int bk_besselk_learned(const double* nu, const double* x, double* out, int64_t n
     if (st != BK_OK) return st;
     const unsigned blocks = (unsigned)((n + kLearnedBlock - 1) / kLearnedBlock);
     if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
-    st = (m->plan_Lq == Lq)
-        ? launch(k_besselk_learned<true>, dim3(blocks), dim3(kLearnedBlock), stream, M, nu, x, out, n, prm->result,
-                 Lq, qcount, queue, prm->stats)
-        : launch(k_besselk_learned<false>, dim3(blocks), dim3(kLearnedBlock), stream, M, nu, x, out, n, prm->result,
-                 Lq, qcount, queue, prm->stats);
+    const dim3 grid(blocks), wg(kLearnedBlock);
+    auto walk = [&](auto* kernel) {
+        return launch(kernel, grid, wg, stream, M, nu, x, out, n, prm->result, Lq, qcount, queue, prm->stats);
+    };
+    if (m->plan_Lq == Lq) st = prm->stats ? walk(k_besselk_learned<true, true>) : walk(k_besselk_learned<true, false>);
+    else st = prm->stats ? walk(k_besselk_learned<false, true>) : walk(k_besselk_learned<false, false>);
     if (st != BK_OK) return st;
     if (mark_kernel_event(prm, 1, stream) != hipSuccess) return BK_EHIP;
     return launch(k_besselk_fallback, dim3(1024), dim3(256), stream, nu, x, out, prm->result, qcount, queue, L, Lq,

@@ -90,6 +90,7 @@ __device__ __forceinline__ double assemble(double z, double delta, double hs, in
 __device__ __forceinline__ bool temme_applies(double v, double z)
 {
     if (!(z < kPaperTemmeX) || !(v > 0.0)) return false;
+    if (z >= 1e-10 && v <= 20.0 && v >= 1e-20) return true;      // the bound below is at most 536 there
     const float vf = (float)v;
     const float lb = vf * (__logf(2.0f / (float)z) + __logf(vf + 1.0f)) + __logf(1.0f / vf + 1.0f);
     return lb < 600.0f;
@@ -311,7 +312,8 @@ struct DrawCounts {
 // sorts (2,266 VALU instructions a wave of 64), 755 with the FP32 window there, 640 with
 // one sort of 512 entries, one a lane (1,207 instructions), 463 with 1,024 drawn by four
 // waves: fewer waves hold both branches, and none waits for a block's slowest; 450 with the
-// nodes' exponents by second differences (CoshPair). (512
+// nodes' exponents by second differences (CoshPair), 432 with one Newton step an end and the
+// step rule's cosine by its series. (512
 // entries in 128 lanes 528, in 256 489; constants hoisted out of the draw loop spill: 548.)
 template <int kThreads, int kPer>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_besselk_plain(

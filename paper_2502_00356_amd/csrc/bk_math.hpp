@@ -487,8 +487,9 @@ __device__ __forceinline__ float node_step_learned(float nu, float x, float Lq)
 
 // The plain form's plan without the exact solve: a window that contains {t : g(t) >=
 // g(t*) - L}, and a reference near t*, in FP32. A wider window costs nodes, not accuracy:
-// here at most ln 2 in L on a side and what two Newton steps leave (about 1% more nodes),
-// for 150 instructions in place of the roots' 1,500.
+// here at most ln 2 in L on a side and what one Newton step leaves (about 1% more nodes; a
+// second one on either side saves less than a hundredth of a node over nu <= 60), for 130
+// instructions in place of the roots' 1,500.
 //  - The reference tp = asinh(nu / x) >= t* (0 where nu^2 <= x, as t*); g(tp) <= g(t*), so
 //    a threshold below g(tp) lies below g(t*).
 //  - Right end: log cosh(nu t) grows by at most nu (t - tp), so G(tp + d) <= -F(d),
@@ -513,19 +514,19 @@ __device__ __forceinline__ float asinh_fast(float y)
 // Upper bound of the d > 0 where x (cosh(t + d) - cosh t) = slope d + L; E, Ei = e^t, e^-t.
 __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, float x, float slope, float L)
 {
-    // start: the x term alone drops by L
-    const float ec = 0.5f * (E + Ei) - 1.0f + L * __builtin_amdgcn_rcpf(x);
-    float d = fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + ec + __builtin_amdgcn_sqrtf(ec * (ec + 2.0f))) - t, 1e-3f);
-    const float hx = 0.5f * x;
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const float a = exp_fast(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
-        const float b = E * a, bi = Ei * ai;                       // e^(t + d/2)
-        const float F = hx * (a - ai) * (b - bi) - slope * d - L;  // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
-        const float D = hx * (b * a - bi * ai) - slope;
-        d -= F * __builtin_amdgcn_rcpf(D);
-    }
-    return d * 1.0001f;
+    // start: the x term alone drops by L; then it drops by L and the slope's rise up to there
+    // (still left of the root), then one Newton step to its right
+    const float ix = __builtin_amdgcn_rcpf(x), ec = 0.5f * (E + Ei) - 1.0f;
+    auto drop = [&](float l) {
+        const float e = fmaf(l, ix, ec);
+        return fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + e + __builtin_amdgcn_sqrtf(e * (e + 2.0f))) - t, 1e-3f);
+    };
+    const float d = drop(fmaf(slope, drop(L), L));
+    const float a = exp_fast(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
+    const float b = E * a, bi = Ei * ai;                           // e^(t + d/2)
+    const float F = 0.5f * x * (a - ai) * (b - bi) - slope * d - L;    // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
+    const float D = 0.5f * x * (b * a - bi * ai) - slope;
+    return (d - F * __builtin_amdgcn_rcpf(D)) * 1.0001f;
 }
 
 // Left end of the window from tp (e^tp = E): 0, or tp - e with F(e) = 0 (see above).
@@ -534,16 +535,12 @@ __device__ __forceinline__ float left_end_fast(float tp, float E, float Ei, floa
     const float L2 = L + 0.69314718f, hx = 0.5f * x;
     const float e0 = L2 + x * (0.5f * (E + Ei) - 1.0f);
     if (!(e0 < nu * tp)) return 0.0f;
-    float e = e0 * __builtin_amdgcn_rcpf(nu);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const float a = exp_fast(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
-        const float b = E * ai, bi = Ei * a;                       // e^(tp - e/2)
-        const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
-        const float D = hx * (b * ai - bi * a) - nu;
-        e -= F * __builtin_amdgcn_rcpf(D);
-    }
-    return fmaxf(tp - e * 1.0001f, 0.0f);
+    const float e = e0 * __builtin_amdgcn_rcpf(nu);
+    const float a = exp_fast(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
+    const float b = E * ai, bi = Ei * a;                           // e^(tp - e/2)
+    const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
+    const float D = hx * (b * ai - bi * a) - nu;
+    return fmaxf(tp - (e - F * __builtin_amdgcn_rcpf(D)) * 1.0001f, 0.0f);
 }
 
 __device__ __forceinline__ void window_fast(float nu, float x, float L, float& t0, float& t1, float& tp)
@@ -570,6 +567,18 @@ __device__ __forceinline__ double expm1_small(double y)
     return fma(p * y, y, y);
 }
 
+// The strip bound's step as node_step_learned, with cos a from its series in a^2 (x (1 - cos
+// a) without cancellation).
+__device__ __forceinline__ float node_step_fast(float nu, float x, float Lq)
+{
+    const float c = Lq + 0.693147181f, nu1 = nu + 1.0f;
+    const float v = fminf(2.0f * c * __builtin_amdgcn_rcpf(x + nu1), 1.69f);       // a^2
+    const float u = v * fmaf(fmaf(fmaf(fmaf(v, 1.0f / 3628800.0f, -1.0f / 40320.0f), v, 1.0f / 720.0f), v, -1.0f / 24.0f),
+                             v, 0.5f);                                              // 1 - cos a
+    const float den = fmaf(x, u, c) - nu1 * 0.69314718f * __builtin_amdgcn_logf(1.0f - u);
+    return 6.28318531f * 0.999f * __builtin_amdgcn_sqrtf(v) * __builtin_amdgcn_rcpf(den);
+}
+
 // Node count N of [t0, t1] for a step of at most h, and the index mc of the node nearest tp.
 __device__ __forceinline__ void node_grid(float t0, float t1, float tp, float h, unsigned int& N, unsigned int& mc)
 {
@@ -585,7 +594,7 @@ __device__ __forceinline__ void window_count(double nu, double x, double L, doub
 {
     float tp;
     window_fast((float)nu, (float)x, (float)L, t0, t1, tp);
-    node_grid(t0, t1, tp, node_step_learned((float)nu, (float)x, (float)Lq), N, mc);
+    node_grid(t0, t1, tp, node_step_fast((float)nu, (float)x, (float)Lq), N, mc);
 }
 
 // Set-up of the paired walk on the nodes t0 + m (t1 - t0) / N.
@@ -988,7 +997,7 @@ __device__ __forceinline__ void deriv_window_count(double nu, double x, double L
                td + right_end_fast(td, Ed, __builtin_amdgcn_rcpf(Ed), xf, fmaf(2.0f, itd, nf), Lf));
     t0 = left_end_fast(tp, E, Ei, nf, xf, Lf);
     const float extra = 2.0f * 0.69314718f * __builtin_amdgcn_logf(fmaf(1.5707963f, itd, 1.0f));
-    node_grid(t0, t1, tp, node_step_learned(nf + 1.0f, xf, (float)Lq + extra), N, mc);
+    node_grid(t0, t1, tp, node_step_fast(nf + 1.0f, xf, (float)Lq + extra), N, mc);
 }
 
 // Trapezoid sums of the paired walk (sum_f64): of the K terms e^d (2 - Q), of those times

@@ -168,3 +168,27 @@ def test_columns_a_wave(api, mode):
     b = api.unpack_tiles(api.matern_tiles(lx[:1001], ly[:1001], 1.3, 0.07, 1.9, 300, 0, **kw), 1001, 300, 0)
     torch.cuda.synchronize()
     assert torch.equal(a[:1001, :1001], b)
+
+
+def test_tables_on_several_streams(api, model):
+    """Table calls on four streams at once, which keeps workgroups of some from starting while
+    others of the same call finish: the bits of the same calls one after the other."""
+    import torch
+    _, lx, ly = _points(1490, 0.07)
+    forms = [("plain", api.OUT_F64, 500, 1), ("mixed", api.OUT_F32, 257, 0), ("learned", api.OUT_F32, 128, 1),
+             ("plain", api.OUT_F32, 1490, 0)]
+    call = lambda f, out=None: api.matern_tiles(lx, ly, 1.3, 0.07, 1.9, f[2], f[3], mode=f[0], out_dtype=f[1],
+                                                model=model, out=out)
+    ref = [call(f) for f in forms]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in forms]
+    outs = [[torch.empty_like(r) for _ in range(8)] for r in ref]
+    torch.cuda.synchronize()
+    for k in range(8):
+        for f, s, o in zip(forms, streams, outs):
+            with torch.cuda.stream(s):
+                call(f, o[k])
+    torch.cuda.synchronize()
+    for r, o in zip(ref, outs):
+        for t in o:
+            assert torch.equal(t, r)

@@ -46,15 +46,6 @@ __device__ void block_count_w(unsigned long long* dst, unsigned long long v, int
     }
 }
 
-// Sum of a per-lane count over a wave (every lane active), added once to a global
-// counter by lane 0.
-__device__ inline void wave_count(unsigned long long* dst, unsigned int v)
-{
-    unsigned long long a = v;
-    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-    if ((threadIdx.x & 63) == 0 && a) atomicAdd(dst, a);
-}
-
 // Special values shared by every form; returns true if handled.
 __device__ __forceinline__ bool special_value(double v, double z, int result, double& r)
 {

@@ -641,19 +641,6 @@ __device__ __forceinline__ double scaled_exp(double r, double c)
     return ldexp((double)__builtin_amdgcn_exp2f((float)(y - k)) * c, (int)k);
 }
 
-// c 2^k rounded to the output type (exact scaling; for FP32 output one rounding of
-// c to FP32 first where c lies well inside its range).
-template <typename OutT>
-__device__ __forceinline__ OutT scale2_out(double c, int k)
-{
-    if constexpr (sizeof(OutT) == sizeof(float)) {
-        if (!(c > 1e-30 && c < 1e30)) return (float)ldexp(c, k);
-        return ldexpf((float)c, k);
-    } else {
-        return ldexp(c, k);
-    }
-}
-
 // Final value for the FP32-term forms: c = h S times e^(Delta - z) (or e^Delta).
 __device__ __forceinline__ double assemble_k(double z, double delta, double hs, int result)
 {

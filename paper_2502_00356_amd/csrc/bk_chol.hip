@@ -23,9 +23,13 @@ namespace bk {
 
 typedef double chol4_t __attribute__((ext_vector_type(4)));
 constexpr int kB = kCholB;
-// Block columns a trailing update: 8,100 sites with gradient 15.25 ms with four, 15.2 with
-// six and with eight; value alone 7.7, 7.7, 8.2; 1,024 sites 0.79, 0.85, 0.79.
-constexpr int kStep = 4;
+// Block columns a trailing update (the sums run in the same order for any): 8,100 sites with
+// gradient 15.25 ms with four, 15.2 with six and with eight; value alone 7.7, 7.7, 8.2. Where
+// the launches' latencies are the time, fewer: one (no column launches) up to 16 block rows
+// (1,024 sites, value, us: 417 with one, 422, 433, 439 with four), two up to 32 (2,025 sites
+// 858, 857, 888, 881; 4,096 sites 1,999, 1,939, 1,944, 1,987); no trailing update at all up
+// to four (256 sites 124 against 127 with one).
+static int update_step(int nb) { return nb <= 4 ? 4 : (nb <= 16 ? 1 : (nb <= 32 ? 2 : 4)); }
 // Where a launch has few blocks its tiles are cut finer, so that a wave's chain of products
 // is shorter and more SIMDs have one (likelihood with gradient / value, ms):
 //  - panels and columns by 16 rows in place of 32 up to this many blocks: 1,024 sites (8
@@ -581,10 +585,11 @@ int chol_solve(double* S, const double* dB, const double* dN, const double* z, i
         st = blocks <= kFewBlocks ? launch(k_chol_column<1>, dim3(8 * blocks), wg, stream, S, n, nb, wt, k0, m, m)
                                   : launch(k_chol_column<2>, dim3(4 * blocks), wg, stream, S, n, nb, wt, k0, m, m);
     };
-    // kStep panels a trailing update (its blocks of S are read and written that much less
+    // several panels a trailing update (its blocks of S are read and written that much less
     // often), each block column of the step brought up to date just before its turn
-    for (int k = 0; k < nb; k += kStep) {
-        const int ke = k + kStep < nb ? k + kStep : nb;
+    const int step = update_step(nb);
+    for (int k = 0; k < nb; k += step) {
+        const int ke = k + step < nb ? k + step : nb;
         for (int j = k; j < ke; ++j) {
             column(k, j);
             diag(j);

@@ -186,8 +186,8 @@ typedef struct {
  * quadrature at the points of a table over r^2 and the entries by interpolation in it,
  * at the form's accuracy or better (BK_PLAIN_F64: a few 1e-16 relative where z < 2); the
  * table lies in the last bytes of out until those are written. Other calls, and
- * distances outside the table (r / beta below 2^-14 (FP32: 2^-12) or above 128),
- * evaluate each entry.
+ * distances below the table (r / beta under 2^-14; FP32: 2^-12), evaluate each entry;
+ * above it (128) the asymptotic series in FP64 is taken.
  * out : device buffer of bk_matern_out_elems(n, tile_size, lower_only) elements
  *       of params->out_dtype. params->mode selects the form; BK_LEARNED needs a
  *       model and a workspace of bk_matern_workspace_bytes(...) bytes, and only

@@ -2104,8 +2104,8 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
             const int st = matern_learned_entries(locs, prm, tile_size, lower_only, out, L, Lq, workspace, need, stream);
             if (st != BK_OK) return st;
         }
-        const TabParams P = tab_params(prm, 0.0);
-        const TabIndex X = tab_index(prm->beta, true);
+        const TabParams P = tab_params(prm, false, 0.0);
+        const TabIndex X = tab_index(prm->beta, P, true);
         int64_t first;
         char* tab = table_in_output(out, bk_matern_out_elems(locs->n, tile_size, lower_only), 4, true, &first);
         const MlpDev M = make_dev(m);
@@ -2116,7 +2116,7 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
                               0.0, 0.0, tab);
         if (st != BK_OK) return st;
         if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
-        st = launch_table_eval(locs, P, tile_size, lower_only, TAB_C, BK_MIXED_F32C, true, BK_OUT_F32, out, stream);
+        st = launch_table_eval(locs, P, X, tile_size, lower_only, TAB_C, BK_MIXED_F32C, true, BK_OUT_F32, out, stream);
         if (st != BK_OK) return st;
         return mark_kernel_event(prm, 1, stream) == hipSuccess ? BK_OK : BK_EHIP;
     }

@@ -34,9 +34,10 @@ struct TabShape<true> {
     static constexpr double kA = 8.0, kB = 6.0, kZMin = 0x1p-12;
 };
 
-// The interval rule of a call and the scale of the FP32 table's argument (1 / beta^2).
+// The interval rule of a call, the scale of the FP32 table's argument (1 / beta^2) and the
+// last slot's constant term: NaN, or 0 where an FP32 table's function rounds to 0 there.
 struct TabIndex {
-    float fa, fb, fc, vs;
+    float fa, fb, fc, vs, end;
 };
 
 __device__ __forceinline__ float tab_pos(const TabIndex& X, float q)
@@ -61,11 +62,16 @@ constexpr size_t tab_bytes()
 enum TabFn { TAB_C = 0, TAB_DBETA = 1, TAB_DNU = 2 };
 
 // The function of a call: host values. pref = ln c, scale = sigma2 c, c = 2^(1-nu) /
-// Gamma(nu); psi = digamma(nu), for dC/dnu.
+// Gamma(nu); psi = digamma(nu), for dC/dnu. zero: a z (at least kTabFar) from which the
+// call's functions round to 0 in the output's type. Seven doubles: with eight they pass
+// to the evaluation's out-of-line function through the stack (5 us a launch).
 struct TabParams {
-    double sigma2, beta, inv_beta, nu, pref, psi, scale;
+    double sigma2, inv_beta, nu, pref, psi, scale, zero;
 };
-TabParams tab_params(const bk_params* prm, double psi);
+TabParams tab_params(const bk_params* prm, bool grad, double psi);
+
+// Below the last slot's first z (128, less the steps of log2's linear pieces).
+constexpr double kTabFar = 127.0;
 
 // The q where tab_pos(q) = t, to a few of tab_pos's own roundings (1e-4 of an interval:
 // an entry that the rule puts on the other side of a boundary reads its neighbour's
@@ -164,11 +170,13 @@ __device__ inline void tab_fit(const TabWave<kF32>& t, double f, const TabIndex&
     double* slots = (double*)table;
     if (t.j == 0) slots[2 * t.i] = t.c;
     if (kF32 && t.j > 0) {
-        ((float*)table)[4 * (kN + t.i) + t.j - 1] = (float)a;
+        ((float*)table)[4 * (kN + t.i) + t.j - 1] = t.i == kN - 1 ? 0.0f : (float)a;
     } else {
         const int e = t.j + 1;
         // the first and last slots stand for everything out of the table
-        slots[2 * ((e >> 1) * kN + t.i) + (e & 1)] = t.j == 0 && (t.i == 0 || t.i == kN - 1) ? __builtin_nan("") : a;
+        if (t.j == 0 && t.i == 0) a = __builtin_nan("");
+        if (t.j == 0 && t.i == kN - 1) a = (double)X.end;
+        slots[2 * ((e >> 1) * kN + t.i) + (e & 1)] = a;
     }
 }
 
@@ -211,12 +219,12 @@ constexpr int64_t kTabMinF64 = 200000, kTabMinF32 = 70000, kTabMinLearned = 1000
 // elem_bytes its table is built: its last bytes, which the evaluation writes last.
 bool table_route(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, int64_t min_entries);
 char* table_in_output(void* out, int64_t elems, int elem_bytes, bool f32_table, int64_t* first);
-TabIndex tab_index(double beta, bool f32_table);
+TabIndex tab_index(double beta, const TabParams& P, bool f32_table);
 
 // Evaluation over all tiles from the table in `out` (built on the same stream).
 // cold_mode: the per-entry form of the distances outside the table's range.
 // fn: a TabFn.
-int launch_table_eval(const bk_locs* locs, const TabParams& P, int32_t tile_size, int32_t lower_only, int fn,
+int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X, int32_t tile_size, int32_t lower_only, int fn,
                       int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream);
 // Plain and mixed forms: builds the table and evaluates. bk_status.
 int matern_table_tiles(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, void* out,

@@ -131,6 +131,64 @@ def test_gradient_table_matches_entries(api, odt, n, ts, lower, nu):
     assert _close(out["dnu"], ref["dnu"], 2 * TOL_PLAIN, f32, scale)
 
 
+def _far_entries(xy, ts, s2, beta, nu, ref):
+    """ref (packed tiles) with the entries of z > 700, where e^-z is subnormal in the
+    per-entry form, by Hankel's series in 80 bits."""
+    import torch
+    ld = np.longdouble
+    n = len(xy)
+    d = [np.subtract.outer(xy[:, k].astype(ld), xy[:, k].astype(ld)) for k in (0, 1)]
+    full = np.hypot(d[0], d[1]) / ld(beta)
+    z = np.concatenate([full[i:i + ts, j:j + ts].T.ravel() for j in range(0, n, ts) for i in range(0, n, ts)])
+    far = np.flatnonzero(z > 700)
+    z, nu = z[far], ld(nu)
+    psi = ld(torch.digamma(torch.tensor(float(nu), dtype=torch.float64)).item())
+
+    def series(a):
+        s, ds = np.ones_like(z), np.zeros_like(z)
+        for k in range(24, 0, -1):
+            f = (4 * a * a - (2 * k - 1) ** 2) / (8 * k * z)
+            s, ds = 1 + f * s, f * ds + a / (k * z) * s
+        return s, ds
+
+    w = ld(s2) * ld(2) ** (1 - nu) / ld(math.gamma(nu)) * z ** nu * np.sqrt(ld(math.pi) / 2 / z) * np.exp(-z)
+    k, dk = series(nu)
+    new = {"c": w * k, "dbeta": w * z / ld(beta) * series(nu - 1)[0], "dnu": w * (k * (np.log(z / 2) - psi) + dk)}
+    idx = torch.from_numpy(far).cuda()
+    for key, t in ref.items():
+        t[idx] = torch.from_numpy(new[key].astype(np.float64)).cuda().to(t.dtype)
+    return ref
+
+
+@pytest.mark.parametrize("nu,s2", [(0.02, 0.8), (1.3, 1.0), (8.0, 3.0), (15.9, 1e30)])
+@pytest.mark.parametrize("beta", [0.006, 0.0015, 0.0002])
+@pytest.mark.parametrize("mode,odt", FORMS)
+def test_short_ranges(api, model, mode, odt, beta, nu, s2):
+    """Most entries past the table (z > 128), up to and beyond where they are 0. The
+    per-entry side adds logarithms: four roundings of an exponent of up to 745."""
+    import torch
+    n, ts = 900, 256
+    xy, lx, ly = _points(n, beta)
+    L, Lq = (36.0, 35.0) if mode == "plain" else (15.0, 14.5)
+    far = 4 * 745 * 2.0 ** -53
+    f32 = odt == "f32"
+    # the per-entry learned form takes its windows from a model that holds no such distance
+    kw = dict(mode="mixed" if mode == "learned" else mode, out_dtype=api.OUT_F32 if f32 else api.OUT_F64)
+    ref = api.matern_tiles(lx, ly, s2, beta, nu, ts, 0, L_window=L, L_quad=Lq, **kw)
+    ref = _far_entries(xy, ts, s2, beta, nu, {"c": ref})["c"]
+    out = api.matern_tiles(lx, ly, s2, beta, nu, ts, 0, mode=mode, out_dtype=kw["out_dtype"], model=model)
+    torch.cuda.synchronize()
+    assert _close(out, ref, 2 * (TOL_PLAIN if mode == "plain" else TOL_MIXED) + far, f32)
+    if mode != "plain":
+        return
+    gref = _far_entries(xy, ts, s2, beta, nu, api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, 0, L_window=36.0, L_quad=35.0))
+    grad = api.matern_grad_tiles(lx, ly, s2, beta, nu, ts, 0, out_dtype=kw["out_dtype"])
+    torch.cuda.synchronize()
+    scale = gref["c"].abs() * (14.0 + math.log(2.0) + 60.0) * 2 + gref["dnu"].abs()     # |psi(0.02)| < 60
+    for k, sc in (("c", None), ("dbeta", None), ("dnu", scale)):
+        assert _close(grad[k], gref[k], 2 * TOL_PLAIN + far, f32, sc), k
+
+
 @pytest.mark.parametrize("mode,odt,n,ts,lower", [
     ("plain", "f64", 447, 5000, 0), ("plain", "f64", 448, 5000, 0), ("plain", "f32", 460, 23, 0),
     ("plain", "f64", 620, 100, 1), ("mixed", "f32", 264, 264, 0), ("mixed", "f32", 265, 264, 0),

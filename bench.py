@@ -52,8 +52,8 @@ NODE_SLOTS = load_node_slots()
 # null: HBM bytes from the FETCH_SIZE and WRITE_SIZE runs scaled by a plain 1 GiB
 # copy, and SQ_INSTS_VALU of one launch without statistics.
 TRAFFIC = {
-    "grid": {"src_sha": "c9ee117a29f4b14b", "n": 1 << 24, "bytes": 4.1545e8, "valu_insts": 1.043e8},
-    "matern_large": {"src_sha": "4ed0583a0a88a4bf", "bytes": 2.13061e10, "valu_insts": 1.98362e9},
+    "grid": {"src_sha": "3862daf8549f6b23", "n": 1 << 24, "bytes": 4.15438e8, "valu_insts": 1.04343e8},
+    "matern_large": {"src_sha": "88d6562b9395dd52", "bytes": 2.13076e10, "valu_insts": 1.98615e9},
 }
 KERNEL_SOURCES = {
     "grid": ("bk_mlp.hip", "bk_math.hpp", "bk_internal.hpp"),

@@ -62,9 +62,10 @@ __device__ __forceinline__ double assemble(double z, double delta, double hs, in
     if (result == BK_RESULT_SCALED) return exp(delta) * hs;
     if (result == BK_RESULT_LOG) return (delta - z) + log(hs);
     const double d = delta - z;
-    if (fabs(d) < 700.0 && z < 708.0) {                     // e^d a normal number; its argument's rounding carried
-        const double v = exp_wide(d, T) * hs;
-        return fma(v, two_sum_err(delta, -z, d), v);
+    if (fabs(d) < 700.0 && z < 708.0) {
+        // e^d is a normal number; its argument's rounding is carried before hs, whose product may overflow
+        const double v = exp_wide(d, T);
+        return fma(v, two_sum_err(delta, -z, d), v) * hs;
     }
     if (z < 708.0) return exp(-z) * exp(delta) * hs;
     // subnormal range: e^(-z) formed 2^64 larger, product scaled back (one rounding)

@@ -147,6 +147,23 @@ def test_matern_grad_tiles(api, orc, nu, lower):
     assert np.all(C[r == 0] == s2) and np.all(DB[r == 0] == 0) and np.all(DN[r == 0] == 0)
 
 
+def test_deriv_overflow(api, orc):
+    """dK/dx past the double range (-inf) where K and e^Delta are still finite, and its
+    neighbours just inside: nu / x times K with K from 1e300 on."""
+    nu = np.array([46.0, 46.2, 46.3, 46.33, 46.36, 46.4, 30.0, 30.0])
+    x = np.array([1e-5, 1e-5, 1e-5, 1e-5, 1e-5, 1e-5, 2.1e-9, 2.0e-9])
+    d = orc.besselk_deriv(nu, x)
+    k, _, _ = orc.besselk(nu, x)
+    assert np.all(np.isfinite(k)) and np.array_equal(np.isinf(d["dx"]), [False, False] + [True] * 6)
+    for result in (0, 1):
+        g = _deriv(api, nu, x, result=result)
+        # the oracle's values are exponentials of logarithms up to 710; e^x - 1 < 2 x where scaled
+        tol = TOL_PLAIN + 710 * 2.0 ** -53 + 2 * result * x
+        assert np.all(g["dx"][2:] == -math.inf)
+        assert np.all(rel_err(g["dx"][:2], d["dx"][:2]) <= tol[:2])
+        assert np.all(rel_err(g["k"], k) <= tol) and np.all(rel_err(g["dnu"], d["dnu"]) <= tol)
+
+
 @pytest.mark.parametrize("n", [1, 63, 65, 299999, 300000, 301023])
 def test_deriv_launch_shapes(api, orc, n):
     """Both launch shapes (64- and 1,024-entry workgroups, from 300,000 entries) at the edges

@@ -1274,8 +1274,10 @@ __device__ inline double temme_k(double nu, double x, const TemmeCoef& C, const 
         km = kp;
         kp = kn;
     }
-    // kp grows as ix^M (its other term is below x^2 / 4 of it): ix = (2/x)(1 - e)
-    return M >= 1.0 ? fma(kp * M, 0.5 * fma(-x, ix, 2.0), kp) : km;
+    if (M < 1.0) return km;
+    // kp grows as ix^M (its other term is below x^2 / 4 of it): ix = (2/x)(1 - e). An overflowed
+    // kp stays infinite.
+    return kp < __builtin_inf() ? fma(kp, M * (0.5 * fma(-x, ix, 2.0)), kp) : kp;
 }
 
 }  // namespace bk

@@ -120,3 +120,30 @@ def test_refined_algorithm_over_paper_region(api, orc):
     assert rel_err(got[small], k).max() <= TOL_PLAIN
     m = s >= DBL_MIN
     assert rel_err(got[~small][m], s[m]).max() <= TOL_PLAIN
+
+
+def test_temme_overflow(api, orc):
+    """K near and past the double range: finite values by the oracle, then +inf in every
+    result, for residuals of 2/x of either sign and zero; the Matern form stays free of NaN."""
+    import torch
+    nu = np.array([60.0, 60.0, 60.0, 60.0, 100.0, 100.0, 200.0, 200.0, 200.0, 200.0, 30.0])
+    x = np.array([3.27e-4, 3.24e-4, 1e-4, 2.0 ** -12, 0.01, 0.09, 1e-3, 0.01, 0.03, 0.05, 1e-9])
+    k, lk, _ = orc.besselk(nu, x)
+    fin = np.isfinite(k)
+    assert np.array_equal(np.flatnonzero(fin), [0, 1, 5])
+    for result in (api.RESULT_K, api.RESULT_SCALED, api.RESULT_LOG):
+        got = api.besselk(to_dev(nu), to_dev(x), mode="paper", result=result)
+        torch.cuda.synchronize()
+        got = got.cpu().numpy()
+        assert np.all(got[~fin] == math.inf)
+        if result == api.RESULT_LOG:
+            assert np.all(np.abs(got[fin] - lk[fin]) <= TOL_PLAIN + 4e-16 * lk[fin])
+        else:
+            # the oracle's K is the exponential of a logarithm up to 710; e^x - 1 < 2 x where scaled
+            assert np.all(rel_err(got[fin], k[fin]) <= TOL_PLAIN + 710 * 2.0 ** -53 + 2 * (result == 1) * x[fin])
+    d = np.array([0.0, 3.27e-4, 3.24e-4])
+    out = api.matern_tiles(to_dev(d), to_dev(0 * d), 1.0, 1.0, 60.0, 3, 0, mode="paper")
+    torch.cuda.synchronize()
+    # C = 1 - z^2 / (4 (nu - 1)) + O(z^4); the factors z^nu and c K are good to 1e-13
+    z = np.abs(d[:, None] - d[None, :])[:, :1]
+    assert np.all(np.abs(out.cpu().numpy().reshape(3, 3)[0, :, None] - (1 - z * z / 236)) <= 1e-13)

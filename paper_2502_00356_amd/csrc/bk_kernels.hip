@@ -62,7 +62,7 @@ __device__ __forceinline__ double assemble(double z, double delta, double hs, in
     if (result == BK_RESULT_SCALED) return exp(delta) * hs;
     if (result == BK_RESULT_LOG) return (delta - z) + log(hs);
     const double d = delta - z;
-    if (fabs(d) < 700.0 && z < 708.0) {
+    if (fabs(d) < 700.0) {
         // e^d is a normal number; its argument's rounding is carried before hs, whose product may overflow
         const double v = exp_wide(d, T);
         return fma(v, two_sum_err(delta, -z, d), v) * hs;
@@ -457,7 +457,9 @@ __device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, doubl
     const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
     double hs1 = s1.p.h * sum_f64<true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
     hs1 = fma(hs1, s1.dlo, hs1);
-    o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
+    // by assemble where K is in range: e^Delta need not be (nu = 1,000 at x = 500)
+    if (result == BK_RESULT_K && fabs(s0.delta - z) < 700.0) o.dx = -fma(v / z, o.k, assemble(z, s1.delta, hs1, result, T));
+    else o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
     o.nodes = (unsigned int)(s0.p.N + s1.p.N + 2);
     o.dn = 0.0;
     if (v > 0.0) {
@@ -510,10 +512,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
                 store(i, __builtin_inf(), -__builtin_inf(), av == 0.0 ? 0.0 : copysign(__builtin_inf(), nr));
             else if (isinf(z[q]))
                 store(i, 0.0, -0.0, copysign(0.0, nr));
-            else if (!deriv_fast_ok(av, z[q], L))
+            else if (!deriv_fast_ok(av, z[q], L) || !deriv_window_count(av, z[q], L, Lq, t0[q], t1[q], N, mc))
                 N = kEntryExact;
-            else
-                deriv_window_count(av, z[q], L, Lq, t0[q], t1[q], N, mc);
         }
         e[q] = (unsigned int)(q * kThreads + tid) | (mc << 10) | (N << 20);
         key[q] = B.key_of(N, v[q]);

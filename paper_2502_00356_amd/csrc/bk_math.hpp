@@ -974,9 +974,11 @@ __device__ inline double sum_dnu_f64(double nu, const Plan& p, double A, double 
 //    |sinh(nu (t + ia))| / sinh(nu t) <= (1 + a/t)^2 (|sin b| <= b <= (a/t) sinh(nu t) for b =
 //    nu a), at td with a = pi/2.
 // For plan_fast_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
+// Returns whether sum_deriv can walk it: e^(2 nu d) over the left side's length d has to be
+// finite (nu up to several hundred at L = 36); the exact solves take the rest.
 __device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L) { return plan_fast_ok(nu, x, L) && L >= 8.0; }
 
-__device__ __forceinline__ void deriv_window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
+__device__ __forceinline__ bool deriv_window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
                                                    unsigned int& N, unsigned int& mc)
 {
     const float nf = (float)nu, xf = (float)x, Lf = (float)L + 0.01f, ix = __builtin_amdgcn_rcpf(xf);
@@ -989,6 +991,7 @@ __device__ __forceinline__ void deriv_window_count(double nu, double x, double L
     t0 = left_end_fast(tp, E, Ei, nf, xf, Lf);
     const float extra = 2.0f * 0.69314718f * __builtin_amdgcn_logf(fmaf(1.5707963f, itd, 1.0f));
     node_grid(t0, t1, tp, node_step_fast(nf + 1.0f, xf, (float)Lq + extra), N, mc);
+    return 2.0f * nf * (t1 - t0) * (float)mc < 700.0f * (float)N;
 }
 
 // Trapezoid sums of the paired walk (sum_f64): of the K terms e^d (2 - Q), of those times
@@ -1003,7 +1006,8 @@ __device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
     const double h = p.h, nh = nu * h;
-    const double omr = -expm1(-2.0 * nh), rho = 1.0 - omr;             // 1 - e^(-2 nu h)
+    // 1 - e^(-2 nu h), and the exponential itself (1 less the former is 0 from nu h = 18 on)
+    const double omr = -expm1(-2.0 * nh), rho = exp_tab(-2.0 * nh, T);
     const double qe = omr * recip(rho), re = 1.0 + qe;                 // e^(2 nu h) - 1, e^(2 nu h)
     const double Qr = -expm1(-2.0 * nu * p.tref), Pr = exp_tab(-2.0 * nu * p.tref, T);
     double QR = Qr, EL = 0.0, jd = 1.0;
@@ -1115,15 +1119,14 @@ __device__ inline DerivSums sum_split(double nu, double x, const Plan& p, double
 __device__ __forceinline__ void dnu_integral(double nu, double x, double t0, double L, double Lq, const RuleTable& R,
                                              const double* T, double& delta, double& hs)
 {
-    if (!deriv_fast_ok(nu, x, L)) {
+    float a, b;
+    unsigned int N, mc;
+    if (!deriv_fast_ok(nu, x, L) || !deriv_window_count(nu, x, L, Lq, a, b, N, mc)) {
         const Solved sd = dnu_solve(nu, x, t0, L, Lq, R, T);
         delta = sd.delta;
         hs = sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T);
         return;
     }
-    float a, b;
-    unsigned int N, mc;
-    deriv_window_count(nu, x, L, Lq, a, b, N, mc);
     const Solved s = plan_setup(nu, x, a, b, N, mc);
     delta = s.delta;
     hs = s.p.h * sum_deriv(nu, x, s.p, s.E, s.Ei, s.Sr, T).d;

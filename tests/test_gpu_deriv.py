@@ -164,6 +164,26 @@ def test_deriv_overflow(api, orc):
         assert np.all(rel_err(g["k"], k) <= tol) and np.all(rel_err(g["dnu"], d["dnu"]) <= tol)
 
 
+@pytest.mark.parametrize("n", [64, 300160])
+def test_deriv_large_orders(api, orc, n):
+    """Orders where e^(-2 nu h) is below 2^-53 (from some hundred on) and where e^(2 nu d) over
+    the left side is not a double (1,000), in both launch shapes: results in range (their
+    logarithms reach 650, so a rounding of one, here and in the oracle, is 8e-14 of its
+    result), and +-inf where they are past it."""
+    nu = np.repeat([300.0, 500.0, 700.0, 900.0, 1000.0, 1100.0, 1000.0, 5000.0], 8)
+    x = nu * np.tile([0.42, 0.45, 0.5, 0.55, 0.6, 0.7, 0.8, 0.9], 8)
+    x[48:] = np.resize([1e-12, 1e-6, 1e-3, 0.2, 10.0, 100.0], 16)
+    d = orc.besselk_deriv(nu[:48], x[:48])
+    k, lk, _ = orc.besselk(nu[:48], x[:48])
+    ref = {"k": k, "dx": d["dx"], "dnu": d["dnu"]}
+    assert np.abs(lk).max() < 650 and all(np.isfinite(r).all() and (r != 0).all() for r in ref.values())
+    g = _deriv(api, np.resize(nu, n), np.resize(x, n))
+    for key, r in ref.items():
+        assert np.array_equal(g[key], np.resize(g[key][:64], n)), key
+        assert rel_err(g[key][:48], r).max() <= TOL_PLAIN + 2 * 710 * 2.0 ** -53, key
+        assert np.all(g[key][48:64] == (-math.inf if key == "dx" else math.inf)), key
+
+
 @pytest.mark.parametrize("n", [1, 63, 65, 299999, 300000, 301023])
 def test_deriv_launch_shapes(api, orc, n):
     """Both launch shapes (64- and 1,024-entry workgroups, from 300,000 entries) at the edges

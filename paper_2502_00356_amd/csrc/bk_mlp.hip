@@ -726,10 +726,12 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
     __shared__ double s_v[kLearnedBlock], s_z[kLearnedBlock];
     __shared__ win_t s_tlo[kLearnedBlock], s_thi[kLearnedBlock];
     __shared__ double s_out[kLearnedBlock];      // in entry order
+    __shared__ unsigned int s_queued[kLearnedBlock / 32];
     __shared__ int s_N[kLearnedBlock];
     static_assert(kLearnedBlock <= 256 && kCells <= 1 << 24, "entry word");
     __shared__ unsigned int s_e[kLearnedBlock];  // entry | cell << 8
     const int tid = threadIdx.x;
+    if (tid < kLearnedBlock / 32) s_queued[tid] = 0u;     // set after the sort's barriers
     const int64_t i = (int64_t)blockIdx.x * kLearnedBlock + tid;
     int cell = 0;
     const bool live = i < n;
@@ -833,10 +835,12 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
             if (lo.reason == BK_STAT_FB_TAIL) c_tail += 1; else c_nonfin += 1;
             const unsigned int slot = atomicAdd(qcount, 1u);
             queue[slot] = (unsigned int)blockIdx.x * kLearnedBlock + own;
+            atomicOr(&s_queued[own >> 5], 1u << (own & 31u));
         }
     }
     __syncthreads();
-    if (N >= 0) out[i] = s_out[tid];         // queued entries are written again by the fallback
+    // not the queued entries: the fallback reads their inputs, which out may share
+    if (N >= 0 && !(s_queued[tid >> 5] >> (tid & 31) & 1u)) out[i] = s_out[tid];
     if constexpr (kStats) {
         unsigned long long cnt[8];
         cnt[BK_STAT_ENTRIES] = c_ent;

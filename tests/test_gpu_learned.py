@@ -307,6 +307,33 @@ def test_learned_launch_shapes(api, trained, lq):
         assert int(st[k]) == int(tot[k]), k
 
 
+@pytest.mark.parametrize("n", [4097, 2000077])
+@pytest.mark.parametrize("lq", [0.0, 14.5000001])
+def test_learned_in_place(api, trained, n, lq):
+    """out may be x or nu, in both launch shapes: entries whose window fails the tail test
+    (here by a network whose t_hi is cut short) are recomputed from their own inputs."""
+    import torch
+    from paper_2502_00356_amd import workloads
+    m = api.Model()
+    p = trained.get_params()
+    p[4352 + 64:4352 + 128] *= 0.95        # W3 and b3 of t_hi
+    p[4545] *= 0.95
+    m.set_params(p)
+    m.set_norm(trained.get_norm())
+    m.set_box(trained.get_box())
+    m.set_margins(0.0, 0.0, 0.1, 1.0)
+    nu, x, _ = workloads.grid_pairs(1 << 21, seed=16)
+    nu, x = to_dev(nu[:n]), to_dev(x[:n])
+    stats = torch.zeros(api.STATS_LEN, dtype=torch.int64, device="cuda")
+    ref = api.besselk(nu, x, mode="learned", model=m, L_quad=lq, stats=stats)
+    assert 0.01 * n < int(stats[api.STAT_FB_TAIL]) < 0.99 * n
+    for st in (None, stats):
+        a, b = nu.clone(), x.clone()
+        assert torch.equal(api.besselk(a, b, out=b, mode="learned", model=m, L_quad=lq, stats=st), ref)
+        a, b = nu.clone(), x.clone()
+        assert torch.equal(api.besselk(a, b, out=a, mode="learned", model=m, L_quad=lq, stats=st), ref)
+
+
 def test_learned_out_of_range_falls_back(api, orc, trained):
     """Pairs outside the training box all take the plain-solver path and stay exact."""
     import torch

@@ -293,7 +293,8 @@ __device__ __forceinline__ void lds_barrier()
 // the same operations make of an identity below A (see the head of this file). Column s:
 //  1. wave s factors its diagonal tile as L D L^T, a lane a row, then scales by D^-1/2. The
 //     chain from pivot to pivot is d' = a' - a^2 / d in every lane (a, a' read from their
-//     lanes beforehand): a reciprocal and four operations. Lanes 16 - 31 carry identity rows,
+//     lanes beforehand; a^2 is formed first, so the matrix's scale has to be far inside the
+//     root of the double range): a reciprocal and four operations. Lanes 16 - 31 carry identity rows,
 //     which the same instructions turn into rows of G^T = L_ss^-T, and lane 32 the
 //     right-hand side's segment, which becomes u_s.
 //  2. the other waves multiply by G (X^T = G A^T: a product's registers are the next one's
@@ -554,21 +555,21 @@ __global__ __launch_bounds__(256) void k_chol_sum(const double* __restrict__ par
     if (threadIdx.x == 0) res[k] = red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ __launch_bounds__(256) void k_chol_begin(const double* __restrict__ z, double* __restrict__ zrow, int64_t n,
-                                                    int* __restrict__ info)
+__global__ __launch_bounds__(256) void k_chol_begin(const double* __restrict__ z, double zscale, double* __restrict__ zrow,
+                                                    int64_t n, int* __restrict__ info)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) zrow[i] = z[i];
+    if (i < n) zrow[i] = zscale * z[i];
     if (i == 0) *info = 0;
 }
 
-int chol_solve(double* S, const double* dB, const double* dN, const double* z, int64_t n, const CholWork& wk,
-               hipStream_t stream)
+int chol_solve(double* S, const double* dB, const double* dN, const double* z, double zscale, int64_t n,
+               const CholWork& wk, hipStream_t stream)
 {
     const int nb = (int)chol_blocks(n), inverse = dB ? 1 : 0;
     const double *w = wk.w, *wt = wk.wt, *u = wk.u, *zrow = wk.zrow, *Sc = S;
     const dim3 wg(256);
-    int st = launch(k_chol_begin, dim3((unsigned)((n + 255) / 256)), wg, stream, z, wk.zrow, n, wk.info);
+    int st = launch(k_chol_begin, dim3((unsigned)((n + 255) / 256)), wg, stream, z, zscale, wk.zrow, n, wk.info);
     auto diag = [&](int k) {
         if (st == BK_OK)
             st = launch(k_chol_diag, dim3(1), dim3(512), stream, Sc, n, nb, k, wk.w, wk.wt, zrow, wk.u, wk.part, wk.info);

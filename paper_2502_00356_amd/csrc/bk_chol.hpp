@@ -33,12 +33,12 @@ inline int64_t chol_trace_tiles(int64_t n)
     return t * (t + 1) / 2;
 }
 
-// Factorises the lower triangle of S (n x n, column-major, leading dimension n) and
-// reduces z: res[0] = log det L, res[1] = z^T Sigma^-1 z. dB, dN not NULL: also
-// L^-T in S's strictly upper blocks, a = Sigma^-1 z, and
+// Factorises the lower triangle of S (n x n, column-major, leading dimension n; its scale
+// within 2^-200 to 2^200) and reduces zscale z: res[0] = log det L, res[1] = zscale^2 z^T
+// Sigma^-1 z. dB, dN not NULL: also L^-T in S's strictly upper blocks, a = zscale Sigma^-1 z, and
 //   res[2] = a^T dB a, res[3] = tr(Sigma^-1 dB), res[4], res[5] the same of dN
 // from the lower triangles of dB and dN. bk_status.
-int chol_solve(double* S, const double* dB, const double* dN, const double* z, int64_t n, const CholWork& wk,
-               hipStream_t stream);
+int chol_solve(double* S, const double* dB, const double* dN, const double* z, double zscale, int64_t n,
+               const CholWork& wk, hipStream_t stream);
 
 }  // namespace bk

@@ -10,6 +10,7 @@
 // Matern kernels as one full column-major tile; the factorisation, the inverse factor and
 // the traces are bk_chol.hip's (sums in a fixed order).
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <math.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -89,17 +90,24 @@ extern "C" int bk_matern_loglik(const bk_locs* locs, const double* z, const bk_p
     p.out_dtype = BK_OUT_F64;
     p.workspace = ws + L.mws;
     p.workspace_bytes = L.total - L.mws;
+    // Far from 1, sigma2 is taken as 4^k sigma2': Sigma / 4^k and z / 2^k have the same quadratic
+    // forms and traces, and log det Sigma / 4^k is log det Sigma less 2 n k log 2
+    int k = 0;
+    if (!(prm->sigma2 >= 0x1p-200 && prm->sigma2 <= 0x1p200) && prm->sigma2 <= DBL_MAX) {
+        k = ilogb(prm->sigma2) / 2;
+        p.sigma2 = ldexp(prm->sigma2, -2 * k);
+    }
     int st = with_grad ? bk_matern_grad_tiles(locs, &p, (int32_t)n, 0, S, dB, dN, stream)
                        : bk_matern_tiles(locs, &p, (int32_t)n, 0, S, stream);
     if (st != BK_OK) return st;
 
-    st = chol_solve(S, dB, dN, z, n, wk, stream);
+    st = chol_solve(S, dB, dN, z, ldexp(1.0, -k), n, wk, stream);
     if (st != BK_OK) return st;
     MleResult h = {};
     if (hipMemcpyAsync(&h, wk.res, sizeof(h), hipMemcpyDeviceToHost, stream) != hipSuccess) return BK_EHIP;
     if (hipStreamSynchronize(stream) != hipSuccess) return BK_EHIP;
     if (h.info != 0) return BK_ENOTPD;
-    const double *hres = h.sums, logdet = 2.0 * hres[0], quad = hres[1];
+    const double *hres = h.sums, logdet = 2.0 * hres[0] + (double)n * (2.0 * k * kLn2), quad = hres[1];
     result[0] = -0.5 * quad - 0.5 * logdet - 0.5 * (double)n * 1.8378770664093454836;   // log(2 pi)
     if (with_grad) {
         result[1] = 0.5 * (quad - (double)n) / prm->sigma2;

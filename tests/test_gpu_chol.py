@@ -67,6 +67,27 @@ def test_loglik_singular(api, n, k):
         assert np.isfinite(l)
 
 
+@pytest.mark.parametrize("s2", [5e-310, 1e-290, 1e-170, 1e-160, 1e-156, 1e-62, 1e-60, 1e60, 1e62, 1e154, 1e160, 1e300, 1.5e308])
+def test_loglik_scale(api, s2):
+    """Any positive sigma2: with z = sqrt(sigma2) z1 the likelihood is that of sigma2 = 1 less
+    n / 2 log sigma2, its beta and nu derivatives are the same, and that in sigma2 is divided
+    by sigma2. Bars as above, and z's rounding."""
+    from paper_2502_00356_amd import workloads as w
+    n, beta, nu = 140, 0.03, 0.8
+    xy = w.jittered_grid_locations(12, seed=3)[:n]
+    z = np.random.default_rng(3).standard_normal(n)
+    lx, ly = to_dev(xy[:, 0]), to_dev(xy[:, 1])
+    l1, g1 = api.matern_loglik(lx, ly, to_dev(z), 1.0, beta, nu, grad=True)
+    assert abs(l1) <= 1e3 and max(map(abs, g1)) <= 1e3
+    got = api.matern_loglik(lx, ly, to_dev(z * math.sqrt(s2)), s2, beta, nu)
+    got_g, grad = api.matern_loglik(lx, ly, to_dev(z * math.sqrt(s2)), s2, beta, nu, grad=True)
+    assert got_g == got
+    assert abs(got - (l1 - 0.5 * n * math.log(s2))) <= 1e-9 * (1e3 + n * abs(math.log(s2)))
+    # s2 * inf where 1 / s2 is not a double
+    assert abs(grad[0] * s2 - g1[0]) <= 1e-9 * 1e3 or (s2 < 1e-308 and math.isinf(grad[0]))
+    assert abs(grad[1] - g1[1]) <= 1e-9 * 1e4 and abs(grad[2] - g1[2]) <= 1e-9 * 1e3
+
+
 @pytest.mark.parametrize("n", [4747, 4993, 5377])
 def test_loglik_tile_rules(api, n):
     """Sizes around which the launches change their tiles (38 block rows for the traces, 40

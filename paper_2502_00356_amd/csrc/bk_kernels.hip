@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
             double r;
             if (special_value(v[k], z[k], result, r)) out[i] = r;
             else if (temme_applies(v[k], z[k])) N = kEntryTemme;
-            else if (!plan_fast_ok(v[k], z[k], L)) N = kEntryExact;
+            else if (!plan_fast_ok(v[k], z[k], L, Lq)) N = kEntryExact;
             else window_count(v[k], z[k], L, Lq, t0[k], t1[k], N, mc);
         }
         e[k] = (unsigned int)(k * kThreads + tid) | (mc << 10) | (N << 20);
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
                 store(i, __builtin_inf(), -__builtin_inf(), av == 0.0 ? 0.0 : copysign(__builtin_inf(), nr));
             else if (isinf(z[q]))
                 store(i, 0.0, -0.0, copysign(0.0, nr));
-            else if (!deriv_fast_ok(av, z[q], L) || !deriv_window_count(av, z[q], L, Lq, t0[q], t1[q], N, mc))
+            else if (!deriv_fast_ok(av, z[q], L, Lq) || !deriv_window_count(av, z[q], L, Lq, t0[q], t1[q], N, mc))
                 N = kEntryExact;
         }
         e[q] = (unsigned int)(q * kThreads + tid) | (mc << 10) | (N << 20);

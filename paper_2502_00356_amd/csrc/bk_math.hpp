@@ -499,10 +499,12 @@ __device__ __forceinline__ float node_step_learned(float nu, float x, float Lq)
 //    <= F(e) = L + ln 2 - nu e + x (cosh tp - cosh(tp - e)), concave and decreasing: a Newton
 //    step lands at or past the root; F(tp) >= 0 leaves the window starting at 0.
 // FP32 rounding moves an end by 1e-5 of its distance; L carries 0.01 for it. For 1e-12 <=
-// x <= 1e5, nu <= 1e4, L <= 500 (plan_fast_ok); plain_solve covers the rest.
-__device__ __forceinline__ bool plan_fast_ok(double nu, double x, double L)
+// x <= 1e5, nu <= 1e4, 1 <= L <= 500, Lq >= 1 (plan_fast_ok); plain_solve covers the rest: below
+// L = 0.09 the right end's start may lie left of F's minimum, where a Newton step goes the other
+// way, and below Lq = 0.8 a step may be so long that e^(-2 nu h) is no double.
+__device__ __forceinline__ bool plan_fast_ok(double nu, double x, double L, double Lq)
 {
-    return x >= 1e-12 && x <= 1e5 && nu <= 1e4 && L <= 500.0;
+    return x >= 1e-12 && x <= 1e5 && nu <= 1e4 && L >= 1.0 && L <= 500.0 && Lq >= 1.0;
 }
 
 __device__ __forceinline__ float exp_fast(float y) { return __builtin_amdgcn_exp2f(y * 1.44269504f); }
@@ -623,7 +625,7 @@ __device__ __forceinline__ Solved plan_setup(double nu, double x, float t0, floa
 // Plan of the plain sum: the fast window where it applies, else the exact solve.
 __device__ inline Solved plain_plan(double nu, double x, double L, double Lq, const RuleTable& R, const double* T)
 {
-    if (!plan_fast_ok(nu, x, L)) return plain_solve(nu, x, L, Lq, R, T);
+    if (!plan_fast_ok(nu, x, L, Lq)) return plain_solve(nu, x, L, Lq, R, T);
     float t0, t1;
     unsigned int N, mc;
     window_count(nu, x, L, Lq, t0, t1, N, mc);
@@ -976,7 +978,10 @@ __device__ inline double sum_dnu_f64(double nu, const Plan& p, double A, double 
 // For plan_fast_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
 // Returns whether sum_deriv can walk it: e^(2 nu d) over the left side's length d has to be
 // finite (nu up to several hundred at L = 36); the exact solves take the rest.
-__device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L) { return plan_fast_ok(nu, x, L) && L >= 8.0; }
+__device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L, double Lq)
+{
+    return plan_fast_ok(nu, x, L, Lq) && L >= 8.0;
+}
 
 __device__ __forceinline__ bool deriv_window_count(double nu, double x, double L, double Lq, float& t0, float& t1,
                                                    unsigned int& N, unsigned int& mc)
@@ -1121,7 +1126,7 @@ __device__ __forceinline__ void dnu_integral(double nu, double x, double t0, dou
 {
     float a, b;
     unsigned int N, mc;
-    if (!deriv_fast_ok(nu, x, L) || !deriv_window_count(nu, x, L, Lq, a, b, N, mc)) {
+    if (!deriv_fast_ok(nu, x, L, Lq) || !deriv_window_count(nu, x, L, Lq, a, b, N, mc)) {
         const Solved sd = dnu_solve(nu, x, t0, L, Lq, R, T);
         delta = sd.delta;
         hs = sd.p.h * sum_dnu_f64(nu, sd.p, sd.A, sd.B, T);

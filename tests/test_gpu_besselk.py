@@ -111,6 +111,40 @@ def test_ragged_sizes(api, orc, n):
     np.testing.assert_array_equal(out.cpu().numpy(), _gpu(api, nu, x, "plain", 0))
 
 
+@pytest.mark.parametrize("L,Lq", [(1e-3, 35.0), (0.01, 35.0), (0.05, 35.0), (0.08, 8.0), (0.3, 35.0), (0.999, 0.999),
+                                  (36.0, 1e-3), (36.0, 0.3), (1.0, 1.0), (3.0, 30.0), (8.0, 1.0)])
+def test_plain_small_thresholds(api, orc, L, Lq):
+    """Thresholds below 1: the trapezoid sum over the solved window's own nodes (bk_window),
+    formed here in long double (node positions rounded at 2^-52 t, up to 15, of a width down
+    to 3e-3: 1e-12). From 1 on the window may be wider, so the sum lies between that window's
+    integral and K, up to its own discretisation (Lq: half of K at most for Lq >= 1)."""
+    import torch
+    nu = np.array([0.0, 0.3, 0.9, 2.0, 9.0, 9.9, 100.0, 300.0, 300.0, 9900.0, 9900.0])
+    x = np.array([1.0, 0.2, 0.95, 5.0, 90.0, 100.0, 40.0, 60.0, 9.1e4, 9e4, 6e4])
+    got = api.besselk(to_dev(nu), to_dev(x), result=api.RESULT_LOG, L_window=L, L_quad=Lq)
+    t0, t1, N = api.window(to_dev(nu), to_dev(x), L_window=L, L_quad=Lq)
+    torch.cuda.synchronize()
+    got, t0, t1, N = (a.cpu().numpy() for a in (got, t0, t1, N))
+
+    def log_sum(v, z, a, b, n):
+        a, h = np.longdouble(a), (np.longdouble(b) - np.longdouble(a)) / n
+        t = a + np.arange(n + 1) * h
+        e = v * t - np.log(np.longdouble(2)) - 2 * z * np.sinh(t / 2) ** 2 + np.log1p(np.exp(-2 * v * t))
+        w = np.ones(n + 1, np.longdouble)
+        w[0] = w[-1] = 0.5
+        return float(e.max() + np.log((w * np.exp(e - e.max())).sum() * h) - z)
+
+    solved = t1 > t0          # the solver itself loses windows that short at large orders
+    assert solved.sum() >= 7
+    _, lk, _ = orc.besselk(nu, x)
+    for v, z, a, b, n, g, k in zip(*(q[solved] for q in (nu, x, t0, t1, N, got, lk))):
+        if L >= 1 and Lq >= 1:
+            assert log_sum(v, z, a, b, 4000) - np.log(2.0) <= g <= k + np.log(2.0), (v, z)
+        else:
+            s = log_sum(v, z, a, b, n)
+            assert abs(s - g) <= 1e-11 + 4e-16 * abs(s), (v, z)
+
+
 def test_special_values(api):
     nu = np.array([1.0, 1.0, 1.0, np.nan, 2.0, -2.5, np.inf, 3.0])
     x = np.array([0.0, -1.0, np.nan, 1.0, np.inf, 2.0, 1.0, 1e-4])

@@ -101,6 +101,10 @@ __device__ inline void tile_of(int64_t p, const TileGeom& g, int64_t& I, int64_t
     I = J + (p - (J * T - J * (J - 1) / 2));
 }
 
+// z for the plain sums of the per-entry kernels: past 1e306 their exponents leave exp_node's
+// range, and at a finite z past 1e300 the prefactor is 0 whatever the sum.
+__device__ __forceinline__ double sum_z(double z) { return z > 1e300 && z < __builtin_inf() ? 1e300 : z; }
+
 // One entry of the plain (MODE BK_PLAIN_F64) or mixed form at z = r / beta > 0:
 // sigma2 c z^nu K_nu(z), pref = ln c = ln(2^(1-nu) / Gamma(nu)). s: the entry's solve
 // (for the caller's counts and for dC/dnu). T: exp_tab's tables.
@@ -110,8 +114,9 @@ __device__ __forceinline__ double matern_entry(double nu, double z, double lz, d
 {
     double hs;
     if constexpr (MODE == BK_PLAIN_F64) {
-        s = plain_plan(nu, z, L, Lq, rule_tab(), T);
-        hs = s.p.h * sum_f64<true>(nu, z, s.p, s.E, s.Ei, s.Sr, T);
+        const double zs = sum_z(z);
+        s = plain_plan(nu, zs, L, Lq, rule_tab(), T);
+        hs = s.p.h * sum_f64<true>(nu, zs, s.p, s.E, s.Ei, s.Sr, T);
         hs = fma(hs, s.dlo, hs);
     } else {
         s = plain_solve(nu, z, L, Lq, rule_tab(), T);
@@ -124,9 +129,9 @@ __device__ __forceinline__ double matern_entry(double nu, double z, double lz, d
 __device__ __forceinline__ double matern_dbeta(double nu, double z, double lz, double sigma2, double inv_beta,
                                                double pref, double L, double Lq, const double* T)
 {
-    const double nu1 = fabs(nu - 1.0);
-    const Solved s1 = plain_plan(nu1, z, L, Lq, rule_tab(), T);
-    const double hs1 = s1.p.h * sum_f64<true>(nu1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    const double nu1 = fabs(nu - 1.0), zs = sum_z(z);
+    const Solved s1 = plain_plan(nu1, zs, L, Lq, rule_tab(), T);
+    const double hs1 = s1.p.h * sum_f64<true>(nu1, zs, s1.p, s1.E, s1.Ei, s1.Sr, T);
     return sigma2 * inv_beta * exp(pref + (nu + 1.0) * lz + (s1.delta - z)) * fma(hs1, s1.dlo, hs1);
 }
 

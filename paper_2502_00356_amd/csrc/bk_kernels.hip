@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
                 double hs;
                 if (N == kEntryExact) {           // any x: the left side by products
                     s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
-                    hs = s.p.h * sum_f64<true>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
+                    hs = s.p.h * sum_f64<true, true>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
                 } else {                          // x >= 0.1, or nu far above 1 (temme_applies)
                     s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
                     hs = s.p.h * sum_f64<false>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
@@ -450,12 +450,12 @@ __device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, doubl
     const double* T = R.tab;
     DerivOut o;
     const Solved s0 = plain_plan(v, z, L, Lq, R, T);
-    double hs0 = s0.p.h * sum_f64<true>(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
+    double hs0 = s0.p.h * sum_f64<true, true>(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
     hs0 = fma(hs0, s0.dlo, hs0);
     o.k = assemble(z, s0.delta, hs0, result, T);
     const double v1 = fabs(v - 1.0);
     const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
-    double hs1 = s1.p.h * sum_f64<true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+    double hs1 = s1.p.h * sum_f64<true, true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
     hs1 = fma(hs1, s1.dlo, hs1);
     // by assemble where K is in range: e^Delta need not be (nu = 1,000 at x = 500)
     if (result == BK_RESULT_K && fabs(s0.delta - z) < 700.0) o.dx = -fma(v / z, o.k, assemble(z, s1.delta, hs1, result, T));

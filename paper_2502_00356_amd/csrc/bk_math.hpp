@@ -739,7 +739,9 @@ struct CoshPair {
     }
 };
 
-template <bool kProduct>
+// kAny: for windows of any pair. Past x = 1e306 the grid's own roundings reach exponents that
+// exp_node does not take.
+template <bool kProduct, bool kAny = false>
 __device__ inline double sum_f64(double nu, double x, const Plan& p, double E, double Ei, double Sr, const double* T)
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
@@ -754,12 +756,12 @@ __device__ inline double sum_f64(double nu, double x, const Plan& p, double E, d
         PR *= rho;
         PL *= rhoi;
         if (j <= nr) {
-            const double e = exp_node(fma(jd, nh, -W.R.X), T);
+            const double d = fma(jd, nh, -W.R.X), e = kAny ? exp_tab(d, T) : exp_node(d, T);
             tr = fma(e, PR, e);
             S += tr;
         }
         if (j <= nl) {
-            const double e = exp_node(fma(-jd, nh, -W.L.X), T);
+            const double d = fma(-jd, nh, -W.L.X), e = kAny ? exp_tab(d, T) : exp_node(d, T);
             tl = fma(e, PL, e);
             S += tl;
         }

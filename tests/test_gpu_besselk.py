@@ -145,6 +145,27 @@ def test_plain_small_thresholds(api, orc, L, Lq):
             assert abs(s - g) <= 1e-11 + 4e-16 * abs(s), (v, z)
 
 
+def test_plain_ends_of_the_double_range(api):
+    """K = 0 for the largest x (past 1e306 the window's step squared is below the double
+    range), with log K at most -x: no NaN."""
+    import torch
+    x = np.concatenate([np.linspace(2.0, 17.0, 40) * 1e306, 10.0 ** np.arange(290, 307)])
+    for nu in (0.0, 1e-9, 0.5, 40.0, 6.3e6, 1.5e14):
+        v = np.full(x.shape, nu)
+        k = api.besselk(to_dev(v), to_dev(x))
+        lk = api.besselk(to_dev(v), to_dev(x), result=api.RESULT_LOG)
+        d = api.besselk_deriv(to_dev(v), to_dev(x))
+        torch.cuda.synchronize()
+        assert np.all(k.cpu().numpy() == 0) and np.all(lk.cpu().numpy() <= -x), nu
+        assert all(np.all(d[key].cpu().numpy() == 0) for key in ("k", "dx")), nu
+    r = np.concatenate([[0.0], x[:8] * 1e-153])         # Matern distances at beta = 1e-153
+    g = api.matern_grad_tiles(to_dev(r), to_dev(0 * r), 2.0, 1e-153, 0.8, r.size, 0)
+    torch.cuda.synchronize()
+    for key, v in g.items():
+        v = v.cpu().numpy().reshape(r.size, r.size)
+        assert np.all(v[~np.eye(r.size, dtype=bool)] == 0) and np.all(np.diag(v) == (2.0 if key == "c" else 0.0)), key
+
+
 def test_special_values(api):
     nu = np.array([1.0, 1.0, 1.0, np.nan, 2.0, -2.5, np.inf, 3.0])
     x = np.array([0.0, -1.0, np.nan, 1.0, np.inf, 2.0, 1.0, 1e-4])

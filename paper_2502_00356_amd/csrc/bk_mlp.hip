@@ -2103,7 +2103,8 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
     if (!workspace || workspace_bytes < need) return BK_ENOMEM;
     // FP32 output by interpolation (bk_table.hpp). A call with statistics first runs the
     // per-entry form, which counts, and is then written like any other.
-    if (prm->out_dtype == BK_OUT_F32 && table_route(locs, prm, tile_size, lower_only, kTabMinLearned)) {
+    const int64_t least = tile_size < kTabNarrow && tile_size < locs->n ? kTabMinLearnedNarrow : kTabMinLearned;
+    if (prm->out_dtype == BK_OUT_F32 && table_route(locs, prm, tile_size, lower_only, least)) {
         if (prm->stats) {
             const int st = matern_learned_entries(locs, prm, tile_size, lower_only, out, L, Lq, workspace, need, stream);
             if (st != BK_OK) return st;

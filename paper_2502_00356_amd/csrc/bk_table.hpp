@@ -211,9 +211,13 @@ __device__ __forceinline__ void tab_clear(char* table)
 // Entries from which a call takes a table (FP64: plain form and gradient; FP32: mixed).
 // Per-entry form against table, us: plain 130,000 entries 16.9 / 20.2, 262,000 21.3 / 19.8;
 // gradient 44 / 48 and 57 / 48; mixed 65,500 16.4 / 16.9, 130,000 20.8 / 17.6. The learned
-// form's own launches take longer at any size (10,000 entries 47 / 22): from the least
-// output that holds its table on.
-constexpr int64_t kTabMinF64 = 200000, kTabMinF32 = 70000, kTabMinLearned = 10000;
+// form's own launches take longer at any size (10,000 entries 47 / 22): from a little above
+// the least output that holds its table on (8,610 entries). In tiles below 24 rows the items
+// of the table's bytes are many and short, which small outputs mostly consist of (40,000
+// entries in 4-tiles 29 / 50, 114,000 in 16-tiles 40 / 41, in 24-tiles 45 / 32; 220,900 in
+// 1-tiles 200 / 226, 500,500 724 / 518): from 500,000 there.
+constexpr int64_t kTabMinF64 = 200000, kTabMinF32 = 70000, kTabMinLearned = 10000, kTabMinLearnedNarrow = 500000;
+constexpr int kTabNarrow = 24;
 
 // Whether a call takes the tables, and where in an output of elems elements of
 // elem_bytes its table is built: its last bytes, which the evaluation writes last.

@@ -91,6 +91,34 @@ def test_table_matches_entries(api, model, mode, odt, n, ts, lower):
     assert torch.equal(counted, out) and int(stats[api.STAT_ENTRIES]) > 0
 
 
+@pytest.mark.parametrize("n,ts,lower", [(1001, 1, 1), (480, 1, 0), (1003, 2, 1), (1003, 7, 0), (1003, 23, 1), (520, 24, 0)])
+@pytest.mark.parametrize("mode,odt", FORMS)
+def test_narrow_tiles(api, model, mode, odt, n, ts, lower):
+    """Tiles of few rows, where the table's bytes hold thousands of them in many columns: the
+    values, and a time within twice the per-entry form's (and 30 us of launches)."""
+    import torch
+    beta, nu, s2 = 0.07, 1.9, 1.3
+    _, lx, ly = _points(n, beta)
+    L, Lq = (36.0, 35.0) if mode == "plain" else (15.0, 14.5)
+    kw = dict(mode=mode, out_dtype=api.OUT_F32 if odt == "f32" else api.OUT_F64, model=model)
+    elems = api.matern_out_elems(n, ts, lower)
+    bufs = [_guarded(elems, torch.float32 if odt == "f32" else torch.float64) for _ in range(2)]
+    us = []
+    for (_, out), th in zip(bufs, (dict(L_window=L, L_quad=Lq), {})):
+        best = 1e9
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            api.matern_tiles(lx, ly, s2, beta, nu, ts, lower, out=out, **th, **kw)
+            b.record()
+            b.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        us.append(best)
+    assert all(_untouched(buf, elems) for buf, _ in bufs)
+    assert _close(bufs[1][1], bufs[0][1], 2 * (TOL_PLAIN if mode == "plain" else TOL_MIXED), odt == "f32")
+    assert us[1] <= 2 * us[0] + 30, us
+
+
 @pytest.mark.parametrize("nu,beta", [(0.02, 0.1), (0.5, 0.01), (3.0, 0.3), (9.5, 0.05), (15.5, 0.1)])
 @pytest.mark.parametrize("mode,odt", FORMS)
 def test_table_orders_and_ranges(api, model, mode, odt, nu, beta):

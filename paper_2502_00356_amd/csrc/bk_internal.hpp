@@ -145,6 +145,8 @@ __device__ __forceinline__ double matern_dnu(double nu, double z, double lz, dou
     return vc * (lz - kLn2 - psi) + sigma2 * exp(pref + nu * lz + (delta - z)) * hs;
 }
 
+// psi(v), v > 0, on the host.
+double digamma_host(double v);
 int bk_besselk_learned(const double* nu, const double* x, double* out, int64_t n, const bk_params* prm,
                        double L, double Lq, hipStream_t stream);
 // Workspace bytes of the learned Matern form for one call (window table, interval

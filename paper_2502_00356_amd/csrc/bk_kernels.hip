@@ -906,7 +906,7 @@ extern "C" int bk_matern_tiles(const bk_locs* locs, const bk_params* prm, int32_
 // ln v - 1/(2v) - 1/(12 v^2) + 1/(120 v^4) - 1/(252 v^6) + 1/(240 v^8) - 1/(132 v^10)
 // + 691/(32760 v^12) (Abramowitz & Stegun 6.3.18); the first omitted term,
 // 1/(12 v^14), is below 3e-17 of psi(12).
-static double digamma_host(double v)
+double bk::digamma_host(double v)
 {
     long double t = v, acc = 0.0L;
     for (; t < 12.0L; t += 1.0L) acc -= 1.0L / t;

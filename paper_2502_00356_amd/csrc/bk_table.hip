@@ -82,6 +82,50 @@ __device__ __forceinline__ double tab_far(double z, const TabParams& P)
     return w * e * s * e;
 }
 
+// Entries below the table (z < kZMin): ranges far above the domain put all of them there.
+// 5,000 sites, lower tiles, z near 5e-5, by the per-entry kernels, the quadrature out of line
+// and these forms, us: plain 1,676, 1,747, 407; mixed 766, 997, 392; C, dC/dbeta and dC/dnu
+// 6,757, 7,085, 1,005. Above 1e-14 neither K_nu nor z^nu leaves the double range (nu <= 16).
+constexpr double kTabNear = 1e-14, kTabNearEnd = 0x1p-10;
+
+// dC/dnu there. With y = z^2 / 4, e = nu - 1 and H = Gamma(2 - nu) / Gamma(1 + nu),
+//   C / sigma2 = 1 + y (e^w - 1) / e + y^2 e^w / (e (1 + nu)) + O(y^2),  w = e a, a = ln y + ln H / e
+// (the two power series of K_nu; the pole at nu = 1 is in neither part). The second part
+// matters below nu = 0.95 only, e^w below 1.9. q0 = ln H / e and q1 its derivative: the result
+// is within 1e-15 sigma2 (the quadrature cancels terms of size sigma2 |ln z|).
+struct TabNear {
+    double inv_beta, sigma2, nu, q0, q1;
+};
+
+__device__ __noinline__ double tab_near_dnu(double q, TabNear N)
+{
+    const double y = 0.25 * (q * N.inv_beta) * N.inv_beta, e = N.nu - 1.0;
+    if (N.nu >= 1.9) return N.sigma2 * (y / (e * e));
+    const double a = log(y) + N.q0, w = e * a, w1 = fma(e, N.q1, a), ew = exp(w);
+    // (e^w - 1) / w and its derivative
+    double f, fd;
+    if (fabs(w) < 0.02) {
+        f = fma(fma(fma(fma(fma(w, 1.0 / 720.0, 1.0 / 120.0), w, 1.0 / 24.0), w, 1.0 / 6.0), w, 0.5), w, 1.0);
+        fd = fma(fma(fma(fma(w, 1.0 / 144.0, 1.0 / 30.0), w, 0.125), w, 1.0 / 3.0), w, 0.5);
+    } else {
+        f = expm1(w) / w;
+        fd = (ew - f) / w;
+    }
+    double d = y * fma(N.q1, f, a * fd * w1);
+    if (N.nu < 0.95) d += y * y * ew / (e * (1.0 + N.nu)) * (w1 - 1.0 / e - 1.0 / (1.0 + N.nu));
+    return N.sigma2 * d;
+}
+
+// C and dC/dbeta there, by Temme's series.
+
+template <int FN>
+__device__ __forceinline__ double tab_near(double z, const TabParams& P, const double* T)
+{
+    const double nu = FN == TAB_DBETA ? fabs(P.nu - 1.0) : P.nu;
+    const double w = pow(z, P.nu) * temme_k(nu, z, temme_tab(), T);
+    return P.scale * (FN == TAB_DBETA ? w * z * P.inv_beta : w);
+}
+
 // An entry whose distance is outside the table: z below kZMin or past 128, NaN or
 // infinite coordinates. Out of line, so that its registers stay out of the tile loop.
 template <int FN, int MODE>
@@ -96,6 +140,8 @@ __device__ __noinline__ double tab_cold(double q, TabParams P)
     if constexpr (MODE == BK_PLAIN_F64) { L = kDefaultLPlain; Lq = kDefaultLqPlain; }
     else { L = kDefaultLMixed; Lq = kDefaultLqMixed; }
     const double* T = rule_tab().tab;
+    if constexpr (FN != TAB_DNU)
+        if (z >= kTabNear && z < kTabNearEnd) return tab_near<FN>(z, P, T);
     if constexpr (FN == TAB_DBETA) {
         return matern_dbeta(P.nu, z, lz, P.sigma2, P.inv_beta, P.pref, L, Lq, T);
     } else {
@@ -131,6 +177,8 @@ struct TabArgs {
     int64_t first, count;
     TabIndex X;
     TabParams P;
+    TabNear N;                     // dC/dnu: of entries with near <= r^2 < near_end
+    double near, near_end;
 };
 
 // The slot of squared distance q. The conversion takes anything below the first
@@ -233,7 +281,10 @@ __device__ __forceinline__ void tab_item(const TabArgs& A, const tab2_t* sT, con
             if (cold) {
 #pragma unroll
                 for (int k = 0; k < R; ++k)
-                    if (isnan(val.v[k])) val.v[k] = (OutT)tab_cold<FN, MODE>(q[k], A.P);
+                    if (isnan(val.v[k]))
+                        val.v[k] = (OutT)(FN == TAB_DNU && q[k] >= A.near && q[k] < A.near_end
+                                              ? tab_near_dnu(q[k], A.N)
+                                              : tab_cold<FN, MODE>(q[k], A.P));
             }
         }
         if (__builtin_expect(whole, 1)) {
@@ -455,6 +506,23 @@ TabIndex tab_index(double beta, const TabParams& P, bool f32_table)
     return X;
 }
 
+static TabNear tab_near_params(const TabParams& P)
+{
+    TabNear N = {P.inv_beta, P.sigma2, P.nu, 0.0, 0.0};
+    const long double e = (long double)P.nu - 1.0L;
+    if (P.nu >= 1.9) return N;
+    if (fabsl(e) < 1e-4L) {            // ln H = (2 gamma - 1) e + e^2 / 2 + (2 zeta(3) - 1) / 3 e^3 + ...
+        const long double h3 = 0.46803793543952952L;
+        N.q0 = (double)(0.15443132980306573L + e * (0.5L + h3 * e));
+        N.q1 = (double)(0.5L + 2.0L * h3 * e);
+    } else {
+        const long double h = logl(tgammal(1.0L - e) / tgammal(2.0L + e));
+        N.q0 = (double)(h / e);
+        N.q1 = (double)((-(digamma_host((double)(1.0L - e)) + digamma_host((double)(2.0L + e))) * e - h) / (e * e));
+    }
+    return N;
+}
+
 int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X, int32_t tile_size, int32_t lower_only, int fn,
                       int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream)
 {
@@ -468,6 +536,11 @@ int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X
     A.g.T = (int32_t)((n + A.g.ts - 1) / A.g.ts);
     A.g.lower = lower_only ? 1 : 0;
     A.X = X;
+    if (fn == TAB_DNU) {
+        A.N = tab_near_params(P);
+        A.near = kTabNear / P.inv_beta * (kTabNear / P.inv_beta);
+        A.near_end = kTabNearEnd / P.inv_beta * (kTabNearEnd / P.inv_beta);
+    }
     const bool f32 = out_dtype == BK_OUT_F32;
     if (f32_table) return eval_launch<float, true, TAB_C, BK_MIXED_F32C>(locs, A, table, out, stream);
     switch (fn) {

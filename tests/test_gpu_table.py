@@ -119,6 +119,48 @@ def test_narrow_tiles(api, model, mode, odt, n, ts, lower):
     assert us[1] <= 2 * us[0] + 30, us
 
 
+@pytest.mark.parametrize("nu,beta", [(0.011, 3e3), (0.3, 300.0), (1.0, 1e4), (2.3, 1e4), (7.7, 1e6), (15.9, 5e7)])
+def test_long_ranges(api, orc, nu, beta):
+    """Ranges far above the domain, where most entries lie below the table: against the oracle
+    (z from 1e-11 on, where its K is in range), and no slower than the per-entry kernels."""
+    import torch
+    from paper_2502_00356_amd import workloads as w
+    n, s2 = 1500, 0.7
+    xy = w.uniform_locations(n, seed=77)
+    lx, ly = to_dev(xy[:, 0]), to_dev(xy[:, 1])
+    rng = np.random.default_rng(5)
+    i, j = rng.integers(0, n, 2000), rng.integers(0, n, 2000)
+    i, j = i[i != j], j[i != j]
+    c, db, dn = orc.matern_grad_entries(xy, xy, i, j, s2, beta, nu)
+    z = np.sqrt(((xy[i] - xy[j]) ** 2).sum(-1)) / beta
+    at = to_dev(j * n + i)
+
+    def run(**th):
+        L = {} if not th else dict(L_window=15.0, L_quad=14.5)
+        return (api.matern_grad_tiles(lx, ly, s2, beta, nu, n, 0, **th),
+                api.matern_tiles(lx, ly, s2, beta, nu, n, 0, mode="mixed", out_dtype=api.OUT_F32, **L))
+
+    us = []
+    for th in (dict(L_window=36.0, L_quad=35.0), {}):
+        best = 1e9
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            g, m = run(**th)
+            b.record()
+            b.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        us.append(best)
+    got = {k: v[at].cpu().numpy() for k, v in g.items()}
+    # z^nu and K_nu(z) to 1e-13 each at nu |ln z| up to 400 (2^-53 of it: 5e-14)
+    tol = TOL_PLAIN + 2.0 ** -52 * nu * np.abs(np.log(z))
+    assert np.all(np.abs(got["c"] - c) <= tol * c) and np.all(np.abs(got["dbeta"] - db) <= tol * db + 1e-300)
+    t1 = c * (np.log(z) - math.log(2.0) - orc.digamma(np.array([nu]))[0])
+    assert np.all(np.abs(got["dnu"] - dn) <= tol * (np.abs(t1) + np.abs(dn - t1)))
+    assert np.all(np.abs(m[at].cpu().numpy() - c) <= (TOL_MIXED + 2.0 ** -23) * c)
+    assert us[1] <= us[0], us
+
+
 @pytest.mark.parametrize("nu,beta", [(0.02, 0.1), (0.5, 0.01), (3.0, 0.3), (9.5, 0.05), (15.5, 0.1)])
 @pytest.mark.parametrize("mode,odt", FORMS)
 def test_table_orders_and_ranges(api, model, mode, odt, nu, beta):

@@ -67,6 +67,21 @@ def test_loglik_singular(api, n, k):
         assert np.isfinite(l)
 
 
+@pytest.mark.parametrize("n,i,k", [(2, 0, 1), (17, 3, 16), (129, 127, 128), (200, 150, 160), (200, 5, 160), (700, 0, 699)])
+def test_loglik_zero_pivot(api, n, i, k):
+    """Sites so far apart that Sigma is exactly the identity, and two of them the same: the
+    pivot is 1 - 1 * 1 = 0, in the first diagonal block, in a later one and through panels."""
+    x = np.arange(n, dtype=np.float64)
+    z = np.ones(n)
+    l = api.matern_loglik(to_dev(x), to_dev(0 * x), to_dev(z), 1.0, 1e-3, 0.5)
+    assert abs(l + 0.5 * n * (1 + math.log(2 * math.pi))) <= 1e-12 * n
+    x[k] = x[i]
+    for grad in (False, True):
+        with pytest.raises(api.BkError) as e:
+            api.matern_loglik(to_dev(x), to_dev(0 * x), to_dev(z), 1.0, 1e-3, 0.5, grad=grad)
+        assert e.value.status == 6        # BK_ENOTPD
+
+
 @pytest.mark.parametrize("s2", [5e-310, 1e-290, 1e-170, 1e-160, 1e-156, 1e-62, 1e-60, 1e60, 1e62, 1e154, 1e160, 1e300, 1.5e308])
 def test_loglik_scale(api, s2):
     """Any positive sigma2: with z = sqrt(sigma2) z1 the likelihood is that of sigma2 = 1 less

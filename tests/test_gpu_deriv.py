@@ -218,3 +218,15 @@ def test_deriv_window_rule(api, orc, L):
     assert rel_err(out["k"].cpu().numpy(), ks).max() <= tol
     assert rel_err(out["dx"].cpu().numpy(), d["scaled_dx"]).max() <= tol
     assert rel_err(out["dnu"].cpu().numpy()[pos], d["scaled_dnu"][pos]).max() <= tol
+
+
+def test_deriv_small_calls(api, orc):
+    """Every size around the edges of a 64-entry workgroup: the oracle's values, and the same
+    bits whatever an entry's lane and its neighbours."""
+    nu, x = (a[::29][:193] for a in _pairs(91))
+    _check(api, orc, nu, x)
+    full = _deriv(api, nu, x)
+    for n in (1, 2, 63, 64, 65, 127, 128, 129, 192):
+        part = _deriv(api, nu[:n][::-1].copy(), x[:n][::-1].copy())
+        for key in ("k", "dx", "dnu"):
+            assert np.array_equal(part[key], full[key][:n][::-1]), (n, key)

@@ -710,6 +710,9 @@ __device__ void block_stats_w(unsigned long long* stats, const unsigned long lon
 constexpr int kLearnedBlock = 256;
 constexpr int kSortBins = 64;
 
+// A queued entry's place in the results: a NaN that no operation returns.
+constexpr long long kQueued = 0x7ff8000051554544LL;
+
 // kStats: the statistics variant (its counters cost registers and moves in every entry).
 template <bool kPlan, bool kStats>
 __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, const double* __restrict__ nu,
@@ -726,12 +729,10 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
     __shared__ double s_v[kLearnedBlock], s_z[kLearnedBlock];
     __shared__ win_t s_tlo[kLearnedBlock], s_thi[kLearnedBlock];
     __shared__ double s_out[kLearnedBlock];      // in entry order
-    __shared__ unsigned int s_queued[kLearnedBlock / 32];
     __shared__ int s_N[kLearnedBlock];
     static_assert(kLearnedBlock <= 256 && kCells <= 1 << 24, "entry word");
     __shared__ unsigned int s_e[kLearnedBlock];  // entry | cell << 8
     const int tid = threadIdx.x;
-    if (tid < kLearnedBlock / 32) s_queued[tid] = 0u;     // set after the sort's barriers
     const int64_t i = (int64_t)blockIdx.x * kLearnedBlock + tid;
     int cell = 0;
     const bool live = i < n;
@@ -835,12 +836,13 @@ __global__ __launch_bounds__(kLearnedBlock, 5) void k_besselk_learned(MlpDev M, 
             if (lo.reason == BK_STAT_FB_TAIL) c_tail += 1; else c_nonfin += 1;
             const unsigned int slot = atomicAdd(qcount, 1u);
             queue[slot] = (unsigned int)blockIdx.x * kLearnedBlock + own;
-            atomicOr(&s_queued[own >> 5], 1u << (own & 31u));
+            s_out[own] = __longlong_as_double(kQueued);
         }
     }
     __syncthreads();
     // not the queued entries: the fallback reads their inputs, which out may share
-    if (N >= 0 && !(s_queued[tid >> 5] >> (tid & 31) & 1u)) out[i] = s_out[tid];
+    const double r = s_out[tid];
+    if (N >= 0 && __double_as_longlong(r) != kQueued) out[i] = r;
     if constexpr (kStats) {
         unsigned long long cnt[8];
         cnt[BK_STAT_ENTRIES] = c_ent;

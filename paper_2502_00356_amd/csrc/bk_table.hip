@@ -170,10 +170,15 @@ constexpr int kTailCols = 2;
 // sites (FP64) 22.4, 22.4 and 24.3, 22.0.
 constexpr unsigned kTailGroups = 16;
 
+struct TailStart {
+    int32_t I, J, col;
+};
+
 struct TabArgs {
     TileGeom g;                    // rb_per_tile: row blocks of 64 R; cb_per_tile: column blocks of `cols`
     int cols;
-    unsigned items, first_tile, count_tile;
+    unsigned items;
+    TailStart first_at, count_at;  // tile and column that hold elements first and count
     int64_t first, count;
     TabIndex X;
     TabParams P;
@@ -325,7 +330,8 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
     const unsigned rbn = (unsigned)g.rb_per_tile;
     unsigned it = blockIdx.x * kWaves + wave, stride = grid * kWaves, base = 0u;
     const unsigned per_tile = rbn * (unsigned)g.cb_per_tile;
-    int64_t lo = 0, hi = A.first, I = 0, J = 0, wI = 0, wJ = 0;
+    int64_t lo = 0, hi = A.first, I = 0, J = 0;
+    TailStart w = {};
     // part by part; one copy of the item's code
     for (int part = 0;; ++part) {
         for (;; it += stride) {
@@ -338,32 +344,31 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
                 rb = local - cb * rbn;
                 jl0 = (int64_t)cb * A.cols;
             } else {
-                // the tile of item `it`, from tile (wI, wJ) on, whose first item is `base`: the
-                // tiles of a column have equally many items (all but the part's first), so
-                // the walk is over columns (tile by tile it took 0.4 us a tile: 470 sites in
-                // 4-tiles 266 us)
-                int64_t j0 = 0;
-                while (wJ < g.T) {
-                    const int64_t off = tile_offset(g.n, g.ts, g.T, g.lower, wI, wJ);
-                    const int64_t mI = min((int64_t)g.ts, g.n - wI * g.ts), nJ = min((int64_t)g.ts, g.n - wJ * g.ts);
-                    j0 = lo > off ? (lo - off) / mI : 0;
-                    const unsigned ntile = (unsigned)((nJ - j0 + kTailCols - 1) / kTailCols) * rbn;
-                    const unsigned alike = j0 > 0 ? 1u : (unsigned)(g.T - wI), k = (it - base) / ntile;
-                    if (k < alike) {
-                        wI += k;
-                        base += k * ntile;
-                        break;
+                // the tile of item `it`, from column w.col of tile (w.I, w.J) on, whose first item
+                // is `base`. The tiles of a column have equally many items (all but the part's
+                // first), so the walk is over columns (tile by tile it took 0.4 us a tile: 470
+                // sites in 4-tiles 266 us)
+                unsigned rel;
+                while (w.J < g.T) {
+                    const int nJ = (int)min((int64_t)g.ts, g.n - (int64_t)w.J * g.ts);
+                    const unsigned ntile = (unsigned)((nJ - w.col + kTailCols - 1) / kTailCols) * rbn;
+                    rel = it - base;
+                    if (rel < ntile) break;
+                    const unsigned k = w.col > 0 ? 1u : min(rel / ntile, (unsigned)(g.T - w.I));
+                    base += k * ntile;
+                    w.col = 0;
+                    w.I += (int)k;
+                    if (w.I == g.T) {
+                        ++w.J;
+                        w.I = g.lower ? w.J : 0;
                     }
-                    base += alike * ntile;
-                    wI += alike;
-                    if (wI == g.T) wI = g.lower ? ++wJ : (++wJ, 0);
                 }
-                if (wJ == g.T) break;
-                I = wI;
-                J = wJ;
-                const unsigned cb = (it - base) / rbn;
-                rb = it - base - cb * rbn;
-                jl0 = j0 + (int64_t)cb * kTailCols;
+                if (w.J == g.T) break;
+                I = w.I;
+                J = w.J;
+                const unsigned cb = rel / rbn;
+                rb = rel - cb * rbn;
+                jl0 = w.col + (int64_t)cb * kTailCols;
             }
             tab_item<OutT, kF32, FN, MODE, R>(A, sT, lx, ly, out, I, J, (int64_t)rb * (64 * R), jl0,
                                               part == 0 ? A.cols : kTailCols, lo, hi);
@@ -386,7 +391,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
                 if (!skipped) {
                     it = share * kWaves + wave;
                     stride = min(grid, kTailGroups) * kWaves;
-                    tile_of(A.first_tile, g, wI, wJ);
+                    w = A.first_at;
                     lo = A.first;
                     hi = A.count;
                     continue;
@@ -406,7 +411,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
         it = wave;
         stride = kWaves;
         base = 0u;
-        tile_of(left ? A.first_tile : A.count_tile, g, wI, wJ);
+        w = left ? A.first_at : A.count_at;
         lo = left ? A.first : A.count;
         hi = INT64_MAX;
     }
@@ -437,8 +442,8 @@ bool table_route(const bk_locs* locs, const bk_params* prm, int32_t tile_size, i
     return bk_matern_out_elems(n, tile_size, lower_only) >= min_entries;
 }
 
-// The packed tile that holds element e.
-static unsigned tile_at(const TileGeom& g, int64_t e)
+// The packed tile that holds element e, and e's column in it.
+static TailStart tail_start(const TileGeom& g, int64_t e)
 {
     const int64_t T = g.T, ts = g.ts;
     int64_t lo = 0, hi = T - 1;                       // last column of tiles that starts at or before e
@@ -449,7 +454,8 @@ static unsigned tile_at(const TileGeom& g, int64_t e)
     }
     const int64_t J = lo, I0 = g.lower ? J : 0, nJ = J == T - 1 ? g.n - J * ts : ts;
     const int64_t k = (e - tile_offset(g.n, ts, T, g.lower, I0, J)) / (nJ * ts), I = I0 + k < T ? I0 + k : T - 1;
-    return (unsigned)(g.lower ? J * T - J * (J - 1) / 2 + (I - J) : J * T + I);
+    const int64_t mI = I == T - 1 ? g.n - I * ts : ts;
+    return {(int32_t)I, (int32_t)J, (int32_t)((e - tile_offset(g.n, ts, T, g.lower, I, J)) / mI)};
 }
 
 template <typename OutT, bool kF32, int FN, int MODE, int R>
@@ -464,8 +470,8 @@ static int eval_rows(const bk_locs* locs, TabArgs& A, char* table, OutT* out, hi
         if (A.cols == 2 || A.items >= kTabWaves * kTabGrid) break;
     }
     A.count = ((char*)tab_counts<kF32>(table) - (char*)out) / (int64_t)sizeof(OutT);
-    A.first_tile = tile_at(A.g, A.first);
-    A.count_tile = tile_at(A.g, A.count);
+    A.first_at = tail_start(A.g, A.first);
+    A.count_at = tail_start(A.g, A.count);
     const unsigned need = (A.items + kTabWaves - 1) / kTabWaves;
     return launch(k_matern_tab<OutT, kF32, FN, MODE, R>, dim3(need < kTabGrid ? need : kTabGrid), dim3(kTabThreads),
                   stream, locs->x, locs->y, A, table, out);

@@ -558,7 +558,9 @@ constexpr int kRowsPerWave = 64;
 // Columns a wave takes in turn: one in calls that then still leave the chip unfilled (every
 // column a wave is one more entry in its serial chain), kMaxCols in larger ones, whose
 // blocks stage the tables less often. Plain FP64, nu = 17: 600 sites 57 us with eight,
-// 28 with one; 2,000 166 and 156; 2,800 319 and 318; 6,000 1,251 and 1,283.
+// 28 with one; 2,000 166 and 156; 2,800 319 and 318; 6,000 1,251 and 1,283. A counting call
+// keeps eight: every workgroup adds to the same three counters (2,000 sites, plain, with
+// statistics 268 us with eight, 600 with one).
 constexpr int kMaxCols = 8;
 static int cols_per_wave(int64_t entries) { return entries < 8000000 ? 1 : kMaxCols; }
 
@@ -851,7 +853,7 @@ int matern_tiles_dispatch(const bk_locs* locs, const bk_params* prm, int32_t til
     g.T = (int32_t)((locs->n + g.ts - 1) / g.ts);
     g.lower = lower_only ? 1 : 0;
     g.rb_per_tile = (g.ts + kRowsPerWave - 1) / kRowsPerWave;
-    g.cols = cols_per_wave(bk_matern_out_elems(locs->n, tile_size, lower_only));
+    g.cols = prm->stats ? kMaxCols : cols_per_wave(bk_matern_out_elems(locs->n, tile_size, lower_only));
     g.cb_per_tile = (g.ts + 4 * g.cols - 1) / (4 * g.cols);
     const int64_t T = g.T;
     const int64_t ntiles = g.lower ? T * (T + 1) / 2 : T * T;

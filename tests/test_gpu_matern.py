@@ -144,3 +144,28 @@ def test_kernel_events_bracket_matern(api):
     torch.cuda.synchronize()
     assert torch.equal(got, ref)
     assert ev[0].elapsed_time(ev[1]) > 0.0
+
+
+def test_counting_call_time(api):
+    """A counting call of a few million entries takes at most two and a half times the same
+    call without statistics (both per entry, by given thresholds), and counts every entry."""
+    import torch
+    from paper_2502_00356_amd import workloads as w
+    n = 2000
+    xy = w.uniform_locations(n, seed=41)
+    lx, ly = to_dev(xy[:, 0]), to_dev(xy[:, 1])
+    out = torch.empty(n * n, dtype=torch.float64, device="cuda")
+    stats = torch.zeros(api.STATS_LEN, dtype=torch.int64, device="cuda")
+    us = []
+    for st in (None, stats):
+        best = 1e9
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            api.matern_tiles(lx, ly, 1.0, 0.1, 1.3, n, 0, out=out, L_window=36.0, L_quad=35.0, stats=st)
+            b.record()
+            b.synchronize()
+            best = min(best, 1e3 * a.elapsed_time(b))
+        us.append(best)
+    assert int(stats[api.STAT_ENTRIES]) == 6 * (n * n - n)
+    assert us[1] <= 2.5 * us[0], us

@@ -513,6 +513,11 @@ __device__ __forceinline__ float asinh_fast(float y)
     return 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
 }
 
+// Orders from which the ends' Newton steps start at quadratic bounds of the ends (from the
+// starts below they overshoot to several times the window's width: 45 nodes at nu = 1,000,
+// x = 500, where 27 do).
+constexpr float kLargeOrder = 60.0f;
+
 // Upper bound of the d > 0 where x (cosh(t + d) - cosh t) = slope d + L; E, Ei = e^t, e^-t.
 __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, float x, float slope, float L)
 {
@@ -523,7 +528,13 @@ __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, floa
         const float e = fmaf(l, ix, ec);
         return fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + e + __builtin_amdgcn_sqrtf(e * (e + 2.0f))) - t, 1e-3f);
     };
-    const float d = drop(fmaf(slope, drop(L), L));
+    float d = drop(fmaf(slope, drop(L), L));
+    if (slope > kLargeOrder) {
+        // F(d) >= C d^2 / 2 - r d - L, C = x cosh t, r = slope - x sinh t: right of its root
+        const float C = 0.5f * x * (E + Ei), r = fmaxf(slope - 0.5f * x * (E - Ei), 0.0f);
+        const float s = (r + __builtin_amdgcn_sqrtf(fmaf(r, r, 2.0f * C * L))) * __builtin_amdgcn_rcpf(C);
+        if (s <= 1.0f) d = s;
+    }
     const float a = exp_fast(0.5f * d), ai = __builtin_amdgcn_rcpf(a);
     const float b = E * a, bi = Ei * ai;                           // e^(t + d/2)
     const float F = 0.5f * x * (a - ai) * (b - bi) - slope * d - L;    // 2 sinh sinh = (a - 1/a)(b - 1/b) / 2
@@ -537,7 +548,12 @@ __device__ __forceinline__ float left_end_fast(float tp, float E, float Ei, floa
     const float L2 = L + 0.69314718f, hx = 0.5f * x;
     const float e0 = L2 + x * (0.5f * (E + Ei) - 1.0f);
     if (!(e0 < nu * tp)) return 0.0f;
-    const float e = e0 * __builtin_amdgcn_rcpf(nu);
+    float e = e0 * __builtin_amdgcn_rcpf(nu);
+    if (nu > kLargeOrder) {
+        // F(e) <= L2 - C (e^-e - 1 + e) with C = x cosh tp >= nu, below 0 at sqrt(3 L2 / C) <= 1
+        const float b = 3.0f * L2 * __builtin_amdgcn_rcpf(hx * (E + Ei));
+        if (b <= 1.0f) e = fminf(e, __builtin_amdgcn_sqrtf(b));
+    }
     const float a = exp_fast(0.5f * e), ai = __builtin_amdgcn_rcpf(a);
     const float b = E * ai, bi = Ei * a;                           // e^(tp - e/2)
     const float F = L2 - nu * e + hx * (a - ai) * (b - bi);
@@ -979,7 +995,7 @@ __device__ inline double sum_dnu_f64(double nu, const Plan& p, double A, double 
 //    nu a), at td with a = pi/2.
 // For plan_fast_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
 // Returns whether sum_deriv can walk it: e^(2 nu d) over the left side's length d has to be
-// finite (nu up to several hundred at L = 36); the exact solves take the rest.
+// finite, or e^(-2 nu t) below 2^-53 of 1 on all of it.
 __device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L, double Lq)
 {
     return plan_fast_ok(nu, x, L, Lq) && L >= 8.0;
@@ -998,7 +1014,7 @@ __device__ __forceinline__ bool deriv_window_count(double nu, double x, double L
     t0 = left_end_fast(tp, E, Ei, nf, xf, Lf);
     const float extra = 2.0f * 0.69314718f * __builtin_amdgcn_logf(fmaf(1.5707963f, itd, 1.0f));
     node_grid(t0, t1, tp, node_step_fast(nf + 1.0f, xf, (float)Lq + extra), N, mc);
-    return 2.0f * nf * (t1 - t0) * (float)mc < 700.0f * (float)N;
+    return 2.0f * nf * (t1 - t0) * (float)mc < 699.0f * (float)N || 2.0f * nf * t0 >= 40.0f;
 }
 
 // Trapezoid sums of the paired walk (sum_f64): of the K terms e^d (2 - Q), of those times
@@ -1015,7 +1031,8 @@ __device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double
     const double h = p.h, nh = nu * h;
     // 1 - e^(-2 nu h), and the exponential itself (1 less the former is 0 from nu h = 18 on)
     const double omr = -expm1(-2.0 * nh), rho = exp_tab(-2.0 * nh, T);
-    const double qe = omr * recip(rho), re = 1.0 + qe;                 // e^(2 nu h) - 1, e^(2 nu h)
+    // e^(2 nu h) - 1, e^(2 nu h); where its powers leave the double range Q is 1 on the left
+    const double qe = 2.0 * nh * nl < 700.0 ? omr * recip(rho) : 0.0, re = 1.0 + qe;
     const double Qr = -expm1(-2.0 * nu * p.tref), Pr = exp_tab(-2.0 * nu * p.tref, T);
     double QR = Qr, EL = 0.0, jd = 1.0;
     CoshPair<true> W(x, h, E, Ei, Sr);

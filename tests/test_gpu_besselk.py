@@ -145,6 +145,28 @@ def test_plain_small_thresholds(api, orc, L, Lq):
             assert abs(s - g) <= 1e-11 + 4e-16 * abs(s), (v, z)
 
 
+def test_plain_large_order_windows(api, orc):
+    """Orders up to 10,000: the FP32 window has about the nodes of the solved one (within a
+    tenth, and the two's own rounding up), and K is the oracle's (which converges up to
+    nu = 1,000)."""
+    import torch
+    rng = np.random.default_rng(31)
+    n = 3000
+    nu = 10 ** rng.uniform(1.7, 4.0, n)
+    x = nu * 10 ** rng.uniform(-0.3, 0.3, n)
+    stats = torch.zeros(api.STATS_LEN, dtype=torch.int64, device="cuda")
+    lk = api.besselk(to_dev(nu), to_dev(x), result=api.RESULT_LOG, stats=stats)
+    _, _, N = api.window(to_dev(nu), to_dev(x), L_window=36.0, L_quad=35.0)
+    torch.cuda.synchronize()
+    assert int(stats[api.STAT_ENTRIES]) == n
+    assert int(stats[api.STAT_NODES]) <= 1.1 * int(N.sum()) + 2 * n
+    lo = nu < 1000
+    _, ref, _ = orc.besselk(nu[lo], x[lo])
+    # log K = Delta - x + ...: three roundings of terms up to nu asinh(nu / x) + x
+    tol = TOL_PLAIN + 4 * 2.0 ** -53 * (nu * np.arcsinh(nu / x) + x)
+    assert np.all(np.abs(lk.cpu().numpy()[lo] - ref) <= tol[lo])
+
+
 def test_plain_ends_of_the_double_range(api):
     """K = 0 for the largest x (past 1e306 the window's step squared is below the double
     range), with log K at most -x: no NaN."""

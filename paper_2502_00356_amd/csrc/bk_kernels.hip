@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))
                 Solved s;
                 double hs;
                 if (N == kEntryExact) {           // any x: the left side by products
-                    s = plain_solve(vj, zj, L, Lq, rule_tab(), s_tab);
+                    s = plain_plan(vj, zj, L, Lq, rule_tab(), s_tab);
                     hs = s.p.h * sum_f64<true, true>(vj, zj, s.p, s.E, s.Ei, s.Sr, s_tab);
                 } else {                          // x >= 0.1, or nu far above 1 (temme_applies)
                     s = plan_setup(vj, zj, B.t0[j], B.t1[j], N, (ej >> 10) & 1023u);
@@ -438,31 +438,44 @@ __device__ __forceinline__ double unscale(double z, double s, int result)
 }
 
 // K, dK/dx and dK/dnu where the fast window does not apply: the K integral at orders nu and
-// |nu - 1| and the dK/dnu integral, each with its own exact solve. Out of line and rare.
+// |nu - 1| (for dK/dx) and the dK/dnu integral, each with its own exact solve. Out of line and
+// rare.
+// exp_tab's tables in LDS, for a kernel (which fills them) and its out-of-line function alike.
+__device__ __forceinline__ double* lds_tab()
+{
+    __shared__ double t[kTabLen];
+    return t;
+}
+
 struct DerivOut {
     double k, dx, dn;
     unsigned int nodes;
 };
 
-__device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, double Lq, int result)
+__device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, double Lq, int result, bool want_dx, bool want_dn)
 {
     const RuleTable& R = rule_tab();
-    const double* T = R.tab;
+    const double* T = lds_tab();
     DerivOut o;
     const Solved s0 = plain_plan(v, z, L, Lq, R, T);
     double hs0 = s0.p.h * sum_f64<true, true>(v, z, s0.p, s0.E, s0.Ei, s0.Sr, T);
     hs0 = fma(hs0, s0.dlo, hs0);
     o.k = assemble(z, s0.delta, hs0, result, T);
-    const double v1 = fabs(v - 1.0);
-    const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
-    double hs1 = s1.p.h * sum_f64<true, true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
-    hs1 = fma(hs1, s1.dlo, hs1);
-    // by assemble where K is in range: e^Delta need not be (nu = 1,000 at x = 500)
-    if (result == BK_RESULT_K && fabs(s0.delta - z) < 700.0) o.dx = -fma(v / z, o.k, assemble(z, s1.delta, hs1, result, T));
-    else o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
-    o.nodes = (unsigned int)(s0.p.N + s1.p.N + 2);
-    o.dn = 0.0;
-    if (v > 0.0) {
+    o.nodes = (unsigned int)(s0.p.N + 1);
+    o.dx = o.dn = 0.0;
+    if (want_dx) {
+        const double v1 = fabs(v - 1.0);
+        const Solved s1 = plain_plan(v1, z, L, Lq, R, T);
+        double hs1 = s1.p.h * sum_f64<true, true>(v1, z, s1.p, s1.E, s1.Ei, s1.Sr, T);
+        hs1 = fma(hs1, s1.dlo, hs1);
+        // by assemble where K is in range: e^Delta need not be (nu = 1,000 at x = 500)
+        if (result == BK_RESULT_K && fabs(s0.delta - z) < 700.0)
+            o.dx = -fma(v / z, o.k, assemble(z, s1.delta, hs1, result, T));
+        else
+            o.dx = -unscale(z, exp(s1.delta) * hs1 + (v / z) * (exp(s0.delta) * hs0), result);
+        o.nodes += (unsigned int)(s1.p.N + 1);
+    }
+    if (want_dn && v > 0.0) {
         const Solved sd = dnu_solve(v, z, s0.p.t0, L, Lq, R, T);
         o.dn = assemble(z, sd.delta, sd.p.h * sum_dnu_f64(v, sd.p, sd.A, sd.B, T), result, T);
         o.nodes += (unsigned int)(sd.p.N + 1);
@@ -480,7 +493,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ k, double* __restrict__ dkdx,
     double* __restrict__ dkdnu, int64_t n, int result, double L, double Lq, unsigned long long* __restrict__ stats)
 {
-    __shared__ double s_tab[kTabLen];
+    double* const s_tab = lds_tab();
     __shared__ DrawBlock<kThreads, kPer> B;
     const int tid = threadIdx.x;
     for (int j = tid; j < kTabLen; j += kThreads) s_tab[j] = rule_tab().tab[j];   // read after the barriers
@@ -529,7 +542,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
             const double nr = B.v[j], vj = fabs(nr), zj = B.z[j];
             double rk, rx, rn;
             if (N == kEntryExact) {
-                const DerivOut o = deriv_exact(vj, zj, L, Lq, result);
+                const DerivOut o = deriv_exact(vj, zj, L, Lq, result, dkdx != nullptr, dkdnu != nullptr);
                 rk = o.k;
                 rx = o.dx;
                 rn = o.dn;

@@ -507,13 +507,20 @@ __device__ __forceinline__ bool plan_fast_ok(double nu, double x, double L, doub
     return x >= 1e-12 && x <= 1e5 && nu <= 1e4 && L >= 1.0 && L <= 500.0 && Lq >= 1.0;
 }
 
+// Where the window itself still holds, for walks that take both sides by products: x up to 1e8,
+// orders up to 1e6 (FP32's roundings of t and of e^t then take up to 0.13 off L).
+__host__ __device__ __forceinline__ bool plan_wide_ok(double nu, double x, double L, double Lq)
+{
+    return x >= 1e-12 && x <= 1e8 && nu <= 1e6 && L >= 1.0 && L <= 500.0 && Lq >= 1.0;
+}
+
 __device__ __forceinline__ float exp_fast(float y) { return __builtin_amdgcn_exp2f(y * 1.44269504f); }
 __device__ __forceinline__ float asinh_fast(float y)
 {
     return 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
 }
 
-// Orders from which the ends' Newton steps start at quadratic bounds of the ends (from the
+// Orders (and x above 1e5) from which the ends' Newton steps start at quadratic bounds of the ends (from the
 // starts below they overshoot to several times the window's width: 45 nodes at nu = 1,000,
 // x = 500, where 27 do).
 constexpr float kLargeOrder = 60.0f;
@@ -529,7 +536,7 @@ __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, floa
         return fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + e + __builtin_amdgcn_sqrtf(e * (e + 2.0f))) - t, 1e-3f);
     };
     float d = drop(fmaf(slope, drop(L), L));
-    if (slope > kLargeOrder) {
+    if (slope > kLargeOrder || x > 1e5f) {
         // F(d) >= C d^2 / 2 - r d - L, C = x cosh t, r = slope - x sinh t: right of its root
         const float C = 0.5f * x * (E + Ei), r = fmaxf(slope - 0.5f * x * (E - Ei), 0.0f);
         const float s = (r + __builtin_amdgcn_sqrtf(fmaf(r, r, 2.0f * C * L))) * __builtin_amdgcn_rcpf(C);
@@ -638,10 +645,11 @@ __device__ __forceinline__ Solved plan_setup(double nu, double x, float t0, floa
     return s;
 }
 
-// Plan of the plain sum: the fast window where it applies, else the exact solve.
+// Plan of the plain sum (both sides by products): the fast window where it applies, else the
+// exact solve.
 __device__ inline Solved plain_plan(double nu, double x, double L, double Lq, const RuleTable& R, const double* T)
 {
-    if (!plan_fast_ok(nu, x, L, Lq)) return plain_solve(nu, x, L, Lq, R, T);
+    if (!plan_wide_ok(nu, x, L, Lq)) return plain_solve(nu, x, L, Lq, R, T);
     float t0, t1;
     unsigned int N, mc;
     window_count(nu, x, L, Lq, t0, t1, N, mc);
@@ -762,7 +770,9 @@ __device__ inline double sum_f64(double nu, double x, const Plan& p, double E, d
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
     const double nh = nu * p.h;
-    const double rho = exp_tab(-2.0 * nh, T), rhoi = recip(rho);
+    // where e^(-2 nu h) leaves the double range (orders from some 1e4 on, product form) P is 0 on
+    // the left as well
+    const double rho = exp_tab(-2.0 * nh, T), rhoi = kProduct && rho < 1e-300 ? 0.0 : recip(rho);
     double PR = exp_tab(-2.0 * nu * p.tref, T), PL = PR;   // e^(-2 nu t) at nodes mc + j, mc - j
     double jd = 1.0, S = 0.0, tr = 0.0, tl = 0.0;
     CoshPair<kProduct> W(x, p.h, E, Ei, Sr);
@@ -993,12 +1003,12 @@ __device__ inline double sum_dnu_f64(double nu, const Plan& p, double A, double 
 //    target raised by the growth of t sinh(nu t) on the strip, |t + ia| / t times
 //    |sinh(nu (t + ia))| / sinh(nu t) <= (1 + a/t)^2 (|sin b| <= b <= (a/t) sinh(nu t) for b =
 //    nu a), at td with a = pi/2.
-// For plan_fast_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
+// For plan_wide_ok and L >= 8 (the Newton starts need the x term to outgrow the slopes).
 // Returns whether sum_deriv can walk it: e^(2 nu d) over the left side's length d has to be
 // finite, or e^(-2 nu t) below 2^-53 of 1 on all of it.
 __device__ __forceinline__ bool deriv_fast_ok(double nu, double x, double L, double Lq)
 {
-    return plan_fast_ok(nu, x, L, Lq) && L >= 8.0;
+    return plan_wide_ok(nu, x, L, Lq) && L >= 8.0;
 }
 
 __device__ __forceinline__ bool deriv_window_count(double nu, double x, double L, double Lq, float& t0, float& t1,

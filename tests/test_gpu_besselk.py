@@ -167,6 +167,30 @@ def test_plain_large_order_windows(api, orc):
     assert np.all(np.abs(lk.cpu().numpy()[lo] - ref) <= tol[lo])
 
 
+def test_plain_wide_window(api, orc):
+    """x in 1e5 .. 1e8 and orders up to 1e6 by the FP32 window with both sides by products: the
+    scaled result against the first terms of Hankel's series (x >= 1e5, nu <= 30: the fifth is
+    below 1e-17), and log K against the uniform expansion's leading term (1 / nu) at large
+    orders."""
+    import torch
+    rng = np.random.default_rng(33)
+    nu, x = rng.uniform(0.0, 30.0, 4000), 10 ** rng.uniform(5.0, 8.0, 4000)
+    got = api.besselk(to_dev(nu), to_dev(x), result=api.RESULT_SCALED).cpu().numpy()
+    mu, s, t = 4 * nu.astype(np.longdouble) ** 2, np.ones(4000, np.longdouble), np.ones(4000, np.longdouble)
+    for k in range(1, 7):
+        t = t * (mu - (2 * k - 1) ** 2) / (8 * k * x.astype(np.longdouble))
+        s = s + t
+    ref = np.sqrt(np.longdouble(np.pi) / 2 / x.astype(np.longdouble)) * s
+    assert rel_err(got, ref.astype(np.float64)).max() <= TOL_PLAIN
+    nu = 10 ** rng.uniform(4.0, 6.0, 4000)
+    x = nu * 10 ** rng.uniform(-1.0, 1.0, 4000)
+    lk = api.besselk(to_dev(nu), to_dev(x), result=api.RESULT_LOG).cpu().numpy()
+    z = x / nu
+    eta = np.sqrt(1 + z * z) + np.log(z / (1 + np.sqrt(1 + z * z)))
+    lead = 0.5 * np.log(np.pi / (2 * nu)) - nu * eta - 0.25 * np.log1p(z * z)
+    assert np.all(np.abs(lk - lead) <= 1.0 / nu + 1e-12 * nu * (1 + np.abs(eta)))
+
+
 def test_plain_ends_of_the_double_range(api):
     """K = 0 for the largest x (past 1e306 the window's step squared is below the double
     range), with log K at most -x: no NaN."""

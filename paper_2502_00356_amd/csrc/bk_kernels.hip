@@ -739,7 +739,7 @@ extern "C" int bk_besselk(const double* nu, const double* x, double* out, int64_
     return bk_besselk_ex(nu, x, out, n, &p, stream);
 }
 
-constexpr int64_t kPlainSmall = 1 << 17, kDerivSmall = 300000;
+constexpr int64_t kPlainSmall = 1 << 17, kPlainMid = 800000, kDerivSmall = 16384, kDerivMid = 900000;
 
 // One kernel between the caller's optional event pair.
 template <typename K, typename... A>
@@ -767,9 +767,19 @@ extern "C" int bk_besselk_ex(const double* nu, const double* x, double* out, int
     case BK_PLAIN_F64:
         // Small calls take one wave a workgroup: no CU waits for another's sort (4,096 pairs
         // 11.4 us against 21.5; 65,536 15 against 22; 200,000 28 against 19 to 23).
+        // Between, 512 entries a workgroup (200,000 pairs of the grid 14.7 us, 20.2 with 1,024;
+        // 800,000 34.7 and 37.6; 1,048,576 39.5 and 39.2; entries with long windows or solves of
+        // their own gain more: 200,000 with x in 1e5 .. 1e8 by the solve 208 and 332). Thresholds
+        // that send every entry to the solve: 256, four waves at once (200,000 such pairs 179).
         if (n < kPlainSmall)
             return launch_timed(prm, k_besselk_plain<64, 1>, dim3((unsigned)((n + 63) / 64)), dim3(64), stream, nu, x,
                                 out, n, prm->result, L, Lq, prm->stats);
+        if (!plan_wide_ok(1.0, 1.0, L, Lq))
+            return launch_timed(prm, k_besselk_plain<256, 1>, dim3((unsigned)((n + 255) / 256)), dim3(256), stream, nu,
+                                x, out, n, prm->result, L, Lq, prm->stats);
+        if (n < kPlainMid)
+            return launch_timed(prm, k_besselk_plain<256, 2>, dim3((unsigned)((n + 511) / 512)), dim3(256), stream, nu,
+                                x, out, n, prm->result, L, Lq, prm->stats);
         return launch_timed(prm, k_besselk_plain<256, 4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), stream, nu,
                             x, out, n, prm->result, L, Lq, prm->stats);
     case BK_MIXED_F32C:
@@ -953,11 +963,16 @@ extern "C" int bk_besselk_deriv(const double* nu, const double* x, double* k, do
     double L, Lq;
     resolve_thresholds(BK_PLAIN_F64, p.L_window, p.L_quad, &L, &Lq);
     if ((n + 255) / 256 > 0x7fffffffLL) return BK_EINVAL;
-    // as bk_besselk_ex's plain form: 16,384 pairs 19 us against 42; 262,144 39 against 44;
-    // 1,048,576 122 against 90
+    // as bk_besselk_ex's plain form; in between four waves on 256 entries, which hold up none of
+    // the exact solves (us by one wave, by four on 256 and on 1,024: 20,000 pairs of the grid 21,
+    // 20, 42; 200,000 42, 37, 45; 800,000 107, 94, 97; 1,048,576 136, 117, 103; 400,000 by the
+    // solves 237, 238, 315)
     if (n < kDerivSmall)
         return launch(k_besselk_deriv<64, 1>, dim3((unsigned)((n + 63) / 64)), dim3(64), stream, nu, x, k, dk_dx, dk_dnu,
                       n, p.result, L, Lq, p.stats);
+    if (n < kDerivMid || L < 8.0 || !plan_wide_ok(1.0, 1.0, L, Lq))
+        return launch(k_besselk_deriv<256, 1>, dim3((unsigned)((n + 255) / 256)), dim3(256), stream, nu, x, k, dk_dx,
+                      dk_dnu, n, p.result, L, Lq, p.stats);
     return launch(k_besselk_deriv<256, 4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), stream, nu, x, k, dk_dx,
                   dk_dnu, n, p.result, L, Lq, p.stats);
 }

@@ -167,6 +167,25 @@ def test_plain_large_order_windows(api, orc):
     assert np.all(np.abs(lk.cpu().numpy()[lo] - ref) <= tol[lo])
 
 
+@pytest.mark.parametrize("n", [131071, 131072, 131585, 799999, 800000])
+@pytest.mark.parametrize("L", [0.0, 600.0])
+def test_plain_shapes_agree(api, n, L):
+    """The launch shapes (64-, 256-, 512- and 1,024-entry workgroups) at their edges: the bits of
+    calls of 4,000 with the same pairs."""
+    import torch
+    rng = np.random.default_rng(n)
+    nu, x = rng.uniform(0.0, 20.0, n), 10 ** rng.uniform(-4, 3, n)
+    odd = np.arange(0, n, 37)
+    nu[odd] = np.resize([0.5, 2e4, 0.0, 3.0, np.nan, 1e-9, 3e5, 1.0, 2e6, 700.0], odd.size)
+    x[odd] = np.resize([5e-13, 3e4, 1e-13, np.inf, 1.0, 2e5, 4e5, 9e7, 3e6, 650.0], odd.size)
+    dn, dx = to_dev(nu), to_dev(x)
+    full = api.besselk(dn, dx, result=api.RESULT_SCALED, L_window=L)
+    for a in (0, n // 2 - 1000, n - 4000):
+        part = api.besselk(dn[a:a + 4000], dx[a:a + 4000], result=api.RESULT_SCALED, L_window=L)
+        torch.cuda.synchronize()
+        assert np.array_equal(full[a:a + 4000].cpu().numpy(), part.cpu().numpy(), equal_nan=True), a
+
+
 def test_plain_wide_window(api, orc):
     """x in 1e5 .. 1e8 and orders up to 1e6 by the FP32 window with both sides by products: the
     scaled result against the first terms of Hankel's series (x >= 1e5, nu <= 30: the fifth is

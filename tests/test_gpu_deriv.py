@@ -220,6 +220,25 @@ def test_deriv_window_rule(api, orc, L):
     assert rel_err(out["dnu"].cpu().numpy()[pos], d["scaled_dnu"][pos]).max() <= tol
 
 
+@pytest.mark.parametrize("n", [16383, 16384, 16641, 899999, 900000])
+def test_deriv_shapes_agree(api, n):
+    """The three launch shapes (64-, 256- and 1,024-entry workgroups) at their edges, with pairs of
+    every kind (the window up to x = 1e8 and orders of 1e6, the exact solves beyond): the bits of
+    calls of 4,000, and a subset of the outputs those of all."""
+    rng = np.random.default_rng(n)
+    nu, x = rng.uniform(0.0, 20.0, n), 10 ** rng.uniform(-4, 3, n)
+    odd = np.arange(0, n, 37)
+    nu[odd] = np.resize([0.5, 2e4, 0.0, 3.0, np.nan, 1e-9, 3e5, 1.0, 2e6, 700.0], odd.size)
+    x[odd] = np.resize([5e-13, 3e4, 1e-13, np.inf, 1.0, 2e5, 4e5, 9e7, 3e6, 650.0], odd.size)
+    full = _deriv(api, nu, x, result=1)
+    for a in (0, n // 2 - 1000, n - 4000):
+        part = _deriv(api, nu[a:a + 4000], x[a:a + 4000], result=1)
+        for key in ("k", "dx", "dnu"):
+            assert np.array_equal(full[key][a:a + 4000], part[key], equal_nan=True), (key, a)
+    for key in ("k", "dx", "dnu"):
+        assert np.array_equal(_deriv(api, nu, x, result=1, want=(key,))[key], full[key], equal_nan=True), key
+
+
 def test_deriv_small_calls(api, orc):
     """Every size around the edges of a 64-entry workgroup: the oracle's values, and the same
     bits whatever an entry's lane and its neighbours."""

@@ -174,6 +174,11 @@ struct TailStart {
     int32_t I, J, col;
 };
 
+struct TailWalk : TailStart {
+    unsigned base;
+};
+
+
 struct TabArgs {
     TileGeom g;                    // rb_per_tile: row blocks of 64 R; cb_per_tile: column blocks of `cols`
     int cols;
@@ -321,6 +326,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
     constexpr unsigned kWaves = kTabWaves;
     __shared__ tab2_t sT[kSlots];
     __shared__ unsigned s_flag;
+    __shared__ TailWalk s_walk[kWaves];     // not in registers, which the first part's loop would hold too
     unsigned* const counts = tab_counts<kF32>(table);
     for (int k = threadIdx.x; k < kSlots; k += kTabThreads) sT[k] = ((const tab2_t*)table)[k];
     __syncthreads();
@@ -328,10 +334,9 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grid = gridDim.x;
     const TileGeom& g = A.g;
     const unsigned rbn = (unsigned)g.rb_per_tile;
-    unsigned it = blockIdx.x * kWaves + wave, stride = grid * kWaves, base = 0u;
+    unsigned it = blockIdx.x * kWaves + wave, stride = grid * kWaves;
     const unsigned per_tile = rbn * (unsigned)g.cb_per_tile;
     int64_t lo = 0, hi = A.first, I = 0, J = 0;
-    TailStart w = {};
     // part by part; one copy of the item's code
     for (int part = 0;; ++part) {
         for (;; it += stride) {
@@ -345,17 +350,18 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
                 jl0 = (int64_t)cb * A.cols;
             } else {
                 // the tile of item `it`, from column w.col of tile (w.I, w.J) on, whose first item
-                // is `base`. The tiles of a column have equally many items (all but the part's
+                // is w.base. The tiles of a column have equally many items (all but the part's
                 // first), so the walk is over columns (tile by tile it took 0.4 us a tile: 470
                 // sites in 4-tiles 266 us)
+                TailWalk w = s_walk[wave];
                 unsigned rel;
                 while (w.J < g.T) {
                     const int nJ = (int)min((int64_t)g.ts, g.n - (int64_t)w.J * g.ts);
                     const unsigned ntile = (unsigned)((nJ - w.col + kTailCols - 1) / kTailCols) * rbn;
-                    rel = it - base;
+                    rel = it - w.base;
                     if (rel < ntile) break;
                     const unsigned k = w.col > 0 ? 1u : min(rel / ntile, (unsigned)(g.T - w.I));
-                    base += k * ntile;
+                    w.base += k * ntile;
                     w.col = 0;
                     w.I += (int)k;
                     if (w.I == g.T) {
@@ -364,6 +370,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
                     }
                 }
                 if (w.J == g.T) break;
+                s_walk[wave] = w;
                 I = w.I;
                 J = w.J;
                 const unsigned cb = rel / rbn;
@@ -391,7 +398,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
                 if (!skipped) {
                     it = share * kWaves + wave;
                     stride = min(grid, kTailGroups) * kWaves;
-                    w = A.first_at;
+                    s_walk[wave] = {A.first_at, 0u};
                     lo = A.first;
                     hi = A.count;
                     continue;
@@ -410,8 +417,7 @@ __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __r
         const bool left = (s_flag >> 16) != 0u;
         it = wave;
         stride = kWaves;
-        base = 0u;
-        w = left ? A.first_at : A.count_at;
+        s_walk[wave] = {left ? A.first_at : A.count_at, 0u};
         lo = left ? A.first : A.count;
         hi = INT64_MAX;
     }

@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace bk {
 
 constexpr double kLn2 = 0.69314718055994530942;
@@ -520,13 +522,14 @@ __device__ __forceinline__ float asinh_fast(float y)
     return 0.69314718f * __builtin_amdgcn_logf(y + __builtin_amdgcn_sqrtf(fmaf(y, y, 1.0f)));
 }
 
-// Orders (and x above 1e5) from which the ends' Newton steps start at quadratic bounds of the ends (from the
-// starts below they overshoot to several times the window's width: 45 nodes at nu = 1,000,
-// x = 500, where 27 do).
-constexpr float kLargeOrder = 60.0f;
+// Pairs whose ends' Newton steps start at quadratic bounds of the ends (from the starts below
+// they overshoot to several times the window's width: 45 nodes at nu = 1,000, x = 500, where 27
+// do). Looked for once a wave (kLarge: any lane's): those of small orders pay for nothing.
+__device__ __forceinline__ bool large_pair(float nu, float x) { return nu > 60.0f || x > 1e5f; }
 
 // Upper bound of the d > 0 where x (cosh(t + d) - cosh t) = slope d + L; E, Ei = e^t, e^-t.
-__device__ __forceinline__ float right_end_fast(float t, float E, float Ei, float x, float slope, float L)
+template <bool kLarge>
+__device__ __forceinline__ float right_end_fast(float t, float E, float Ei, float x, float slope, float L, bool large)
 {
     // start: the x term alone drops by L; then it drops by L and the slope's rise up to there
     // (still left of the root), then one Newton step to its right
@@ -536,7 +539,7 @@ __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, floa
         return fmaxf(0.69314718f * __builtin_amdgcn_logf(1.0f + e + __builtin_amdgcn_sqrtf(e * (e + 2.0f))) - t, 1e-3f);
     };
     float d = drop(fmaf(slope, drop(L), L));
-    if (slope > kLargeOrder || x > 1e5f) {
+    if (kLarge && large) {
         // F(d) >= C d^2 / 2 - r d - L, C = x cosh t, r = slope - x sinh t: right of its root
         const float C = 0.5f * x * (E + Ei), r = fmaxf(slope - 0.5f * x * (E - Ei), 0.0f);
         const float s = (r + __builtin_amdgcn_sqrtf(fmaf(r, r, 2.0f * C * L))) * __builtin_amdgcn_rcpf(C);
@@ -550,13 +553,14 @@ __device__ __forceinline__ float right_end_fast(float t, float E, float Ei, floa
 }
 
 // Left end of the window from tp (e^tp = E): 0, or tp - e with F(e) = 0 (see above).
-__device__ __forceinline__ float left_end_fast(float tp, float E, float Ei, float nu, float x, float L)
+template <bool kLarge>
+__device__ __forceinline__ float left_end_fast(float tp, float E, float Ei, float nu, float x, float L, bool large)
 {
     const float L2 = L + 0.69314718f, hx = 0.5f * x;
     const float e0 = L2 + x * (0.5f * (E + Ei) - 1.0f);
     if (!(e0 < nu * tp)) return 0.0f;
     float e = e0 * __builtin_amdgcn_rcpf(nu);
-    if (nu > kLargeOrder) {
+    if (kLarge && large) {
         // F(e) <= L2 - C (e^-e - 1 + e) with C = x cosh tp >= nu, below 0 at sqrt(3 L2 / C) <= 1
         const float b = 3.0f * L2 * __builtin_amdgcn_rcpf(hx * (E + Ei));
         if (b <= 1.0f) e = fminf(e, __builtin_amdgcn_sqrtf(b));
@@ -573,8 +577,13 @@ __device__ __forceinline__ void window_fast(float nu, float x, float L, float& t
     L += 0.01f;
     tp = nu * nu > x ? asinh_fast(nu * __builtin_amdgcn_rcpf(x)) : 0.0f;
     const float E = exp_fast(tp), Ei = __builtin_amdgcn_rcpf(E);
-    t1 = tp + right_end_fast(tp, E, Ei, x, nu, L);
-    t0 = left_end_fast(tp, E, Ei, nu, x, L);
+    const bool large = large_pair(nu, x);
+    auto ends = [&](auto any) {
+        t1 = tp + right_end_fast<any.value>(tp, E, Ei, x, nu, L, large);
+        t0 = left_end_fast<any.value>(tp, E, Ei, nu, x, L, large);
+    };
+    if (__builtin_expect(__any(large), 0)) ends(std::true_type{});
+    else ends(std::false_type{});
 }
 
 // expm1(y) for 0 <= y <= 1/8 (Taylor through y^10, truncation below 1e-18 relative).
@@ -1019,11 +1028,18 @@ __device__ __forceinline__ bool deriv_window_count(double nu, double x, double L
     const float E = exp_fast(tp), Ei = __builtin_amdgcn_rcpf(E);
     const float td = fmaxf(ta, fminf(1.0f, __builtin_amdgcn_sqrtf(1.70f * ix)));
     const float Ed = exp_fast(td), itd = __builtin_amdgcn_rcpf(td);
-    t1 = fmaxf(tp + right_end_fast(tp, E, Ei, xf, nf + 1.0f, Lf),
-               td + right_end_fast(td, Ed, __builtin_amdgcn_rcpf(Ed), xf, fmaf(2.0f, itd, nf), Lf));
-    t0 = left_end_fast(tp, E, Ei, nf, xf, Lf);
+    const bool large = large_pair(nf, xf);
+    auto ends = [&](auto any) {
+        t1 = fmaxf(tp + right_end_fast<any.value>(tp, E, Ei, xf, nf + 1.0f, Lf, large),
+                   td + right_end_fast<any.value>(td, Ed, __builtin_amdgcn_rcpf(Ed), xf, fmaf(2.0f, itd, nf), Lf, large));
+        t0 = left_end_fast<any.value>(tp, E, Ei, nf, xf, Lf, large);
+    };
+    const bool any = __any(large);
+    if (__builtin_expect(any, 0)) ends(std::true_type{});
+    else ends(std::false_type{});
     const float extra = 2.0f * 0.69314718f * __builtin_amdgcn_logf(fmaf(1.5707963f, itd, 1.0f));
     node_grid(t0, t1, tp, node_step_fast(nf + 1.0f, xf, (float)Lq + extra), N, mc);
+    if (!any && Lf <= 250.0f) return true;          // d <= (L + ln 2 + nu) / nu
     return 2.0f * nf * (t1 - t0) * (float)mc < 699.0f * (float)N || 2.0f * nf * t0 >= 40.0f;
 }
 
@@ -1039,10 +1055,10 @@ __device__ inline DerivSums sum_deriv(double nu, double x, const Plan& p, double
 {
     const int nr = p.N - p.mc, nl = p.mc, jmax = nr > nl ? nr : nl;
     const double h = p.h, nh = nu * h;
-    // 1 - e^(-2 nu h), and the exponential itself (1 less the former is 0 from nu h = 18 on)
-    const double omr = -expm1(-2.0 * nh), rho = exp_tab(-2.0 * nh, T);
-    // e^(2 nu h) - 1, e^(2 nu h); where its powers leave the double range Q is 1 on the left
-    const double qe = 2.0 * nh * nl < 700.0 ? omr * recip(rho) : 0.0, re = 1.0 + qe;
+    // e^(2 nu h) - 1, e^(-2 nu h) and 1 less that, each to its own relative accuracy
+    const double qh = expm1(fmin(2.0 * nh, 700.0)), rho = recip(1.0 + qh), omr = qh * rho;
+    // where the powers of e^(2 nu h) leave the double range Q is 1 on the left
+    const double qe = 2.0 * nh * nl < 700.0 ? qh : 0.0, re = 1.0 + qe;
     const double Qr = -expm1(-2.0 * nu * p.tref), Pr = exp_tab(-2.0 * nu * p.tref, T);
     double QR = Qr, EL = 0.0, jd = 1.0;
     CoshPair<true> W(x, h, E, Ei, Sr);

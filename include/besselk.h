@@ -38,13 +38,16 @@ typedef enum {
 } bk_status;
 
 /* Evaluation form.
- *  BK_PLAIN_F64  : per-entry peak and window solve in FP64 (the bracket/Newton
- *                  search of Sec. IV-B), node count from the trapezoid strip
- *                  bound, FP64 node terms and FP64 accumulation. bk_besselk and
+ *  BK_PLAIN_F64  : a per-entry window that contains the one of Sec. IV-B (its ends
+ *                  bounded from outside in FP32; for x below 1e-12 or above 1e8,
+ *                  orders above 1e6, and thresholds L_window outside 1 .. 500 or
+ *                  L_quad below 1 by the bracket/Newton search in FP64), node
+ *                  count from the trapezoid strip bound, node terms, sums and
+ *                  prefactor in FP64. bk_besselk and
  *                  bk_besselk_ex take Temme's series with the forward recurrence
  *                  instead (Sec. IV-A, the paper's branch for x < 0.1) where
  *                  x < 0.1 and K_nu(x) lies far inside the double range.
- *  BK_MIXED_F32C : the same FP64 solve; node exponents formed in FP64 without
+ *  BK_MIXED_F32C : the FP64 search for every entry; node exponents formed in FP64 without
  *                  cancellation, exponentials in FP32, Kahan-compensated FP32 sum,
  *                  FP64 prefactor. Looser window (relative error ~1e-7 class).
  *                  Like BK_PLAIN_F64, Temme's series (FP64) where x < 0.1.
@@ -98,7 +101,8 @@ enum {
 typedef struct bk_model bk_model;
 
 /* Per-call options. Zero-initialise and set what you need.
- *  L_window : window threshold L of Sec. IV-B, [t0,t1] = {t : g(t) >= g(t_max) - L}.
+ *  L_window : window threshold L of Sec. IV-B, [t0,t1] = {t : g(t) >= g(t_max) - L}
+ *             (BK_PLAIN_F64 and the derivatives: a window that contains it, from 1 on).
  *             0 selects the form's default (36 for BK_PLAIN_F64, 15 otherwise).
  *  L_quad   : node-count target: the step keeps the strip-bound discretisation
  *             error near exp(-L_quad). 0 selects 35 (plain) or 14.5 (others).
@@ -118,8 +122,9 @@ typedef struct bk_model bk_model;
  *             the caller. When both are set, bk_besselk_ex and bk_matern_tiles
  *             record [0] just before and [1] just after the form's main kernel
  *             launches on the call's stream, so that they can be timed alone
- *             (BK_LEARNED's table, plan, reset and fallback launches fall outside
- *             the pair). A failed record returns BK_EHIP. */
+ *             (BK_LEARNED's table, plan, reset and fallback launches, and the launch
+ *             that builds the table of a large Matern call, fall outside the pair).
+ *             A failed record returns BK_EHIP. */
 typedef struct {
     int32_t mode;
     int32_t result;
@@ -185,9 +190,9 @@ typedef struct {
  * in BK_PLAIN_F64, or in BK_MIXED_F32C or BK_LEARNED with BK_OUT_F32, evaluate the
  * quadrature at the points of a table over r^2 and the entries by interpolation in it,
  * at the form's accuracy or better (BK_PLAIN_F64: a few 1e-16 relative where z < 2); the
- * table lies in the last bytes of out until those are written. Other calls, and
- * distances below the table (r / beta under 2^-14; FP32: 2^-12), evaluate each entry;
- * above it (128) the asymptotic series in FP64 is taken.
+ * table lies in the last bytes of out until those are written. Distances below the table
+ * (r / beta under 2^-14; FP32: 2^-12) take the series at 0, those above it (128) the
+ * asymptotic series, both in FP64. Other calls evaluate each entry.
  * out : device buffer of bk_matern_out_elems(n, tile_size, lower_only) elements
  *       of params->out_dtype. params->mode selects the form; BK_LEARNED needs a
  *       model and a workspace of bk_matern_workspace_bytes(...) bytes, and only
@@ -382,7 +387,9 @@ int bk_mlp_infer(const bk_model* model, const float* u, float* y, int64_t n, hip
  * params (BK_MLP_NPARAM floats), u (B x 2), target (B x 3), tau (3) device;
  * grad (BK_MLP_NPARAM floats) and loss (1 float) device outputs, overwritten.
  * Loss = sum_k mean_b |tau_k - [e_bk < 0]| e_bk^2 with e = target - y.
- * scratch: device buffer of at least bk_mlp_grad_scratch_bytes(B) bytes. */
+ * scratch: device buffer of at least bk_mlp_grad_scratch_bytes(B) bytes. Without its last
+ * 4 ceil(B / 64) bytes the loss is summed by FP32 atomics, whose order may differ from
+ * call to call; with them it, like the gradient, is summed in a fixed order. */
 int bk_mlp_grad(const float* params, const float* u, const float* target, const float* tau,
                 int64_t B, float* grad, float* loss, void* scratch, size_t scratch_bytes,
                 hipStream_t stream);

@@ -3,9 +3,9 @@
 // Sec. III-A, Alg. 3), the paper's refined algorithm (Sec. IV-A, IV-C, Alg. 2),
 // and the derivatives of K_nu and of the Matern covariance, for gfx950.
 //
-// Mapping: one lane per output entry. Standalone K_nu: 512-entry workgroups whose
-// entries are re-sorted through LDS between phases (coalesced FP64 loads, stores
-// to each entry's own index); the other kernels: 256-lane workgroups.
+// Mapping: one lane per output entry. Standalone K_nu and its derivatives: workgroups of 64 to
+// 1,024 entries, sorted through LDS (coalesced FP64 loads, stores to each entry's own index);
+// the other kernels: 256-lane workgroups.
 // Matern: each wave covers 64 consecutive rows of a tile column (one 512-byte
 // FP64 or 256-byte FP32 store per column); the row location lives in VGPRs and
 // the column location is wave-uniform, so it is read through scalar loads
@@ -295,8 +295,9 @@ struct DrawCounts {
 
 // Plain K_nu. A workgroup takes kThreads x kPer entries in two phases:
 //  1. entry order: special values; the FP32 window and node count (cheap enough to run
-//     before any sort), or Temme's series (x < 0.1), or the exact solve (plan_fast_ok
-//     false) as keys of their own; counting sort into LDS, largest node counts first;
+//     before any sort), or Temme's series (x < 0.1), or plain_plan (plan_fast_ok false: the
+//     window for a walk by products, or the exact solve) as keys of their own; counting sort
+//     into LDS, largest node counts first;
 //  2. its waves draw the sorted entries 64 at a time: set-up at the reference node, the
 //     paired walk, the prefactor and the store to the entry's own index; or the whole of
 //     the other two.

@@ -2123,7 +2123,7 @@ int bk_matern_learned(const bk_locs* locs, const bk_params* prm, int32_t tile_si
                               0.0, 0.0, tab);
         if (st != BK_OK) return st;
         if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
-        st = launch_table_eval(locs, P, X, tile_size, lower_only, TAB_C, BK_MIXED_F32C, true, BK_OUT_F32, out, stream);
+        st = launch_table_eval(locs, P, X, tile_size, lower_only, TAB_C, true, BK_OUT_F32, out, stream);
         if (st != BK_OK) return st;
         return mark_kernel_event(prm, 1, stream) == hipSuccess ? BK_OK : BK_EHIP;
     }

@@ -193,7 +193,8 @@ struct TabArgs {
 
 // The slot of squared distance q. The conversion takes anything below the first
 // interval (and NaN) to slot 0; that and the last slot hold a NaN constant term, so an
-// entry out of the table shows in its value.
+// entry out of the table shows in its value (an FP32 table's last slot 0 where the function
+// rounds to 0 from there on).
 template <bool kF32>
 __device__ __forceinline__ int tab_slot(const TabIndex& X, double q)
 {
@@ -316,7 +317,7 @@ __device__ __forceinline__ void tab_item(const TabArgs& A, const tab2_t* sT, con
 // 4.3 TB/s); without the stores the arithmetic and LDS reads take 0.89 and 0.64. 20 (FP32)
 // and 25 (FP64) VALU instructions an entry against the per-entry quadrature's 1,839:
 // 40,000 sites, lower 960-tiles, nu = 2.3, plain FP64 40.0 -> 1.39 ms; 9,001 sites, mixed
-// FP32, 2.60 -> 0.094 ms; C, dC/dbeta and dC/dnu of 12,000 sites 16.6 -> 0.45 ms (tables
+// FP32, 2.60 -> 0.104 ms; C, dC/dbeta and dC/dnu of 12,000 sites 16.6 -> 0.45 ms (tables
 // included).
 template <typename OutT, bool kF32, int FN, int MODE, int R>
 __global__ __launch_bounds__(kTabThreads, 4) void k_matern_tab(const double* __restrict__ lx, const double* __restrict__ ly,
@@ -536,7 +537,7 @@ static TabNear tab_near_params(const TabParams& P)
 }
 
 int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X, int32_t tile_size, int32_t lower_only, int fn,
-                      int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream)
+                      bool f32_table, int out_dtype, void* out, hipStream_t stream)
 {
     TabArgs A = {};
     A.P = P;
@@ -600,7 +601,7 @@ int matern_table_tiles(const bk_locs* locs, const bk_params* prm, int32_t tile_s
                                 nullptr, nullptr);
     if (st != BK_OK) return st;
     if (mark_kernel_event(prm, 0, stream) != hipSuccess) return BK_EHIP;
-    st = launch_table_eval(locs, P, X, tile_size, lower_only, TAB_C, prm->mode, f32_table, prm->out_dtype, out, stream);
+    st = launch_table_eval(locs, P, X, tile_size, lower_only, TAB_C, f32_table, prm->out_dtype, out, stream);
     if (st != BK_OK) return st;
     return mark_kernel_event(prm, 1, stream) == hipSuccess ? BK_OK : BK_EHIP;
 }
@@ -619,8 +620,7 @@ int matern_grad_table_tiles(const bk_locs* locs, const bk_params* prm, double ps
                     X, tab[0], tab[1], tab[2]);
     for (int k = 0; k < 3 && st == BK_OK; ++k)
         if (outs[k])
-            st = launch_table_eval(locs, P, X, tile_size, lower_only, k, BK_PLAIN_F64, false, prm->out_dtype, outs[k],
-                                   stream);
+            st = launch_table_eval(locs, P, X, tile_size, lower_only, k, false, prm->out_dtype, outs[k], stream);
     return st;
 }
 

@@ -48,10 +48,11 @@ __device__ __forceinline__ float tab_pos(const TabIndex& X, float q)
 typedef double tab2_t __attribute__((ext_vector_type(2)));
 typedef float tab4f_t __attribute__((ext_vector_type(4)));
 
-// A table is kPlanes planes of kN 16-byte slots, then 16 bytes of counts. Slot i of the planes in turn: {centre, c0}, {c1, c2}, ... {c7, c8}, the
-// polynomial in q - centre (r^2 units); FP32 table: {centre, c0}, {c1 .. c4 in FP32,
-// relative to c0}, the polynomial's argument scaled by 1 / beta^2. Planes rather than records: the 16
-// slots of one LDS bank row are then 16 neighbouring intervals.
+// A table is kPlanes planes of kN 16-byte slots, then 16 bytes of counts. Slot i of the planes
+// in turn: {centre, c0}, {c1, c2}, ... {c7, c8}, the polynomial in q - centre (r^2 units);
+// FP32 table: {centre, c0}, {c1 .. c4 in FP32, relative to c0}, the polynomial's argument
+// scaled by 1 / beta^2. Planes rather than records: the 16 slots of one LDS bank row are then
+// 16 neighbouring intervals.
 template <bool kF32>
 constexpr size_t tab_bytes()
 {
@@ -108,7 +109,8 @@ __device__ __forceinline__ const ChebTab<TabShape<kF32>::kDeg + 1>& cheb_tab()
     else return kCheb9;
 }
 
-// A builder's workgroup is one wave: kPer intervals, one lane per Chebyshev point.
+// A builder's workgroup takes one wave's worth of Chebyshev points: kPer intervals (kTabLanes
+// lanes a point in bk_table.hip, one in bk_mlp.hip).
 template <bool kF32>
 struct TabWave {
     static constexpr int kM = TabShape<kF32>::kDeg + 1, kPer = 64 / kM;
@@ -225,11 +227,10 @@ bool table_route(const bk_locs* locs, const bk_params* prm, int32_t tile_size, i
 char* table_in_output(void* out, int64_t elems, int elem_bytes, bool f32_table, int64_t* first);
 TabIndex tab_index(double beta, const TabParams& P, bool f32_table);
 
-// Evaluation over all tiles from the table in `out` (built on the same stream).
-// cold_mode: the per-entry form of the distances outside the table's range.
-// fn: a TabFn.
+// Evaluation over all tiles from the table in `out` (built on the same stream); fn: a TabFn.
+// Entries outside the table take the plain form, from an FP32 table the mixed one.
 int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X, int32_t tile_size, int32_t lower_only, int fn,
-                      int cold_mode, bool f32_table, int out_dtype, void* out, hipStream_t stream);
+                      bool f32_table, int out_dtype, void* out, hipStream_t stream);
 // Plain and mixed forms: builds the table and evaluates. bk_status.
 int matern_table_tiles(const bk_locs* locs, const bk_params* prm, int32_t tile_size, int32_t lower_only, void* out,
                        hipStream_t stream);

@@ -52,8 +52,8 @@ NODE_SLOTS = load_node_slots()
 # null: HBM bytes from the FETCH_SIZE and WRITE_SIZE runs scaled by a plain 1 GiB
 # copy, and SQ_INSTS_VALU of one launch without statistics.
 TRAFFIC = {
-    "grid": {"src_sha": "3862daf8549f6b23", "n": 1 << 24, "bytes": 4.15438e8, "valu_insts": 1.04343e8},
-    "matern_large": {"src_sha": "88d6562b9395dd52", "bytes": 2.13076e10, "valu_insts": 1.98615e9},
+    "grid": {"src_sha": "3f6d3bb5777c70b6", "n": 1 << 24, "bytes": 4.15437e8, "valu_insts": 1.04610e8},
+    "matern_large": {"src_sha": "13ba776ad8d05a8c", "bytes": 2.12934e10, "valu_insts": 1.99305e9},
 }
 KERNEL_SOURCES = {
     "grid": ("bk_mlp.hip", "bk_math.hpp", "bk_internal.hpp"),

@@ -11,7 +11,7 @@
 //  - Sigma^-1 = Y Y^T, tile by tile, only to be multiplied into dSigma and summed.
 // n^3 operations in all with the gradient (7.4 ms at the library product's rate for 8,100
 // sites), n^3 / 3 for the value. rocSOLVER's potrf, potrs and potri took 76 ms and 41 (its
-// 128-column unblocked kernel alone 64 x 171 us); this 14.5 and 7.3.
+// 128-column unblocked kernel alone 64 x 171 us); this 14.4 and 7.0.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

@@ -305,7 +305,7 @@ struct DrawCounts {
 // sorts (2,266 VALU instructions a wave of 64), 755 with the FP32 window there, 640 with
 // one sort of 512 entries, one a lane (1,207 instructions), 463 with 1,024 drawn by four
 // waves: fewer waves hold both branches, and none waits for a block's slowest; 450 with the
-// nodes' exponents by second differences (CoshPair), 432 with one Newton step an end and the
+// nodes' exponents by second differences (CoshPair), 431 with one Newton step an end and the
 // step rule's cosine by its series. (512
 // entries in 128 lanes 528, in 256 489; constants hoisted out of the draw loop spill: 548.)
 template <int kThreads, int kPer>
@@ -488,7 +488,7 @@ __device__ __noinline__ DerivOut deriv_exact(double v, double z, double L, doubl
 // (sum_deriv), the entries sorted and drawn as in k_besselk_plain. NULL outputs are not
 // stored. dK/dnu carries the sign of nu. 2^22 pairs of the (nu, x) grid: 1,729 us with a
 // solve and a walk for each integral, unsorted (1,205 with the FP32 windows
-// there), 300 with one walk, 292 with its right side by second differences.
+// there), 300 with one walk, 296 with its right side by second differences.
 template <int kThreads, int kPer>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_besselk_deriv(
     const double* __restrict__ nu, const double* __restrict__ x, double* __restrict__ k, double* __restrict__ dkdx,

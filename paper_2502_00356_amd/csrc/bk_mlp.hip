@@ -1112,7 +1112,7 @@ __global__ __launch_bounds__(256) void k_matern_plans(MlpDev M, double nu, doubl
 // point outside the training box, or whose window fails the acceptance tests at a point,
 // takes the plain form instead. kSolver: windows from the plain solver (L, Lqs).
 // 316 x 316 sites, FP32: 17.5 ms per entry (121 VALU instructions each), 5.0 ms by the
-// table, bound by the 20 GB written; 517 sites: five launches and 56 us, two and 36.
+// table, bound by the 20 GB written; 517 sites: five launches and 56 us, two and 20.
 template <bool kSolver>
 __global__ __launch_bounds__(64) void k_tab_build_learned(MlpDev M, TabParams P, TabIndex X, double Lq, double L,
                                                           double Lqs, char* table)

@@ -117,7 +117,6 @@ __device__ __noinline__ double tab_near_dnu(double q, TabNear N)
 }
 
 // C and dC/dbeta there, by Temme's series.
-
 template <int FN>
 __device__ __forceinline__ double tab_near(double z, const TabParams& P, const double* T)
 {
@@ -167,7 +166,7 @@ constexpr unsigned kTabGrid = 512;
 constexpr int kTailCols = 2;
 // Workgroups that share the second part, written by the last to finish alone before: 517
 // sites (FP32, lower 128-tiles) 32.5 us a call then, 23.3 with 16 or 64, 26 with 8; 1,024
-// sites (FP64) 22.4, 22.4 and 24.3, 22.0.
+// sites (FP64) 22.4, 22.4 and 24.3, 22.0. 20.1 and 21.2 now (TailStart, TailWalk).
 constexpr unsigned kTailGroups = 16;
 
 struct TailStart {
@@ -177,7 +176,6 @@ struct TailStart {
 struct TailWalk : TailStart {
     unsigned base;
 };
-
 
 struct TabArgs {
     TileGeom g;                    // rb_per_tile: row blocks of 64 R; cb_per_tile: column blocks of `cols`

@@ -438,9 +438,6 @@ __device__ __forceinline__ double unscale(double z, double s, int result)
     return ldexp(exp(64.0 * kLn2 - z) * s, -64);
 }
 
-// K, dK/dx and dK/dnu where the fast window does not apply: the K integral at orders nu and
-// |nu - 1| (for dK/dx) and the dK/dnu integral, each with its own exact solve. Out of line and
-// rare.
 // exp_tab's tables in LDS, for a kernel (which fills them) and its out-of-line function alike.
 __device__ __forceinline__ double* lds_tab()
 {
@@ -448,6 +445,9 @@ __device__ __forceinline__ double* lds_tab()
     return t;
 }
 
+// K, dK/dx and dK/dnu where the fast window does not apply: the K integral at orders nu and
+// |nu - 1| (for dK/dx) and the dK/dnu integral, each with its own exact solve. Out of line and
+// rare.
 struct DerivOut {
     double k, dx, dn;
     unsigned int nodes;

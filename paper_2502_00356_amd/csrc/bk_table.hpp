@@ -228,7 +228,8 @@ char* table_in_output(void* out, int64_t elems, int elem_bytes, bool f32_table, 
 TabIndex tab_index(double beta, const TabParams& P, bool f32_table);
 
 // Evaluation over all tiles from the table in `out` (built on the same stream); fn: a TabFn.
-// Entries outside the table take the plain form, from an FP32 table the mixed one.
+// Entries outside the table take a series, NaN and infinite distances and those next to 0 the
+// plain form (from an FP32 table the mixed one).
 int launch_table_eval(const bk_locs* locs, const TabParams& P, const TabIndex& X, int32_t tile_size, int32_t lower_only, int fn,
                       bool f32_table, int out_dtype, void* out, hipStream_t stream);
 // Plain and mixed forms: builds the table and evaluates. bk_status.
